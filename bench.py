@@ -27,7 +27,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_update_or_c4_counters.md")
-KERNEL_SOURCES = ["k_update.hip", "device_common.hpp"]
+KERNEL_SOURCES = ["k_update.hip", "link_update.hpp", "device_common.hpp"]
 
 
 def _code_only(text: str) -> bytes:
@@ -43,7 +43,7 @@ def _code_only(text: str) -> bytes:
 
 def kernel_source_hash() -> str:
     """Hash of what the update kernel is built from and how it is launched:
-    its two source files, the records it reads (the ensemble descriptor and the
+    its source files, the records it reads (the ensemble descriptor and the
     per-block record; the rest of the shared header holds other kernels'
     declarations and constants) and the host function that builds the block
     records and their order, comments left out."""

@@ -308,9 +308,13 @@ __device__ inline BfEnvF32 bf_env_f32(float kappa)
 }
 
 // Attempts 2j and 2j+1 of the block b (words 0, 1 then 2, 3); returns which
-// accepted first (1 or 2, with (cos psi, sin psi) of that attempt) or 0.
+// accepted first (1 or 2, with (cos psi, sin psi) of that attempt) or 0.  Both
+// attempts are evaluated by every lane: a wave runs each step once whichever
+// attempt its lanes accept, and the two chains overlap.
 __device__ inline int bf_pair_f32(const BfEnvF32& v, const Block4& b, float* cpsi, float* spsi)
 {
+    float g[2], ch2[2], inv[2];
+    bool acc[2];
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
         const uint32_t a = half ? b.w[2] : b.w[0];
@@ -318,22 +322,23 @@ __device__ inline int bf_pair_f32(const BfEnvF32& v, const Block4& b, float* cps
         // pi U1 / 2 in revolutions, U1 = ((a >> 9) + 1/2) 2^-23 (exact)
         const float q = fmaf((float)(a >> 9), 1.0f / 33554432.0f, 1.0f / 67108864.0f);
         const float sh = __builtin_amdgcn_sinf(q), ch = __builtin_amdgcn_cosf(q);
-        const float sh2 = sh * sh, ch2 = ch * ch;
-        const float inv = __builtin_amdgcn_rcpf(v.half_rm1 + ch2);
-        const float g = v.rm1 * sh2 * inv;
-        const float c = fmaf(v.kappa, g, v.krm1);
+        const float sh2 = sh * sh;
+        ch2[half] = ch * ch;
+        inv[half] = __builtin_amdgcn_rcpf(v.half_rm1 + ch2[half]);
+        g[half] = v.rm1 * sh2 * inv[half];
+        const float c = fmaf(v.kappa, g[half], v.krm1);
         const float u2 = fmaf((float)(bb >> 9), 1.0f / 8388608.0f, 1.0f / 16777216.0f);
-        bool acc = c * (2.0f - c) - u2 > 0.0f;
-        if (!acc) acc = __builtin_amdgcn_logf(c * __builtin_amdgcn_rcpf(u2)) >= (c - 1.0f) * 1.44269504f;
-        if (acc) {
-            const float h = v.rp1 * ch2 * inv;
-            const float sp = __builtin_amdgcn_sqrtf(g * h);
-            *cpsi = g <= 1.0f ? 1.0f - g : h - 1.0f;
-            *spsi = __uint_as_float(__float_as_uint(sp) ^ (a << 31));
-            return half + 1;
-        }
+        const bool quick = c * (2.0f - c) - u2 > 0.0f;
+        const bool slow = __builtin_amdgcn_logf(c * __builtin_amdgcn_rcpf(u2)) >= (c - 1.0f) * 1.44269504f;
+        acc[half] = quick || slow;
     }
-    return 0;
+    if (!acc[0] && !acc[1]) return 0;
+    const float gg = acc[0] ? g[0] : g[1], cc = acc[0] ? ch2[0] : ch2[1], ii = acc[0] ? inv[0] : inv[1];
+    const float h = v.rp1 * cc * ii;
+    const float sp = __builtin_amdgcn_sqrtf(gg * h);
+    *cpsi = gg <= 1.0f ? 1.0f - gg : h - 1.0f;
+    *spsi = __uint_as_float(__float_as_uint(sp) ^ ((acc[0] ? b.w[0] : b.w[2]) << 31));
+    return acc[0] ? 1 : 2;
 }
 
 __device__ inline void vonmises_cs_f32(float kappa, uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1, uint32_t domain,

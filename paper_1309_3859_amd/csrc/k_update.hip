@@ -6,8 +6,8 @@
 // as phases, even then odd sites, in place).
 //
 // One work-item per link of the phase (direction mu, parity p, not frozen),
-// every ensemble of the batch in the same launch: work-group b reads its
-// ensemble, its block index within that ensemble and the geometry from one
+// every ensemble of the batch in the same launch: work-group b reads its time
+// slice, its stretch of that slice and the geometry from one
 // record (UpdBlock), the records dealt to the 8 XCDs in contiguous stretches
 // and, within an ensemble, ordered time slice fastest (set by the host).
 // The staple of a link reads 18 angles: 12 of the other parity (coalesced,
@@ -15,11 +15,11 @@
 // phase, so the update is in place.  The all-link kernels below (start,
 // health check, canonical gather and scatter, plaquettes) find their ensemble
 // from block start offsets or a fixed number of blocks per ensemble.
-#include "device_common.hpp"
 #include <hip/hip_ext.h>
 
 #include <mutex>
 
+#include "link_update.hpp"
 #include "u1ml_internal.hpp"
 
 namespace u1ml {
@@ -42,287 +42,157 @@ struct LinkView {
     }
 };
 
-// kind 0: heatbath theta = wrap(psi - arg A), psi ~ vonMises(0, beta |A|);
-// kind 1: overrelaxation theta = wrap(-theta - 2 arg A) (unchanged if A = 0);
-// kind 2: Metropolis (the paper's update), one hit per link.
-// Staple sum A = sum_{nu != mu} exp(i phi_f) + exp(i phi_b), nu ascending,
-// forward before backward, phi_f = v0 - v1 - v2, phi_b = v3 - v4 - v5.
-//
-// Heatbath: every lane makes the first two rejection attempts (one Philox
-// block); the links still pending (about 1 in 10) are compacted, in lane
-// order, into a queue in LDS and finished by consecutive threads, so a wave no
-// longer waits for its slowest lane.  A link's result depends only on its own
-// counters, so the queue changes no result.  A queue entry holds what the
-// link's final angle needs besides its deviate: the staple sum A, theta =
-// arg(e^{i psi} conj A) by one atan2 (wrap(psi - arg A) up to rounding).
+// Byte offsets, within a time slice of one (direction, parity) array, of a
+// site and its six spatial neighbours, for the link whose site has half index
+// i in the slice (xh + Nx/2 (y + Ny z), x = 2 xh + odd).  The x step of an odd
+// (even) x crosses to the next (previous) half index or stays; the others move
+// by whole rows.  Offsets are those of the neighbour, so two of them combine
+// as p + m - c.
 template <typename real>
-struct RetryQ;
-template <>
-struct RetryQ<float> {
-    float kappa, ar, ai;
-    unsigned lid, off;
+struct SliceNb {
+    unsigned c, p[3], m[3];
+    int odd_mask;  // all ones where x is odd
+
+    // work-item tid of work-group record B, link parity par
+    __device__ inline SliceNb(const UpdBlock& B, int tid, int par)
+    {
+        constexpr int w = sizeof(real);
+        const int rx = B.x0 + tid;
+        const int row = fdiv_small(rx, B.inv_nxh);
+        const int xh = rx - __mul24(row, B.nxh);
+        const int ry = B.y0 + row;
+        const int dz = fdiv_small(ry, B.inv_ny);
+        const int y = ry - __mul24(dz, B.ny);
+        odd_mask = ((B.zt + par + y + dz) << 31) >> 31;
+        const int sy = B.nxh * w, sz = sy * B.ny, st = B.slice * w;
+        const int v = (B.i0 + tid) * w;
+        c = (unsigned)v;
+        p[0] = (unsigned)(v + (odd_mask & (xh == B.nxh - 1 ? w - sy : w)));
+        m[0] = (unsigned)(v + (~odd_mask & (xh == 0 ? sy - w : -w)));
+        p[1] = (unsigned)(v + (y == B.ny - 1 ? sy - sz : sy));
+        m[1] = (unsigned)(v + (y == 0 ? sz - sy : -sy));
+        p[2] = (unsigned)(v + (v >= st - sz ? sz - st : sz));
+        m[2] = (unsigned)(v + (v < sz ? st - sz : -sz));
+    }
 };
-template <>
-struct RetryQ<double> {
-    double kappa, ar, ai;
-    unsigned lid, off;
-};
 
-// the link's new angle from an accepted deviate
-__device__ inline float hb_angle(const RetryQ<float>& q, float cp, float sp)
+// The six angles of the two staples of link (x, MU) in the plane (MU, NU):
+//   v[0..2] = th_nu(x+mu), th_mu(x+nu), th_nu(x)          (forward)
+//   v[3..5] = th_nu(x-nu), th_nu(x+mu-nu), th_mu(x-nu)    (backward)
+// for a link of parity p in time slice t0 (byte offsets t0, tp, tm of the
+// slice and its neighbours); vhb bytes per (direction, parity) array.
+template <typename real, int MU, int NU>
+__device__ inline void gather_slice(const LinkBuf<real>& lb, unsigned vhb, unsigned t0, unsigned tp, unsigned tm,
+                                    const SliceNb<real>& nb, int p, real* v)
 {
-    const float th = atan2_fast(sp * q.ar - cp * q.ai, cp * q.ar + sp * q.ai);
-    return th >= 3.14159265f ? -3.14159265f : th;
-}
-// FP64: e^{i theta} = e^{i psi} conj(A) / |A| with e^{i psi} = f + i sin psi,
-// sin psi = +-sqrt((1 - f)(1 + f)) (1 - f and 1 + f exact where they
-// cancel), so one atan2 gives theta = psi - arg A in [-pi, pi)
-__device__ inline double hb_angle(const RetryQ<double>& q, double cp, double sp)
-{
-    const double th = M<double>::atan2_(sp * q.ar - cp * q.ai, cp * q.ar + sp * q.ai);
-    return th >= M<double>::pi ? -M<double>::pi : th;
+    const unsigned pp = (unsigned)p * vhb, pq = vhb - pp;
+    const unsigned nu_p = NU * 2 * vhb + pp, nu_q = NU * 2 * vhb + pq, mu_q = MU * 2 * vhb + pq;
+    // slice and offset of x + mu, x + nu, x - nu, x + mu - nu
+    const unsigned s_pm = MU == 3 ? tp : t0, s_pn = NU == 3 ? tp : t0, s_mn = NU == 3 ? tm : t0;
+    const unsigned s_pmmn = MU == 3 ? tp : (NU == 3 ? tm : t0);
+    const unsigned o_pm = MU == 3 ? nb.c : nb.p[MU % 3], o_pn = NU == 3 ? nb.c : nb.p[NU % 3];
+    const unsigned o_mn = NU == 3 ? nb.c : nb.m[NU % 3];
+    const unsigned o_pmmn = MU == 3 ? o_mn : (NU == 3 ? o_pm : o_pm + (o_mn - nb.c));
+    v[0] = lb.ld(o_pm, nu_q + s_pm);
+    v[1] = lb.ld(o_pn, mu_q + s_pn);
+    v[2] = lb.ld(nb.c, nu_p + t0);
+    v[3] = lb.ld(o_mn, nu_q + s_mn);
+    v[4] = lb.ld(o_pmmn, nu_p + s_pmmn);
+    v[5] = lb.ld(o_mn, mu_q + s_mn);
 }
 
-// attempts of one Philox block; true with the new angle if one accepted
-__device__ inline bool hb_block(const RetryQ<float>& q, const BfEnvF32& v, const Block4& b, float* th)
-{
-    float cp, sp;
-    if (!bf_pair_f32(v, b, &cp, &sp)) return false;
-    *th = hb_angle(q, cp, sp);
-    return true;
-}
-__device__ inline bool hb_block(const RetryQ<double>& q, double r, const Block4& b, double* th)
-{
-    double f;
-    bool neg;
-    if (!bf_pair_f64(q.kappa, r, b, &f, &neg)) return false;
-    const double sp = M<double>::sqrt_((1.0 - f) * (1.0 + f));
-    *th = hb_angle(q, f, neg ? -sp : sp);
-    return true;
-}
-__device__ inline BfEnvF32 hb_env(const RetryQ<float>& q) { return bf_env_f32(q.kappa); }
-__device__ inline double hb_env(const RetryQ<double>& q) { return bf_r_f64(q.kappa); }
-
+// One work-item per link of one checkerboard phase.  What bounds it: memory on
+// lattices beyond the caches, launch and instruction latency on small ones (a
+// dependent launch costs 1.85 us with 18 loads and a store in it; each further
+// dependent instruction 2 to 3 ns).  So the index arithmetic is kept short: a
+// work-group lies in one time slice, t and everything that follows from it is
+// scalar, and the vector part of an address is one byte offset within the
+// slice.
 template <typename real, int KIND, int MU>
 __global__ void __launch_bounds__(1024) k_update(const EnsDesc* __restrict__ ens, const UpdBlock* __restrict__ blocks,
                                                  real* __restrict__ links, const uint32_t* __restrict__ upd,
-                                                 int pass_offset, int parity, int tau, float inv_tm1)
+                                                 int pass_offset, int parity, double metro_delta)
 {
-    constexpr bool kQueue = KIND == 0;
-    // a padding block of the XCD-aware order carries a block index past its
-    // ensemble's links, so all its work-items are inactive (no branch on the
-    // record, whose fields then all load at once)
-    const UpdBlock B = blocks[blockIdx.x];
-    const EnsDesc& E = ens[B.e];  // coupling, key and step: read after the link loads are issued
-    const Geo g{B.nx, B.ny, B.nz, B.nt, B.nxh, B.nxh * B.ny, B.nxh * B.ny * B.nz};
-    const bool masked = (MU < 3) && (tau > 1);
-    const int slice = g.st;
-    const int item = B.blk * (int)blockDim.x + (int)threadIdx.x;
-    const bool active = item < B.n_items;
-    if (!kQueue && !active) return;
-    real* lb = links + B.link_off;
-    const unsigned vh = (unsigned)B.vh;
-    bool pending = false;
-    RetryQ<real> mine{};
-    if (active) {
-        const int j = fdiv(item, slice, B.inv_slice);
-        const int rem = item - (int)__umul24(j, slice);
-        int t = j;
-        if (masked) {
-            if (tau == 2) {  // uniform: the thinnest slabs skip the division
-                t = 2 * j + 1;
-            } else {
-                const int jt = fdiv(j, tau - 1, inv_tm1);
-                t = jt * tau + 1 + (j - jt * (tau - 1));
-            }
-        }
-        const int yz = fdiv(rem, g.sy, B.inv_nxh);
-        const int xh = rem - (int)__umul24(yz, g.sy);
-        const int z = fdiv(yz, g.ny, B.inv_ny);
-        const int y = yz - (int)__umul24(z, g.ny);
-        const int x = 2 * xh + ((y + z + t + parity) & 1);
-        const Site c{x, y, z, t, (int)(__umul24(g.sy, yz) + __umul24(g.st, t))};
+    constexpr unsigned w = sizeof(real);
+    extern __shared__ __align__(16) unsigned char queue_bytes[];
+    // the whole record before the first branch: its loads are one round trip
+    UpdBlock B = blocks[blockIdx.x];
+    asm volatile("" : "+s"(B.i0), "+s"(B.x0), "+s"(B.t0), "+s"(B.nxh), "+s"(B.inv_nxh), "+s"(B.link_off));
+    const EnsDesc& E = ens[B.e];
+    const int tid = (int)threadIdx.x, n = B.slice - B.i0;
+    if ((tid & ~63) >= n) return;  // no link in this wave
+    const bool active = tid < n;
+    const SliceNb<real> nb(B, active ? tid : 0, parity);
+    const LinkBuf<real> lb(links + B.link_off);
+    const unsigned vhb = (unsigned)B.vh * w, t0 = B.t0 * w, tp = B.tp * w, tm = B.tm * w;
 
-        // every load of the update is issued before any arithmetic
-        const Site cpm = mv<MU, +1>(c, g);
-        real v[3][6];
-        gather_plane<real, MU, Nu<MU, 0>::v>(lb, vh, g, c, cpm, parity, v[0]);
-        gather_plane<real, MU, Nu<MU, 1>::v>(lb, vh, g, c, cpm, parity, v[1]);
-        gather_plane<real, MU, Nu<MU, 2>::v>(lb, vh, g, c, cpm, parity, v[2]);
-        const unsigned self = ((MU * 2 + parity) * vh + (unsigned)(xh + c.hrow)) * (unsigned)sizeof(real);
-        real old = real(0);
-        if (KIND != 0) old = ldo(lb, self);
-        real* dst = reinterpret_cast<real*>(reinterpret_cast<char*>(lb) + self);
+    // every load of the update is issued before any arithmetic
+    real v[3][6];
+    gather_slice<real, MU, Nu<MU, 0>::v>(lb, vhb, t0, tp, tm, nb, parity, v[0]);
+    gather_slice<real, MU, Nu<MU, 1>::v>(lb, vhb, t0, tp, tm, nb, parity, v[1]);
+    gather_slice<real, MU, Nu<MU, 2>::v>(lb, vhb, t0, tp, tm, nb, parity, v[2]);
+    const unsigned self = (MU * 2 + (unsigned)parity) * vhb + t0;
+    real old = real(0);
+    if (KIND != 0) old = lb.ld(nb.c, self);
 
-        // the first Philox block depends only on the link's id and the counter:
-        // formed here, it runs while the link angles are still in flight
-        // canonical site x + Nx (y + Ny (z + Nz t)) = x + 2 hrow, so no multiplication
-        const uint32_t lid = (uint32_t)MU + 4u * (uint32_t)x + 8u * (uint32_t)c.hrow;
-        const uint32_t ctr = upd[B.res_index] + (uint32_t)pass_offset;
-        Block4 b0;
-        if (kQueue || KIND == 2)
-            b0 = philox4x32_10(lid, ctr, 0u, KIND == 2 ? DOM_METRO : DOM_HB, E.seed, E.key_id);
+    // the first Philox block depends only on the link's id and the counter:
+    // formed here, it runs while the link angles are still in flight
+    // canonical site x + Nx (y + Ny (z + Nz t)) = 2 (i + t0) + odd
+    const uint32_t lid = (uint32_t)MU + 8u * ((uint32_t)(B.i0 + tid) + B.t0) + (nb.odd_mask & 4u);
+    const uint32_t ctr = KIND == 1 ? 0u : upd[B.e] + (uint32_t)pass_offset;
+    Block4 b0{};
+    if (KIND != 1) b0 = philox4x32_10(lid, ctr, 0u, KIND == 2 ? DOM_METRO : DOM_HB, E.seed, E.key_id);
 
-        real ar, ai;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            real s, co;
-            M<real>::sincos_(v[k][0] - v[k][1] - v[k][2], &s, &co);
-            if (k == 0) {
-                ar = co;
-                ai = s;
-            } else {
-                ar += co;
-                ai += s;
-            }
-            M<real>::sincos_(v[k][3] - v[k][4] - v[k][5], &s, &co);
-            ar += co;
-            ai += s;
-        }
-        if constexpr (KIND == 0) {
-            const real R = M<real>::sqrt_(ar * ar + ai * ai);
-            const real kappa = (real)E.beta * R;
-            RetryQ<real> q;
-            real th;
-            bool done = true;
-            if constexpr (sizeof(real) == 4) {
-                // theta = psi - arg A as one angle: exp(i theta) is proportional to
-                // exp(i psi) conj(A), so a single atan2 replaces arccos, atan2 and wrap
-                q = RetryQ<float>{kappa, ar, ai, lid, self};
-                if (kappa == 0.0f) {
-                    // psi uniform from attempt 0: pi (2 U1 - 1), in revolutions U1 - 1/2
-                    // (with A = 0 as well, theta = psi)
-                    const float rev = M<float>::u1(b0.w[0]) - 0.5f;
-                    if (R == 0.0f) q.ar = 1.0f;
-                    th = hb_angle(q, __builtin_amdgcn_cosf(rev), __builtin_amdgcn_sinf(rev));
-                } else {
-                    done = hb_block(q, bf_env_f32(kappa), b0, &th);
-                }
-            } else {
-                q = RetryQ<double>{kappa, ar, ai, lid, self};
-                if (kappa == 0.0) {
-                    // psi uniform from attempt 0: pi (2 U1 - 1) (with A = 0 as well, theta = psi)
-                    double sp, cp;
-                    sincos_bounded(M<double>::pi * (2.0 * M<double>::u1(b0.w[0]) - 1.0), &sp, &cp);
-                    if (R == 0.0) q.ar = 1.0;
-                    th = hb_angle(q, cp, sp);
-                } else {
-                    done = hb_block(q, bf_r_f64(kappa), b0, &th);
-                }
-            }
-            if (done) {
-                *dst = th;
-            } else {
-                pending = true;
-                mine = q;
-            }
-        } else if (KIND == 2) {
-            // Metropolis: theta' = theta + delta (2 U1 - 1), accepted when
-            // U2 < exp(beta (Re(e^{i theta'} A) - Re(e^{i theta} A)))
-            const Block4& b = b0;
-            using m = M<real>;
-            const real thn = wrap_angle<real>(old + (real)E.metro_delta * (real(2) * m::u1(b.w[0]) - real(1)));
-            real sn, cn, so, co;
-            m::sincos_(thn, &sn, &cn);
-            m::sincos_(old, &so, &co);
-            const real dl = (real)E.beta * ((ar * cn - ai * sn) - (ar * co - ai * so));
-            if (dl >= real(0) || m::u2(b.w[1]) < m::exp_(dl)) *dst = thn;
-        } else {
-            // stored unconditionally (A = 0 writes the old angle back), so the
-            // load of the old angle is issued with the staple loads
-            const real phiA = M<real>::atan2_(ai, ar);
-            const real th = wrap_angle<real>(-old - real(2) * phiA);
-            *dst = (ar == real(0) && ai == real(0)) ? old : th;
-        }
-    }
-    if constexpr (kQueue) {
-        extern __shared__ __align__(16) unsigned char queue_bytes[];
-        RetryQ<real>* queue = reinterpret_cast<RetryQ<real>*>(queue_bytes);
-        __shared__ int wave_count[16];
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        const unsigned long long m = __ballot(pending);
-        if (lane == 0) wave_count[wave] = __popcll(m);
-        __syncthreads();
-        int base = 0, total = 0;
-        const int nw = (blockDim.x + 63) >> 6;
-        for (int w = 0; w < nw; ++w) {
-            base += w < wave ? wave_count[w] : 0;
-            total += wave_count[w];
-        }
-        if (pending) {
-            const int pos = base + __popcll(m & ((1ull << lane) - 1ull));
-            queue[pos] = mine;
-        }
-        __syncthreads();
-        const uint32_t ctr = upd[B.res_index] + (uint32_t)pass_offset;
-        for (int i = threadIdx.x; i < total; i += blockDim.x) {
-            const RetryQ<real> r = queue[i];
-            const auto env = hb_env(r);
-            real th = real(0);
-            bool done = false;
-            // attempts 2 .. 65535 (blocks 1 .. 32767); past the cap the link keeps its angle
-            for (uint32_t jp = 1; jp < 32768u && !done; ++jp)
-                done = hb_block(r, env, philox4x32_10(r.lid, ctr, jp, DOM_HB, E.seed, E.key_id), &th);
-            if (done) *reinterpret_cast<real*>(reinterpret_cast<char*>(lb) + r.off) = th;
-        }
-    }
+    HbQ<real>* wave_q = reinterpret_cast<HbQ<real>*>(queue_bytes) + (tid & ~63);
+    const real th = update_link<real, KIND>(active, v, b0, lid, ctr, E.beta, E.seed, E.key_id, metro_delta, wave_q,
+                                            [&] { return KIND == 0 ? lb.ld(nb.c, self) : old; });
+    if (active) lb.st(th, nb.c, self);
 }
 
 // With a start/stop event pair the launch goes through hipExtLaunchKernelGGL,
 // whose events take the dispatch's own begin and end timestamps.
 template <typename real, int KIND, int MU>
-static void launch_update_mu(dim3 g, dim3 b, size_t lds, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1,
-                             const EnsDesc* d_ens, const UpdBlock* d_bmap, real* links, const uint32_t* d_upd,
-                             int pass_offset, int parity, int tau, float inv_tm1)
+static void launch_update_mu(const UpdLaunch& a)
 {
-    if (ev0)
-        hipExtLaunchKernelGGL((k_update<real, KIND, MU>), g, b, lds, st, ev0, ev1, 0, d_ens, d_bmap, links, d_upd,
-                              pass_offset, parity, tau, inv_tm1);
+    const dim3 g(a.total_blocks), b(a.block);
+    const size_t lds = KIND == 0 ? sizeof(HbQ<real>) * b.x : 0;
+    if (a.ev_start)
+        hipExtLaunchKernelGGL((k_update<real, KIND, MU>), g, b, lds, a.st, a.ev_start, a.ev_stop, 0, a.d_ens,
+                              a.d_blocks, (real*)a.links, a.d_upd, a.pass_offset, a.parity, a.metro_delta);
     else
-        hipLaunchKernelGGL((k_update<real, KIND, MU>), g, b, lds, st, d_ens, d_bmap, links, d_upd, pass_offset,
-                           parity, tau, inv_tm1);
+        hipLaunchKernelGGL((k_update<real, KIND, MU>), g, b, lds, a.st, a.d_ens, a.d_blocks, (real*)a.links,
+                           a.d_upd, a.pass_offset, a.parity, a.metro_delta);
 }
 
 template <typename real, int KIND>
-static void launch_update_t(dim3 g, dim3 b, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, const EnsDesc* d_ens,
-                            const UpdBlock* d_bmap, real* links, const uint32_t* d_upd, int pass_offset, int mu,
-                            int parity, int tau, float inv_tm1)
+static void launch_update_t(const UpdLaunch& a)
 {
-    const size_t lds = KIND == 0 ? sizeof(RetryQ<real>) * b.x : 0;
-    switch (mu) {
-    case 0: launch_update_mu<real, KIND, 0>(g, b, lds, st, ev0, ev1, d_ens, d_bmap, links, d_upd, pass_offset, parity, tau, inv_tm1); break;
-    case 1: launch_update_mu<real, KIND, 1>(g, b, lds, st, ev0, ev1, d_ens, d_bmap, links, d_upd, pass_offset, parity, tau, inv_tm1); break;
-    case 2: launch_update_mu<real, KIND, 2>(g, b, lds, st, ev0, ev1, d_ens, d_bmap, links, d_upd, pass_offset, parity, tau, inv_tm1); break;
-    default: launch_update_mu<real, KIND, 3>(g, b, lds, st, ev0, ev1, d_ens, d_bmap, links, d_upd, pass_offset, parity, tau, inv_tm1); break;
+    switch (a.mu) {
+    case 0: launch_update_mu<real, KIND, 0>(a); break;
+    case 1: launch_update_mu<real, KIND, 1>(a); break;
+    case 2: launch_update_mu<real, KIND, 2>(a); break;
+    default: launch_update_mu<real, KIND, 3>(a); break;
     }
 }
 
-hipError_t launch_update(const EnsDesc* d_ens, const UpdBlock* d_bmap, int total_blocks, int block, int precision,
-                         void* links, const uint32_t* d_upd, int pass_offset, int kind, int mu, int parity, int tau,
-                         hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+template <typename real>
+static void launch_update_r(const UpdLaunch& a)
 {
-    if (total_blocks <= 0) return hipSuccess;
-    if ((ev_start == nullptr) != (ev_stop == nullptr)) return hipErrorInvalidValue;
-    const dim3 g(total_blocks), b(block);
-    const float inv_tm1 = tau > 1 ? 1.0f / (float)(tau - 1) : 1.0f;
-    if (kind < 0 || kind > 2) return hipErrorInvalidValue;
-    if (precision == 0) {
-        double* lk = (double*)links;
-        if (kind == 0)
-            launch_update_t<double, 0>(g, b, st, ev_start, ev_stop, d_ens, d_bmap, lk, d_upd, pass_offset, mu, parity, tau, inv_tm1);
-        else if (kind == 1)
-            launch_update_t<double, 1>(g, b, st, ev_start, ev_stop, d_ens, d_bmap, lk, d_upd, pass_offset, mu, parity, tau, inv_tm1);
-        else
-            launch_update_t<double, 2>(g, b, st, ev_start, ev_stop, d_ens, d_bmap, lk, d_upd, pass_offset, mu, parity, tau, inv_tm1);
-    } else {
-        float* lk = (float*)links;
-        if (kind == 0)
-            launch_update_t<float, 0>(g, b, st, ev_start, ev_stop, d_ens, d_bmap, lk, d_upd, pass_offset, mu, parity, tau, inv_tm1);
-        else if (kind == 1)
-            launch_update_t<float, 1>(g, b, st, ev_start, ev_stop, d_ens, d_bmap, lk, d_upd, pass_offset, mu, parity, tau, inv_tm1);
-        else
-            launch_update_t<float, 2>(g, b, st, ev_start, ev_stop, d_ens, d_bmap, lk, d_upd, pass_offset, mu, parity, tau, inv_tm1);
+    switch (a.kind) {
+    case 0: launch_update_t<real, 0>(a); break;
+    case 1: launch_update_t<real, 1>(a); break;
+    default: launch_update_t<real, 2>(a); break;
     }
+}
+
+hipError_t launch_update(const UpdLaunch& a)
+{
+    if (a.total_blocks <= 0) return hipSuccess;
+    if ((a.ev_start == nullptr) != (a.ev_stop == nullptr) || a.kind < 0 || a.kind > 2) return hipErrorInvalidValue;
+    if (a.precision == 0)
+        launch_update_r<double>(a);
+    else
+        launch_update_r<float>(a);
     return hipGetLastError();
 }
 

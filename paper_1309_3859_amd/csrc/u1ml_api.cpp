@@ -425,8 +425,8 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
         const size_t nsig = (size_t)E.ns[0] * E.ns[1] * E.ns[2];
         const size_t V = nsig * E.nt;
         maxV = std::max(maxV, V);
-        blocks64 += (V / 2 + 63) / 64;
-        blocks64 += 8;  // padding of the XCD-aware block order
+        blocks64 += (nsig / 2 + 63) / 64 * E.nt;  // update work-groups lie in one time slice
+        blocks64 += 8;                            // padding of the XCD-aware block order
         const size_t si = E.nt / P.tau_i, so = E.nt / P.tau_o;
         size_t v, t;
         // links: 4 V words, padded to 256 bytes
@@ -630,7 +630,7 @@ struct Lane {
     std::vector<int> idx;        // problem indices of the lane's ensembles
     std::vector<EnsDesc> h_ens;  // their descriptors, lane order
     std::vector<int> h_bstart;   // kNumTabs x (n + 1)
-    std::vector<UpdBlock> h_bmap;  // per-block update records, kUpdateClasses x bmap_stride
+    std::vector<UpdBlock> h_bmap[kUpdateClasses];  // per-block update records of each class
     std::vector<int2> h_mmap;    // measurement block -> (lane ensemble, block)
     EnsDesc* d_ens = nullptr;
     int* d_bstart = nullptr;
@@ -732,19 +732,18 @@ void build_update_tabs(const u1ml_ctx* c, Lane& L)
 {
     const Problem& P = c->P;
     const int n = L.n;
-    std::vector<long long> it0(n), it1(n), it2(n), it3(n);
-    for (int e = 0; e < n; ++e) {
-        const EnsDesc& E = L.h_ens[e];
-        const long long slice = (long long)E.nxh * E.ny * E.nz;
-        it0[e] = (long long)E.vh;
-        it1[e] = (long long)E.vh;
-        it2[e] = slice * (P.tau_i > 1 ? E.nt - E.nt / P.tau_i : E.nt);
-        it3[e] = slice * (P.tau_o > 1 ? E.nt - E.nt / P.tau_o : E.nt);
+    // time slices whose links a class updates: temporal, spatial full, spatial inner tau, spatial outer tau
+    const int skip[kUpdateClasses] = {0, 0, P.tau_i > 1 ? P.tau_i : 0, P.tau_o > 1 ? P.tau_o : 0};
+    std::vector<long long> items(n);
+    for (int cls = 0; cls < kUpdateClasses; ++cls) {
+        for (int e = 0; e < n; ++e) {
+            const EnsDesc& E = L.h_ens[e];
+            const long long slice = (long long)E.nxh * E.ny * E.nz;
+            const long long ns = skip[cls] ? E.nt - E.nt / skip[cls] : E.nt;
+            items[e] = ns * ((slice + c->block - 1) / c->block);
+        }
+        build_tab(L, kTabUpd + cls, items, 1);
     }
-    build_tab(L, kTabUpd + 0, it0, c->block);
-    build_tab(L, kTabUpd + 1, it1, c->block);
-    build_tab(L, kTabUpd + 2, it2, c->block);
-    build_tab(L, kTabUpd + 3, it3, c->block);
     // Blocks are dealt to the 8 XCDs round-robin (block b runs on XCD b mod 8),
     // and each XCD has its own L2.  Logical block L(b) = (b mod 8) per + b / 8
     // gives every XCD one contiguous stretch of the lattice, so neighbouring
@@ -752,50 +751,45 @@ void build_update_tabs(const u1ml_ctx* c, Lane& L)
     // several.  Launches have 8 per blocks; entries past the end are idle.
     UpdBlock pad;
     std::memset(&pad, 0, sizeof pad);
-    pad.e = -1;
-    L.h_bmap.assign((size_t)kUpdateClasses * L.bmap_stride, pad);
-    const std::vector<long long>* items[kUpdateClasses] = {&it0, &it1, &it2, &it3};
+    for (auto& m : L.h_bmap) m.clear();
     for (int cls = 0; cls < kUpdateClasses; ++cls) {
-        const int* b = &L.h_bstart[(size_t)(kTabUpd + cls) * (n + 1)];
-        const int total = b[n];
+        const int total = L.h_bstart[(size_t)(kTabUpd + cls) * (n + 1) + n];
         const int per = (total + kXcds - 1) / kXcds;
-        std::vector<UpdBlock> logical(total);
+        std::vector<UpdBlock> logical;
+        logical.reserve(total);
         for (int e = 0; e < n; ++e) {
             const EnsDesc& E = L.h_ens[e];
             UpdBlock r = pad;
-            r.e = e;
-            r.nx = E.nx;
-            r.ny = E.ny;
-            r.nz = E.nz;
-            r.nt = E.nt;
+            r.slice = E.nxh * E.ny * E.nz;
             r.nxh = E.nxh;
+            r.ny = E.ny;
             r.vh = E.vh;
-            r.inv_slice = E.inv_slice;
             r.inv_nxh = E.inv_nxh;
             r.inv_ny = E.inv_ny;
-            r.res_index = E.res_index;
+            r.e = E.res_index;
             r.link_off = E.link_off;
-            r.n_items = (int)(*items[cls])[e];
-            // Time slice fastest: when a slice of sites is a whole number of
-            // blocks, the blocks of one stretch of the slice at consecutive
-            // times follow each other, so the links a slice shares with the
-            // next one are reused while they are still in the XCD's L2.
-            const int nb = b[e + 1] - b[e];
-            const long long slice = (long long)E.nxh * E.ny * E.nz;
-            const int bps = slice % c->block == 0 ? (int)(slice / c->block) : 0;
-            const int ns = bps > 0 ? nb / bps : 0;
-            for (int k = 0; k < nb; ++k) {
-                r.blk = (ns > 1 && ns * bps == nb) ? (k % ns) * bps + k / ns : k;
-                logical[b[e] + k] = r;
-            }
+            // Time slice fastest: the blocks of one stretch of the slice at
+            // consecutive times follow each other, so the links a slice shares
+            // with the next one are reused while they are still in the XCD's L2.
+            for (r.i0 = 0; r.i0 < r.slice; r.i0 += c->block)
+                for (int t = 0; t < E.nt; ++t) {
+                    if (skip[cls] && t % skip[cls] == 0) continue;
+                    const int row = r.i0 / E.nxh;
+                    r.x0 = r.i0 % E.nxh;
+                    r.y0 = row % E.ny;
+                    r.zt = row / E.ny + t;
+                    r.t0 = (unsigned)t * (unsigned)r.slice;
+                    r.tp = (unsigned)((t + 1) % E.nt) * (unsigned)r.slice;
+                    r.tm = (unsigned)((t + E.nt - 1) % E.nt) * (unsigned)r.slice;
+                    logical.push_back(r);
+                }
         }
-        // padding blocks: the last ensemble's record with a block index past
-        // its links (every work-item inactive)
+        // padding blocks: a record that starts past its slice (every work-item inactive)
         UpdBlock idle = total > 0 ? logical[total - 1] : pad;
-        idle.blk = total > 0 ? b[n] - b[n - 1] : 0;
+        idle.i0 = idle.slice;
         for (int phys = 0; phys < per * kXcds; ++phys) {
             const int lg = (phys % kXcds) * per + phys / kXcds;
-            L.h_bmap[(size_t)cls * L.bmap_stride + phys] = lg < total ? logical[lg] : idle;
+            L.h_bmap[cls].push_back(lg < total ? logical[lg] : idle);
         }
         L.upd_grid[cls] = per * kXcds;
     }
@@ -854,12 +848,22 @@ void build_lane_tables(const u1ml_ctx* c, Lane& L)
         for (int k = b[e]; k < b[e + 1]; ++k) L.h_mmap.push_back(make_int2(e, k - b[e]));
 }
 
+hipError_t upload_update_tabs(const Lane& L)
+{
+    hipError_t e = hipSuccess;
+    for (int cls = 0; cls < kUpdateClasses && e == hipSuccess; ++cls)
+        if (!L.h_bmap[cls].empty())
+            e = hipMemcpy(L.d_bmap + (size_t)cls * L.bmap_stride, L.h_bmap[cls].data(),
+                          sizeof(UpdBlock) * L.h_bmap[cls].size(), hipMemcpyHostToDevice);
+    return e;
+}
+
 hipError_t upload_lane(const Lane& L)
 {
     const int ring0[4] = {0, 0, 0, 0};
     hipError_t e = hipMemcpy(L.d_ens, L.h_ens.data(), sizeof(EnsDesc) * L.n, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(L.d_bstart, L.h_bstart.data(), sizeof(int) * L.h_bstart.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(L.d_bmap, L.h_bmap.data(), sizeof(UpdBlock) * L.h_bmap.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = upload_update_tabs(L);
     if (e == hipSuccess && !L.h_mmap.empty())
         e = hipMemcpy(L.d_mmap, L.h_mmap.data(), sizeof(int2) * L.h_mmap.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(L.d_ring, ring0, sizeof ring0, hipMemcpyHostToDevice);
@@ -954,8 +958,8 @@ hipError_t enq_phase(u1ml_ctx* c, const Lane& L, hipStream_t st, int kind, int m
     bool ok;
     const int cls = update_class(c, mu, tau, &ok);
     if (!ok) return hipErrorInvalidValue;
-    return launch_update(L.d_ens, L.bmap_dev(cls), L.upd_grid[cls], c->block, c->P.precision, c->links, c->d_upd,
-                         pass_offset, kind, mu, parity, (mu < 3 && tau > 1) ? tau : 0, st, ev_start, ev_stop);
+    return launch_update(UpdLaunch{c->whole.d_ens, L.bmap_dev(cls), L.upd_grid[cls], c->block, c->P.precision, c->links, c->d_upd,
+                                   pass_offset, kind, mu, parity, c->P.metro_delta, st, ev_start, ev_stop});
 }
 
 hipError_t enq_pass(u1ml_ctx* c, const Lane& L, hipStream_t st, int kind, int tau, int pass_offset)
@@ -1746,7 +1750,7 @@ u1ml_status u1ml_set_block(u1ml_ctx* ctx, int block)
         if (!L->n) continue;
         build_update_tabs(ctx, *L);
         HIPCHK(ctx, hipMemcpy(L->d_bstart, L->h_bstart.data(), sizeof(int) * 4 * (L->n + 1), hipMemcpyHostToDevice));
-        HIPCHK(ctx, hipMemcpy(L->d_bmap, L->h_bmap.data(), sizeof(UpdBlock) * L->h_bmap.size(), hipMemcpyHostToDevice));
+        HIPCHK(ctx, upload_update_tabs(*L));
     }
     drop_graphs(ctx);
     return U1ML_OK;

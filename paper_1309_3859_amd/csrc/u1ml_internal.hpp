@@ -32,20 +32,19 @@ struct EnsDesc {
     long long cpl_off, opl_off;  // plane-major copies of one measurement's slab phases (double2) and O rows (real)
 };
 
-// One work-group of an update launch: its ensemble and block index within it
-// (a padding block of the XCD-aware order has an index past the ensemble's
-// links), the number of links of the ensemble that the launch's phase class
-// updates, and the geometry the update kernel needs before its loads, so that
-// one 64-byte scalar load replaces a block-map load followed by descriptor
-// loads.
+// One work-group of an update launch: a stretch of one time slice of one
+// ensemble, links i0 .. i0 + work-group size - 1 of the slice's Nx/2 Ny Nz (a
+// padding block of the XCD-aware order starts past them), with the geometry
+// its addresses need in one 64-byte scalar load.
 struct alignas(64) UpdBlock {
-    int e, blk;
-    int nx, ny, nz, nt, nxh, vh;
-    float inv_slice, inv_nxh, inv_ny;
-    int res_index;
+    int e;                 // the ensemble (problem order)
+    int i0;                // first link within the slice
+    int x0, y0;            // half index along x and y coordinate of link i0
+    int zt;                // z of link i0 plus t (parity)
+    unsigned t0, tp, tm;   // half indices of the slices t, t + 1, t - 1
+    int nxh, ny, slice, vh;
+    float inv_nxh, inv_ny;
     long long link_off;
-    int n_items;  // non-frozen links of one (direction, parity) of this class
-    int pad1;
 };
 static_assert(sizeof(UpdBlock) == 64, "UpdBlock is one 64-byte scalar load");
 
@@ -122,11 +121,20 @@ constexpr int kStaticPlaqEns = 32;  // allocation-free plaquettes: ensembles who
 // --- launchers (k_update.hip) ---
 hipError_t launch_init_links(const EnsDesc* d_ens, const int* d_bstart_all, int n_ens, int total_blocks, int precision,
                              void* links, int start, hipStream_t st);
-// d_blocks[b]: ensemble, block index within the ensemble and geometry of every block of the launch;
+// One checkerboard phase over the work-groups d_blocks[0 .. total_blocks);
 // ev_start/ev_stop (both or neither) record the dispatch's begin and end timestamps
-hipError_t launch_update(const EnsDesc* d_ens, const UpdBlock* d_blocks, int total_blocks, int block, int precision,
-                         void* links, const uint32_t* d_upd, int pass_offset, int kind, int mu, int parity, int tau,
-                         hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+struct UpdLaunch {
+    const EnsDesc* d_ens;  // problem order
+    const UpdBlock* d_blocks;
+    int total_blocks, block, precision;
+    void* links;
+    const uint32_t* d_upd;
+    int pass_offset, kind, mu, parity;
+    double metro_delta;
+    hipStream_t st;
+    hipEvent_t ev_start, ev_stop;
+};
+hipError_t launch_update(const UpdLaunch& a);
 hipError_t launch_health(const EnsDesc* d_ens, const int* d_bstart_all, int n_ens, int total_blocks, int precision,
                          const void* links, unsigned long long* d_count, hipStream_t st);
 hipError_t launch_plaquette(const EnsDesc* d_ens, int n_ens, int max_blocks_per_ens, int precision, const void* links,
