@@ -80,13 +80,15 @@ struct SliceNb {
 //   v[0..2] = th_nu(x+mu), th_mu(x+nu), th_nu(x)          (forward)
 //   v[3..5] = th_nu(x-nu), th_nu(x+mu-nu), th_mu(x-nu)    (backward)
 // for a link of parity p in time slice t0 (byte offsets t0, tp, tm of the
-// slice and its neighbours); vhb bytes per (direction, parity) array.
+// slice and its neighbours); vhb bytes per (direction, parity) array, src the
+// byte offset of each direction's current buffer.
 template <typename real, int MU, int NU>
-__device__ inline void gather_slice(const LinkBuf<real>& lb, unsigned vhb, unsigned t0, unsigned tp, unsigned tm,
-                                    const SliceNb<real>& nb, int p, real* v)
+__device__ inline void gather_slice(const LinkBuf<real>& lb, unsigned vhb, const unsigned* src, unsigned t0, unsigned tp,
+                                    unsigned tm, const SliceNb<real>& nb, int p, real* v)
 {
     const unsigned pp = (unsigned)p * vhb, pq = vhb - pp;
-    const unsigned nu_p = NU * 2 * vhb + pp, nu_q = NU * 2 * vhb + pq, mu_q = MU * 2 * vhb + pq;
+    const unsigned nu_p = NU * 2 * vhb + pp + src[NU], nu_q = NU * 2 * vhb + pq + src[NU];
+    const unsigned mu_q = MU * 2 * vhb + pq + src[MU];
     // slice and offset of x + mu, x + nu, x - nu, x + mu - nu
     const unsigned s_pm = MU == 3 ? tp : t0, s_pn = NU == 3 ? tp : t0, s_mn = NU == 3 ? tm : t0;
     const unsigned s_pmmn = MU == 3 ? tp : (NU == 3 ? tm : t0);
@@ -111,7 +113,8 @@ __device__ inline void gather_slice(const LinkBuf<real>& lb, unsigned vhb, unsig
 template <typename real, int KIND, int MU>
 __global__ void __launch_bounds__(1024) k_update(const EnsDesc* __restrict__ ens, const UpdBlock* __restrict__ blocks,
                                                  real* __restrict__ links, const uint32_t* __restrict__ upd,
-                                                 int pass_offset, int parity, double metro_delta)
+                                                 int pass_offset, int parity, unsigned src0, unsigned src1,
+                                                 unsigned src2, unsigned src3, double metro_delta)
 {
     constexpr unsigned w = sizeof(real);
     extern __shared__ __align__(16) unsigned char queue_bytes[];
@@ -125,13 +128,14 @@ __global__ void __launch_bounds__(1024) k_update(const EnsDesc* __restrict__ ens
     const SliceNb<real> nb(B, active ? tid : 0, parity);
     const LinkBuf<real> lb(links + B.link_off);
     const unsigned vhb = (unsigned)B.vh * w, t0 = B.t0 * w, tp = B.tp * w, tm = B.tm * w;
+    const unsigned src[4] = {src0, src1, src2, src3};
 
     // every load of the update is issued before any arithmetic
     real v[3][6];
-    gather_slice<real, MU, Nu<MU, 0>::v>(lb, vhb, t0, tp, tm, nb, parity, v[0]);
-    gather_slice<real, MU, Nu<MU, 1>::v>(lb, vhb, t0, tp, tm, nb, parity, v[1]);
-    gather_slice<real, MU, Nu<MU, 2>::v>(lb, vhb, t0, tp, tm, nb, parity, v[2]);
-    const unsigned self = (MU * 2 + (unsigned)parity) * vhb + t0;
+    gather_slice<real, MU, Nu<MU, 0>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[0]);
+    gather_slice<real, MU, Nu<MU, 1>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[1]);
+    gather_slice<real, MU, Nu<MU, 2>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[2]);
+    const unsigned self = (MU * 2 + (unsigned)parity) * vhb + src[MU] + t0;
     real old = real(0);
     if (KIND != 0) old = lb.ld(nb.c, self);
 
@@ -158,10 +162,12 @@ static void launch_update_mu(const UpdLaunch& a)
     const size_t lds = KIND == 0 ? sizeof(HbQ<real>) * b.x : 0;
     if (a.ev_start)
         hipExtLaunchKernelGGL((k_update<real, KIND, MU>), g, b, lds, a.st, a.ev_start, a.ev_stop, 0, a.d_ens,
-                              a.d_blocks, (real*)a.links, a.d_upd, a.pass_offset, a.parity, a.metro_delta);
+                              a.d_blocks, (real*)a.links, a.d_upd, a.pass_offset, a.parity, a.src[0], a.src[1], a.src[2],
+                           a.src[3], a.metro_delta);
     else
         hipLaunchKernelGGL((k_update<real, KIND, MU>), g, b, lds, a.st, a.d_ens, a.d_blocks, (real*)a.links,
-                           a.d_upd, a.pass_offset, a.parity, a.metro_delta);
+                           a.d_upd, a.pass_offset, a.parity, a.src[0], a.src[1], a.src[2],
+                           a.src[3], a.metro_delta);
 }
 
 template <typename real, int KIND>

@@ -4,9 +4,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <string>
 #include <vector>
 
@@ -41,9 +43,10 @@ struct Layout {
     size_t sz_wf, sz_gf, sz_sph, sz_spo, sz_facc, sz_saved, sz_cpl, sz_opl;
     // scratch sub-offsets (bytes from off_scr)
     size_t s_ens, s_obs, s_r, s_probe, s_comp, s_bstart, s_upd, s_ring, s_vpart, s_ppart, s_pout, s_count,
-        s_stage, s_bmap, s_mmap, s_prodpart, s_pgroup, s_gdesc, s_pblk;
+        s_stage, s_bmap, s_mmap, s_prodpart, s_pgroup, s_gdesc, s_pblk, s_prow, s_pmap[kPairClasses];
+    size_t off_alt;  // the other link buffer (both-parities updates)
     // the lanes' descriptors and tables (each sized for the whole batch)
-    size_t s_lens[4], s_lbstart[4], s_lbmap[4], s_lmmap[4], s_lring[4];
+    size_t s_lens[4], s_lbstart[4], s_lbmap[4], s_lmmap[4], s_lring[4], s_lpmap[4][kPairClasses];
     size_t bmap_stride;  // entries per update class (blocks of 64 threads)
     int n_bstart_tables;
 };
@@ -67,6 +70,12 @@ constexpr int kMaxLanes = 4;  // streams that sweeps and configurations are spre
 // FP64 phases gain about 2.5 % more from four (C4 on MI355X: FP32 8.50,
 // 8.43, 8.64 ms per configuration with 2, 3, 4 lanes; FP64 17.96, 17.78, 17.56)
 int default_lanes(int precision) { return precision == U1ML_FP64 ? 4 : 2; }
+
+// Tile of a both-parities launch (k_pair): core rows along y, z, t.
+struct PairTile {
+    int L[3] = {0, 0, 0};
+    long long blocks = 0;
+};
 
 struct Problem {
     int n_ens = 0;
@@ -99,6 +108,17 @@ struct Problem {
     int ins_ks_vec = 1;           // the vector kernel's slots per block
     bool ins_mfma_est = false;    // the matrix-core kernel is estimated faster (and applies)
     long long nd_cfg = 0;
+    // both-parities launches: per class whether sweeps use them, the ensembles' tiles, the work-group
+    // size; the row tables of every tile shape
+    bool pair_on[kPairClasses] = {};
+    int pair_block[kPairClasses] = {};
+    std::vector<PairTile> pair_tile[kPairClasses];
+    std::vector<PairRow> pair_rows;
+    std::map<std::array<int, 15>, int> pair_shape;  // shape -> first row
+
+    bool any_pair() const { return std::find(pair_on, pair_on + kPairClasses, true) != pair_on + kPairClasses; }
+    // time slices per slab whose links a class updates at thickness tau, and slabs (temporal or full: all, one)
+    int pair_tau(int cls) const { return cls == 9 || cls % 3 == 0 ? 0 : (cls % 3 == 1 ? tau_i : tau_o); }
 };
 
 // frame components whose plaquette spans the charge axis: E_par (P_{par t}),
@@ -327,6 +347,221 @@ long long body_launches(const Problem& P)
 // buffer and the launch all use this count
 int prod_groups(const Problem& P) { return (!P.spectral && !P.probes.empty()) ? (int)P.probes.size() : 1; }
 
+// --- both-parities launches (k_pair.hip) ----------------------------------
+// Core rows along one axis k (y, z, t) of a class: its extent, whether the
+// halo applies (not along mu, not across frozen layers, not where the tile is
+// the whole extent).
+struct PairGeo {
+    int mu, nxh, N[3], slabs;
+    int ext[3];  // lattice extents along y, z, t
+    bool masked;
+    bool halo(int k, int L) const { return k + 1 != mu && !(masked && k == 2) && L < N[k]; }
+    PairGeo(const u1ml_ensemble& E, int cls, int tau)
+        : mu(cls == 9 ? 3 : cls / 3), nxh(E.ns[0] / 2), slabs(tau > 1 ? E.nt / tau : 1), masked(tau > 1)
+    {
+        N[0] = E.ns[1];
+        N[1] = E.ns[2];
+        N[2] = masked ? tau - 1 : E.nt;
+        ext[0] = N[0];
+        ext[1] = N[1];
+        ext[2] = E.nt;
+    }
+    int rows(const int* L) const  // of a tile, with its halo
+    {
+        const int core = L[0] * L[1] * L[2];
+        int n = core;
+        for (int k = 0; k < 3; ++k)
+            if (halo(k, L[k])) n += 2 * (core / L[k]);
+        return n;
+    }
+    // what a tile's rows depend on: direction, lattice, core, and how far (up
+    // to the two steps its rows reach) the core lies from the lattice's ends
+    std::array<int, 15> shape(const int* o, const int* L) const
+    {
+        std::array<int, 15> key = {mu, masked, nxh};
+        for (int k = 0; k < 3; ++k) {
+            const int v[4] = {ext[k], L[k], std::min(o[k], 2), std::min(ext[k] - o[k] - L[k], 2)};
+            std::copy(v, v + 4, &key[3 + 4 * k]);
+        }
+        return key;
+    }
+};
+
+// The tile with the least time per SIMD: a work-group's waves run on one
+// compute unit (4 SIMDs), all work-groups of the batch (share: this ensemble's
+// part of it) on 1024; halo rows are updated once more for every tile they
+// touch, so large batches take large tiles and small ones many small tiles.
+PairTile pair_tile(const PairGeo& G, double share, int max_threads, double* waves)
+{
+    PairTile best;
+    double best_cost = 1e300;
+    for (int ly = 1; ly <= std::min(G.N[0], 64); ++ly)
+        for (int lz = 1; lz <= std::min(G.N[1], 64); ++lz)
+            for (int lt = G.masked ? G.N[2] : 1; lt <= std::min(G.N[2], 64); ++lt) {
+                const int L[3] = {ly, lz, lt};
+                const long long core = (long long)ly * lz * lt;
+                if (core * G.nxh > max_threads) break;
+                long long rows = core, tiles = G.slabs;
+                for (int k = 0; k < 3; ++k) {
+                    if (G.halo(k, L[k])) rows += 2 * core / L[k];
+                    tiles *= (G.N[k] + L[k] - 1) / L[k];
+                }
+                if (rows * G.nxh > max_threads) continue;
+                const double w1 = (double)((rows * G.nxh + 63) / 64), w2 = (double)((core * G.nxh + 63) / 64);
+                const double lat = std::max(1.0, w1 / 4), thr = (double)tiles / share * (w1 + w2) / 2 / 1024;
+                const double cost = std::max(lat, thr) + 0.1 * thr;
+                if (cost < best_cost) {
+                    best_cost = cost;
+                    std::copy(L, L + 3, best.L);
+                    best.blocks = tiles;
+                    *waves = (double)tiles * (w1 + w2) / 2;
+                }
+            }
+    return best;
+}
+
+// The rows of the tile with origin o (y, z, t) and core L; returns the first
+// row's index in the table.
+int pair_rows(Problem* P, const PairGeo& G, const int* o, const int* L)
+{
+    const std::array<int, 15> key = G.shape(o, L);
+    auto it = P->pair_shape.find(key);
+    if (it != P->pair_shape.end()) return it->second;
+    const int word = P->precision == U1ML_FP64 ? 8 : 4;
+    const int first = (int)P->pair_rows.size();
+    int halo[3], n = L[0] * L[1] * L[2];  // first halo row of axis k: the faces below, then the faces above
+    for (int k = 0; k < 3; ++k) {
+        halo[k] = n;
+        if (G.halo(k, L[k])) n += 2 * (L[0] * L[1] * L[2] / L[k]);
+    }
+    auto core = [&](const int* i) { return i[0] + L[0] * (i[1] + L[1] * i[2]); };
+    auto face = [&](int k, int up, const int* i) {
+        const int a = (k + 1) % 3, b = (k + 2) % 3;
+        return halo[k] + up * (L[a] * L[b]) + i[a] + L[a] * i[b];
+    };
+    // byte offset from the origin of the row displaced by d, and one step further along axis k
+    auto offset = [&](const int* d, int k, int step) {
+        int c[3];
+        for (int a = 0; a < 3; ++a) c[a] = (o[a] + d[a] + (a == k ? step : 0) + 2 * G.ext[a]) % G.ext[a] - o[a];
+        return word * G.nxh * (c[0] + G.ext[0] * (c[1] + G.ext[1] * c[2]));
+    };
+    auto fill = [&](PairRow* r, const int* d) {
+        r->c = offset(d, 0, 0);
+        r->p1 = offset(d, 0, 1), r->m1 = offset(d, 0, -1);
+        r->p2 = offset(d, 1, 1), r->m2 = offset(d, 1, -1);
+        r->p3 = offset(d, 2, 1), r->m3 = offset(d, 2, -1);
+        r->par = (d[0] + d[1] + d[2]) & 1;
+    };
+    P->pair_rows.resize(first + n, PairRow{});
+    PairRow* rows = &P->pair_rows[first];
+    int i[3];
+    for (i[2] = 0; i[2] < L[2]; ++i[2])
+        for (i[1] = 0; i[1] < L[1]; ++i[1])
+            for (i[0] = 0; i[0] < L[0]; ++i[0]) {
+                PairRow* r = &rows[core(i)];
+                fill(r, i);
+                unsigned* lds[3] = {&r->ly, &r->lz, &r->lt};
+                for (int k = 0; k < 3; ++k) {
+                    if (k + 1 == G.mu) continue;
+                    unsigned code[2];
+                    for (int up = 0; up < 2; ++up) {
+                        int j[3] = {i[0], i[1], i[2]};
+                        j[k] += up ? 1 : -1;
+                        int id;
+                        if (j[k] >= 0 && j[k] < L[k]) {
+                            id = core(j);
+                        } else if (G.masked && k == 2) {
+                            id = -1;
+                        } else if (!G.halo(k, L[k])) {
+                            j[k] = up ? 0 : L[k] - 1;
+                            id = core(j);
+                        } else {
+                            id = face(k, up, i);
+                            fill(&rows[id], j);
+                        }
+                        code[up] = id < 0 ? kPairFrozen : (unsigned)(id * G.nxh * word);
+                    }
+                    *lds[k] = code[1] << 16 | code[0];
+                }
+            }
+    P->pair_shape[key] = first;
+    return first;
+}
+
+// Every tile of ensemble k in class cls: f(origin, core extents), time
+// fastest (the tiles of one stretch of the slices at consecutive times follow
+// each other).
+template <typename F>
+void pair_for_tiles(const Problem& P, int cls, int k, F f)
+{
+    const int tau = P.pair_tau(cls);
+    const PairGeo G(P.ens[k], cls, tau);
+    const PairTile& T = P.pair_tile[cls][k];
+    for (int z = 0; z < G.N[1]; z += T.L[1])
+        for (int y = 0; y < G.N[0]; y += T.L[0])
+            for (int s = 0; s < G.slabs; ++s)
+                for (int t = 0; t < G.N[2]; t += T.L[2]) {
+                    const int L[3] = {std::min(T.L[0], G.N[0] - y), std::min(T.L[1], G.N[1] - z),
+                                      std::min(T.L[2], G.N[2] - t)};
+                    const int o[3] = {y, z, G.masked ? s * tau + 1 : t};
+                    f(o, L);
+                }
+}
+
+// Chooses, per class, whether sweeps update both parities in one launch, and
+// the tiles.  Two launches cost two launch times (about 1.9 us each) plus 0.4 us
+// per wave and SIMD of either parity; one costs one launch time plus 0.55 us per
+// wave and SIMD, halo included (its waves hold more, so fewer hide each other's
+// latency).  Measured: sweeps inside the slabs of one 24^3 x 8 lattice 69 us with
+// every class paired, 87 us with none (x, y, z 5 us each, t 3); two levels on
+// 32^3 x 8 94 against 101 ms a configuration; the 16 ensembles of 16^3 .. 32^3
+// 14.0 against 12.2 ms, 48^3 x 12 72.6 against 70.6, full sweeps of 24^3 x 8,
+// whose tiles have halos in t as well, 90 against 88 us: those stay single.
+void plan_pairs(Problem* P)
+{
+    double vol = 0.0;
+    size_t bytes = 0;
+    const size_t word = P->precision == U1ML_FP64 ? 8 : 4;
+    for (const u1ml_ensemble& E : P->ens) {
+        const double v = (double)E.ns[0] * E.ns[1] * E.ns[2] * E.nt;
+        vol += v;
+        bytes += (size_t)(4.0 * v) * word;
+    }
+    const int max_threads = P->precision == U1ML_FP64 ? kPairThreads<double> : kPairThreads<float>;
+    for (int cls = 0; cls < kPairClasses; ++cls) {
+        P->pair_on[cls] = false;
+        P->pair_tile[cls].assign(P->n_ens, PairTile());
+        const int tau = P->pair_tau(cls);
+        // both buffers of an ensemble within 32-bit offsets of its links; sweeps of an even number of passes
+        bool ok = 2 * bytes < 4294967296.0 && (cls % 3 != 2 || P->two);
+        double one = 0.0, two = 0.0, lat = 1.0;
+        P->pair_block[cls] = 64;
+        for (int k = 0; ok && k < P->n_ens; ++k) {
+            const u1ml_ensemble& E = P->ens[k];
+            const PairGeo G(E, cls, tau);
+            const double v = (double)E.ns[0] * E.ns[1] * E.ns[2] * E.nt;
+            double waves = 0.0;
+            const PairTile T = pair_tile(G, v / vol, max_threads, &waves);
+            ok = T.blocks > 0;
+            P->pair_tile[cls][k] = T;
+            one += waves;
+            const double slice = (double)G.nxh * G.N[0] * G.N[1];
+            two += std::ceil(slice / 64) * G.N[2] * G.slabs;
+            if (ok) P->pair_block[cls] = std::max(P->pair_block[cls], (G.rows(T.L) * G.nxh + 63) / 64 * 64);
+        }
+        lat = std::max(1.0, P->pair_block[cls] / 256.0);
+        const double t_one = 1.9 + 2 * 0.55 * std::max(lat, one / 1024), t_two = 2 * (1.9 + 0.4 * std::max(1.0, two / 1024));
+        P->pair_on[cls] = ok && t_one < 0.9 * t_two;
+    }
+    P->pair_rows.clear();
+    P->pair_shape.clear();
+    for (int cls = 0; cls < kPairClasses; ++cls)
+        for (int k = 0; P->pair_on[cls] && k < P->n_ens; ++k) {
+            const PairGeo G(P->ens[k], cls, P->pair_tau(cls));
+            pair_for_tiles(*P, cls, k, [&](const int* o, const int* L) { pair_rows(P, G, o, L); });
+        }
+}
+
 bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::string* err)
 {
     const size_t word = P.precision == U1ML_FP64 ? 8 : 4;
@@ -402,6 +637,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
         const int ks = P.ins_mfma_est ? kMfSlots : P.ins_ks_vec;
         if (P.ins_ks != ks) pack_slot_blocks(&P, ks);
     }
+    plan_pairs(&P);
     const bool spec = P.spectral;
     size_t L = 0, HC = 0, HO = 0, AT = 0, ATO = 0, OT = 0, OTO = 0, VAC = 0, PP = 0;
     size_t maxV = 0, paper = 0, upd_cfg = 0, upd_sweep = 0, blocks64 = 0, mblocks = 0;
@@ -541,6 +777,14 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
     Lo->bmap_stride = blocks64;
     Lo->s_bmap = take(sizeof(UpdBlock) * kUpdateClasses * blocks64);
     Lo->s_mmap = take(sizeof(int2) * mblocks);
+    Lo->s_prow = take(sizeof(PairRow) * P.pair_rows.size());
+    size_t pair_bytes[kPairClasses] = {};
+    for (int cls = 0; cls < kPairClasses; ++cls) {
+        size_t blocks = kXcds;  // padding of the XCD-aware block order
+        for (const PairTile& T : P.pair_tile[cls]) blocks += (size_t)T.blocks;
+        pair_bytes[cls] = P.pair_on[cls] ? sizeof(PairBlock) * blocks : 0;
+        Lo->s_pmap[cls] = take(pair_bytes[cls]);
+    }
     Lo->s_prodpart = take(sizeof(double) * PP);
     for (int l = 0; l < kMaxLanes; ++l) {
         Lo->s_lens[l] = take(sizeof(EnsDesc) * n);
@@ -548,6 +792,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
         Lo->s_lbmap[l] = take(sizeof(UpdBlock) * kUpdateClasses * blocks64);
         Lo->s_lmmap[l] = take(sizeof(int2) * mblocks);
         Lo->s_lring[l] = take(sizeof(int) * 4);
+        for (int cls = 0; cls < kPairClasses; ++cls) Lo->s_lpmap[l][cls] = take(pair_bytes[cls]);
     }
     Lo->s_pgroup = take(sizeof(int) * std::max<size_t>(Np, 1));
     Lo->s_gdesc = take(sizeof(int) * std::max<size_t>(2 * NG, 2));
@@ -556,6 +801,8 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
     size_t off = 0;
     Lo->off_links = off;
     off += Lo->sz_links;
+    Lo->off_alt = off;
+    if (P.any_pair()) off += Lo->sz_links;
     Lo->off_hc = off;
     off += Lo->sz_hc;
     Lo->off_ho = off;
@@ -639,6 +886,8 @@ struct Lane {
     int* d_ring = nullptr;
     double* prodpart = nullptr;
     size_t bmap_stride = 0;
+    PairBlock* d_pmap[kPairClasses] = {};
+    std::vector<PairBlock> h_pmap[kPairClasses];  // work-groups of the both-parities launches
     int upd_grid[kUpdateClasses] = {0, 0, 0, 0};  // grid size of each update class (multiple of 8)
     int max_s_in = 1;                              // largest number of inner slabs in the lane
     hipStream_t stream = nullptr;
@@ -678,6 +927,7 @@ struct u1ml_ctx {
     long long spec_n12max = 0;                     // largest transverse plane (sites)
     int spec_tile = 4;                             // plane-transform tile (4, or 2 if an extent is not a multiple of 4)
     int *d_pgroup = nullptr, *d_gdesc = nullptr, *d_pblk = nullptr;
+    PairRow* d_prow = nullptr;  // row tables of the both-parities launches
     size_t ins_lds = 0;  // insertion contraction dynamic LDS per work-group
     int ins_block = 64;  // insertion contraction work-group size
     int ins_line_len = 0;  // sites of every charge-axis line of every ensemble where they are all the same, else 0
@@ -795,6 +1045,45 @@ void build_update_tabs(const u1ml_ctx* c, Lane& L)
     }
 }
 
+void build_pair_tabs(const u1ml_ctx* c, Lane& L)
+{
+    const Problem& P = c->P;
+    const int word = P.precision == U1ML_FP64 ? 8 : 4;
+    for (int cls = 0; cls < kPairClasses; ++cls) {
+        L.h_pmap[cls].clear();
+        if (!P.pair_on[cls]) continue;
+        std::vector<PairBlock> logical;
+        for (int e = 0; e < L.n; ++e) {
+            const EnsDesc& E = L.h_ens[e];
+            const int k = E.res_index;
+            const PairGeo G(P.ens[k], cls, P.pair_tau(cls));
+            PairBlock r;
+            std::memset(&r, 0, sizeof r);
+            r.e = k;
+            r.nxh = E.nxh;
+            r.vh = E.vh;
+            r.inv_nxh = E.inv_nxh;
+            r.link_off = E.link_off;
+            pair_for_tiles(P, cls, k, [&](const int* o, const int* C) {
+                r.base = word * E.nxh * (o[0] + E.ny * (o[1] + E.nz * o[2]));
+                r.par = o[0] + o[1] + o[2];
+                r.row_tab = P.pair_shape.at(G.shape(o, C));
+                r.n1 = G.rows(C) * E.nxh;
+                r.n2 = C[0] * C[1] * C[2] * E.nxh;
+                logical.push_back(r);
+            });
+        }
+        // the XCD-aware order of build_update_tabs; padding blocks have no links
+        PairBlock idle = logical.back();
+        idle.n1 = idle.n2 = 0;
+        const int total = (int)logical.size(), per = (total + kXcds - 1) / kXcds;
+        for (int phys = 0; phys < per * kXcds; ++phys) {
+            const int lg = (phys % kXcds) * per + phys / kXcds;
+            L.h_pmap[cls].push_back(lg < total ? logical[lg] : idle);
+        }
+    }
+}
+
 // Every launch table of a lane, from its ensembles' descriptors (whose
 // contraction and product fields are already set).
 void build_lane_tables(const u1ml_ctx* c, Lane& L)
@@ -803,6 +1092,7 @@ void build_lane_tables(const u1ml_ctx* c, Lane& L)
     const int n = L.n;
     L.h_bstart.assign((size_t)kNumTabs * (n + 1), 0);
     build_update_tabs(c, L);
+    build_pair_tabs(c, L);
     const size_t R = P.r.size(), NG = P.gdesc.size() / 2;
     std::vector<long long> all(n), meas(n), con(n), comb(n), prod(n), site(n), plane(n), mac(n), stage(n), ins(n);
     L.max_s_in = 1;
@@ -864,6 +1154,10 @@ hipError_t upload_lane(const Lane& L)
     hipError_t e = hipMemcpy(L.d_ens, L.h_ens.data(), sizeof(EnsDesc) * L.n, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(L.d_bstart, L.h_bstart.data(), sizeof(int) * L.h_bstart.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = upload_update_tabs(L);
+    for (int cls = 0; cls < kPairClasses && e == hipSuccess; ++cls)
+        if (!L.h_pmap[cls].empty())
+            e = hipMemcpy(L.d_pmap[cls], L.h_pmap[cls].data(), sizeof(PairBlock) * L.h_pmap[cls].size(),
+                          hipMemcpyHostToDevice);
     if (e == hipSuccess && !L.h_mmap.empty())
         e = hipMemcpy(L.d_mmap, L.h_mmap.data(), sizeof(int2) * L.h_mmap.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(L.d_ring, ring0, sizeof ring0, hipMemcpyHostToDevice);
@@ -906,6 +1200,7 @@ hipError_t split_lanes(u1ml_ctx* c, int nl)
         L.d_bmap = (UpdBlock*)(s + Lo.s_lbmap[l]);
         L.d_mmap = (int2*)(s + Lo.s_lmmap[l]);
         L.d_ring = (int*)(s + Lo.s_lring[l]);
+        for (int cls = 0; cls < kPairClasses; ++cls) L.d_pmap[cls] = (PairBlock*)(s + Lo.s_lpmap[l][cls]);
         // the lanes use disjoint parts of the slab-product partials
         L.prodpart = (double*)(s + Lo.s_prodpart) + pp_off;
         L.stream = l == 0 ? c->stream : c->lane_stream[l];
@@ -952,34 +1247,71 @@ int update_class(const u1ml_ctx* c, int mu, int tau, bool* ok)
     return -1;
 }
 
+// 0: every link updated, 1: inner slabs, 2: outer slabs (tau one of the problem's)
+int update_class_tau(const u1ml_ctx* c, int tau) { return tau <= 1 ? 0 : (tau == c->P.tau_i ? 1 : 2); }
+
+constexpr unsigned kInPlace[4] = {0, 0, 0, 0};  // every direction in the first link buffer
+
 hipError_t enq_phase(u1ml_ctx* c, const Lane& L, hipStream_t st, int kind, int mu, int parity, int tau,
-                     int pass_offset, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr)
+                     int pass_offset, const unsigned* src, hipEvent_t ev_start = nullptr,
+                     hipEvent_t ev_stop = nullptr)
 {
     bool ok;
     const int cls = update_class(c, mu, tau, &ok);
     if (!ok) return hipErrorInvalidValue;
-    return launch_update(UpdLaunch{c->whole.d_ens, L.bmap_dev(cls), L.upd_grid[cls], c->block, c->P.precision, c->links, c->d_upd,
-                                   pass_offset, kind, mu, parity, c->P.metro_delta, st, ev_start, ev_stop});
+    return launch_update(UpdLaunch{c->whole.d_ens, L.bmap_dev(cls), L.upd_grid[cls], c->block, c->P.precision, c->links,
+                                   c->d_upd, pass_offset, kind, mu, parity, {src[0], src[1], src[2], src[3]},
+                                   c->P.metro_delta, st, ev_start, ev_stop});
 }
 
-hipError_t enq_pass(u1ml_ctx* c, const Lane& L, hipStream_t st, int kind, int tau, int pass_offset)
+// One pass over the directions, each in both parities.  src: the byte offset
+// of each direction's current link buffer; a both-parities launch turns its
+// direction's over.
+hipError_t enq_pass(u1ml_ctx* c, const Lane& L, hipStream_t st, int kind, int tau, int pass_offset, bool pairs,
+                    unsigned* src)
 {
-    for (int mu = 0; mu < 4; ++mu)
-        for (int p = 0; p < 2; ++p) {
-            hipError_t e = enq_phase(c, L, st, kind, mu, p, tau, pass_offset);
-            if (e != hipSuccess) return e;
+    const unsigned alt = (unsigned)c->Lo.off_alt;
+    for (int mu = 0; mu < 4; ++mu) {
+        const int cls = mu == 3 ? 9 : 3 * mu + update_class_tau(c, tau);
+        hipError_t e = hipSuccess;
+        if (pairs && c->P.pair_on[cls]) {
+            const unsigned dst = src[mu] ? 0u : alt;
+            e = launch_pair(PairLaunch{c->whole.d_ens, L.d_pmap[cls], c->d_prow, (int)L.h_pmap[cls].size(),
+                                       c->P.pair_block[cls], c->P.precision, c->links, c->d_upd, pass_offset, kind, mu,
+                                       {src[0], src[1], src[2], src[3]}, dst, c->P.metro_delta, st});
+            src[mu] = dst;
+        } else {
+            for (int p = 0; p < 2 && e == hipSuccess; ++p)
+                e = enq_phase(c, L, st, kind, mu, p, tau, pass_offset, src);
         }
+        if (e != hipSuccess) return e;
+    }
     return hipSuccess;
 }
 
 // one sweep: stochastic pass (heatbath or Metropolis) with counter offset hb,
-// then n_or overrelaxation passes
-hipError_t enq_sweep(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau, int hb)
+// then n_or overrelaxation passes.  It starts and ends in the first link
+// buffer: of an odd number of passes the last one updates in place.
+// pairs: both-parities launches where the plan has them.
+hipError_t enq_sweep(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau, int hb, bool pairs = true)
 {
     const int stoch = c->P.update == U1ML_UPDATE_METROPOLIS ? U1ML_METROPOLIS : U1ML_HEATBATH;
-    hipError_t e = enq_pass(c, L, st, stoch, tau, hb);
-    for (int k = 0; e == hipSuccess && k < c->P.n_or; ++k) e = enq_pass(c, L, st, U1ML_OVERRELAX, tau, hb);
+    const int paired = pairs ? (c->P.n_or + 1) / 2 * 2 : 0;  // passes that may turn the buffers over
+    unsigned src[4] = {0, 0, 0, 0};
+    hipError_t e = hipSuccess;
+    for (int k = 0; e == hipSuccess && k <= c->P.n_or; ++k)
+        e = enq_pass(c, L, st, k == 0 ? stoch : U1ML_OVERRELAX, tau, hb, k < paired, src);
     return e;
+}
+
+// Before sweeps inside slabs of thickness tau: both link buffers hold the
+// frozen links.
+hipError_t enq_mirror(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau)
+{
+    bool any = false;
+    for (int mu = 0; mu < 3; ++mu) any = any || c->P.pair_on[3 * mu + update_class_tau(c, tau)];
+    if (!any && !c->P.pair_on[9]) return hipSuccess;
+    return launch_mirror(L.d_ens, L.n, c->P.precision, c->links, (unsigned)c->Lo.off_alt, 256, st);
 }
 
 // The n_o outer iterations of Algorithm 1 (one iteration for one level).
@@ -1000,8 +1332,11 @@ hipError_t enq_levels(u1ml_ctx* c, const Lane& L, hipStream_t st, bool store_o, 
     }
     int hb = 0;
     for (int ko = 0; e == hipSuccess && ko < P.n_o; ++ko) {
-        if (P.two)
+        if (P.two && P.k_o > 0) {
+            e = enq_mirror(c, L, st, P.tau_o);
             for (int k = 0; e == hipSuccess && k < P.k_o; ++k) e = enq_sweep(c, L, st, P.tau_o, hb++);
+        }
+        if (e == hipSuccess && P.k_i > 0) e = enq_mirror(c, L, st, P.tau_i);
         for (int m = 0; e == hipSuccess && m < P.n_i; ++m) {
             for (int k = 0; e == hipSuccess && k < P.k_i; ++k) e = enq_sweep(c, L, st, P.tau_i, hb++);
             if (e == hipSuccess)
@@ -1317,6 +1652,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
     c->d_pgroup = (int*)(s + Lo.s_pgroup);
     c->d_gdesc = (int*)(s + Lo.s_gdesc);
     c->d_pblk = (int*)(s + Lo.s_pblk);
+    c->d_prow = (PairRow*)(s + Lo.s_prow);
     c->wf = (double2*)(w + Lo.off_wf);
     c->gf = (double2*)(w + Lo.off_gf);
     c->sph = (double2*)(w + Lo.off_sph);
@@ -1497,6 +1833,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         L.d_bmap = (UpdBlock*)(s + Lo.s_bmap);
         L.d_mmap = (int2*)(s + Lo.s_mmap);
         L.d_ring = (int*)(s + Lo.s_ring);
+        for (int cls = 0; cls < kPairClasses; ++cls) L.d_pmap[cls] = (PairBlock*)(s + Lo.s_pmap[cls]);
         L.prodpart = (double*)(s + Lo.s_prodpart);
         L.stream = c->stream;
         build_lane_tables(c, L);
@@ -1529,6 +1866,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
     up(c->d_pgroup, P.pgroup.data(), sizeof(int) * P.pgroup.size());
     up(c->d_gdesc, P.gdesc.data(), sizeof(int) * P.gdesc.size());
     up(c->d_pblk, P.pblk.data(), sizeof(int) * P.pblk.size());
+    up(c->d_prow, P.pair_rows.data(), sizeof(PairRow) * P.pair_rows.size());
     up(c->d_upd, zeros.data(), sizeof(uint32_t) * n);
     if (st == U1ML_OK) {
         hipError_t e = upload_lane(c->whole);
@@ -1613,7 +1951,7 @@ u1ml_status u1ml_phase(u1ml_ctx* ctx, int kind, int mu, int parity, int tau, int
     bool ok;
     update_class(ctx, mu, tau, &ok);
     if (!ok) return set_err(ctx, U1ML_EINVAL, "tau must be <= 1 or one of the problem's level thicknesses");
-    HIPCHK(ctx, enq_phase(ctx, ctx->whole, ctx->stream, kind, mu, parity, tau, pass_offset));
+    HIPCHK(ctx, enq_phase(ctx, ctx->whole, ctx->stream, kind, mu, parity, tau, pass_offset, kInPlace));
     return U1ML_OK;
 }
 
@@ -1795,7 +2133,7 @@ u1ml_status time_lane_phase(u1ml_ctx* ctx, const Lane& L, int kind, int mu, int 
     for (auto& x : ev) HIPCHK(ctx, hipEventCreate(&x));
     hipError_t he = hipSuccess;
     for (int i = 0; i < n_rep && he == hipSuccess; ++i)
-        he = enq_phase(ctx, L, ctx->stream, kind, mu, parity, tau, 0, ev[2 * i], ev[2 * i + 1]);
+        he = enq_phase(ctx, L, ctx->stream, kind, mu, parity, tau, 0, kInPlace, ev[2 * i], ev[2 * i + 1]);
     if (he == hipSuccess) he = hipEventSynchronize(ev.back());
     double total = 0.0;
     for (int i = 0; i < n_rep && he == hipSuccess; ++i) {
@@ -1892,9 +2230,9 @@ u1ml_status u1ml_autotune(u1ml_ctx* ctx, u1ml_tune_report* report)
             st = set_err(ctx, U1ML_EDEVICE, "event creation failed");
             break;
         }
-        hipError_t e = enq_sweep(ctx, ctx->whole, ctx->stream, tau, 0);  // warm-up
+        hipError_t e = enq_sweep(ctx, ctx->whole, ctx->stream, tau, 0, false);  // warm-up
         if (e == hipSuccess) e = hipEventRecord(a, ctx->stream);
-        for (int k = 0; k < 5 && e == hipSuccess; ++k) e = enq_sweep(ctx, ctx->whole, ctx->stream, tau, 0);
+        for (int k = 0; k < 5 && e == hipSuccess; ++k) e = enq_sweep(ctx, ctx->whole, ctx->stream, tau, 0, false);
         if (e == hipSuccess) e = hipEventRecord(b, ctx->stream);
         if (e == hipSuccess) e = hipEventSynchronize(b);
         float ms = 0.f;

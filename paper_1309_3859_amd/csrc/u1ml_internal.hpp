@@ -48,6 +48,37 @@ struct alignas(64) UpdBlock {
 };
 static_assert(sizeof(UpdBlock) == 64, "UpdBlock is one 64-byte scalar load");
 
+// One work-group of a launch that updates both parities of one direction: its
+// tile's origin, its work-items (rows of the tile with and without the halo,
+// times Nx/2) and its first entry in the table of rows.
+struct alignas(64) PairBlock {
+    int e;         // the ensemble (problem order)
+    int base;      // byte offset of the origin row in a (direction, parity) array
+    int par;       // y + z + t of the origin
+    int n1, n2, row_tab;
+    int nxh, vh;
+    float inv_nxh;
+    int pad;
+    long long link_off;
+};
+// One row of a tile, in bytes from the origin row, periodic steps included:
+// itself and its neighbours one step up (p) and down (m) in y, z, t; parity of
+// y + z + t from the origin; the byte offsets in LDS of the rows one step down
+// (low half) and up (high half), kPairFrozen: not in the tile, its links are
+// frozen.  Tiles of one shape at the same distance (up to 2) from the
+// lattice's ends share their rows.
+struct PairRow {
+    int p1, m1, p2, m2;
+    int p3, m3, c, par;
+    unsigned ly, lz, lt, pad;
+};
+constexpr unsigned kPairFrozen = 0xFFFFu;
+static_assert(sizeof(PairBlock) == 64, "PairBlock is one 64-byte scalar load");
+// largest work-group (FP64 holds both parities' angles in twice the registers)
+template <typename real>
+constexpr int kPairThreads = sizeof(real) == 8 ? 512 : 1024;
+constexpr int kPairClasses = 10;  // direction x, y, z by full, inner tau, outer tau; temporal
+
 // Observable tables in device memory.
 struct ObsDesc {
     int n_dirs;
@@ -130,11 +161,28 @@ struct UpdLaunch {
     void* links;
     const uint32_t* d_upd;
     int pass_offset, kind, mu, parity;
+    unsigned src[4];  // byte offset of each direction's current link buffer
     double metro_delta;
     hipStream_t st;
     hipEvent_t ev_start, ev_stop;
 };
 hipError_t launch_update(const UpdLaunch& a);
+// Both parities of direction mu, even first, from the current buffers to dst (k_pair.hip)
+struct PairLaunch {
+    const EnsDesc* d_ens;  // problem order
+    const PairBlock* d_blocks;
+    const PairRow* d_rows;
+    int total_blocks, block, precision;
+    void* links;
+    const uint32_t* d_upd;
+    int pass_offset, kind, mu;
+    unsigned src[4], dst;
+    double metro_delta;
+    hipStream_t st;
+};
+hipError_t launch_pair(const PairLaunch& a);
+hipError_t launch_mirror(const EnsDesc* d_ens, int n_ens, int precision, void* links, unsigned alt, int blocks,
+                         hipStream_t st);
 hipError_t launch_health(const EnsDesc* d_ens, const int* d_bstart_all, int n_ens, int total_blocks, int precision,
                          const void* links, unsigned long long* d_count, hipStream_t st);
 hipError_t launch_plaquette(const EnsDesc* d_ens, int n_ens, int max_blocks_per_ens, int precision, const void* links,

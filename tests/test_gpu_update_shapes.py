@@ -68,3 +68,59 @@ def test_work_group_size_changes_no_bit(ns, nt, precision):
             ctx.phase(kind, mu, p, tau, pass_offset=mu)
         got.append(ctx.links(0))
     assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
+# slabs of one, two and three inner layers, extents of 2, tiles that do not
+# divide the extents, rows of 1 .. 40 half sites, two levels, odd and even
+# numbers of passes
+RUNS = [((4, 4, 4), 4, [(2, 2, 1)], 3), ((2, 2, 2), 2, [(2, 2, 2)], 3), ((24, 24, 24), 4, [(2, 1, 1)], 3),
+        ((10, 14, 6), 12, [(4, 2, 1), (2, 2, 1)], 2), ((18, 2, 22), 6, [(3, 2, 1)], 1), ((80, 6, 10), 8, [(4, 1, 1)], 0),
+        ((2, 26, 14), 8, [(8, 1, 1), (4, 2, 1)], 3)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ns,nt,levels,n_or", RUNS)
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("update", [0, 1])
+def test_sweeps_equal_their_phases(ns, nt, levels, n_or, precision, update):
+    """Sweeps and configurations, however many phases a launch does, leave the
+    links that one launch per phase leaves, bit for bit, on a batch of the
+    lattice and of one half its time extent."""
+    from paper_1309_3859_amd import u1ml
+
+    print("run", ns, nt, levels, n_or, precision, update, flush=True)
+    ens = [u1ml.Ens(ns, nt, 1.05, seed=3, key_id=j) for j in range(2)]
+    if nt % 4 == 0 and nt // 2 % levels[0][0] == 0:
+        ens.append(u1ml.Ens(ns, nt // 2, 0.9, seed=3, key_id=2))
+    spec = u1ml.Spec(ensembles=ens, levels=levels, r=[1], precision=precision, n_or=n_or, update=update,
+                     metro_delta=0.7)
+
+    def sweep(ctx, tau, offset):
+        for k in range(1 + n_or):
+            kind = (u1ml.METROPOLIS if update else u1ml.HEATBATH) if k == 0 else u1ml.OVERRELAX
+            for mu, p in itertools.product(range(4), (0, 1)):
+                ctx.phase(kind, mu, p, tau, offset)
+
+    a, b = u1ml.Context(spec), u1ml.Context(spec)
+    for c in (a, b):
+        c.init_links(u1ml.HOT)
+    a.sweeps(3)
+    for k in range(3):
+        sweep(b, 0, k)
+    for e in range(len(ens)):
+        assert np.array_equal(a.links(e), b.links(e))
+        assert a.counter(e) == 3
+        b.set_counter(3, e)
+    a.multilevel()
+    offset = 0
+    outer = levels[0] if len(levels) == 2 else (0, 1, 0)
+    for _ in range(outer[1]):
+        for _ in range(outer[2]):
+            sweep(b, outer[0], offset)
+            offset += 1
+        for _ in range(levels[-1][1] * levels[-1][2]):
+            sweep(b, levels[-1][0], offset)
+            offset += 1
+    for e in range(len(ens)):
+        assert np.array_equal(a.links(e), b.links(e))
+        assert a.counter(e) == 3 + offset
