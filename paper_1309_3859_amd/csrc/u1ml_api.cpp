@@ -387,10 +387,12 @@ struct PairGeo {
     }
 };
 
-// The tile with the least time per SIMD: a work-group's waves run on one
-// compute unit (4 SIMDs), all work-groups of the batch (share: this ensemble's
-// part of it) on 1024; halo rows are updated once more for every tile they
-// touch, so large batches take large tiles and small ones many small tiles.
+// The tile with the least time per SIMD: a work-group's waves run on one of 256
+// compute units (4 SIMDs each), so a unit holds its share of whole work-groups
+// (share: this ensemble's part of the batch); halo rows are updated once more
+// for every tile they touch.  24^3 x 8, temporal links: 3 x 3 rows (512
+// work-groups, two per unit, of 4 waves) 84.4 us a sweep, 4 x 4 (288, on some
+// units two, of 6 waves) 87.0, 6 x 6 87.7.
 PairTile pair_tile(const PairGeo& G, double share, int max_threads, double* waves)
 {
     PairTile best;
@@ -408,7 +410,8 @@ PairTile pair_tile(const PairGeo& G, double share, int max_threads, double* wave
                 }
                 if (rows * G.nxh > max_threads) continue;
                 const double w1 = (double)((rows * G.nxh + 63) / 64), w2 = (double)((core * G.nxh + 63) / 64);
-                const double lat = std::max(1.0, w1 / 4), thr = (double)tiles / share * (w1 + w2) / 2 / 1024;
+                const double lat = std::ceil((double)tiles / share / 256) * std::max(1.0, w1 / 4);
+                const double thr = (double)tiles / share * (w1 + w2) / 2 / 1024;
                 const double cost = std::max(lat, thr) + 0.1 * thr;
                 if (cost < best_cost) {
                     best_cost = cost;
