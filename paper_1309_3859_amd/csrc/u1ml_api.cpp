@@ -65,11 +65,19 @@ constexpr int kTabIns = 13;   // insertion contraction: work-groups
 constexpr int kNumTabs = 14;
 constexpr int kXcds = 8;  // accelerator complex dies of an MI355X, each with its own L2
 constexpr int kMaxLanes = 4;  // streams that sweeps and configurations are spread over
-// lanes a context starts with: FP32 phases are short enough that two lanes
-// fill the device and a third adds under 1 %; the longer, arithmetic-bound
-// FP64 phases gain about 2.5 % more from four (C4 on MI355X: FP32 8.50,
-// 8.43, 8.64 ms per configuration with 2, 3, 4 lanes; FP64 17.96, 17.78, 17.56)
-int default_lanes(int precision) { return precision == U1ML_FP64 ? 4 : 2; }
+// Lanes a context starts with, by the batch's sites: two where a phase of half
+// the batch still fills the device, else one (a second stream costs more than
+// its overlap gains, and more than two never gain).  MI355X, us per sweep inside
+// slabs with 1 / 2 / 4 lanes: FP32 8 x 24^3 x 8 (0.88M sites) 122 / 140 / 173,
+// 16 x 24^3 x 8 (1.77M) 187 / 174 / 200, 32 x 24^3 x 8 329 / 280 / 300; FP64
+// 8 x 24^3 x 4 (0.44M) 164 / 177 / 207, 8 x 24^3 x 8 250 / 222 / 240,
+// 16 x 24^3 x 8 418 / 388 / 388.
+int default_lanes(const std::vector<u1ml_ensemble>& ens, int precision)
+{
+    double sites = 0.0;
+    for (const u1ml_ensemble& E : ens) sites += (double)E.ns[0] * E.ns[1] * E.ns[2] * E.nt;
+    return ens.size() > 1 && sites >= (precision == U1ML_FP64 ? 0.7e6 : 1.3e6) ? 2 : 1;
+}
 
 // Tile of a both-parities launch (k_pair): core rows along y, z, t.
 struct PairTile {
@@ -908,7 +916,6 @@ struct u1ml_ctx {
     u1ml_plan_info plan;
     char* ws = nullptr;
     hipStream_t stream = nullptr;
-    hipStream_t cap = nullptr;
     hipStream_t lane_stream[kMaxLanes] = {};  // streams of lanes 1.. (lane 0 runs on the context's stream)
     hipEvent_t ev_fork = nullptr, ev_join[kMaxLanes] = {};
     int device = 0;
@@ -1173,6 +1180,15 @@ hipError_t upload_lane(const Lane& L)
 // emptied; their device areas stay reserved.
 hipError_t split_lanes(u1ml_ctx* c, int nl)
 {
+    // streams as they are needed: the runtime maps streams to a few hardware
+    // queues, and a lane that shares one with the context's stream (or with
+    // another context's) waits for it
+    for (int l = 1; l < nl; ++l) {
+        hipError_t e = hipSuccess;
+        if (!c->lane_stream[l]) e = hipStreamCreateWithFlags(&c->lane_stream[l], hipStreamNonBlocking);
+        if (e == hipSuccess && !c->ev_join[l]) e = hipEventCreateWithFlags(&c->ev_join[l], hipEventDisableTiming);
+        if (e != hipSuccess) return e;
+    }
     const int n = c->P.n_ens;
     const Layout& Lo = c->Lo;
     char* s = c->ws + Lo.off_scr;
@@ -1480,7 +1496,6 @@ void release(u1ml_ctx* c)
         if (c->ev_join[l]) (void)hipEventDestroy(c->ev_join[l]);
         if (c->lane_stream[l]) (void)hipStreamDestroy(c->lane_stream[l]);
     }
-    if (c->cap) (void)hipStreamDestroy(c->cap);
     delete c;
 }
 
@@ -1508,9 +1523,10 @@ template <typename F>
 u1ml_status capture(u1ml_ctx* c, F&& body, hipGraphExec_t* out)
 {
     hipGraph_t g = nullptr;
-    HIPCHK(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeRelaxed));
-    hipError_t e = body(c->cap);
-    hipError_t e2 = hipStreamEndCapture(c->cap, &g);
+    const hipStream_t cap = c->lane_stream[1];
+    HIPCHK(c, hipStreamBeginCapture(cap, hipStreamCaptureModeRelaxed));
+    hipError_t e = body(cap);
+    hipError_t e2 = hipStreamEndCapture(cap, &g);
     if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
         return set_err(c, U1ML_EDEVICE, std::string("kernel launch during capture: ") + hipGetErrorString(e));
@@ -1626,7 +1642,8 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
     c->stream = (hipStream_t)hip_stream;
     hipError_t he = hipGetDevice(&c->device);
     if (he == hipSuccess) he = static_scratch(&c->static_partials);
-    if (he == hipSuccess) he = hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking);
+    // lane 1's stream, also the one that graphs are captured on
+    if (he == hipSuccess) he = hipStreamCreateWithFlags(&c->lane_stream[1], hipStreamNonBlocking);
     if (he != hipSuccess) {
         delete c;
         return set_err(nullptr, U1ML_EDEVICE, std::string("stream creation: ") + hipGetErrorString(he));
@@ -1877,11 +1894,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
     }
     if (st == U1ML_OK) {
         hipError_t e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
-        for (int l = 1; l < kMaxLanes && e == hipSuccess; ++l) {
-            e = hipStreamCreateWithFlags(&c->lane_stream[l], hipStreamNonBlocking);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join[l], hipEventDisableTiming);
-        }
-        if (e == hipSuccess) e = split_lanes(c, std::min(n, default_lanes(P.precision)));
+        if (e == hipSuccess) e = split_lanes(c, default_lanes(P.ens, P.precision));
         if (e != hipSuccess) st = set_err(nullptr, U1ML_EDEVICE, std::string("lanes: ") + hipGetErrorString(e));
     }
     if (st != U1ML_OK) {
@@ -2108,6 +2121,14 @@ u1ml_status u1ml_set_lanes(u1ml_ctx* ctx, int n_lanes)
     const int ring[4] = {ctx->ring_count, 0, 0, 0};
     for (Lane* L : all_lanes(ctx))
         if (L->n) HIPCHK(ctx, hipMemcpy(L->d_ring, ring, sizeof ring, hipMemcpyHostToDevice));
+    return U1ML_OK;
+}
+
+u1ml_status u1ml_get_lanes(u1ml_ctx* ctx, int* n_lanes)
+{
+    if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
+    if (!n_lanes) return set_err(ctx, U1ML_EINVAL, "n_lanes is NULL");
+    *n_lanes = ctx->n_lanes;
     return U1ML_OK;
 }
 

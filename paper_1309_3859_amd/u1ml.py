@@ -105,6 +105,7 @@ def lib():
         "u1ml_set_block": [vp, i32],
         "u1ml_set_graphs": [vp, i32],
         "u1ml_set_lanes": [vp, i32],
+        "u1ml_get_lanes": [vp, C.POINTER(i32)],
         "u1ml_time_phase": [vp, i32, i32, i32, i32, i32, pd],
         "u1ml_time_phase_lane": [vp, i32, i32, i32, i32, i32, i32, pd, pd, C.POINTER(C.c_long)],
         "u1ml_phase_bytes": [vp, i32, i32, i32, i32, pd, C.POINTER(C.c_long)],
@@ -250,7 +251,6 @@ class Context:
         self._h = h
         self.n_ens = len(spec.ensembles)
         self.nd = self.plan["n_doubles_per_config"]
-        self._n_lanes = min(self.n_ens, 4 if spec.precision == FP64 else 2)  # the library's default
 
     def close(self):
         if getattr(self, "_h", None):
@@ -337,7 +337,6 @@ class Context:
 
     def set_lanes(self, n_lanes: int):
         self._c(lib().u1ml_set_lanes(self._h, int(n_lanes)))
-        self._n_lanes = int(n_lanes)
 
     def time_phase(self, kind: int, mu: int, parity: int, tau: int, n_rep: int) -> float:
         us = C.c_double()
@@ -353,7 +352,9 @@ class Context:
 
     @property
     def n_lanes(self) -> int:
-        return self._n_lanes
+        n = C.c_int()
+        self._c(lib().u1ml_get_lanes(self._h, C.byref(n)))
+        return int(n.value)
 
     def phase_bytes(self, kind: int, mu: int, parity: int, tau: int):
         b, u = C.c_double(), C.c_long()
