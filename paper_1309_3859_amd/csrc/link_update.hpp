@@ -105,16 +105,61 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Attempts 2, 3, ... of the wave's pending links (about 1 in 12).  The wave's
-// lanes are dealt to the n pending links, 2^lg consecutive lanes each, and a
-// round tries 2^lg further Philox blocks of every link at once; the first
-// accepting block in attempt order decides, so the result is that of trying
-// them one after another.  With the usual 5 pending links a round covers 8
-// blocks (16 attempts) and one round is enough, where a queue of one lane per
-// link over the whole work-group took three serial rounds between two
-// barriers.  (Four attempts by every lane before this step measured slower:
-// 24^3 x 8 sweeps 89 instead of 88 us, the FP64 batch of 16 ensembles 22.7
-// instead of 21.9 ms.)  Called by whole waves.
+// theta = arg(e^{i psi} conj A): one atan2 for wrap(psi - arg A), in [-pi, pi)
+__device__ inline float hb_angle(float ar, float ai, float cp, float sp)
+{
+    const float th = atan2_fast(sp * ar - cp * ai, cp * ar + sp * ai);
+    return th >= 3.14159265f ? -3.14159265f : th;
+}
+__device__ inline double hb_angle(double ar, double ai, double cp, double sp)
+{
+    const double th = M<double>::atan2_(sp * ar - cp * ai, cp * ar + sp * ai);
+    return th >= M<double>::pi ? -M<double>::pi : th;
+}
+
+// sin psi of an accepted deviate (c, s), or of the uniform psi (s itself)
+__device__ inline float hb_sin(bool, float, float s) { return s; }
+__device__ inline double hb_sin(bool draw, double c, double s)
+{
+    if (!draw) return s;
+    // +-sqrt((1 - f)(1 + f)) (1 - f and 1 + f exact where they cancel)
+    const double sq = M<double>::sqrt_((1.0 - c) * (1.0 + c));
+    return s < 0.0 ? -sq : sq;
+}
+
+// One round after another of further Philox blocks (1 .. 32767, attempts 2 ..
+// 65535) for the links dealt to a wave, 2^lg consecutive lanes each: a round
+// tries 2^lg blocks of every link at once and the first accepting block in
+// attempt order decides, so the result is that of trying them one after
+// another.  take(c, s) is called once per link, by one of its lanes; links
+// that never accept call it with c = 2.
+template <typename real, typename Take>
+__device__ inline void hb_rounds(bool open, int lg, const HbEnv<real>& env, uint32_t lid, uint32_t ctr, uint32_t seed,
+                                 uint32_t key, Take take)
+{
+    const int lane = threadIdx.x & 63, sub = lane & ((1 << lg) - 1);
+    const unsigned long long gm = (lg == 6 ? ~0ull : (1ull << (1 << lg)) - 1ull) << (lane - sub);
+    for (uint32_t j0 = 1; j0 < 32768u && __any(open); j0 += 1u << lg) {
+        const uint32_t jp = j0 + (uint32_t)sub;
+        real c = real(0), s = real(0);
+        bool ok = open && jp < 32768u;
+        if (ok) ok = hb_try(env, philox4x32_10(lid, ctr, jp, DOM_HB, seed, key), &c, &s);
+        const unsigned long long hit = __ballot(ok) & gm;
+        if (hit) {
+            if (lane == __ffsll(hit) - 1) take(c, s);
+            open = false;
+        }
+    }
+    if (open && sub == 0) take(real(2), real(0));
+}
+
+// The wave's pending links (about 1 in 12) after the first block: its lanes are
+// dealt to them, with the usual 5 pending links 8 blocks (16 attempts) of each
+// in a round, so one round is enough, where one lane per link over the whole
+// work-group took three serial rounds between two barriers.  (Four attempts by
+// every lane before this step measured slower: 24^3 x 8 sweeps 89 instead of 88
+// us, the FP64 batch of 16 ensembles 22.7 instead of 21.9 ms.)  Called by whole
+// waves.
 template <typename real>
 __device__ inline void hb_retry(HbQ<real>* q, bool pending, const HbEnv<real>& mine, uint32_t lid, uint32_t ctr,
                                 uint32_t seed, uint32_t key, real* c, real* s)
@@ -127,38 +172,116 @@ __device__ inline void hb_retry(HbQ<real>* q, bool pending, const HbEnv<real>& m
     if (pending) q[rank].put(mine, lid);
     wave_lds_sync();
     const int lg = __clz(n - 1) - 26;  // floor(log2(64 / n))
-    const int g = lane >> lg, sub = lane - (g << lg);
-    bool open = g < n;
-    const HbQ<real> r = q[open ? g : 0];
-    const HbEnv<real> env = r.env();
-    const unsigned long long gm = (lg == 6 ? ~0ull : (1ull << (1 << lg)) - 1ull) << (lane - sub);
-    // blocks 1 .. 32767 (attempts 2 .. 65535)
-    for (uint32_t j0 = 1; j0 < 32768u && __any(open); j0 += 1u << lg) {
-        const uint32_t jp = j0 + (uint32_t)sub;
-        real cc = real(0), ss = real(0);
-        bool ok = open && jp < 32768u;
-        if (ok) ok = hb_try(env, philox4x32_10(r.lid(), ctr, jp, DOM_HB, seed, key), &cc, &ss);
-        const unsigned long long hit = __ballot(ok) & gm;
-        if (hit) {
-            if (lane == __ffsll(hit) - 1) q[g].a = cc, q[g].b = ss;
-            open = false;
-        }
-    }
-    if (open && sub == 0) q[g].a = real(2);
+    const int g = lane >> lg;
+    const HbQ<real> r = q[g < n ? g : 0];
+    hb_rounds<real>(g < n, lg, r.env(), r.lid(), ctr, seed, key, [&](real cc, real ss) { q[g].a = cc, q[g].b = ss; });
     wave_lds_sync();
     if (pending) *c = q[rank].a, *s = q[rank].b;
 }
 
-// theta = arg(e^{i psi} conj A): one atan2 for wrap(psi - arg A), in [-pi, pi)
-__device__ inline float hb_angle(float ar, float ai, float cp, float sp)
+// A pending link's entry in its work-group's LDS queue: what further attempts
+// and the new angle need.
+template <typename real>
+struct HbWgQ {
+    HbQ<real> q;
+    real ar, ai;
+    unsigned off;  // the link's byte offset from the launch's link base
+};
+
+// The work-group's pending links: every wave leaves its own in its 64 entries,
+// and after a barrier they are dealt to as few waves as hold them (one of four
+// with work-groups of 256); the others are done.  Fewer rounds for the chip
+// than wave by wave (a round costs a Philox block, 480 cycles of quarter-rate
+// multiplications, and two attempts), one barrier more for each work-group, so
+// large launches use it.  put(theta, off) stores a link's new angle;
+// old(off) reads its old one.  Called by whole work-groups.
+template <typename real, typename Put, typename Old>
+__device__ inline void hb_retry_wg(HbWgQ<real>* queue, int* counts, bool pending, const HbEnv<real>& mine, uint32_t lid,
+                                   real ar, real ai, unsigned off, uint32_t ctr, uint32_t seed, uint32_t key, Put put,
+                                   Old old)
 {
-    const float th = atan2_fast(sp * ar - cp * ai, cp * ar + sp * ai);
-    return th >= 3.14159265f ? -3.14159265f : th;
+    const unsigned long long m = __ballot(pending);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    if (lane == 0) counts[wave] = __popcll(m);
+    if (pending) {
+        HbWgQ<real>& e = queue[(wave << 6) +
+                               __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0))];
+        e.q.put(mine, lid);
+        e.ar = ar, e.ai = ai, e.off = off;
+    }
+    __syncthreads();
+    int total = 0;
+    for (int w = 0; w < nw; ++w) total += counts[w];
+    total = __builtin_amdgcn_readfirstlane(total);
+    // links 64 wave .. 64 wave + 63 of the work-group's pending ones
+    const int n = min(total - (wave << 6), 64);
+    if (n <= 0) return;  // uniform
+    const int lg = __clz(n - 1) - 26;
+    const int g = lane >> lg, k = (wave << 6) + (g < n ? g : 0);
+    int slot = 0, base = 0;
+    for (int w = 0; w < nw; ++w) {
+        const int c = counts[w];
+        if (k >= base && k < base + c) slot = (w << 6) + k - base;
+        base += c;
+    }
+    const HbWgQ<real> e = queue[slot];
+    hb_rounds<real>(g < n, lg, e.q.env(), e.q.lid(), ctr, seed, key, [&](real c, real s) {
+        put(c == real(2) ? old(e.off) : hb_angle(e.ar, e.ai, c, hb_sin(true, c, s)), e.off);
+    });
 }
-__device__ inline double hb_angle(double ar, double ai, double cp, double sp)
+
+// Staple sum A = sum_{nu != mu} exp(i phi_f) + exp(i phi_b), nu ascending,
+// forward before backward, phi_f = v0 - v1 - v2, phi_b = v3 - v4 - v5.
+template <typename real>
+__device__ inline void staple(const real (&v)[3][6], real* ar, real* ai)
 {
-    const double th = M<double>::atan2_(sp * ar - cp * ai, cp * ar + sp * ai);
-    return th >= M<double>::pi ? -M<double>::pi : th;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        real s, co;
+        M<real>::sincos_(v[k][0] - v[k][1] - v[k][2], &s, &co);
+        if (k == 0) {
+            *ar = co;
+            *ai = s;
+        } else {
+            *ar += co;
+            *ai += s;
+        }
+        M<real>::sincos_(v[k][3] - v[k][4] - v[k][5], &s, &co);
+        *ar += co;
+        *ai += s;
+    }
+}
+
+// A link's envelope and its first Philox block's attempts.  draw: kappa > 0
+// (else psi is uniform, (c, s) its cosine and sine, and with A = 0 as well
+// theta = psi, for which *ar becomes 1); pending: neither attempt accepted.
+template <typename real>
+__device__ inline HbEnv<real> hb_first(bool active, const Block4& b0, double beta, real* ar, real ai, real* cp, real* sp,
+                                       bool* draw, bool* pending)
+{
+    using m = M<real>;
+    real kappa = real(1);
+    *cp = *sp = real(0);
+    if (active) {
+        const real R = m::sqrt_(*ar * *ar + ai * ai);
+        kappa = (real)beta * R;
+        if (kappa == real(0)) {
+            // attempt 0: pi (2 U1 - 1)
+            if (R == real(0)) *ar = real(1);
+            if constexpr (sizeof(real) == 4) {
+                const float rev = m::u1(b0.w[0]) - 0.5f;  // in revolutions
+                *cp = __builtin_amdgcn_cosf(rev);
+                *sp = __builtin_amdgcn_sinf(rev);
+            } else {
+                sincos_bounded(m::pi * (2.0 * m::u1(b0.w[0]) - 1.0), sp, cp);
+            }
+        }
+    }
+    *draw = active && kappa != real(0);
+    const HbEnv<real> env(*draw ? kappa : real(1));
+    *pending = false;
+    if (*draw) *pending = !hb_try(env, b0, cp, sp);
+    return env;
 }
 
 // ---------------------------------------------------------------------------
@@ -179,55 +302,13 @@ __device__ inline real update_link(bool active, const real (&v)[3][6], const Blo
 {
     using m = M<real>;
     real ar = real(0), ai = real(0), th = real(0);
-    if (active) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            real s, co;
-            m::sincos_(v[k][0] - v[k][1] - v[k][2], &s, &co);
-            if (k == 0) {
-                ar = co;
-                ai = s;
-            } else {
-                ar += co;
-                ai += s;
-            }
-            m::sincos_(v[k][3] - v[k][4] - v[k][5], &s, &co);
-            ar += co;
-            ai += s;
-        }
-    }
+    if (active) staple(v, &ar, &ai);
     if constexpr (KIND == 0) {
-        real kappa = real(1), cp = real(0), sp = real(0);
-        bool pending = false;
-        if (active) {
-            const real R = m::sqrt_(ar * ar + ai * ai);
-            kappa = (real)beta * R;
-            if (kappa == real(0)) {
-                // psi uniform from attempt 0: pi (2 U1 - 1) (with A = 0 as well, theta = psi)
-                if (R == real(0)) ar = real(1);
-                if constexpr (sizeof(real) == 4) {
-                    const float rev = m::u1(b0.w[0]) - 0.5f;  // in revolutions
-                    cp = __builtin_amdgcn_cosf(rev);
-                    sp = __builtin_amdgcn_sinf(rev);
-                } else {
-                    sincos_bounded(m::pi * (2.0 * m::u1(b0.w[0]) - 1.0), &sp, &cp);
-                }
-            }
-        }
-        const bool draw = active && kappa != real(0);
-        const HbEnv<real> env(draw ? kappa : real(1));
-        if (draw) pending = !hb_try(env, b0, &cp, &sp);
+        real cp, sp;
+        bool draw, pending;
+        const HbEnv<real> env = hb_first(active, b0, beta, &ar, ai, &cp, &sp, &draw, &pending);
         hb_retry<real>(wave_q, pending, env, lid, ctr, seed, key, &cp, &sp);
-        if (active) {
-            if constexpr (sizeof(real) == 8) {
-                // sin psi = +-sqrt((1 - f)(1 + f)) (1 - f and 1 + f exact where they cancel)
-                if (draw) {
-                    const double sq = m::sqrt_((1.0 - cp) * (1.0 + cp));
-                    sp = sp < 0.0 ? -sq : sq;
-                }
-            }
-            th = cp == real(2) ? old_angle() : hb_angle(ar, ai, cp, sp);
-        }
+        if (active) th = cp == real(2) ? old_angle() : hb_angle(ar, ai, cp, hb_sin(draw, cp, sp));
     } else if constexpr (KIND == 2) {
         // Metropolis: theta' = theta + delta (2 U1 - 1), accepted when
         // U2 < exp(beta (Re(e^{i theta'} A) - Re(e^{i theta} A)))

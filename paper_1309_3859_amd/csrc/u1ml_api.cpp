@@ -1028,21 +1028,35 @@ void build_update_tabs(const u1ml_ctx* c, Lane& L)
             r.inv_ny = E.inv_ny;
             r.e = E.res_index;
             r.link_off = E.link_off;
-            // Time slice fastest: the blocks of one stretch of the slice at
-            // consecutive times follow each other, so the links a slice shares
-            // with the next one are reused while they are still in the XCD's L2.
-            for (r.i0 = 0; r.i0 < r.slice; r.i0 += c->block)
-                for (int t = 0; t < E.nt; ++t) {
-                    if (skip[cls] && t % skip[cls] == 0) continue;
-                    const int row = r.i0 / E.nxh;
-                    r.x0 = r.i0 % E.nxh;
-                    r.y0 = row % E.ny;
-                    r.zt = row / E.ny + t;
-                    r.t0 = (unsigned)t * (unsigned)r.slice;
-                    r.tp = (unsigned)((t + 1) % E.nt) * (unsigned)r.slice;
-                    r.tm = (unsigned)((t + E.nt - 1) % E.nt) * (unsigned)r.slice;
-                    logical.push_back(r);
-                }
+            // The order keeps what neighbours share within the XCD's L2 (4 MiB):
+            // time slice fastest (the blocks of one stretch of the slice at
+            // consecutive times follow each other), then the stretches of a
+            // group of rows, then z; the group is sized so that one z step,
+            // eight (direction, parity) arrays of it, takes 1 MiB, and only the
+            // rows at its ends are fetched twice.  With whole planes per z step
+            // (8 MiB) one phase of 128^3 x 16 FP32 fetched 815 MB for 537 MB of
+            // distinct words.  Planes that are no whole number of blocks are
+            // walked as they lie.
+            const int plane = E.nxh * E.ny, word = P.precision == U1ML_FP64 ? 8 : 4;
+            const bool grouped = plane % c->block == 0;
+            const int step = std::max(1, (1 << 20) / (E.nt * c->block * 8 * word)) * c->block;
+            const int group = grouped ? std::min(step, plane) : r.slice;
+            const int nz = grouped ? E.nz : 1, width = grouped ? plane : r.slice;
+            for (int g0 = 0; g0 < width; g0 += group)
+                for (int z = 0; z < nz; ++z)
+                    for (int i = g0; i < std::min(g0 + group, width); i += c->block)
+                        for (int t = 0; t < E.nt; ++t) {
+                            if (skip[cls] && t % skip[cls] == 0) continue;
+                            r.i0 = z * plane + i;
+                            const int row = r.i0 / E.nxh;
+                            r.x0 = r.i0 % E.nxh;
+                            r.y0 = row % E.ny;
+                            r.zt = row / E.ny + t;
+                            r.t0 = (unsigned)t * (unsigned)r.slice;
+                            r.tp = (unsigned)((t + 1) % E.nt) * (unsigned)r.slice;
+                            r.tm = (unsigned)((t + E.nt - 1) % E.nt) * (unsigned)r.slice;
+                            logical.push_back(r);
+                        }
         }
         // padding blocks: a record that starts past its slice (every work-item inactive)
         UpdBlock idle = total > 0 ? logical[total - 1] : pad;
