@@ -40,7 +40,7 @@ struct LinkBuf {
 };
 
 // Quotient a / b of a small index by an extent: 0 <= a < b + 2^10 and b <=
-// 2^22, inv_b = 1/b rounded.  (a + 1/2) / b lies at least 1/(2b) from an
+// 2^22, or a < 2^21; inv_b = 1/b rounded.  (a + 1/2) / b lies at least 1/(2b) from an
 // integer, further than the rounding of the reciprocal and of the one product,
 // so no correction step is needed.
 __device__ inline int fdiv_small(int a, float inv_b) { return (int)(((float)a + 0.5f) * inv_b); }

@@ -43,10 +43,10 @@ struct Layout {
     size_t sz_wf, sz_gf, sz_sph, sz_spo, sz_facc, sz_saved, sz_cpl, sz_opl;
     // scratch sub-offsets (bytes from off_scr)
     size_t s_ens, s_obs, s_r, s_probe, s_comp, s_bstart, s_upd, s_ring, s_vpart, s_ppart, s_pout, s_count,
-        s_stage, s_bmap, s_mmap, s_prodpart, s_pgroup, s_gdesc, s_pblk, s_prow, s_pmap[kPairClasses];
+        s_stage, s_bmap, s_mmap, s_prodpart, s_pgroup, s_gdesc, s_pblk, s_prow, s_pmap[kPairClasses], s_smap[3];
     size_t off_alt;  // the other link buffer (both-parities updates)
     // the lanes' descriptors and tables (each sized for the whole batch)
-    size_t s_lens[4], s_lbstart[4], s_lbmap[4], s_lmmap[4], s_lring[4], s_lpmap[4][kPairClasses];
+    size_t s_lens[4], s_lbstart[4], s_lbmap[4], s_lmmap[4], s_lring[4], s_lpmap[4][kPairClasses], s_lsmap[4][3];
     size_t bmap_stride;  // entries per update class (blocks of 64 threads)
     int n_bstart_tables;
 };
@@ -123,6 +123,12 @@ struct Problem {
     std::vector<PairTile> pair_tile[kPairClasses];
     std::vector<PairRow> pair_rows;
     std::map<std::array<int, 15>, int> pair_shape;  // shape -> first row
+
+    // whole sweeps in LDS (k_slab), per class full / inner tau / outer tau: on, work-group size, LDS, work-groups
+    bool slab_on[3] = {};
+    int slab_block[3] = {};
+    size_t slab_lds_bytes[3] = {};
+    size_t slab_blocks[3] = {};
 
     bool any_pair() const { return std::find(pair_on, pair_on + kPairClasses, true) != pair_on + kPairClasses; }
     // time slices per slab whose links a class updates at thickness tau, and slabs (temporal or full: all, one)
@@ -519,6 +525,40 @@ void pair_for_tiles(const Problem& P, int cls, int k, F f)
                 }
 }
 
+// Chooses, per class of sweeps (full, inner slabs, outer slabs), whether sweeps
+// run in LDS, one work-group per slab or lattice: where a phase of every
+// ensemble's slab has at most one link per work-item of a work-group and its
+// links fit LDS.  MI355X, us per sweep otherwise / in LDS: FP32 4^4 full 48 / 27,
+// 8^3 x 4 (1024 links a phase) 59 / 52, 10^3 x 4 (2000) 69 / 97; slabs of 2 with a
+// measurement each, 8^3 (512) 55 / 45, 10^3 (1000) 65 / 59, 12^3 (1728) 63 / 83;
+// FP64 4^4 full 80 / 52, 6^3 x 4 (432) 94 / 83, 8^3 x 4 (1024) 92 / 157; slabs of
+// 8^3 (512) 90 / 78, 10^3 (1000) 99 / 121.
+void plan_slabs(Problem* P)
+{
+    const int word = P->precision == U1ML_FP64 ? 8 : 4;
+    const int max_threads = P->precision == U1ML_FP64 ? kSlabThreads<double> : kSlabThreads<float>;
+    const bool hb = P->update == U1ML_UPDATE_HEATBATH;
+    for (int cls = 0; cls < 3; ++cls) {
+        const int tau = cls == 0 ? 0 : (cls == 1 ? P->tau_i : P->tau_o);
+        bool ok = cls != 2 || P->two;
+        size_t lds = 0, blocks = 0;
+        int threads = 64;
+        for (const u1ml_ensemble& E : P->ens) {
+            const double links = (double)E.ns[0] / 2 * E.ns[1] * E.ns[2] * (tau ? tau : E.nt);  // of the largest phase
+            ok = ok && links <= max_threads;
+            if (ok) threads = std::max(threads, ((int)links + 63) / 64 * 64);
+            blocks += tau ? E.nt / tau : 1;
+        }
+        for (const u1ml_ensemble& E : P->ens)
+            if (ok)
+                lds = std::max(lds, slab_lds(E.ns[0] / 2 * E.ns[1] * E.ns[2], tau ? tau + 1 : E.nt, threads, hb, word));
+        P->slab_on[cls] = ok && lds <= kSlabLds;
+        P->slab_block[cls] = threads;
+        P->slab_lds_bytes[cls] = P->slab_on[cls] ? lds : 0;
+        P->slab_blocks[cls] = P->slab_on[cls] ? blocks : 0;
+    }
+}
+
 // Chooses, per class, whether sweeps update both parities in one launch, and
 // the tiles.  Two launches cost two launch times (about 1.9 us each) plus 0.4 us
 // per wave and SIMD of either parity; one costs one launch time plus 0.55 us per
@@ -543,8 +583,10 @@ void plan_pairs(Problem* P)
         P->pair_on[cls] = false;
         P->pair_tile[cls].assign(P->n_ens, PairTile());
         const int tau = P->pair_tau(cls);
-        // both buffers of an ensemble within 32-bit offsets of its links; sweeps of an even number of passes
+        // both buffers of an ensemble within 32-bit offsets of its links; not for sweeps in LDS
         bool ok = 2 * bytes < 4294967296.0 && (cls % 3 != 2 || P->two);
+        if (cls < 9) ok = ok && !P->slab_on[cls % 3];
+        else ok = ok && !(P->slab_on[0] && P->slab_on[1] && (!P->two || P->slab_on[2]));
         double one = 0.0, two = 0.0, lat = 1.0;
         P->pair_block[cls] = 64;
         for (int k = 0; ok && k < P->n_ens; ++k) {
@@ -648,6 +690,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
         const int ks = P.ins_mfma_est ? kMfSlots : P.ins_ks_vec;
         if (P.ins_ks != ks) pack_slot_blocks(&P, ks);
     }
+    plan_slabs(&P);
     plan_pairs(&P);
     const bool spec = P.spectral;
     size_t L = 0, HC = 0, HO = 0, AT = 0, ATO = 0, OT = 0, OTO = 0, VAC = 0, PP = 0;
@@ -796,6 +839,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
         pair_bytes[cls] = P.pair_on[cls] ? sizeof(PairBlock) * blocks : 0;
         Lo->s_pmap[cls] = take(pair_bytes[cls]);
     }
+    for (int cls = 0; cls < 3; ++cls) Lo->s_smap[cls] = take(sizeof(SlabBlock) * P.slab_blocks[cls]);
     Lo->s_prodpart = take(sizeof(double) * PP);
     for (int l = 0; l < kMaxLanes; ++l) {
         Lo->s_lens[l] = take(sizeof(EnsDesc) * n);
@@ -804,6 +848,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
         Lo->s_lmmap[l] = take(sizeof(int2) * mblocks);
         Lo->s_lring[l] = take(sizeof(int) * 4);
         for (int cls = 0; cls < kPairClasses; ++cls) Lo->s_lpmap[l][cls] = take(pair_bytes[cls]);
+        for (int cls = 0; cls < 3; ++cls) Lo->s_lsmap[l][cls] = take(sizeof(SlabBlock) * P.slab_blocks[cls]);
     }
     Lo->s_pgroup = take(sizeof(int) * std::max<size_t>(Np, 1));
     Lo->s_gdesc = take(sizeof(int) * std::max<size_t>(2 * NG, 2));
@@ -897,6 +942,8 @@ struct Lane {
     int* d_ring = nullptr;
     double* prodpart = nullptr;
     size_t bmap_stride = 0;
+    SlabBlock* d_smap[3] = {};
+    std::vector<SlabBlock> h_smap[3];  // work-groups of the sweeps in LDS
     PairBlock* d_pmap[kPairClasses] = {};
     std::vector<PairBlock> h_pmap[kPairClasses];  // work-groups of the both-parities launches
     int upd_grid[kUpdateClasses] = {0, 0, 0, 0};  // grid size of each update class (multiple of 8)
@@ -1108,6 +1155,33 @@ void build_pair_tabs(const u1ml_ctx* c, Lane& L)
     }
 }
 
+void build_slab_tabs(const u1ml_ctx* c, Lane& L)
+{
+    const Problem& P = c->P;
+    for (int cls = 0; cls < 3; ++cls) {
+        L.h_smap[cls].clear();
+        if (!P.slab_on[cls]) continue;
+        const int tau = cls == 0 ? 0 : (cls == 1 ? P.tau_i : P.tau_o);
+        for (const EnsDesc& E : L.h_ens) {
+            SlabBlock r;
+            std::memset(&r, 0, sizeof r);
+            r.e = E.res_index;
+            r.tau = tau;
+            r.layers = tau ? tau + 1 : E.nt;
+            r.nxh = E.nxh;
+            r.ny = E.ny;
+            r.slice = E.nxh * E.ny * E.nz;
+            r.vh = E.vh;
+            r.nt = E.nt;
+            r.inv_nxh = E.inv_nxh;
+            r.inv_ny = E.inv_ny;
+            r.inv_slice = E.inv_slice;
+            r.link_off = E.link_off;
+            for (r.t0 = 0; r.t0 < E.nt; r.t0 += tau ? tau : E.nt) L.h_smap[cls].push_back(r);
+        }
+    }
+}
+
 // Every launch table of a lane, from its ensembles' descriptors (whose
 // contraction and product fields are already set).
 void build_lane_tables(const u1ml_ctx* c, Lane& L)
@@ -1117,6 +1191,7 @@ void build_lane_tables(const u1ml_ctx* c, Lane& L)
     L.h_bstart.assign((size_t)kNumTabs * (n + 1), 0);
     build_update_tabs(c, L);
     build_pair_tabs(c, L);
+    build_slab_tabs(c, L);
     const size_t R = P.r.size(), NG = P.gdesc.size() / 2;
     std::vector<long long> all(n), meas(n), con(n), comb(n), prod(n), site(n), plane(n), mac(n), stage(n), ins(n);
     L.max_s_in = 1;
@@ -1182,6 +1257,10 @@ hipError_t upload_lane(const Lane& L)
         if (!L.h_pmap[cls].empty())
             e = hipMemcpy(L.d_pmap[cls], L.h_pmap[cls].data(), sizeof(PairBlock) * L.h_pmap[cls].size(),
                           hipMemcpyHostToDevice);
+    for (int cls = 0; cls < 3 && e == hipSuccess; ++cls)
+        if (!L.h_smap[cls].empty())
+            e = hipMemcpy(L.d_smap[cls], L.h_smap[cls].data(), sizeof(SlabBlock) * L.h_smap[cls].size(),
+                          hipMemcpyHostToDevice);
     if (e == hipSuccess && !L.h_mmap.empty())
         e = hipMemcpy(L.d_mmap, L.h_mmap.data(), sizeof(int2) * L.h_mmap.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(L.d_ring, ring0, sizeof ring0, hipMemcpyHostToDevice);
@@ -1234,6 +1313,7 @@ hipError_t split_lanes(u1ml_ctx* c, int nl)
         L.d_mmap = (int2*)(s + Lo.s_lmmap[l]);
         L.d_ring = (int*)(s + Lo.s_lring[l]);
         for (int cls = 0; cls < kPairClasses; ++cls) L.d_pmap[cls] = (PairBlock*)(s + Lo.s_lpmap[l][cls]);
+        for (int cls = 0; cls < 3; ++cls) L.d_smap[cls] = (SlabBlock*)(s + Lo.s_lsmap[l][cls]);
         // the lanes use disjoint parts of the slab-product partials
         L.prodpart = (double*)(s + Lo.s_prodpart) + pp_off;
         L.stream = l == 0 ? c->stream : c->lane_stream[l];
@@ -1342,9 +1422,29 @@ hipError_t enq_sweep(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau, int hb
 hipError_t enq_mirror(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau)
 {
     bool any = false;
+    if (c->P.slab_on[update_class_tau(c, tau)]) return hipSuccess;
     for (int mu = 0; mu < 3; ++mu) any = any || c->P.pair_on[3 * mu + update_class_tau(c, tau)];
     if (!any && !c->P.pair_on[9]) return hipSuccess;
     return launch_mirror(L.d_ens, L.n, c->P.precision, c->links, (unsigned)c->Lo.off_alt, 256, st);
+}
+
+// n sweeps, in LDS where the plan has them so (at most kSlabSweeps a launch),
+// with counter offsets hb, hb + 1, ...
+hipError_t enq_sweeps(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau, int hb, int n)
+{
+    const Problem& P = c->P;
+    const int cls = update_class_tau(c, tau);
+    hipError_t e = hipSuccess;
+    if (!P.slab_on[cls]) {
+        for (int k = 0; e == hipSuccess && k < n; ++k) e = enq_sweep(c, L, st, tau, hb + k);
+        return e;
+    }
+    const int stoch = P.update == U1ML_UPDATE_METROPOLIS ? U1ML_METROPOLIS : U1ML_HEATBATH;
+    for (int k = 0; e == hipSuccess && k < n; k += kSlabSweeps)
+        e = launch_slab(SlabLaunch{c->whole.d_ens, L.d_smap[cls], (int)L.h_smap[cls].size(), P.slab_block[cls], P.precision,
+                                   P.slab_lds_bytes[cls], c->links, c->d_upd, hb + k, std::min(kSlabSweeps, n - k), stoch,
+                                   P.n_or, P.metro_delta, st});
+    return e;
 }
 
 // The n_o outer iterations of Algorithm 1 (one iteration for one level).
@@ -1367,11 +1467,13 @@ hipError_t enq_levels(u1ml_ctx* c, const Lane& L, hipStream_t st, bool store_o, 
     for (int ko = 0; e == hipSuccess && ko < P.n_o; ++ko) {
         if (P.two && P.k_o > 0) {
             e = enq_mirror(c, L, st, P.tau_o);
-            for (int k = 0; e == hipSuccess && k < P.k_o; ++k) e = enq_sweep(c, L, st, P.tau_o, hb++);
+            if (e == hipSuccess) e = enq_sweeps(c, L, st, P.tau_o, hb, P.k_o);
+            hb += P.k_o;
         }
         if (e == hipSuccess && P.k_i > 0) e = enq_mirror(c, L, st, P.tau_i);
         for (int m = 0; e == hipSuccess && m < P.n_i; ++m) {
-            for (int k = 0; e == hipSuccess && k < P.k_i; ++k) e = enq_sweep(c, L, st, P.tau_i, hb++);
+            if (e == hipSuccess) e = enq_sweeps(c, L, st, P.tau_i, hb, P.k_i);
+            hb += P.k_i;
             if (e == hipSuccess)
                 e = launch_measure(L.d_ens, L.d_mmap, L.tab_total(kTabMeas), P.precision, c->links, c->hc, c->ho,
                                    c->vpart, m, ko * P.n_i + m, P.tau_i, store_o ? 1 : 0, P.multihit ? 1 : 0, st);
@@ -1868,6 +1970,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         L.d_mmap = (int2*)(s + Lo.s_mmap);
         L.d_ring = (int*)(s + Lo.s_ring);
         for (int cls = 0; cls < kPairClasses; ++cls) L.d_pmap[cls] = (PairBlock*)(s + Lo.s_pmap[cls]);
+        for (int cls = 0; cls < 3; ++cls) L.d_smap[cls] = (SlabBlock*)(s + Lo.s_smap[cls]);
         L.prodpart = (double*)(s + Lo.s_prodpart);
         L.stream = c->stream;
         build_lane_tables(c, L);
@@ -1878,7 +1981,8 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         hipError_t ea = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device);
         const size_t plane_lds = P.spectral ? (2 * (size_t)c->spec_n12max + 2 * (size_t)c->spec_npm) * sizeof(double2) : 0;
         const size_t mac_lds = P.spectral ? spec_mac_lds(c->spec_npm) : 0;
-        const size_t need = std::max(std::max(c->con_lds, c->ins_lds), std::max(plane_lds, mac_lds));
+        const size_t slab_bytes = *std::max_element(P.slab_lds_bytes, P.slab_lds_bytes + 3);
+        const size_t need = std::max({c->con_lds, c->ins_lds, plane_lds, mac_lds, slab_bytes});
         if (ea != hipSuccess || (size_t)lds_max < need) {
             release(c);
             return set_err(nullptr, ea != hipSuccess ? U1ML_EDEVICE : U1ML_ENOTSUP,
@@ -1948,6 +2052,10 @@ u1ml_status u1ml_sweeps(u1ml_ctx* ctx, int n)
     if (n == 0) return U1ML_OK;
     // one lane's n sweeps on its stream (graph of one sweep, launched n times)
     auto lane_sweeps = [&](Lane& L) -> hipError_t {
+        if (ctx->P.slab_on[0]) {  // one launch for many sweeps
+            const hipError_t e = enq_sweeps(ctx, L, L.stream, 0, 0, n);
+            return e == hipSuccess ? launch_advance_counters(L.d_ens, ctx->d_upd, L.n, n, L.stream) : e;
+        }
         if (ctx->use_graphs) {
             if (!L.g_sweep &&
                 capture(ctx, [&](hipStream_t st) { return enq_sweep_with_counter(ctx, L, st); }, &L.g_sweep) != U1ML_OK)

@@ -79,6 +79,28 @@ template <typename real>
 constexpr int kPairThreads = sizeof(real) == 8 ? 512 : 1024;
 constexpr int kPairClasses = 10;  // direction x, y, z by full, inner tau, outer tau; temporal
 
+// One work-group of a launch that runs whole sweeps in LDS: a slab of
+// thickness tau from time t0 (layers t0 .. t0 + tau, the last only frozen
+// spatial links), or with tau = 0 a whole lattice of nt layers.
+struct alignas(64) SlabBlock {
+    int e;  // the ensemble (problem order)
+    int t0, tau, layers;
+    int nxh, ny, slice, vh;
+    int nt;
+    float inv_nxh, inv_ny, inv_slice;
+    long long link_off;
+};
+static_assert(sizeof(SlabBlock) == 64, "SlabBlock is one 64-byte scalar load");
+template <typename real>
+constexpr int kSlabThreads = sizeof(real) == 8 ? 512 : 1024;  // largest work-group, and links of a phase
+constexpr size_t kSlabLds = 160 * 1024;  // LDS of a compute unit
+constexpr int kSlabSweeps = 64;         // sweeps a launch runs at most
+// dynamic LDS: 16-byte neighbour records of a slice, the heatbath's queue, the links
+inline size_t slab_lds(int slice, int layers, int threads, bool heatbath, int word)
+{
+    return (size_t)slice * 16 + (heatbath ? (size_t)threads * (word == 8 ? 24 : 8) : 0) + (size_t)8 * layers * slice * word;
+}
+
 // Observable tables in device memory.
 struct ObsDesc {
     int n_dirs;
@@ -181,6 +203,19 @@ struct PairLaunch {
     hipStream_t st;
 };
 hipError_t launch_pair(const PairLaunch& a);
+// n_sweeps whole sweeps (the stochastic kind, then n_or overrelaxation passes) in LDS (k_slab.hip)
+struct SlabLaunch {
+    const EnsDesc* d_ens;  // problem order
+    const SlabBlock* d_blocks;
+    int total_blocks, block, precision;
+    size_t lds_bytes;
+    void* links;
+    const uint32_t* d_upd;
+    int pass_offset, n_sweeps, stoch, n_or;
+    double metro_delta;
+    hipStream_t st;
+};
+hipError_t launch_slab(const SlabLaunch& a);
 hipError_t launch_mirror(const EnsDesc* d_ens, int n_ens, int precision, void* links, unsigned alt, int blocks,
                          hipStream_t st);
 hipError_t launch_health(const EnsDesc* d_ens, const int* d_bstart_all, int n_ens, int total_blocks, int precision,

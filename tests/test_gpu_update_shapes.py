@@ -72,10 +72,12 @@ def test_work_group_size_changes_no_bit(ns, nt, precision):
 
 # slabs of one, two and three inner layers, extents of 2, tiles that do not
 # divide the extents, rows of 1 .. 40 half sites, two levels, odd and even
-# numbers of passes
+# numbers of passes, slabs of 512 and 1024 links a phase (the most that sweeps
+# in LDS take) and just fewer
 RUNS = [((4, 4, 4), 4, [(2, 2, 1)], 3), ((2, 2, 2), 2, [(2, 2, 2)], 3), ((24, 24, 24), 4, [(2, 1, 1)], 3),
         ((10, 14, 6), 12, [(4, 2, 1), (2, 2, 1)], 2), ((18, 2, 22), 6, [(3, 2, 1)], 1), ((80, 6, 10), 8, [(4, 1, 1)], 0),
-        ((2, 26, 14), 8, [(8, 1, 1), (4, 2, 1)], 3)]
+        ((2, 26, 14), 8, [(8, 1, 1), (4, 2, 1)], 3), ((8, 8, 8), 4, [(2, 2, 3)], 3), ((6, 8, 10), 4, [(2, 2, 1)], 3),
+        ((6, 8, 12), 12, [(6, 1, 2), (2, 2, 1)], 2), ((2, 4, 6), 24, [(24, 1, 1)], 3)]
 
 
 @pytest.mark.gpu
