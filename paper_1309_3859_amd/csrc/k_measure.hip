@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "device_common.hpp"
+#include "link_update.hpp"
 #include "scaled.hpp"
 #include "u1ml_internal.hpp"
 
@@ -133,41 +134,90 @@ struct SlabO<float> {
     __device__ inline double olin(double sqrt_beta) const { return sqrt_beta * (double)s; }
 };
 
-// Sum of 12 per-thread doubles over a 256-thread block in a fixed order (lanes
-// l and l + 32 of a wave added by one exchange, the 128 pair sums staged in
+// v of the lane CTRL names within its row of 16 (data-parallel primitives: a
+// register move, where a shuffle goes through LDS)
+template <int CTRL>
+__device__ inline double dpp(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)hi << 32 | (unsigned)lo);
+}
+// v + (v of lane ^ 32), v + (v of lane ^ 16): the halves (rows) of a wave swapped in registers
+__device__ inline double add_xor32(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return __longlong_as_double((long long)hi[0] << 32 | lo[0]) + __longlong_as_double((long long)hi[1] << 32 | lo[1]);
+}
+__device__ inline double add_xor16(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return __longlong_as_double((long long)hi[0] << 32 | lo[0]) + __longlong_as_double((long long)hi[1] << 32 | lo[1]);
+}
+// sum over the wave, lane ^ 32, ^ 16, ... ^ 1 added in turn (every lane holds
+// it); from lane ^ 4 on the values repeat every 8 lanes, so a rotation of the
+// row serves
+__device__ inline double wave_sum(double a)
+{
+    a = add_xor16(add_xor32(a));
+    a += dpp<0x128>(a);  // row_ror:8
+    a += dpp<0x124>(a);  // row_ror:4
+    a += dpp<0x4E>(a);   // quad_perm [2, 3, 0, 1]
+    a += dpp<0xB1>(a);   // quad_perm [1, 0, 3, 2]
+    return a;
+}
+
+// Sum of 12 per-thread doubles over the first four waves of a work-group in a
+// fixed order (lanes l and l + 32 of a wave added, the 128 pair sums staged in
 // LDS, then each wave reduces three of the quantities), added to the block's
-// running double-double partials acc[12][2] of the configuration; the first
+// running double-double partials acc[12][2] of the configuration, which the
+// caller read beforehand (before, in lane kk those of quantity 3 wave + kk); the first
 // measurement (first != 0) overwrites them instead, so they need no clearing
 // between configurations.  12 KB of LDS, so that LDS does not limit a CU to
 // fewer work-groups than its wave slots hold.
-__device__ inline void block_sum12(const double* v, double* acc, int first)
+__device__ inline void block_sum12(const double* v, double2 before, double* acc, int first)
 {
     __shared__ double red[12][128];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave < 4) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        const double a = v[k] + __shfl_xor(v[k], 32);
-        if (lane < 32) red[k][wave * 32 + lane] = a;
+        for (int k = 0; k < 12; ++k) {
+            const double a = add_xor32(v[k]);
+            if (lane < 32) red[k][wave * 32 + lane] = a;
+        }
     }
     __syncthreads();
+    if (wave >= 4) return;
+    double sum[3];
 #pragma unroll
-    for (int kk = 0; kk < 3; ++kk) {
-        const int k = 3 * wave + kk;
-        double a = red[k][lane] + red[k][lane + 64];
-        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-        if (lane == 0) {
-            const dd r = first ? dd{a, 0.0} : dd_add(dd{acc[2 * k], acc[2 * k + 1]}, a);
-            acc[2 * k] = r.hi;
-            acc[2 * k + 1] = r.lo;
-        }
+    for (int kk = 0; kk < 3; ++kk) sum[kk] = wave_sum(red[3 * wave + kk][lane] + red[3 * wave + kk][lane + 64]);
+    if (lane < 3) {
+        const double a = lane == 0 ? sum[0] : (lane == 1 ? sum[1] : sum[2]);
+        const dd r = first ? dd{a, 0.0} : dd_add(dd{before.x, before.y}, a);
+        reinterpret_cast<double2*>(acc)[3 * wave + lane] = make_double2(r.hi, r.lo);
     }
 }
 
+// With MULTIHIT the conditional means of the slab's temporal links (a staple
+// sum and a continued fraction of 40 and more divisions each) are formed first,
+// one link per work-item: 256 items times kHitLanes slices at a time, the
+// products over the slices then in order.
+constexpr int kHitLanes = 4;
+
+// What bounds it: the chain of one work-item on small lattices (its loads, two
+// slices' sines, the block sums), so the geometry comes in one record, the
+// running sums are read while the angles are in flight and the reductions stay
+// in registers.
 template <typename real, bool MULTIHIT>
-__global__ void __launch_bounds__(256) k_measure(const EnsDesc* __restrict__ ens, const int2* __restrict__ bmap,
-                                                 const real* __restrict__ links, double2* __restrict__ hist_c,
-                                                 real* __restrict__ hist_o, double* __restrict__ vac_part, int m_in,
-                                                 int m, int tau, int store_o, int n_blocks)
+__global__ void __launch_bounds__(MULTIHIT ? 256 * kHitLanes : 256)
+    k_measure(const EnsDesc* __restrict__ ens, const MeasBlock* __restrict__ blocks, const real* __restrict__ links,
+              double2* __restrict__ hist_c, real* __restrict__ hist_o, double* __restrict__ vac_part, int m_in, int m,
+              int tau, int store_o, int n_blocks)
 {
     // XCD-aware order: the hardware deals consecutive work-groups to the eight
     // XCDs in turn, so work-group b takes block (b mod 8) G/8 + b/8 of the map
@@ -175,61 +225,81 @@ __global__ void __launch_bounds__(256) k_measure(const EnsDesc* __restrict__ ens
     // sites and finds the neighbours' links in its own L2
     const int bid = (int)(blockIdx.x & 7u) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
     if (bid >= n_blocks) return;  // uniform: padding of the launch to a multiple of 8
-    const int2 be = bmap[bid];
-    const EnsDesc& E = ens[be.x];
-    const int nsig = E.nsig, S = E.s_in;
-    const int item = be.y * 256 + (int)threadIdx.x;
-    const real* lb = links + E.link_off;
-    const unsigned vh = (unsigned)E.vh;
-    constexpr unsigned w = sizeof(real);
+    const MeasBlock B = blocks[bid];
+    const EnsDesc& E = ens[B.e];
+    const int nsig = B.nsig;
+    constexpr int w = sizeof(real);
+    const int tid = (int)threadIdx.x & 255;
+    // item tid: slab s, site xs (a block may reach into the next slabs)
+    const int rel = B.xs0 + tid;
+    const int ds = nsig >= 256 ? (int)(rel >= nsig) : fdiv_small(rel, B.inv_nsig);
+    const int s = B.s0 + ds, xs = rel - ds * nsig;
+    const bool active = s < B.slabs;
+    const int yz = fdiv(active ? xs : 0, B.nx, B.inv_nx);
+    const int x = (active ? xs : 0) - yz * B.nx;
+    const int z = fdiv(yz, B.ny, B.inv_ny);
+    const int y = yz - z * B.ny;
+    const int t0 = (active ? s : 0) * tau;
+    double* acc = vac_part + E.vac_part_off + (size_t)B.blk * 24;
+    double2 before = make_double2(0.0, 0.0);
+    if (m != 0) before = reinterpret_cast<const double2*>(acc)[3 * (tid >> 6) + min(tid & 63, 2)];
+    double2 cm = make_double2(1.0, 0.0);  // multihit slab phase
+    if constexpr (MULTIHIT) {
+        __shared__ double2 hit[kHitLanes][256];
+        const unsigned vh = (unsigned)B.vh;
+        const Geo g{B.nx, B.ny, E.nz, B.nt, B.nx >> 1, (B.nx >> 1) * B.ny, nsig >> 1};
+        const int q = (int)threadIdx.x >> 8;
+        for (int k0 = 0; k0 < tau; k0 += kHitLanes) {
+            if (k0 + q < tau && active) {
+                // conditional mean of the temporal link: e^{-i arg A} I1/I0(beta |A|)
+                const int t = t0 + k0 + q;
+                const Site c{x, y, z, t, g.sy * yz + g.st * t};
+                real ar, ai;
+                staple_sum<real, 3>(links + B.link_off, vh, g, c, (x + y + z + t) & 1, &ar, &ai);
+                const double R = sqrt((double)ar * (double)ar + (double)ai * (double)ai);
+                const double f = R > 0.0 ? bessel_ratio(E.beta * R) / R : 0.0;
+                hit[q][tid] = make_double2((double)ar * f, -(double)ai * f);
+            }
+            __syncthreads();
+            if (q == 0)
+                for (int k = k0; k < min(tau, k0 + kHitLanes); ++k) {
+                    const double ur = hit[k - k0][tid].x, ui = hit[k - k0][tid].y;
+                    cm = make_double2(cm.x * ur - cm.y * ui, cm.x * ui + cm.y * ur);
+                }
+            __syncthreads();
+        }
+    }
     double vac[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) vac[k] = 0.0;
-    if (item < nsig * S) {
-        const Geo g{E.nx, E.ny, E.nz, E.nt, E.nxh, E.nxh * E.ny, E.nxh * E.ny * E.nz};
-        // division-free decode; N_sigma is even, so item / N_sigma = (item / 2) / (N_sigma / 2)
-        // with the divisor N_sigma / 2 (the slice) inside fdiv's 24-bit range, and
-        // 1/Nx = (1/(Nx/2)) / 2 exactly
-        const int s = fdiv(item >> 1, nsig >> 1, E.inv_slice);
-        const int xs = item - s * nsig;
-        const int yz = fdiv(xs, E.nx, 0.5f * E.inv_nxh);
-        const int x = xs - yz * E.nx;
-        const int z = fdiv(yz, E.ny, E.inv_ny);
-        const int y = yz - z * E.ny;
+    if (active && threadIdx.x < 256) {
+        const LinkBuf<real> lb(const_cast<real*>(links) + B.link_off);
+        const unsigned vhb = (unsigned)B.vh * w;
+        const int nxh = B.nx >> 1, row = nxh * yz, st = nsig >> 1;
+        // half indices of the site and of its neighbours one step up, in bytes
+        const unsigned h = (unsigned)((row + (x >> 1)) * w);
+        const unsigned hx = (unsigned)((row + (x == B.nx - 1 ? 0 : (x + 1) >> 1)) * w);
+        const unsigned hy = h + (unsigned)((y == B.ny - 1 ? nxh - nxh * B.ny : nxh) * w);
+        const unsigned hz = h + (unsigned)((row + nxh * B.ny - nxh * y >= st ? nxh * B.ny - st : nxh * B.ny) * w);
         double Th = 0.0;
-        double2 cm = make_double2(1.0, 0.0);  // multihit slab phase
         SlabO<real> so[6];
-        Site c{x, y, z, s * tau, g.sy * yz + g.st * (s * tau)};
         // the 16 link angles of the six plaquettes at (x, t): u[0..3] the four
         // links at the site, then the ones at x + x, x + y, x + z, x + t
-        auto load_slice = [&](const Site& c, real* u) {
-            // element offsets of the site's parity and the other one (a select,
-            // not a multiplication by the per-thread parity)
-            const bool odd = ((x + y + z + c.t) & 1) != 0;
-            const unsigned po = odd ? vh : 0u, qo = odd ? 0u : vh;
-            const Site cx = mv<0, +1>(c, g), cy = mv<1, +1>(c, g), cz = mv<2, +1>(c, g), ct = mv<3, +1>(c, g);
-            auto L = [&](unsigned dir, unsigned par_off, const Site& st) {
-                return ldo(lb, (dir * 2u * vh + par_off + hidx(st)) * w);
-            };
-            u[0] = L(0, po, c), u[1] = L(1, po, c), u[2] = L(2, po, c), u[3] = L(3, po, c);
-            u[4] = L(3, qo, cx), u[5] = L(3, qo, cy), u[6] = L(3, qo, cz);   // t-links at x + x, x + y, x + z
-            u[7] = L(0, qo, ct), u[8] = L(1, qo, ct), u[9] = L(2, qo, ct);   // x, y, z-links at x + t
-            u[10] = L(2, qo, cy), u[11] = L(1, qo, cz);                       // z at x + y, y at x + z
-            u[12] = L(0, qo, cz), u[13] = L(2, qo, cx);                       // x at x + z, z at x + x
-            u[14] = L(1, qo, cx), u[15] = L(0, qo, cy);                       // y at x + x, x at x + y
+        auto load_slice = [&](int t, real* u) {
+            const bool odd = ((x + y + z + t) & 1) != 0;
+            const unsigned at = (unsigned)(t * st) * w, up = t == B.nt - 1 ? 0u : at + (unsigned)st * w;
+            const unsigned q = odd ? 0u : vhb;  // the other parity
+            const unsigned c = h + at + (vhb - q), cx = hx + at + q, cy = hy + at + q, cz = hz + at + q, ct = h + up + q;
+            const unsigned d1 = 2 * vhb, d2 = 4 * vhb, d3 = 6 * vhb;
+            u[0] = lb.ld(c, 0), u[1] = lb.ld(c, d1), u[2] = lb.ld(c, d2), u[3] = lb.ld(c, d3);
+            u[4] = lb.ld(cx, d3), u[5] = lb.ld(cy, d3), u[6] = lb.ld(cz, d3);  // t-links at x + x, x + y, x + z
+            u[7] = lb.ld(ct, 0), u[8] = lb.ld(ct, d1), u[9] = lb.ld(ct, d2);   // x, y, z-links at x + t
+            u[10] = lb.ld(cy, d2), u[11] = lb.ld(cz, d1);                      // z at x + y, y at x + z
+            u[12] = lb.ld(cz, 0), u[13] = lb.ld(cx, d2);                       // x at x + z, z at x + x
+            u[14] = lb.ld(cx, d1), u[15] = lb.ld(cy, 0);                       // y at x + x, x at x + y
         };
-        auto use_slice = [&](const Site& c, const real* u) {
+        auto use_slice = [&](const real* u) {
             Th += (double)u[3];
-            if (MULTIHIT) {
-                // conditional mean of the temporal link: e^{-i arg A} I1/I0(beta |A|)
-                real ar, ai;
-                const int p = ((x + y + z + c.t) & 1);
-                staple_sum<real, 3>(lb, vh, g, c, p, &ar, &ai);
-                const double R = sqrt((double)ar * (double)ar + (double)ai * (double)ai);
-                const double f = R > 0.0 ? bessel_ratio(E.beta * R) / R : 0.0;
-                const double ur = (double)ar * f, ui = -(double)ai * f;
-                cm = make_double2(cm.x * ur - cm.y * ui, cm.x * ui + cm.y * ur);
-            }
             real th[6];
             th[0] = u[0] + u[4] - u[7] - u[3];   // P_xt
             th[1] = u[1] + u[5] - u[8] - u[3];   // P_yt
@@ -243,18 +313,16 @@ __global__ void __launch_bounds__(256) k_measure(const EnsDesc* __restrict__ ens
         // slices two at a time, all 32 loads issued before either is used
         int k = 0;
         for (; k + 1 < tau; k += 2) {
-            const Site c1 = mv<3, +1>(c, g);
             real a[16], b[16];
-            load_slice(c, a);
-            load_slice(c1, b);
-            use_slice(c, a);
-            use_slice(c1, b);
-            c = mv<3, +1>(c1, g);
+            load_slice(t0 + k, a);
+            load_slice(t0 + k + 1, b);
+            use_slice(a);
+            use_slice(b);
         }
         if (k < tau) {
             real a[16];
-            load_slice(c, a);
-            use_slice(c, a);
+            load_slice(t0 + k, a);
+            use_slice(a);
         }
         double os[12];
 #pragma unroll
@@ -264,44 +332,48 @@ __global__ void __launch_bounds__(256) k_measure(const EnsDesc* __restrict__ ens
         }
         double sn, cs;
         sincos_bounded(Th, &sn, &cs);  // |Th| <= tau pi
-        hist_c[E.hc_off + ((size_t)m_in * S + s) * nsig + xs] = make_double2(cs, sn);
-        if (MULTIHIT) hist_c[E.hcm_off + ((size_t)m_in * S + s) * nsig + xs] = cm;
+        const size_t rowm = ((size_t)m_in * B.slabs + s) * nsig + xs;
+        hist_c[E.hc_off + rowm] = make_double2(cs, sn);
+        if (MULTIHIT) hist_c[E.hcm_off + rowm] = cm;
         if (store_o) {
             // per-measurement slab sums are stored in the link precision; the sums
             // over measurements are formed in FP64 by the contraction
-            real* ho = hist_o + E.ho_off + ((size_t)m_in * S + s) * 12 * nsig + xs;
+            real* ho = hist_o + E.ho_off + ((size_t)m_in * B.slabs + s) * 12 * nsig + xs;
 #pragma unroll
             for (int k = 0; k < 12; ++k) ho[(size_t)k * nsig] = (real)os[k];
         }
 #pragma unroll
         for (int k = 0; k < 12; ++k) vac[k] = os[k];
     }
-    block_sum12(vac, vac_part + E.vac_part_off + (size_t)be.y * 24, m == 0);
+    block_sum12(vac, before, acc, m == 0);
 }
 
-hipError_t launch_measure(const EnsDesc* d_ens, const int2* d_bmap, int total_blocks, int precision, const void* links,
-                          double2* hist_c, void* hist_o, double* vac_part, int m_in, int m, int tau, int store_o,
-                          int multihit, hipStream_t st)
+template <typename real>
+static void launch_measure_t(const EnsDesc* d_ens, const MeasBlock* d_blocks, int total_blocks, const void* links,
+                             double2* hist_c, void* hist_o, double* vac_part, int m_in, int m, int tau, int store_o,
+                             int multihit, hipStream_t st)
+{
+    const dim3 g((total_blocks + 7) / 8 * 8);
+    if (multihit)
+        hipLaunchKernelGGL((k_measure<real, true>), g, dim3(256 * (tau < kHitLanes ? tau : kHitLanes)), 0, st, d_ens,
+                           d_blocks, (const real*)links, hist_c, (real*)hist_o, vac_part, m_in, m, tau, store_o,
+                           total_blocks);
+    else
+        hipLaunchKernelGGL((k_measure<real, false>), g, dim3(256), 0, st, d_ens, d_blocks, (const real*)links, hist_c,
+                           (real*)hist_o, vac_part, m_in, m, tau, store_o, total_blocks);
+}
+
+hipError_t launch_measure(const EnsDesc* d_ens, const MeasBlock* d_blocks, int total_blocks, int precision,
+                          const void* links, double2* hist_c, void* hist_o, double* vac_part, int m_in, int m, int tau,
+                          int store_o, int multihit, hipStream_t st)
 {
     if (total_blocks <= 0) return hipSuccess;
-    const dim3 g((total_blocks + 7) / 8 * 8), b(256);
-    if (precision == 0) {
-        const double* l = (const double*)links;
-        if (multihit)
-            hipLaunchKernelGGL((k_measure<double, true>), g, b, 0, st, d_ens, d_bmap, l, hist_c, (double*)hist_o,
-                               vac_part, m_in, m, tau, store_o, total_blocks);
-        else
-            hipLaunchKernelGGL((k_measure<double, false>), g, b, 0, st, d_ens, d_bmap, l, hist_c, (double*)hist_o,
-                               vac_part, m_in, m, tau, store_o, total_blocks);
-    } else {
-        const float* l = (const float*)links;
-        if (multihit)
-            hipLaunchKernelGGL((k_measure<float, true>), g, b, 0, st, d_ens, d_bmap, l, hist_c, (float*)hist_o,
-                               vac_part, m_in, m, tau, store_o, total_blocks);
-        else
-            hipLaunchKernelGGL((k_measure<float, false>), g, b, 0, st, d_ens, d_bmap, l, hist_c, (float*)hist_o,
-                               vac_part, m_in, m, tau, store_o, total_blocks);
-    }
+    if (precision == 0)
+        launch_measure_t<double>(d_ens, d_blocks, total_blocks, links, hist_c, hist_o, vac_part, m_in, m, tau, store_o,
+                                 multihit, st);
+    else
+        launch_measure_t<float>(d_ens, d_blocks, total_blocks, links, hist_c, hist_o, vac_part, m_in, m, tau, store_o,
+                                multihit, st);
     return hipGetLastError();
 }
 

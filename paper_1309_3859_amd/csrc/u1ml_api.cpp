@@ -830,7 +830,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
     Lo->s_stage = take(sizeof(double) * 4 * maxV);
     Lo->bmap_stride = blocks64;
     Lo->s_bmap = take(sizeof(UpdBlock) * kUpdateClasses * blocks64);
-    Lo->s_mmap = take(sizeof(int2) * mblocks);
+    Lo->s_mmap = take(sizeof(MeasBlock) * mblocks);
     Lo->s_prow = take(sizeof(PairRow) * P.pair_rows.size());
     size_t pair_bytes[kPairClasses] = {};
     for (int cls = 0; cls < kPairClasses; ++cls) {
@@ -845,7 +845,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
         Lo->s_lens[l] = take(sizeof(EnsDesc) * n);
         Lo->s_lbstart[l] = take(sizeof(int) * (n + 1) * kNumTabs);
         Lo->s_lbmap[l] = take(sizeof(UpdBlock) * kUpdateClasses * blocks64);
-        Lo->s_lmmap[l] = take(sizeof(int2) * mblocks);
+        Lo->s_lmmap[l] = take(sizeof(MeasBlock) * mblocks);
         Lo->s_lring[l] = take(sizeof(int) * 4);
         for (int cls = 0; cls < kPairClasses; ++cls) Lo->s_lpmap[l][cls] = take(pair_bytes[cls]);
         for (int cls = 0; cls < 3; ++cls) Lo->s_lsmap[l][cls] = take(sizeof(SlabBlock) * P.slab_blocks[cls]);
@@ -934,11 +934,11 @@ struct Lane {
     std::vector<EnsDesc> h_ens;  // their descriptors, lane order
     std::vector<int> h_bstart;   // kNumTabs x (n + 1)
     std::vector<UpdBlock> h_bmap[kUpdateClasses];  // per-block update records of each class
-    std::vector<int2> h_mmap;    // measurement block -> (lane ensemble, block)
+    std::vector<MeasBlock> h_mmap;  // work-groups of a measurement
     EnsDesc* d_ens = nullptr;
     int* d_bstart = nullptr;
     UpdBlock* d_bmap = nullptr;
-    int2* d_mmap = nullptr;
+    MeasBlock* d_mmap = nullptr;
     int* d_ring = nullptr;
     double* prodpart = nullptr;
     size_t bmap_stride = 0;
@@ -1234,7 +1234,27 @@ void build_lane_tables(const u1ml_ctx* c, Lane& L)
     L.h_mmap.clear();
     const int* b = &L.h_bstart[(size_t)kTabMeas * (n + 1)];
     for (int e = 0; e < n; ++e)
-        for (int k = b[e]; k < b[e + 1]; ++k) L.h_mmap.push_back(make_int2(e, k - b[e]));
+        for (int k = b[e]; k < b[e + 1]; ++k) {
+            const EnsDesc& E = L.h_ens[e];
+            MeasBlock r;
+            std::memset(&r, 0, sizeof r);
+            r.e = e;
+            r.blk = k - b[e];
+            const long long item = 256ll * r.blk;
+            r.s0 = (int)(item / E.nsig);
+            r.xs0 = (int)(item % E.nsig);
+            r.nx = E.nx;
+            r.ny = E.ny;
+            r.nt = E.nt;
+            r.slabs = E.s_in;
+            r.nsig = E.nsig;
+            r.vh = E.vh;
+            r.inv_nx = 0.5f * E.inv_nxh;
+            r.inv_ny = E.inv_ny;
+            r.inv_nsig = 0.5f * E.inv_slice;
+            r.link_off = E.link_off;
+            L.h_mmap.push_back(r);
+        }
 }
 
 hipError_t upload_update_tabs(const Lane& L)
@@ -1262,7 +1282,7 @@ hipError_t upload_lane(const Lane& L)
             e = hipMemcpy(L.d_smap[cls], L.h_smap[cls].data(), sizeof(SlabBlock) * L.h_smap[cls].size(),
                           hipMemcpyHostToDevice);
     if (e == hipSuccess && !L.h_mmap.empty())
-        e = hipMemcpy(L.d_mmap, L.h_mmap.data(), sizeof(int2) * L.h_mmap.size(), hipMemcpyHostToDevice);
+        e = hipMemcpy(L.d_mmap, L.h_mmap.data(), sizeof(MeasBlock) * L.h_mmap.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(L.d_ring, ring0, sizeof ring0, hipMemcpyHostToDevice);
     return e;
 }
@@ -1310,7 +1330,7 @@ hipError_t split_lanes(u1ml_ctx* c, int nl)
         L.d_ens = (EnsDesc*)(s + Lo.s_lens[l]);
         L.d_bstart = (int*)(s + Lo.s_lbstart[l]);
         L.d_bmap = (UpdBlock*)(s + Lo.s_lbmap[l]);
-        L.d_mmap = (int2*)(s + Lo.s_lmmap[l]);
+        L.d_mmap = (MeasBlock*)(s + Lo.s_lmmap[l]);
         L.d_ring = (int*)(s + Lo.s_lring[l]);
         for (int cls = 0; cls < kPairClasses; ++cls) L.d_pmap[cls] = (PairBlock*)(s + Lo.s_lpmap[l][cls]);
         for (int cls = 0; cls < 3; ++cls) L.d_smap[cls] = (SlabBlock*)(s + Lo.s_lsmap[l][cls]);
@@ -1967,7 +1987,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         L.d_ens = (EnsDesc*)(s + Lo.s_ens);
         L.d_bstart = (int*)(s + Lo.s_bstart);
         L.d_bmap = (UpdBlock*)(s + Lo.s_bmap);
-        L.d_mmap = (int2*)(s + Lo.s_mmap);
+        L.d_mmap = (MeasBlock*)(s + Lo.s_mmap);
         L.d_ring = (int*)(s + Lo.s_ring);
         for (int cls = 0; cls < kPairClasses; ++cls) L.d_pmap[cls] = (PairBlock*)(s + Lo.s_pmap[cls]);
         for (int cls = 0; cls < 3; ++cls) L.d_smap[cls] = (SlabBlock*)(s + Lo.s_smap[cls]);

@@ -101,6 +101,20 @@ inline size_t slab_lds(int slice, int layers, int threads, bool heatbath, int wo
     return (size_t)slice * 16 + (heatbath ? (size_t)threads * (word == 8 ? 24 : 8) : 0) + (size_t)8 * layers * slice * word;
 }
 
+// One work-group of a measurement launch: 256 (slab, site) items of one
+// ensemble from slab s0, site xs0 on, with the geometry its loads need in one
+// 64-byte scalar load.
+struct alignas(64) MeasBlock {
+    int e, blk;  // the ensemble (lane order), the block of its running vacuum sums
+    int s0, xs0;
+    int nx, ny, nt, slabs;
+    int nsig, vh;
+    float inv_nx, inv_ny, inv_nsig;
+    int pad;
+    long long link_off;
+};
+static_assert(sizeof(MeasBlock) == 64, "MeasBlock is one 64-byte scalar load");
+
 // Observable tables in device memory.
 struct ObsDesc {
     int n_dirs;
@@ -238,7 +252,7 @@ hipError_t launch_scatter_links(const EnsDesc* d_ens, int ens, int precision, vo
 
 // --- launchers (k_measure.hip) ---
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
-hipError_t launch_measure(const EnsDesc* d_ens, const int2* d_bmap, int total_blocks, int precision, const void* links,
+hipError_t launch_measure(const EnsDesc* d_ens, const MeasBlock* d_blocks, int total_blocks, int precision, const void* links,
                           double2* hist_c, void* hist_o, double* vac_part, int m_in, int m, int tau, int store_o,
                           int multihit, hipStream_t st);
 // work-groups of `block` threads, each holding E.con_lpb lines; lds_bytes of dynamic LDS
