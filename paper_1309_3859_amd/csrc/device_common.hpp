@@ -75,6 +75,15 @@ __device__ inline float atan2_fast(float y, float x)
     return copysignf(r, y);
 }
 
+// x with its sign flipped where bit 31 of m is set: one three-input operation
+// (a ^ (b & c), truth table 0x78) on the high word
+__device__ inline double flip_sign(double x, unsigned m)
+{
+    const long long b = __double_as_longlong(x);
+    const unsigned hi = __builtin_amdgcn_bitop3_b32((unsigned)(b >> 32), m, 0x80000000u, 0x78);
+    return __longlong_as_double((long long)((unsigned long long)hi << 32 | (unsigned)b));
+}
+
 // ---------------------------------------------------------------------------
 // FP64 sine and cosine for |x| < 2^22, the arguments of this library (angle
 // sums of a few links, pi u with u in (0, 1), slab sums of temporal links).
@@ -112,11 +121,12 @@ __device__ inline void sincos_bounded(double x, double* sp, double* cp)
     // by Sterbenz's lemma, so the sum keeps the low bits w dropped
     const double w = fma(-0.5, z, 1.0);
     const double c = w + fma(z * z, pc, (1.0 - w) - 0.5 * z);
-    const int n = (int)q & 3;
+    const unsigned n = (unsigned)(int)q;
     const double a = (n & 1) ? c : s;   // sine before the sign
     const double b = (n & 1) ? s : c;   // cosine before the sign
-    *sp = (n & 2) ? -a : a;
-    *cp = ((n + 1) & 2) ? -b : b;
+    // sine negative where n & 2, cosine where (n + 1) & 2
+    *sp = flip_sign(a, n << 30);
+    *cp = flip_sign(b, (n << 30) + 0x40000000u);
 }
 
 // ---------------------------------------------------------------------------
