@@ -203,20 +203,57 @@ __device__ inline void block_sum12(const double* v, double2 before, double* acc,
     }
 }
 
-// With MULTIHIT the conditional means of the slab's temporal links (a staple
-// sum and a continued fraction of 40 and more divisions each) are formed first,
-// one link per work-item: 256 items times kHitLanes slices at a time, the
-// products over the slices then in order.
-constexpr int kHitLanes = 4;
+// Item tid of a measurement work-group: slab s, site xs = (x, y, z), yz = y + Ny z
+struct MeasItem {
+    bool active;
+    int s, xs, x, y, z, yz;
+    __device__ inline MeasItem(const MeasBlock& B, int tid)
+    {
+        // (a block may reach into the next slabs)
+        const int rel = B.xs0 + tid;
+        const int ds = B.nsig >= 256 ? (int)(rel >= B.nsig) : fdiv_small(rel, B.inv_nsig);
+        s = B.s0 + ds, xs = rel - ds * B.nsig;
+        active = s < B.slabs;
+        if (!active) s = xs = 0;
+        yz = fdiv(xs, B.nx, B.inv_nx);
+        x = xs - yz * B.nx;
+        z = fdiv(yz, B.ny, B.inv_ny);
+        y = yz - z * B.ny;
+    }
+};
+
+// Conditional means of the temporal links for the multihit slab phases,
+// e^{-i arg A} I1/I0(beta |A|), to hit[t][site]: a staple sum and a continued
+// fraction of 40 and more divisions for each link, one link per work-item in
+// work-groups of one wave, so that they spread over the device (14 x 10 x 18 x 6
+// FP64: with the measurement, slices of a site in turn 21.9 us, four work-items
+// a site 18.3, so 7.2 and the measurement after it 7.7).  Launch: (blocks x 4, tau).
+template <typename real>
+__global__ void __launch_bounds__(64) k_multihit(const EnsDesc* __restrict__ ens, const MeasBlock* __restrict__ blocks,
+                                                 const real* __restrict__ links, double2* __restrict__ hit, int tau)
+{
+    const MeasBlock B = blocks[blockIdx.x >> 2];
+    const EnsDesc& E = ens[B.e];
+    const MeasItem I(B, (int)(blockIdx.x & 3u) * 64 + (int)threadIdx.x);
+    if (!I.active) return;
+    const Geo g{B.nx, B.ny, E.nz, B.nt, B.nx >> 1, (B.nx >> 1) * B.ny, B.nsig >> 1};
+    const int t = I.s * tau + (int)blockIdx.y;
+    const Site c{I.x, I.y, I.z, t, g.sy * I.yz + g.st * t};
+    real ar, ai;
+    staple_sum<real, 3>(links + B.link_off, (unsigned)B.vh, g, c, (I.x + I.y + I.z + t) & 1, &ar, &ai);
+    const double R = sqrt((double)ar * (double)ar + (double)ai * (double)ai);
+    const double f = R > 0.0 ? bessel_ratio(E.beta * R) / R : 0.0;
+    hit[E.hit_off + (size_t)t * B.nsig + I.xs] = make_double2((double)ar * f, -(double)ai * f);
+}
 
 // What bounds it: the chain of one work-item on small lattices (its loads, two
 // slices' sines, the block sums), so the geometry comes in one record, the
 // running sums are read while the angles are in flight and the reductions stay
 // in registers.
 template <typename real, bool MULTIHIT>
-__global__ void __launch_bounds__(MULTIHIT ? 256 * kHitLanes : 256)
+__global__ void __launch_bounds__(256)
     k_measure(const EnsDesc* __restrict__ ens, const MeasBlock* __restrict__ blocks, const real* __restrict__ links,
-              double2* __restrict__ hist_c, real* __restrict__ hist_o, double* __restrict__ vac_part, int m_in, int m,
+              const double2* __restrict__ hit, double2* __restrict__ hist_c, real* __restrict__ hist_o, double* __restrict__ vac_part, int m_in, int m,
               int tau, int store_o, int n_blocks)
 {
     // XCD-aware order: the hardware deals consecutive work-groups to the eight
@@ -229,50 +266,24 @@ __global__ void __launch_bounds__(MULTIHIT ? 256 * kHitLanes : 256)
     const EnsDesc& E = ens[B.e];
     const int nsig = B.nsig;
     constexpr int w = sizeof(real);
-    const int tid = (int)threadIdx.x & 255;
-    // item tid: slab s, site xs (a block may reach into the next slabs)
-    const int rel = B.xs0 + tid;
-    const int ds = nsig >= 256 ? (int)(rel >= nsig) : fdiv_small(rel, B.inv_nsig);
-    const int s = B.s0 + ds, xs = rel - ds * nsig;
-    const bool active = s < B.slabs;
-    const int yz = fdiv(active ? xs : 0, B.nx, B.inv_nx);
-    const int x = (active ? xs : 0) - yz * B.nx;
-    const int z = fdiv(yz, B.ny, B.inv_ny);
-    const int y = yz - z * B.ny;
-    const int t0 = (active ? s : 0) * tau;
+    const int tid = (int)threadIdx.x;
+    const MeasItem I(B, tid);
+    const bool active = I.active;
+    const int s = I.s, xs = I.xs, x = I.x, y = I.y, z = I.z, yz = I.yz;
+    const int t0 = s * tau;
     double* acc = vac_part + E.vac_part_off + (size_t)B.blk * 24;
     double2 before = make_double2(0.0, 0.0);
     if (m != 0) before = reinterpret_cast<const double2*>(acc)[3 * (tid >> 6) + min(tid & 63, 2)];
     double2 cm = make_double2(1.0, 0.0);  // multihit slab phase
-    if constexpr (MULTIHIT) {
-        __shared__ double2 hit[kHitLanes][256];
-        const unsigned vh = (unsigned)B.vh;
-        const Geo g{B.nx, B.ny, E.nz, B.nt, B.nx >> 1, (B.nx >> 1) * B.ny, nsig >> 1};
-        const int q = (int)threadIdx.x >> 8;
-        for (int k0 = 0; k0 < tau; k0 += kHitLanes) {
-            if (k0 + q < tau && active) {
-                // conditional mean of the temporal link: e^{-i arg A} I1/I0(beta |A|)
-                const int t = t0 + k0 + q;
-                const Site c{x, y, z, t, g.sy * yz + g.st * t};
-                real ar, ai;
-                staple_sum<real, 3>(links + B.link_off, vh, g, c, (x + y + z + t) & 1, &ar, &ai);
-                const double R = sqrt((double)ar * (double)ar + (double)ai * (double)ai);
-                const double f = R > 0.0 ? bessel_ratio(E.beta * R) / R : 0.0;
-                hit[q][tid] = make_double2((double)ar * f, -(double)ai * f);
-            }
-            __syncthreads();
-            if (q == 0)
-                for (int k = k0; k < min(tau, k0 + kHitLanes); ++k) {
-                    const double ur = hit[k - k0][tid].x, ui = hit[k - k0][tid].y;
-                    cm = make_double2(cm.x * ur - cm.y * ui, cm.x * ui + cm.y * ur);
-                }
-            __syncthreads();
+    if (MULTIHIT && active)
+        for (int k = 0; k < tau; ++k) {
+            const double2 u = hit[E.hit_off + (size_t)(t0 + k) * nsig + xs];
+            cm = make_double2(cm.x * u.x - cm.y * u.y, cm.x * u.y + cm.y * u.x);
         }
-    }
     double vac[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) vac[k] = 0.0;
-    if (active && threadIdx.x < 256) {
+    if (active) {
         const LinkBuf<real> lb(const_cast<real*>(links) + B.link_off);
         const unsigned vhb = (unsigned)B.vh * w;
         const int nxh = B.nx >> 1, row = nxh * yz, st = nsig >> 1;
@@ -350,30 +361,32 @@ __global__ void __launch_bounds__(MULTIHIT ? 256 * kHitLanes : 256)
 
 template <typename real>
 static void launch_measure_t(const EnsDesc* d_ens, const MeasBlock* d_blocks, int total_blocks, const void* links,
-                             double2* hist_c, void* hist_o, double* vac_part, int m_in, int m, int tau, int store_o,
-                             int multihit, hipStream_t st)
+                             double2* hit, double2* hist_c, void* hist_o, double* vac_part, int m_in, int m, int tau,
+                             int store_o, int multihit, hipStream_t st)
 {
-    const dim3 g((total_blocks + 7) / 8 * 8);
-    if (multihit)
-        hipLaunchKernelGGL((k_measure<real, true>), g, dim3(256 * (tau < kHitLanes ? tau : kHitLanes)), 0, st, d_ens,
-                           d_blocks, (const real*)links, hist_c, (real*)hist_o, vac_part, m_in, m, tau, store_o,
-                           total_blocks);
-    else
-        hipLaunchKernelGGL((k_measure<real, false>), g, dim3(256), 0, st, d_ens, d_blocks, (const real*)links, hist_c,
+    const dim3 g((total_blocks + 7) / 8 * 8), b(256);
+    if (multihit) {
+        hipLaunchKernelGGL((k_multihit<real>), dim3(4 * total_blocks, tau), dim3(64), 0, st, d_ens, d_blocks,
+                           (const real*)links, hit, tau);
+        hipLaunchKernelGGL((k_measure<real, true>), g, b, 0, st, d_ens, d_blocks, (const real*)links, hit, hist_c,
                            (real*)hist_o, vac_part, m_in, m, tau, store_o, total_blocks);
+    } else {
+        hipLaunchKernelGGL((k_measure<real, false>), g, b, 0, st, d_ens, d_blocks, (const real*)links, hit, hist_c,
+                           (real*)hist_o, vac_part, m_in, m, tau, store_o, total_blocks);
+    }
 }
 
 hipError_t launch_measure(const EnsDesc* d_ens, const MeasBlock* d_blocks, int total_blocks, int precision,
-                          const void* links, double2* hist_c, void* hist_o, double* vac_part, int m_in, int m, int tau,
-                          int store_o, int multihit, hipStream_t st)
+                          const void* links, double2* hit, double2* hist_c, void* hist_o, double* vac_part, int m_in,
+                          int m, int tau, int store_o, int multihit, hipStream_t st)
 {
     if (total_blocks <= 0) return hipSuccess;
     if (precision == 0)
-        launch_measure_t<double>(d_ens, d_blocks, total_blocks, links, hist_c, hist_o, vac_part, m_in, m, tau, store_o,
-                                 multihit, st);
+        launch_measure_t<double>(d_ens, d_blocks, total_blocks, links, hit, hist_c, hist_o, vac_part, m_in, m, tau,
+                                 store_o, multihit, st);
     else
-        launch_measure_t<float>(d_ens, d_blocks, total_blocks, links, hist_c, hist_o, vac_part, m_in, m, tau, store_o,
-                                multihit, st);
+        launch_measure_t<float>(d_ens, d_blocks, total_blocks, links, hit, hist_c, hist_o, vac_part, m_in, m, tau,
+                                store_o, multihit, st);
     return hipGetLastError();
 }
 

@@ -30,7 +30,7 @@ bool add_ok(size_t a, size_t b, size_t* out) { return !__builtin_add_overflow(a,
 
 struct Sizes {
     // per ensemble element offsets
-    std::vector<size_t> links, hc, ho, at, ato, ot, oto, vac;
+    std::vector<size_t> links, hc, ho, at, ato, ot, oto, vac, hit;
     std::vector<size_t> wf, gf, sph, spo, facc;  // spectral form (double2 elements)
     std::vector<size_t> cpl, opl;                // plane-major copies (double2, real elements)
 };
@@ -43,7 +43,7 @@ struct Layout {
     size_t sz_wf, sz_gf, sz_sph, sz_spo, sz_facc, sz_saved, sz_cpl, sz_opl;
     // scratch sub-offsets (bytes from off_scr)
     size_t s_ens, s_obs, s_r, s_probe, s_comp, s_bstart, s_upd, s_ring, s_vpart, s_ppart, s_pout, s_count,
-        s_stage, s_bmap, s_mmap, s_prodpart, s_pgroup, s_gdesc, s_pblk, s_prow, s_pmap[kPairClasses], s_smap[3];
+        s_stage, s_bmap, s_mmap, s_prodpart, s_pgroup, s_gdesc, s_pblk, s_prow, s_pmap[kPairClasses], s_smap[3], s_hit;
     size_t off_alt;  // the other link buffer (both-parities updates)
     // the lanes' descriptors and tables (each sized for the whole batch)
     size_t s_lens[4], s_lbstart[4], s_lbmap[4], s_lmmap[4], s_lring[4], s_lpmap[4][kPairClasses], s_lsmap[4][3];
@@ -344,10 +344,10 @@ constexpr long long kMaxGraphLaunches = 8192;
 long long body_launches(const Problem& P)
 {
     const long long sweep = (1ll + P.n_or) * 8;
-    // per measurement: the measurement, and in the spectral form staging,
+    // per measurement: the measurement (two with multihit), and in the spectral form staging,
     // plane transforms and spectral sums (at most 6); per inner level: the two
     // contractions, the combine, the exponent pass (2) and the weights
-    const long long meas = 1 + (P.spectral ? 6 : 0);
+    const long long meas = 1 + (P.multihit ? 1 : 0) + (P.spectral ? 6 : 0);
     const long long level = (long long)P.n_o * ((long long)P.k_o * sweep + (long long)P.n_i * (P.k_i * sweep + meas) + 6);
     const long long passes = (P.spectral && P.two) ? 2 : 1;
     // per configuration: products (4), vacuum, spectral final (2), outer
@@ -693,7 +693,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
     plan_slabs(&P);
     plan_pairs(&P);
     const bool spec = P.spectral;
-    size_t L = 0, HC = 0, HO = 0, AT = 0, ATO = 0, OT = 0, OTO = 0, VAC = 0, PP = 0;
+    size_t L = 0, HC = 0, HO = 0, AT = 0, ATO = 0, OT = 0, OTO = 0, VAC = 0, PP = 0, HIT = 0;
     size_t maxV = 0, paper = 0, upd_cfg = 0, upd_sweep = 0, blocks64 = 0, mblocks = 0;
     S->links.clear();
     S->hc.clear();
@@ -703,6 +703,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
     S->ot.clear();
     S->oto.clear();
     S->vac.clear();
+    S->hit.clear();
     S->wf.clear();
     S->gf.clear();
     S->sph.clear();
@@ -770,6 +771,8 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
             FACC = align_up(FACC * 16) / 16;
         }
         S->vac.push_back(VAC);
+        S->hit.push_back(HIT);
+        if (P.multihit) HIT += V;
         // running double-double vacuum partials, one set of 12 per measurement block
         VAC += ((nsig * si + 255) / 256) * 24;
         // slab-product partials: per (r, probe group, site chunk) work-group
@@ -824,6 +827,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
     Lo->s_upd = take(sizeof(uint32_t) * n);
     Lo->s_ring = take(sizeof(int) * 4);
     Lo->s_vpart = take(sizeof(double) * VAC);
+    Lo->s_hit = take(sizeof(double2) * HIT);
     Lo->s_ppart = take(sizeof(double) * 6 * kPlaqBlocks * n);
     Lo->s_pout = take(sizeof(double) * 6 * n);
     Lo->s_count = take(sizeof(unsigned long long) * 2);
@@ -968,7 +972,7 @@ struct u1ml_ctx {
     int device = 0;
     // device pointers
     void* links = nullptr;
-    double2 *hc = nullptr, *at = nullptr, *ato = nullptr, *ot = nullptr, *oto = nullptr;
+    double2 *hit = nullptr, *hc = nullptr, *at = nullptr, *ato = nullptr, *ot = nullptr, *oto = nullptr;
     void* ho = nullptr;
     double *res = nullptr, *vpart = nullptr, *ppart = nullptr, *pout = nullptr,
            *stage = nullptr;
@@ -1495,7 +1499,7 @@ hipError_t enq_levels(u1ml_ctx* c, const Lane& L, hipStream_t st, bool store_o, 
             if (e == hipSuccess) e = enq_sweeps(c, L, st, P.tau_i, hb, P.k_i);
             hb += P.k_i;
             if (e == hipSuccess)
-                e = launch_measure(L.d_ens, L.d_mmap, L.tab_total(kTabMeas), P.precision, c->links, c->hc, c->ho,
+                e = launch_measure(L.d_ens, L.d_mmap, L.tab_total(kTabMeas), P.precision, c->links, c->hit, c->hc, c->ho,
                                    c->vpart, m, ko * P.n_i + m, P.tau_i, store_o ? 1 : 0, P.multihit ? 1 : 0, st);
         }
         if (e == hipSuccess)
@@ -1801,6 +1805,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
     c->d_comp = (int*)(s + Lo.s_comp);
     c->d_upd = (uint32_t*)(s + Lo.s_upd);
     c->vpart = (double*)(s + Lo.s_vpart);
+    c->hit = (double2*)(s + Lo.s_hit);
     c->ppart = (double*)(s + Lo.s_ppart);
     c->pout = (double*)(s + Lo.s_pout);
     c->d_count = (unsigned long long*)(s + Lo.s_count);
@@ -1852,6 +1857,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         E.ot_off = (long long)c->S.ot[e];
         E.oto_off = (long long)c->S.oto[e];
         E.vac_part_off = (long long)c->S.vac[e];
+        E.hit_off = (long long)c->S.hit[e];
         E.wf_off = (long long)c->S.wf[e];
         E.gf_off = (long long)c->S.gf[e];
         E.sph_off = (long long)c->S.sph[e];

@@ -24,6 +24,7 @@ struct EnsDesc {
     long long link_off;
     long long hc_off, ho_off;
     long long hcm_off;  // multihit slab phases (double2), [m][s][site], when multihit
+    long long hit_off;  // conditional means of the temporal links (double2), [t][site], when multihit
     long long at_off, ato_off;
     long long ot_off, oto_off;
     long long vac_part_off;  // double, [n_vac_blocks][12][hi, lo]: running sums over the configuration's measurements
@@ -252,9 +253,10 @@ hipError_t launch_scatter_links(const EnsDesc* d_ens, int ens, int precision, vo
 
 // --- launchers (k_measure.hip) ---
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
-hipError_t launch_measure(const EnsDesc* d_ens, const MeasBlock* d_blocks, int total_blocks, int precision, const void* links,
-                          double2* hist_c, void* hist_o, double* vac_part, int m_in, int m, int tau, int store_o,
-                          int multihit, hipStream_t st);
+// hit: the lane's conditional means of the temporal links (multihit)
+hipError_t launch_measure(const EnsDesc* d_ens, const MeasBlock* d_blocks, int total_blocks, int precision,
+                          const void* links, double2* hit, double2* hist_c, void* hist_o, double* vac_part, int m_in,
+                          int m, int tau, int store_o, int multihit, hipStream_t st);
 // work-groups of `block` threads, each holding E.con_lpb lines; lds_bytes of dynamic LDS
 hipError_t launch_contract(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int block,
                            size_t lds_bytes, const ObsDesc* d_obs, const int* d_r, const double2* hist_c,
