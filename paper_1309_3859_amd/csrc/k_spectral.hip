@@ -39,6 +39,7 @@ __device__ inline int find_ens_s(const int* __restrict__ bstart, int n_ens, int 
 __device__ inline double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 
 __device__ inline int orient_of(int c, int dir) { return c < 3 ? (dir + c) % 3 : 3 + (dir + c - 3) % 3; }
+__device__ inline int extent(const EnsDesc& E, int dir) { return dir == 0 ? E.nx : dir == 1 ? E.ny : E.nz; }
 __device__ inline bool spans_axis(int c) { return c == 0 || c == 4 || c == 5; }
 
 // Position of site xs = x + nx (y + ny z) in the plane-major order of charge
@@ -560,24 +561,36 @@ __global__ void __launch_bounds__(kPlaneThreads) k_dft_planes(const EnsDesc* __r
 // with l = l_g + (mode_g ? l_mid(r, c) : 0) and row = 2 o(c, axis) + kind.
 // Work-item (k, r slot) takes r = slot, slot + kMacThreads / kMacK, ...  Every
 // sum runs over x_par in ascending order.
+//
+// Bound by the latency of its loads: 48^3 x 12 with 19 separations moves 430
+// MB in 1728 work-groups of three waves, two to a CU.  So the O rows go
+// straight from memory to LDS (global_load_lds), all in flight together with
+// the first T spectra and the running sums, and the T spectra then come in
+// two register buffers of kMacAhead values, one summed while the other loads
+// (8 instead of 6 values: the same within noise).  NC, the number of
+// components, is a constant, so that no branch separates the LDS reads of one
+// position from the next.  Staged through registers, with every load awaited
+// where it was used, the launch took 240 us; now 152 us (2.8 TB/s).
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kMacThreads) k_spec_mac(const EnsDesc* __restrict__ ens,
-                                                          const int* __restrict__ bstart, int n_ens,
-                                                          const ObsDesc* __restrict__ obs,
-                                                          const int* __restrict__ rlist, const int* __restrict__ comps,
-                                                          const int* __restrict__ gdesc, const double2* __restrict__ sph,
-                                                          const double2* __restrict__ spo, double2* __restrict__ facc)
+constexpr int kMacAhead = 6;
+
+template <int NC>
+__global__ void __launch_bounds__(kMacThreads, 2) k_spec_mac(const EnsDesc* __restrict__ ens,
+                                                             const int* __restrict__ bstart, int n_ens,
+                                                             const ObsDesc* __restrict__ obs,
+                                                             const int* __restrict__ rlist, const int* __restrict__ comps,
+                                                             const int* __restrict__ gdesc, const double2* __restrict__ sph,
+                                                             const double2* __restrict__ spo, double2* __restrict__ facc)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     double2* os = reinterpret_cast<double2*>(lds_raw);  // [row][x_par][kk]
-    constexpr int KC = kMacK;
+    constexpr int KC = kMacK, A = kMacAhead;
     const int e = find_ens_s(bstart, n_ens, blockIdx.x);
     const EnsDesc& E = ens[e];
     const ObsDesc& O = *obs;
-    const int nsig = E.nsig, Si = E.s_in, R = O.n_r, Nc = O.n_comp, NG = O.n_groups;
-    const int n3[3] = {E.nx, E.ny, E.nz};
+    const int nsig = E.nsig, Si = E.s_in, R = O.n_r, NG = O.n_groups;
     int n12max = 0;
-    for (int i = 0; i < O.n_dirs; ++i) n12max = max(n12max, nsig / n3[O.dirs[i]]);
+    for (int i = 0; i < O.n_dirs; ++i) n12max = max(n12max, nsig / extent(E, O.dirs[i]));
     const int nkc = (n12max + KC - 1) / KC;
     int local = blockIdx.x - bstart[e];
     const int kc = local % nkc;
@@ -588,70 +601,103 @@ __global__ void __launch_bounds__(kMacThreads) k_spec_mac(const EnsDesc* __restr
     const int id = local / Si;
     if (id >= O.n_dirs) return;
     const int dir = O.dirs[id];
-    const int N = n3[dir], n12 = nsig / N;
+    const int N = extent(E, dir), n12 = nsig / N;
     const int k0 = kc * KC;
     if (k0 >= n12) return;  // uniform for the block
     const size_t ps = (size_t)id * Si + s;
-    // staged four elements per work-item and round, all loads issued before the LDS stores
-    const int n_os = 12 * N * KC;
-    for (int i0 = threadIdx.x; i0 < n_os; i0 += 4 * blockDim.x) {
-        double2 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = min(i0 + u * (int)blockDim.x, n_os - 1);
-            const int kk = i % KC, t = i / KC;
-            const int xp = t % N, row = t / N;
-            v[u] = k0 + kk < n12 ? spo[E.spo_off + (ps * 12 + row) * nsig + (size_t)xp * n12 + k0 + kk]
-                                 : make_double2(0.0, 0.0);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (i0 + u * (int)blockDim.x < n_os) os[i0 + u * blockDim.x] = v[u];
-    }
-    __syncthreads();
     const int kk = threadIdx.x % KC, slot = threadIdx.x / KC;
-    const int k = k0 + kk;
-    if (k >= n12) return;
-    for (int ir = slot; ir < R; ir += blockDim.x / KC) {
-        const int r = rlist[ir];
-        const double2* h = sph + E.sph_off + (ps * R + ir) * nsig + k;
-        int xo[kMacComps], orow[kMacComps];
-        double re[kMacComps][2], im[kMacComps][2];
+    const int k = min(k0 + kk, n12 - 1);  // past the plane's end: a copy of the last k, not stored
+    // element i = (row N + x_par) KC + kk of the tile: 64 consecutive ones per wave and round
+    {
+        const double2* src = spo + E.spo_off + ps * 12 * nsig + k;
+        const int n_os = 12 * N * KC, lane = threadIdx.x & 63;
+        for (int j = (int)threadIdx.x & ~63; j < n_os; j += kMacThreads) {
+            const int i = j + lane;
+            if (i < n_os) {  // lane % KC is kk: KC divides 64
+                const int t = i / KC;
+                __builtin_amdgcn_global_load_lds((const void*)(src + (size_t)t * n12),
+                                                 (__attribute__((address_space(3))) void*)(os + j), 16, 0, 0);
+            }
+        }
+    }
+    const int wrap = N * KC;
+    bool first = true;
+    for (int ir = slot; ir < R || first; ir += kMacThreads / KC) {
+        const bool act = ir < R;  // the first round has every work-item, for the barrier
+        const int irc = act ? ir : R - 1;
+        const int r = rlist[irc];
+        const double2* h = sph + E.sph_off + (ps * R + irc) * nsig + k;
+        double2 b0[A], b1[A];
+        auto fetch = [&](double2(&b)[A], int x0) {
 #pragma unroll
-        for (int ic = 0; ic < kMacComps; ++ic) {
-            const int c = comps[ic < Nc ? ic : 0];
-            const int l = gdesc[2 * g] + (gdesc[2 * g + 1] ? (spans_axis(c) ? (r - 1) / 2 : r / 2) : 0);
-            xo[ic] = ((l % N) + N) % N;
-            orow[ic] = 2 * orient_of(c, dir);
+            for (int u = 0; u < A; ++u) b[u] = h[(size_t)min(x0 + u, N - 1) * n12];
+        };
+        fetch(b0, 0);
+        const size_t sl0 = (ps * R + irc) * NC * 2 * NG + g;
+        double2* F = facc + E.facc_off + sl0 * n12max + k;
+        const size_t fstep = (size_t)NG * n12max;
+        double2 f[NC][2];
+#pragma unroll
+        for (int ic = 0; ic < NC; ++ic)
+#pragma unroll
+            for (int kind = 0; kind < 2; ++kind) f[ic][kind] = F[(size_t)(2 * ic + kind) * fstep];
+        // LDS offsets of O at x_par + l: xa for components that lie across the axis, xb for those that span it
+        const int lg = gdesc[2 * g], mid = gdesc[2 * g + 1];
+        int xa = ((((lg + (mid ? r / 2 : 0)) % N) + N) % N) * KC + kk;
+        int xb = ((((lg + (mid ? (r - 1) / 2 : 0)) % N) + N) % N) * KC + kk;
+        int ob[NC], span[NC];  // span: all bits set or none
+        double re[NC][2], im[NC][2];
+#pragma unroll
+        for (int ic = 0; ic < NC; ++ic) {
+            const int c = comps[ic];
+            span[ic] = spans_axis(c) ? -1 : 0;
+            ob[ic] = 2 * orient_of(c, dir) * wrap;
             re[ic][0] = im[ic][0] = re[ic][1] = im[ic][1] = 0.0;
         }
-#pragma unroll 8
-        for (int xp = 0; xp < N; ++xp) {
-            const double2 b = h[(size_t)xp * n12];
+        auto sum = [&](const double2& b) {
+            const int dx = xb - xa;
 #pragma unroll
-            for (int ic = 0; ic < kMacComps; ++ic) {
-                if (ic < Nc) {
-#pragma unroll
-                    for (int kind = 0; kind < 2; ++kind) {
-                        const double2 a = os[((orow[ic] + kind) * N + xo[ic]) * KC + kk];
-                        re[ic][kind] += a.x * b.x - a.y * b.y;
-                        im[ic][kind] += a.x * b.y + a.y * b.x;
-                    }
-                    if (++xo[ic] == N) xo[ic] = 0;
-                }
-            }
-        }
-#pragma unroll
-        for (int ic = 0; ic < kMacComps; ++ic) {
-            if (ic < Nc) {
+            for (int ic = 0; ic < NC; ++ic) {
+                const int o = ob[ic] + xa + (dx & span[ic]);
 #pragma unroll
                 for (int kind = 0; kind < 2; ++kind) {
-                    const size_t sl = (((ps * R + ir) * Nc + ic) * 2 + kind) * NG + g;
-                    double2* F = facc + E.facc_off + sl * n12max + k;
-                    *F = make_double2(F->x + re[ic][kind], F->y + im[ic][kind]);
+                    const double2 a = os[o + kind * wrap];
+                    re[ic][kind] += a.x * b.x - a.y * b.y;
+                    im[ic][kind] += a.x * b.y + a.y * b.x;
                 }
             }
+            xa += KC;
+            xb += KC;
+            if (xa >= wrap) xa -= wrap;
+            if (xb >= wrap) xb -= wrap;
+        };
+        if (first) {
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's copies into LDS have landed
+            __syncthreads();
+            first = false;
         }
+        int x0 = 0;
+        for (; x0 + 2 * A <= N; x0 += 2 * A) {
+            fetch(b1, x0 + A);
+#pragma unroll
+            for (int u = 0; u < A; ++u) sum(b0[u]);
+            fetch(b0, x0 + 2 * A);
+#pragma unroll
+            for (int u = 0; u < A; ++u) sum(b1[u]);
+        }
+        fetch(b1, x0 + A);
+#pragma unroll
+        for (int u = 0; u < A; ++u)
+            if (x0 + u < N) sum(b0[u]);
+#pragma unroll
+        for (int u = 0; u < A; ++u)
+            if (x0 + A + u < N) sum(b1[u]);
+        if (!act || k0 + kk >= n12) continue;
+#pragma unroll
+        for (int ic = 0; ic < NC; ++ic)
+#pragma unroll
+            for (int kind = 0; kind < 2; ++kind)
+                F[(size_t)(2 * ic + kind) * fstep] = make_double2(f[ic][kind].x + re[ic][kind], f[ic][kind].y + im[ic][kind]);
     }
 }
 
@@ -813,12 +859,28 @@ hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_en
 }
 
 hipError_t launch_spec_mac(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int npm,
-                           const ObsDesc* d_obs, const int* d_r, const int* d_comp, const int* d_gdesc,
+                           int n_comp, const ObsDesc* d_obs, const int* d_r, const int* d_comp, const int* d_gdesc,
                            const double2* sph, const double2* spo, double2* facc, hipStream_t st)
 {
     if (total_blocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_spec_mac, dim3(total_blocks), dim3(kMacThreads), spec_mac_lds(npm), st, d_ens, d_bstart,
-                       n_ens, d_obs, d_r, d_comp, d_gdesc, sph, spo, facc);
+    const dim3 gr(total_blocks), bl(kMacThreads);
+    const size_t lds = spec_mac_lds(npm);
+#define U1ML_MAC(NC)                                                                                                   \
+    case NC:                                                                                                           \
+        hipLaunchKernelGGL(k_spec_mac<NC>, gr, bl, lds, st, d_ens, d_bstart, n_ens, d_obs, d_r, d_comp, d_gdesc, sph,  \
+                           spo, facc);                                                                                 \
+        break;
+    switch (n_comp) {
+        case 0: return hipSuccess;
+        U1ML_MAC(1)
+        U1ML_MAC(2)
+        U1ML_MAC(3)
+        U1ML_MAC(4)
+        U1ML_MAC(5)
+        U1ML_MAC(6)
+        default: return hipErrorInvalidValue;
+    }
+#undef U1ML_MAC
     return hipGetLastError();
 }
 

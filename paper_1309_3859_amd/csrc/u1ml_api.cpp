@@ -1529,8 +1529,9 @@ hipError_t enq_levels(u1ml_ctx* c, const Lane& L, hipStream_t st, bool store_o, 
                                           c->d_r, c->cpl, c->opl, c->gf, c->sph, c->spo, P.precision,
                                           c->spec_tile, st);
                 if (e == hipSuccess)
-                    e = launch_spec_mac(L.d_ens, L.tab_dev(kTabMac), n, L.tab_total(kTabMac), c->spec_npm, c->d_obs,
-                                        c->d_r, c->d_comp, c->d_gdesc, c->sph, c->spo, c->facc, st);
+                    e = launch_spec_mac(L.d_ens, L.tab_dev(kTabMac), n, L.tab_total(kTabMac), c->spec_npm,
+                                        (int)P.comps.size(), c->d_obs, c->d_r, c->d_comp, c->d_gdesc, c->sph, c->spo,
+                                        c->facc, st);
             }
         }
     }

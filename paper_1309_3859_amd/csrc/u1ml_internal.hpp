@@ -311,7 +311,7 @@ constexpr int kMacK = 8;
 constexpr int kMacThreads = 192;
 constexpr int kMacComps = 6;
 inline size_t spec_mac_lds(int npm) { return (size_t)12 * npm * kMacK * 16; }
-hipError_t launch_spec_mac(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int npm,
+hipError_t launch_spec_mac(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int npm, int n_comp,
                            const ObsDesc* d_obs, const int* d_r, const int* d_comp, const int* d_gdesc,
                            const double2* sph, const double2* spo, double2* facc, hipStream_t st);
 hipError_t launch_spec_final(const EnsDesc* d_ens, int n_ens, const ObsDesc* d_obs, long long n_outputs, int npm,

@@ -100,6 +100,22 @@ def test_spectral_transform_sizes_match_history(env):
     _compare(mk(), rh, rs, 1e-12)
 
 
+@pytest.mark.parametrize("n_comp", [1, 2, 3, 4, 5, 6])
+def test_spectral_sums_of_every_component_count(env, n_comp):
+    """Each number of components is a kernel of its own; 25 separations take
+    two rounds of its work-items, 26 positions end in a partial buffer and
+    planes of 36 sites in a partial tile.  Both forms sum the same products
+    (|T|, |O| <= 1) in FP64: the shared bar of this file."""
+    u1, O, _ = env
+    mk = lambda: u1.Spec(ensembles=[u1.Ens((26, 6, 6), 4, 1.0, seed=17)], levels=[(2, 2, 1)], r=list(range(1, 26)),
+                         dirs=[0], probes=_disk(1) + [(3, 1, 0, 0)], comps=list(range(6))[6 - n_comp:],
+                         precision=u1.FP64, n_or=1)
+    say("components", n_comp)
+    rh, _, _ = _run(u1, mk(), u1.FORM_HISTORY)
+    rs, _, _ = _run(u1, mk(), u1.FORM_SPECTRAL)
+    _compare(mk(), rh, rs, 1e-12)
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_spectral_two_levels_replay_matches_history(env, prec):
     u1, O, _ = env
