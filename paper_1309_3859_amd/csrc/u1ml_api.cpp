@@ -1520,7 +1520,7 @@ hipError_t enq_levels(u1ml_ctx* c, const Lane& L, hipStream_t st, bool store_o, 
             if (e == hipSuccess)
                 e = launch_gfac(L.d_ens, L.tab_dev(kTabSite), n, L.tab_total(kTabSite), c->d_obs, c->at,
                                 P.two ? c->wf : nullptr, P.two ? P.tau_o / P.tau_i : 0, c->gf, c->res, L.d_ring, st);
-            const size_t lds = (2 * (size_t)c->spec_n12max + 2 * (size_t)c->spec_npm) * sizeof(double2);
+            const size_t lds = plane_lds(c->spec_n12max, c->spec_npm);
             for (int m = 0; e == hipSuccess && m < P.n_i; ++m) {
                 e = launch_plane_stage(L.d_ens, L.tab_dev(kTabStage), n, L.tab_total(kTabStage), c->d_obs, c->hc,
                                        c->ho, m, P.precision, c->cpl, c->opl, st);
@@ -1578,7 +1578,7 @@ hipError_t enq_multilevel(u1ml_ctx* c, const Lane& L, hipStream_t st)
         return launch_product(L.d_ens, L.tab_dev(kTabProd), n, L.tab_total(kTabProd), c->d_obs, R, npg, c->at,
                               ins ? c->ato : nullptr, 0, 1.0, L.prodpart, c->res, L.d_ring, st);
     };
-    const long long n_out = (long long)R * P.probes.size() * P.comps.size() * 2;
+    const long long n_sums = P.probes.empty() ? 0 : (long long)R * P.comps.size() * 2 * (P.gdesc.size() / 2);
     if (!P.spectral) {
         e = enq_levels(c, L, st, probes, probes, false, &hb);
         if (e == hipSuccess) e = product(probes);
@@ -1588,8 +1588,8 @@ hipError_t enq_multilevel(u1ml_ctx* c, const Lane& L, hipStream_t st)
         if (e == hipSuccess) e = enq_levels(c, L, st, true, false, true, &hb);
         if (e == hipSuccess) e = product(false);
         if (e == hipSuccess)
-            e = launch_spec_final(L.d_ens, n, c->d_obs, n_out, c->spec_npm, c->d_probe, c->d_pgroup, c->facc,
-                                  (double)P.n_i, c->res, L.d_ring, st);
+            e = launch_spec_final(L.d_ens, n, c->d_obs, n_sums, c->spec_npm, c->spec_n12max, c->d_probe,
+                                  c->d_pgroup, c->facc, (double)P.n_i, c->res, L.d_ring, st);
         if (e == hipSuccess) e = launch_vac_final(L.d_ens, n, c->d_obs, c->vpart, P.n_i, c->res, L.d_ring, st);
     } else {
         e = copy_lane_links(c, L, c->links, c->saved, st);
@@ -1604,8 +1604,8 @@ hipError_t enq_multilevel(u1ml_ctx* c, const Lane& L, hipStream_t st)
         int hb2 = 0;
         if (e == hipSuccess) e = enq_levels(c, L, st, true, false, true, &hb2);
         if (e == hipSuccess)
-            e = launch_spec_final(L.d_ens, n, c->d_obs, n_out, c->spec_npm, c->d_probe, c->d_pgroup, c->facc,
-                                  (double)P.n_o * P.n_i, c->res, L.d_ring, st);
+            e = launch_spec_final(L.d_ens, n, c->d_obs, n_sums, c->spec_npm, c->spec_n12max, c->d_probe,
+                                  c->d_pgroup, c->facc, (double)P.n_o * P.n_i, c->res, L.d_ring, st);
     }
     if (e == hipSuccess) e = launch_ring_advance(L.d_ring, st);
     if (e == hipSuccess && hb > 0) e = launch_advance_counters(L.d_ens, c->d_upd, n, hb, st);
@@ -2006,10 +2006,10 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         // every dynamic LDS request must fit the device's limit per work-group
         int lds_max = 0;
         hipError_t ea = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device);
-        const size_t plane_lds = P.spectral ? (2 * (size_t)c->spec_n12max + 2 * (size_t)c->spec_npm) * sizeof(double2) : 0;
+        const size_t dft_lds = P.spectral ? plane_lds(c->spec_n12max, c->spec_npm) : 0;
         const size_t mac_lds = P.spectral ? spec_mac_lds(c->spec_npm) : 0;
         const size_t slab_bytes = *std::max_element(P.slab_lds_bytes, P.slab_lds_bytes + 3);
-        const size_t need = std::max({c->con_lds, c->ins_lds, plane_lds, mac_lds, slab_bytes});
+        const size_t need = std::max({c->con_lds, c->ins_lds, dft_lds, mac_lds, slab_bytes});
         if (ea != hipSuccess || (size_t)lds_max < need) {
             release(c);
             return set_err(nullptr, ea != hipSuccess ? U1ML_EDEVICE : U1ML_ENOTSUP,

@@ -301,6 +301,8 @@ hipError_t launch_gfac(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int
 hipError_t launch_plane_stage(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks,
                               const ObsDesc* d_obs, const double2* hist_c, const void* hist_o, int m_in,
                               int precision, double2* cpl, void* opl, hipStream_t st);
+// dynamic LDS of the kernels that hold two planes (largest n12max sites) and the twiddles of two axes
+inline size_t plane_lds(int n12max, int npm) { return (2 * (size_t)n12max + 2 * (size_t)npm) * 16; }
 hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, size_t lds_bytes,
                              const ObsDesc* d_obs, const int* d_r, const double2* cpl, const void* opl,
                              const double2* gf, double2* sph, double2* spo, int precision, int tile,
@@ -309,14 +311,13 @@ hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_en
 // dynamic LDS spec_mac_lds(largest extent)
 constexpr int kMacK = 8;
 constexpr int kMacThreads = 192;
-constexpr int kMacComps = 6;
 inline size_t spec_mac_lds(int npm) { return (size_t)12 * npm * kMacK * 16; }
 hipError_t launch_spec_mac(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int npm, int n_comp,
                            const ObsDesc* d_obs, const int* d_r, const int* d_comp, const int* d_gdesc,
                            const double2* sph, const double2* spo, double2* facc, hipStream_t st);
-hipError_t launch_spec_final(const EnsDesc* d_ens, int n_ens, const ObsDesc* d_obs, long long n_outputs, int npm,
-                             const int* d_probe, const int* d_pgroup, const double2* facc, double n_meas_total,
-                             double* results, const int* d_ring, hipStream_t st);
+hipError_t launch_spec_final(const EnsDesc* d_ens, int n_ens, const ObsDesc* d_obs, long long n_sums, int npm,
+                             int n12max, const int* d_probe, const int* d_pgroup, const double2* facc,
+                             double n_meas_total, double* results, const int* d_ring, hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t st);
 
 }  // namespace u1ml

@@ -116,6 +116,21 @@ def test_spectral_sums_of_every_component_count(env, n_comp):
     _compare(mk(), rh, rs, 1e-12)
 
 
+@pytest.mark.parametrize("n_probe", [1, 512, 513])
+def test_spectral_probe_counts(env, n_probe):
+    """One work-item reads off one probe: a single probe, a full work-group
+    and one more (a second pass), up to seven groups, axes of unequal
+    planes.  The shared bar of this file."""
+    u1, O, _ = env
+    probes = [(i // 81 - 3, i % 9 - 4, i // 9 % 9 - 4, 1) for i in range(n_probe)]
+    mk = lambda: u1.Spec(ensembles=[u1.Ens((12, 14, 10), 4, 1.0, seed=19)], levels=[(2, 2, 1)], r=[1, 2],
+                         dirs=[0, 1, 2], probes=probes, comps=[1, 5], precision=u1.FP64, n_or=1)
+    say("probes", n_probe)
+    rh, _, _ = _run(u1, mk(), u1.FORM_HISTORY)
+    rs, _, _ = _run(u1, mk(), u1.FORM_SPECTRAL)
+    _compare(mk(), rh, rs, 1e-12)
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_spectral_two_levels_replay_matches_history(env, prec):
     u1, O, _ = env
