@@ -228,14 +228,10 @@ __device__ inline FftPlan fft_plan(int n)
 // (se = 1), else the same butterfly of consecutive sequences (sq = 1), so the
 // 16-byte LDS accesses of a wave stay on distinct banks and the last stage's
 // global stores are contiguous.
-// NC, RC, SC: the length, the number of sequences and Ns as compile-time
-// constants (0: taken from the arguments), so that a fixed plane size folds
-// the index arithmetic
-template <int R, int NC = 0, int RC = 0, int SC = 0>
+template <int R>
 __device__ inline void fft_stage(const double2* __restrict__ src, int sq, int se, double2* __restrict__ dst, int dq,
-                                 int de, int n_, int rows_, int Ns_, const double2* __restrict__ tw, double sg)
+                                 int de, int n, int rows, int Ns, const double2* __restrict__ tw, double sg)
 {
-    const int n = NC ? NC : n_, rows = RC ? RC : rows_, Ns = SC ? SC : Ns_;
     const int m = n / R;
     const int tstep = n / (Ns * R);
     const int total = rows * m;
@@ -308,40 +304,6 @@ __device__ inline void fft_axis(const FftPlan& P, double2* cur, double2* other, 
         double2* t = cur;
         cur = other;
         other = t;
-    }
-}
-
-// The same FFT for an axis of compile-time length N on an N x N plane: the
-// stages of fft_plan(N) in the same order with the same arithmetic, every
-// length, count and stride constant.
-__host__ __device__ constexpr int cplan_stage(int n, int st, bool want_ns)
-{
-    int i = 0, ns = 1;
-    const int radices[4] = {4, 2, 3, 5};
-    for (int ri = 0; ri < 4; ++ri) {
-        const int r = radices[ri];
-        while (n % r == 0) {
-            if (i == st) return want_ns ? ns : r;
-            ++i;
-            ns *= r;
-            n /= r;
-        }
-    }
-    return want_ns ? ns : (n == 1 ? -i : 0);  // past the last stage: minus the stage count
-}
-__host__ __device__ constexpr int cplan_nst(int n) { return -cplan_stage(n, 64, false); }
-
-template <int N, int ST>
-__device__ inline void fft_axis_c(double2* cur, double2* other, int sq, int se, const double2* tw, double sg,
-                                  double2* out, int oq, int oe)
-{
-    constexpr int NST = cplan_nst(N);
-    if constexpr (ST < NST) {
-        constexpr int R = cplan_stage(N, ST, false), NS = cplan_stage(N, ST, true);
-        constexpr bool last = ST == NST - 1;
-        fft_stage<R, N, N, NS>(cur, sq, se, last ? out : other, last ? oq : sq, last ? oe : se, N, N, NS, tw, sg);
-        __syncthreads();
-        fft_axis_c<N, ST + 1>(other, cur, sq, se, tw, sg, out, oq, oe);
     }
 }
 
@@ -450,7 +412,7 @@ __global__ void __launch_bounds__(256) k_plane_stage(const EnsDesc* __restrict__
 // ---------------------------------------------------------------------------
 constexpr int kPlaneThreads = 512;  // two work-groups fill a CU's LDS; more threads per plane hide latency
 
-template <typename ot, int T, int NP>
+template <typename ot, int T>
 __global__ void __launch_bounds__(kPlaneThreads) k_dft_planes(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart,
                                                     int n_ens, const ObsDesc* __restrict__ obs,
                                                     const int* __restrict__ rlist, const double2* __restrict__ cpl,
@@ -536,13 +498,6 @@ __global__ void __launch_bounds__(kPlaneThreads) k_dft_planes(const EnsDesc* __r
         // along v (sequences u, contiguous), result left in X or Y, then along u
         // (sequences k2, stride n2), the last stage writing out[k1 n2 + k2]
         double2* mid = (P2.n_st & 1) ? Y : X;
-        if constexpr (NP > 0) {
-            if (n1 == NP && n2 == NP) {  // uniform for the block
-                fft_axis_c<NP, 0>(X, Y, n2, 1, w2, sg, mid, n2, 1);
-                fft_axis_c<NP, 0>(mid, mid == X ? Y : X, 1, n2, w1, sg, out, 1, n2);
-                return;
-            }
-        }
         fft_axis(P2, X, Y, n2, 1, n2, n1, w2, sg, mid, n2, 1);
         fft_axis(P1, mid, mid == X ? Y : X, 1, n2, n1, n2, w1, sg, out, 1, n2);
         return;
@@ -551,6 +506,223 @@ __global__ void __launch_bounds__(kPlaneThreads) k_dft_planes(const EnsDesc* __r
     dft_axis<T>(X, n1, n2, n2, 1, w2, Y, n2, 1);
     __syncthreads();
     dft_axis<T>(Y, n2, n1, 1, n2, w1, out, 1, n2);
+}
+
+// ---------------------------------------------------------------------------
+// Small DFTs in registers, kernel exp(+2 pi i / R), in place, natural order.
+// R = 6 and 12 by the prime-factor maps (Good 1958, Thomas 1963): inputs
+// (R2 a + R1 b) mod R, outputs by the Chinese remainders, no twiddles.
+// ---------------------------------------------------------------------------
+__device__ inline double2 add2(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ inline double2 sub2(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+
+__device__ inline void dft3(double2& v0, double2& v1, double2& v2)
+{
+    constexpr double h = 0.86602540378443864676;  // sin(pi/3)
+    const double2 s = add2(v1, v2), d = sub2(v1, v2);
+    const double2 t = make_double2(v0.x - 0.5 * s.x, v0.y - 0.5 * s.y);
+    v0 = add2(v0, s);
+    v1 = make_double2(t.x - h * d.y, t.y + h * d.x);
+    v2 = make_double2(t.x + h * d.y, t.y - h * d.x);
+}
+
+__device__ inline void dft4(double2& v0, double2& v1, double2& v2, double2& v3)
+{
+    const double2 a = add2(v0, v2), c = sub2(v0, v2), b = add2(v1, v3), d = sub2(v1, v3);
+    v0 = add2(a, b);
+    v1 = make_double2(c.x - d.y, c.y + d.x);
+    v2 = sub2(a, b);
+    v3 = make_double2(c.x + d.y, c.y - d.x);
+}
+
+template <int R>
+__device__ inline void dft_reg(double2 (&v)[R])
+{
+    static_assert(R == 3 || R == 4 || R == 5 || R == 6 || R == 8 || R == 12, "no DFT of this length");
+    if constexpr (R == 3) {
+        dft3(v[0], v[1], v[2]);
+    } else if constexpr (R == 4) {
+        dft4(v[0], v[1], v[2], v[3]);
+    } else if constexpr (R == 5) {
+        constexpr double c1 = 0.30901699437494742410, c2 = -0.80901699437494742410;  // cos(2 pi/5), cos(4 pi/5)
+        constexpr double s1 = 0.95105651629515357212, s2 = 0.58778525229247312917;   // sin(2 pi/5), sin(4 pi/5)
+        const double2 a1 = add2(v[1], v[4]), a2 = add2(v[2], v[3]), d1 = sub2(v[1], v[4]), d2 = sub2(v[2], v[3]);
+        const double2 t1 = make_double2(v[0].x + c1 * a1.x + c2 * a2.x, v[0].y + c1 * a1.y + c2 * a2.y);
+        const double2 t2 = make_double2(v[0].x + c2 * a1.x + c1 * a2.x, v[0].y + c2 * a1.y + c1 * a2.y);
+        const double2 u1 = make_double2(s1 * d1.x + s2 * d2.x, s1 * d1.y + s2 * d2.y);
+        const double2 u2 = make_double2(s2 * d1.x - s1 * d2.x, s2 * d1.y - s1 * d2.y);
+        v[0] = add2(v[0], add2(a1, a2));
+        v[1] = make_double2(t1.x - u1.y, t1.y + u1.x);
+        v[4] = make_double2(t1.x + u1.y, t1.y - u1.x);
+        v[2] = make_double2(t2.x - u2.y, t2.y + u2.x);
+        v[3] = make_double2(t2.x + u2.y, t2.y - u2.x);
+    } else if constexpr (R == 8) {
+        constexpr double h = 0.70710678118654752440;  // cos(pi/4)
+        dft4(v[0], v[2], v[4], v[6]);
+        dft4(v[1], v[3], v[5], v[7]);
+        const double2 o1 = make_double2(h * (v[3].x - v[3].y), h * (v[3].x + v[3].y));
+        const double2 o2 = make_double2(-v[5].y, v[5].x);
+        const double2 o3 = make_double2(h * (-v[7].x - v[7].y), h * (v[7].x - v[7].y));
+        const double2 e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6], o0 = v[1];
+        v[0] = add2(e0, o0);
+        v[4] = sub2(e0, o0);
+        v[1] = add2(e1, o1);
+        v[5] = sub2(e1, o1);
+        v[2] = add2(e2, o2);
+        v[6] = sub2(e2, o2);
+        v[3] = add2(e3, o3);
+        v[7] = sub2(e3, o3);
+    } else {
+        constexpr int R1 = R / 3;  // 2 or 4: inputs (3 a + R1 b) mod R -> outputs a' mod R1, b' mod 3
+#pragma unroll
+        for (int a = 0; a < R1; ++a) dft3(v[(3 * a) % R], v[(3 * a + R1) % R], v[(3 * a + 2 * R1) % R]);
+        double2 w[R];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            double2 x[R1];
+#pragma unroll
+            for (int a = 0; a < R1; ++a) x[a] = v[(3 * a + R1 * b) % R];
+            if constexpr (R1 == 4) {
+                dft4(x[0], x[1], x[2], x[3]);
+            } else {
+                const double2 s = add2(x[0], x[1]);
+                x[1] = sub2(x[0], x[1]);
+                x[0] = s;
+            }
+            // output k with k = a mod R1 and k = b mod 3
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                if (k % 3 == b) w[k] = x[k % R1];
+        }
+#pragma unroll
+        for (int k = 0; k < R; ++k) v[k] = w[k];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The plane transforms on square planes of N = RA RB sites a side: the same
+// fields, inputs and outputs as k_dft_planes, two radices an axis,
+//   y_j[q] = sum_r x[j + RB r] w_RA^(r q),  X[q + RA t] = sum_j w_N^(j q) y_j[q] w_RB^(j t),
+// each a DFT in one work-item's registers.  The u axis comes first, so that
+// memory is read into registers and written from them in runs of a row; one
+// LDS plane (rows of N + 1, so that work-items down a column fall on
+// different banks) carries the data between the four steps.  The rows of O
+// are real: their plain kernel is the conjugate of the other one's output.
+//
+// Bound by memory at 48 x 48 (8928 planes: 240 MB read, 330 MB written).  The
+// mixed-radix passes of k_dft_planes take three LDS round trips an axis
+// through two buffers (two work-groups to a CU, 180 us); here it is three for
+// the plane through one buffer (four work-groups to a CU): 124 us, 4.6 TB/s.
+// ---------------------------------------------------------------------------
+template <int RA, int RB>
+constexpr int fft_threads()
+{
+    return (RA * RB * RB + 63) / 64 * 64;  // one radix-RA butterfly each
+}
+
+template <typename ot, int RA, int RB>
+__global__ void __launch_bounds__((fft_threads<RA, RB>()), (fft_threads<RA, RB>() >= 512 ? 4 : 3))
+    k_fft_planes(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart, int n_ens,
+                 const ObsDesc* __restrict__ obs, const int* __restrict__ rlist, const double2* __restrict__ cpl,
+                 const ot* __restrict__ opl, const double2* __restrict__ gf, double2* __restrict__ sph,
+                 double2* __restrict__ spo)
+{
+    constexpr int N = RA * RB, S = N + 1, N2 = N * N, T = fft_threads<RA, RB>();
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    double2* X = reinterpret_cast<double2*>(lds_raw);  // [N][S]
+    double2* tw = X + N * S;
+    const int e = find_ens_s(bstart, n_ens, blockIdx.x);
+    const EnsDesc& E = ens[e];
+    const ObsDesc& O = *obs;
+    const int nsig = E.nsig, Si = E.s_in, R = O.n_r, NF = R + 12;
+    const int npm = max(E.nx, max(E.ny, E.nz));
+    int local = blockIdx.x - bstart[e];
+    const int xpar = local % npm;
+    local /= npm;
+    const int f = local % NF;
+    local /= NF;
+    const int s = local % Si;
+    const int id = local / Si;
+    if (id >= O.n_dirs) return;
+    const int Np = extent(E, O.dirs[id]);
+    if (xpar >= Np) return;  // uniform for the block
+    const int tid = threadIdx.x;
+    const size_t ps = (size_t)id * Si + s;
+    const bool t_field = f < R;
+    {
+        const int v = tid % N, j = tid / N;
+        const bool act = tid < N * RB;
+        const int i0 = act ? j * N + v : 0;  // element r: i0 + RB r N
+        double2 x[RA];
+        if (t_field) {
+            const int r = rlist[f];
+            const double2* ca = cpl + E.cpl_off + ps * nsig + (size_t)xpar * N2 + i0;
+            const double2* cb = cpl + E.cpl_off + ps * nsig + (size_t)((xpar + r) % Np) * N2 + i0;
+            const double2* g = gf + E.gf_off + (((size_t)id * R + f) * Si + s) * nsig + (size_t)xpar * N2 + i0;
+#pragma unroll
+            for (int q = 0; q < RA; ++q) {
+                const double2 a = ca[q * RB * N], b = cb[q * RB * N];
+                x[q] = cmul(g[q * RB * N], make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x));
+            }
+        } else {
+            const ot* op = opl + E.opl_off + (ps * 12 + (f - R)) * nsig + (size_t)xpar * N2 + i0;
+#pragma unroll
+            for (int q = 0; q < RA; ++q) x[q] = make_double2((double)op[q * RB * N], 0.0);
+        }
+        for (int i = tid; i < N; i += T) {
+            double sn, cs;
+            sincospi(2.0 * (double)i / (double)N, &sn, &cs);
+            tw[i] = make_double2(cs, sn);
+        }
+        dft_reg<RA>(x);
+        if (act) {
+#pragma unroll
+            for (int q = 0; q < RA; ++q) X[(q * RB + j) * S + v] = x[q];
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < N * RA; i += T) {  // row q RB + t then holds k1 = q + RA t
+        const int v = i % N, q = i / N;
+        double2 y[RB];
+#pragma unroll
+        for (int j = 0; j < RB; ++j) {
+            y[j] = X[(q * RB + j) * S + v];
+            if (j) y[j] = cmul(y[j], tw[j * q]);
+        }
+        dft_reg<RB>(y);
+#pragma unroll
+        for (int t = 0; t < RB; ++t) X[(q * RB + t) * S + v] = y[t];
+    }
+    __syncthreads();
+    {
+        const int p = tid % N, j = tid / N;
+        const bool act = tid < N * RB;
+        double2 x[RA];
+        if (act) {
+#pragma unroll
+            for (int q = 0; q < RA; ++q) x[q] = X[p * S + j + RB * q];
+        }
+        __syncthreads();  // every column read before the rows are written in another order
+        if (act) {
+            dft_reg<RA>(x);
+#pragma unroll
+            for (int q = 0; q < RA; ++q) X[p * S + j * RA + q] = q ? cmul(x[q], tw[j * q]) : x[q];
+        }
+    }
+    __syncthreads();
+    double2* out = t_field ? sph + E.sph_off + (ps * R + f) * nsig + (size_t)xpar * N2
+                           : spo + E.spo_off + (ps * 12 + (f - R)) * nsig + (size_t)xpar * N2;
+    const double sg = t_field ? 1.0 : -1.0;
+    for (int i = tid; i < N * RA; i += T) {
+        const int q = i % RA, p = i / RA;
+        double2 y[RB];
+#pragma unroll
+        for (int j = 0; j < RB; ++j) y[j] = X[p * S + j * RA + q];
+        dft_reg<RB>(y);
+        const int k1 = p / RB + RA * (p % RB);
+#pragma unroll
+        for (int t = 0; t < RB; ++t) out[k1 * N + q + RA * t] = make_double2(y[t].x, sg * y[t].y);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -855,26 +1027,57 @@ hipError_t launch_plane_stage(const EnsDesc* d_ens, const int* d_bstart, int n_e
     return hipGetLastError();
 }
 
-hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, size_t lds_bytes,
-                             const ObsDesc* d_obs, const int* d_r, const double2* cpl, const void* opl,
-                             const double2* gf, double2* sph, double2* spo, int precision, int tile,
+// square: the side of every plane of the launch, 0 if they differ or are not square; n12max, npm: largest plane and extent
+hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int square,
+                             int n12max, int npm, const ObsDesc* d_obs, const int* d_r, const double2* cpl,
+                             const void* opl, const double2* gf, double2* sph, double2* spo, int precision, int tile,
                              hipStream_t st)
 {
+    // Square planes of one size whose side has two radices take the transform
+    // in registers (48 x 48: 124 instead of 180 us); every other plane the
+    // mixed-radix passes or, with a prime factor above 5, the direct sums.
+    if (square > 0) {
+        const size_t lds = (size_t)square * (square + 2) * 16;
+#define U1ML_FFT(RA, RB)                                                                                               \
+    case RA * RB:                                                                                                      \
+        if (precision == 0)                                                                                            \
+            hipLaunchKernelGGL((k_fft_planes<double, RA, RB>), dim3(total_blocks), dim3(fft_threads<RA, RB>()), lds,   \
+                               st, d_ens, d_bstart, n_ens, d_obs, d_r, cpl, (const double*)opl, gf, sph, spo);         \
+        else                                                                                                           \
+            hipLaunchKernelGGL((k_fft_planes<float, RA, RB>), dim3(total_blocks), dim3(fft_threads<RA, RB>()), lds,    \
+                               st, d_ens, d_bstart, n_ens, d_obs, d_r, cpl, (const float*)opl, gf, sph, spo);          \
+        return hipGetLastError();
+        switch (square) {
+            U1ML_FFT(4, 3)
+            U1ML_FFT(4, 4)
+            U1ML_FFT(6, 3)
+            U1ML_FFT(5, 4)
+            U1ML_FFT(6, 4)
+            U1ML_FFT(6, 5)
+            U1ML_FFT(8, 4)
+            U1ML_FFT(6, 6)
+            U1ML_FFT(8, 5)
+            U1ML_FFT(12, 4)
+            U1ML_FFT(12, 5)
+            U1ML_FFT(8, 8)
+        }
+#undef U1ML_FFT
+    }
     const dim3 g(total_blocks), b(kPlaneThreads);
-    // 48 x 48 planes (the 48^3 lattice) take the transform with constant sizes
+    const size_t lds_bytes = plane_lds(n12max, npm);
     if (precision == 0) {
         if (tile == 4)
-            hipLaunchKernelGGL((k_dft_planes<double, 4, 48>), g, b, lds_bytes, st, d_ens, d_bstart, n_ens, d_obs, d_r,
+            hipLaunchKernelGGL((k_dft_planes<double, 4>), g, b, lds_bytes, st, d_ens, d_bstart, n_ens, d_obs, d_r,
                                cpl, (const double*)opl, gf, sph, spo);
         else
-            hipLaunchKernelGGL((k_dft_planes<double, 2, 0>), g, b, lds_bytes, st, d_ens, d_bstart, n_ens, d_obs, d_r,
+            hipLaunchKernelGGL((k_dft_planes<double, 2>), g, b, lds_bytes, st, d_ens, d_bstart, n_ens, d_obs, d_r,
                                cpl, (const double*)opl, gf, sph, spo);
     } else {
         if (tile == 4)
-            hipLaunchKernelGGL((k_dft_planes<float, 4, 48>), g, b, lds_bytes, st, d_ens, d_bstart, n_ens, d_obs, d_r,
+            hipLaunchKernelGGL((k_dft_planes<float, 4>), g, b, lds_bytes, st, d_ens, d_bstart, n_ens, d_obs, d_r,
                                cpl, (const float*)opl, gf, sph, spo);
         else
-            hipLaunchKernelGGL((k_dft_planes<float, 2, 0>), g, b, lds_bytes, st, d_ens, d_bstart, n_ens, d_obs, d_r,
+            hipLaunchKernelGGL((k_dft_planes<float, 2>), g, b, lds_bytes, st, d_ens, d_bstart, n_ens, d_obs, d_r,
                                cpl, (const float*)opl, gf, sph, spo);
     }
     return hipGetLastError();

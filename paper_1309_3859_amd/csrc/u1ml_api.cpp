@@ -987,6 +987,7 @@ struct u1ml_ctx {
     int spec_npm = 0;                              // largest lattice extent (spectral launches)
     long long spec_n12max = 0;                     // largest transverse plane (sites)
     int spec_tile = 4;                             // plane-transform tile (4, or 2 if an extent is not a multiple of 4)
+    int spec_square = -1;                          // side of every plane if all are squares of one side, else 0
     int *d_pgroup = nullptr, *d_gdesc = nullptr, *d_pblk = nullptr;
     PairRow* d_prow = nullptr;  // row tables of the both-parities launches
     size_t ins_lds = 0;  // insertion contraction dynamic LDS per work-group
@@ -1520,14 +1521,13 @@ hipError_t enq_levels(u1ml_ctx* c, const Lane& L, hipStream_t st, bool store_o, 
             if (e == hipSuccess)
                 e = launch_gfac(L.d_ens, L.tab_dev(kTabSite), n, L.tab_total(kTabSite), c->d_obs, c->at,
                                 P.two ? c->wf : nullptr, P.two ? P.tau_o / P.tau_i : 0, c->gf, c->res, L.d_ring, st);
-            const size_t lds = plane_lds(c->spec_n12max, c->spec_npm);
             for (int m = 0; e == hipSuccess && m < P.n_i; ++m) {
                 e = launch_plane_stage(L.d_ens, L.tab_dev(kTabStage), n, L.tab_total(kTabStage), c->d_obs, c->hc,
                                        c->ho, m, P.precision, c->cpl, c->opl, st);
                 if (e == hipSuccess)
-                    e = launch_dft_planes(L.d_ens, L.tab_dev(kTabPlane), n, L.tab_total(kTabPlane), lds, c->d_obs,
-                                          c->d_r, c->cpl, c->opl, c->gf, c->sph, c->spo, P.precision,
-                                          c->spec_tile, st);
+                    e = launch_dft_planes(L.d_ens, L.tab_dev(kTabPlane), n, L.tab_total(kTabPlane), c->spec_square,
+                                          c->spec_n12max, c->spec_npm, c->d_obs, c->d_r, c->cpl, c->opl, c->gf, c->sph,
+                                          c->spo, P.precision, c->spec_tile, st);
                 if (e == hipSuccess)
                     e = launch_spec_mac(L.d_ens, L.tab_dev(kTabMac), n, L.tab_total(kTabMac), c->spec_npm,
                                         (int)P.comps.size(), c->d_obs, c->d_r, c->d_comp, c->d_gdesc, c->sph, c->spo,
@@ -1982,6 +1982,12 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         for (int i = 0; i < P.n_dirs; ++i)
             for (int k = 1; k < 3; ++k)
                 if (n3[(P.dirs[i] + k) % 3] % 4 != 0) c->spec_tile = 2;
+        for (int i = 0; i < P.n_dirs; ++i)
+            for (int k = 1; k < 3; ++k) {
+                const int n = n3[(P.dirs[i] + k) % 3];
+                if (c->spec_square < 0) c->spec_square = n;
+                if (c->spec_square != n) c->spec_square = 0;
+            }
     }
     // the whole batch as one lane; the split into lanes follows the streams below
     {

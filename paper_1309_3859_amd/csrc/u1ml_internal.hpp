@@ -303,9 +303,9 @@ hipError_t launch_plane_stage(const EnsDesc* d_ens, const int* d_bstart, int n_e
                               int precision, double2* cpl, void* opl, hipStream_t st);
 // dynamic LDS of the kernels that hold two planes (largest n12max sites) and the twiddles of two axes
 inline size_t plane_lds(int n12max, int npm) { return (2 * (size_t)n12max + 2 * (size_t)npm) * 16; }
-hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, size_t lds_bytes,
-                             const ObsDesc* d_obs, const int* d_r, const double2* cpl, const void* opl,
-                             const double2* gf, double2* sph, double2* spo, int precision, int tile,
+hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int square,
+                             int n12max, int npm, const ObsDesc* d_obs, const int* d_r, const double2* cpl,
+                             const void* opl, const double2* gf, double2* sph, double2* spo, int precision, int tile,
                              hipStream_t st);
 // spectral sums: work-groups of kMacThreads per (axis, slab, probe group, kMacK values of k);
 // dynamic LDS spec_mac_lds(largest extent)

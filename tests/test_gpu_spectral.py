@@ -132,6 +132,22 @@ def test_spectral_probe_counts(env, n_probe):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("side", [12, 16, 18, 20, 24, 30, 32, 36, 40, 48, 60, 64])
+def test_spectral_square_planes(env, side, prec):
+    """Each side that has a transform in registers, both link types; the
+    extent along the charge axis differs from the planes' sides.  The shared
+    bar of this file."""
+    u1, O, _ = env
+    mk = lambda: u1.Spec(ensembles=[u1.Ens((6, side, side), 4, 1.0, seed=23)], levels=[(2, 2, 1)], r=[1, 2],
+                         dirs=[0], probes=_disk(2), comps=[0, 3], precision=u1.FP64 if prec == "fp64" else u1.FP32,
+                         n_or=1)
+    say("square planes", side, prec)
+    rh, _, _ = _run(u1, mk(), u1.FORM_HISTORY)
+    rs, _, _ = _run(u1, mk(), u1.FORM_SPECTRAL)
+    _compare(mk(), rh, rs, 1e-12)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_spectral_two_levels_replay_matches_history(env, prec):
     u1, O, _ = env
     mk = lambda: u1.Spec(ensembles=[u1.Ens((6, 6, 6), 8, 1.0, seed=21)], levels=[(4, 2, 1), (2, 3, 1)], r=[1, 2],
