@@ -1248,6 +1248,12 @@ hipError_t launch_combine(const EnsDesc* d_ens, const int* d_bstart, int n_ens, 
 //                    work-group into part[wg][26][hi, lo];
 //   k_product_final: the chunks of each (e, r, probe) in chunk order.
 // src_t  = A * scale_t, src_to = B * scale_t (scale_t = 1 or 1/n_outer).
+// Bound by memory: B is read once (24^3 x 8, 11 separations, 10 probes, 6
+// components: 1.26 GB).  The loads of a slab's components are issued together
+// before its weight is formed, and 1024 items a work-group fill the two
+// work-groups a CU holds evenly (1386 of them; of 2048 items, 1.35 rounds):
+// 267 us, 4.7 TB/s (386 us with a load per use and a barrier per step of
+// every quantity's reduction).
 // ---------------------------------------------------------------------------
 struct ProdItem {
     int e, ir, p, ch;
@@ -1275,12 +1281,16 @@ __device__ inline T* record_of(const EnsDesc& E, const ObsDesc& O, T* results, c
 __device__ inline sc slab_product(const double2* __restrict__ row, int S, int nsig, int skip, double scale_t)
 {
     sc P{1.0, 0.0, 0};
-    for (int s = 0; s < S; ++s) {
-        if (s == skip) continue;
-        double2 a = row[(size_t)s * nsig];
-        a.x *= scale_t;
-        a.y *= scale_t;
-        P = sc_mul(P, a);
+    constexpr int A = 4;  // slabs loaded together
+    for (int s0 = 0; s0 < S; s0 += A) {
+        double2 a[A];
+#pragma unroll
+        for (int u = 0; u < A; ++u) a[u] = row[(size_t)min(s0 + u, S - 1) * nsig];
+#pragma unroll
+        for (int u = 0; u < A; ++u) {
+            if (s0 + u >= S || s0 + u == skip) continue;
+            P = sc_mul(P, make_double2(a[u].x * scale_t, a[u].y * scale_t));
+        }
     }
     return P;
 }
@@ -1332,7 +1342,7 @@ __global__ void __launch_bounds__(64) k_prod_exp_final(const EnsDesc* __restrict
     record_of(E, O, results, ring)[O.n_doubles_per_config - O.n_r + ir] = emax == kNoExp ? 0.0 : (double)emax;
 }
 
-__global__ void __launch_bounds__(256) k_product(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart,
+__global__ void __launch_bounds__(256, 2) k_product(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart,
                                                  int n_ens, const ObsDesc* __restrict__ obs, int n_pgroups,
                                                  const double2* __restrict__ src_t, const double2* __restrict__ src_to,
                                                  int use_outer, double scale_t, double* __restrict__ part,
@@ -1370,57 +1380,58 @@ __global__ void __launch_bounds__(256) k_product(const EnsDesc* __restrict__ ens
         }
         if (!has_probe) continue;
         for (int s = 0; s < S; ++s) {
+            const double2* B = src_to + to_off + ((((size_t)id * n_r + ir) * O.n_probe + p) * nc * 2 * S + s) * nsig + xs;
+            double2 b[12];
+#pragma unroll
+            for (int k = 0; k < 12; ++k)
+                if (k < 2 * nc) b[k] = B[(size_t)k * S * nsig];
             const sc W = slab_product(row, S, nsig, s, scale_t);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 if (k < 2 * nc) {
-                    const size_t krow = ((((size_t)id * n_r + ir) * O.n_probe + p) * nc) * 2 + k;
-                    double2 b = src_to[to_off + (krow * S + s) * nsig + xs];
-                    b.x *= scale_t;
-                    b.y *= scale_t;
-                    const double2 v = sc_rel(sc_mul(W, b), Er);
+                    const double2 v = sc_rel(sc_mul(W, make_double2(b[k].x * scale_t, b[k].y * scale_t)), Er);
                     ore[k] = dd_add(ore[k], v.x);
                     oim[k] = dd_add(oim[k], v.y);
                 }
             }
         }
     }
-    __shared__ double shh[256], shl[256];
-    auto reduce = [&](dd v) -> dd {
-        shh[threadIdx.x] = v.hi;
-        shl[threadIdx.x] = v.lo;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) {
-                const dd a = dd_add(dd{shh[threadIdx.x], shl[threadIdx.x]},
-                                    dd{shh[threadIdx.x + w], shl[threadIdx.x + w]});
-                shh[threadIdx.x] = a.hi;
-                shl[threadIdx.x] = a.lo;
-            }
-            __syncthreads();
-        }
-        const dd r{shh[0], shl[0]};
-        __syncthreads();
-        return r;
-    };
+    // Fixed-order tree over the work-group, kProdRed quantities at a time: each
+    // wave takes its share of them, adding the values of lanes i, i + 64, i + 128
+    // and i + 192, then across its lanes (a barrier per step of every quantity
+    // took 25 us of a work-group's 165)
+    constexpr int kProdRed = 8;
+    __shared__ double2 sh[kProdRed][256];
     double* out = part + (size_t)blockIdx.x * kProdQ * 2;
-    auto put = [&](int q, dd v) {
-        if (threadIdx.x == 0) {
-            out[2 * q] = v.hi;
-            out[2 * q + 1] = v.lo;
+    const int tid = threadIdx.x, lane = tid & 63;
+    auto reduce = [&](const dd* v, int n, int q0) {  // v[0 .. n) of every work-item to out[q0 ...], n <= kProdRed
+        __syncthreads();                             // the previous batch has been read
+#pragma unroll
+        for (int k = 0; k < kProdRed; ++k)
+            if (k < n) sh[k][tid] = make_double2(v[k].hi, v[k].lo);
+        __syncthreads();
+        for (int k = tid >> 6; k < n; k += 4) {
+            auto at = [&](int i) { return dd{sh[k][i].x, sh[k][i].y}; };
+            dd a = dd_add(dd_add(at(lane), at(lane + 128)), dd_add(at(lane + 64), at(lane + 192)));
+#pragma unroll
+            for (int w = 32; w > 0; w >>= 1) a = dd_add(a, dd{__shfl_xor(a.hi, w), __shfl_xor(a.lo, w)});
+            if (lane == 0) {
+                out[2 * (q0 + k)] = a.hi;
+                out[2 * (q0 + k) + 1] = a.lo;
+            }
         }
     };
     if (p == 0) {
-        put(0, reduce(cre));
-        put(1, reduce(cim));
+        const dd v[kProdRed] = {cre, cim};
+        reduce(v, 2, 0);
     }
     if (has_probe) {
 #pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            if (k < 2 * nc) {  // uniform
-                put(2 + 2 * k, reduce(ore[k]));
-                put(3 + 2 * k, reduce(oim[k]));
-            }
+        for (int k = 0; k < 12; k += 4) {
+            if (k >= 2 * nc) continue;  // uniform
+            const dd v[kProdRed] = {ore[k],     oim[k],     ore[k + 1], oim[k + 1],
+                                    ore[k + 2], oim[k + 2], ore[k + 3], oim[k + 3]};
+            reduce(v, min(kProdRed, 2 * (2 * nc - k)), 2 + 2 * k);
         }
     }
 }

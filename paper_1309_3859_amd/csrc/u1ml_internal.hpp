@@ -180,7 +180,7 @@ __host__ __device__ inline bool mf_chunk_fits(int mc, int N, int R, int nrows, i
 }
 
 constexpr int kUpdateClasses = 4;  // temporal, spatial full, spatial inner tau, spatial outer tau
-constexpr int kProdChunk = 2048;    // slab products: (axis, site) items per work-group
+constexpr int kProdChunk = 1024;    // slab products: (axis, site) items per work-group
 constexpr int kProdQ = 26;          // slab products: correlator re, im and 12 insertion quantities re, im
 constexpr int kConLds = 49152;      // contraction: LDS budget per work-group (bytes)
 constexpr int kPlaqBlocks = 1024;   // plaquette means: work-groups (and partials) per ensemble
