@@ -314,22 +314,23 @@ __device__ inline void fft_axis(const FftPlan& P, double2* cur, double2* other, 
 //   cpl[axis][s][plane_index],  opl[axis][s][row][plane_index]
 // Work-group per (ensemble, axis, slab, tile): the target's fastest
 // coordinate is v (z for the x axis, x for the y axis, y for the z axis); a
-// tile is 32 x values by 32 v values at fixed remaining coordinate, read with
-// x fastest and written with v fastest through LDS (the slab phase and four O
-// rows per pass), so both sides are contiguous.  For the y axis (v = x) the
-// tile is 32 x values of 32 rows, copied directly.
+// tile is 16 x values by 16 v values at fixed remaining coordinate, one per
+// work-item, read with x fastest and written with v fastest through LDS, so
+// both sides are contiguous.  For the y axis (v = x) the tile is 16 x values
+// of 16 rows, copied directly.
+// Bound by latency (48^3 x 12: 83 MB): tiles of 32 x 32 in three passes of
+// four rows took 37 us, the passes as work-groups of their own 31 us, and
+// half of the work-items of every second tile lie outside 48 sites; now 22 us (3.7 TB/s).
 // ---------------------------------------------------------------------------
-constexpr int kStageTile = 32;
-
 template <typename ot>
-__global__ void __launch_bounds__(256) k_plane_stage(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart,
+__global__ void __launch_bounds__(kStageTile * kStageTile) k_plane_stage(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart,
                                                      int n_ens, const ObsDesc* __restrict__ obs,
                                                      const double2* __restrict__ hist_c, const ot* __restrict__ hist_o,
                                                      int m_in, double2* __restrict__ cpl, ot* __restrict__ opl)
 {
     constexpr int TT = kStageTile;
     __shared__ double2 tc[TT][TT + 1];
-    __shared__ ot to[4][TT][TT + 1];  // four O rows per pass
+    __shared__ ot to[12][TT][TT + 1];
     const int e = find_ens_s(bstart, n_ens, blockIdx.x);
     const EnsDesc& E = ens[e];
     const ObsDesc& O = *obs;
@@ -347,56 +348,45 @@ __global__ void __launch_bounds__(256) k_plane_stage(const EnsDesc* __restrict__
     // v: the target's fastest axis; w: the remaining one (y axis: v = x, rows y, w = z)
     const int vax = dir == 0 ? 2 : dir == 1 ? 0 : 1;
     const int wax = dir == 0 ? 1 : 2;
-    const int n3[3] = {nx, ny, nz};
-    const int nrow = vax == 0 ? ny : n3[vax];  // extent of the tile's second index
+    const int nrow = vax == 2 ? nz : ny;  // extent of the tile's second index
     const int x0 = (tile % tx_n) * TT;
     const int v0 = ((tile / tx_n) % tv_n) * TT;
     const int w = tile / (tx_n * tv_n);
-    if (w >= n3[wax] || v0 >= nrow) return;  // uniform for the block
+    if (w >= extent(E, wax) || v0 >= nrow) return;  // uniform for the block
     const size_t ps = (size_t)id * Si + s;
     const double2* hc = hist_c + E.hc_off + ((size_t)m_in * Si + s) * nsig;
     const ot* ho = hist_o + E.ho_off + ((size_t)m_in * Si + s) * 12 * nsig;
     double2* dc = cpl + E.cpl_off + ps * nsig;
     ot* dob = opl + E.opl_off + ps * 12 * nsig;
-    const int lx = threadIdx.x % TT, ly = threadIdx.x / TT;  // 32 x 8 work-items
-    if (vax == 0) {
-        // y axis: plane index (y nz + z) nx + x keeps x fastest: a plain copy of 32 rows
-        for (int i = ly; i < TT; i += 8) {
-            const int y = v0 + i, x = x0 + lx;
-            if (y >= ny || x >= nx) continue;
-            const int xs = x + nx * (y + ny * w);
-            const int p = (y * nz + w) * nx + x;
-            dc[p] = hc[xs];
+    const int lx = threadIdx.x % TT, ly = threadIdx.x / TT;
+    // read with x fastest, every load issued before the first store
+    const int v = min(v0 + ly, nrow - 1), x = min(x0 + lx, nx - 1);
+    const int y = vax == 2 ? w : v, z = vax == 2 ? v : w;
+    const int xs = x + nx * (y + ny * z);
+    const double2 c = hc[xs];
+    ot o[12];
 #pragma unroll
-            for (int row = 0; row < 12; ++row) dob[(size_t)row * nsig + p] = ho[(size_t)row * nsig + xs];
-        }
+    for (int row = 0; row < 12; ++row) o[row] = ho[(size_t)row * nsig + xs];
+    if (vax == 0) {
+        // y axis: plane index (y nz + z) nx + x keeps x fastest: a plain copy of TT rows
+        if (v0 + ly >= ny || x0 + lx >= nx) return;
+        const int p = (y * nz + z) * nx + x;
+        dc[p] = c;
+#pragma unroll
+        for (int row = 0; row < 12; ++row) dob[(size_t)row * nsig + p] = o[row];
         return;
     }
-    for (int pass = 0; pass < 3; ++pass) {
-        // read with x fastest
-        for (int i = ly; i < TT; i += 8) {
-            const int v = v0 + i, x = x0 + lx;
-            if (v < nrow && x < nx) {
-                const int y = vax == 1 ? v : w, z = vax == 2 ? v : w;
-                const int xs = x + nx * (y + ny * z);
-                if (pass == 0) tc[i][lx] = hc[xs];
+    tc[ly][lx] = c;
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) to[r4][i][lx] = ho[(size_t)(4 * pass + r4) * nsig + xs];
-            }
-        }
-        __syncthreads();
-        // write with v fastest: x axis p = (x ny + y) nz + z (y = w, z = v); z axis p = (z nx + x) ny + y (z = w, y = v)
-        for (int i = ly; i < TT; i += 8) {
-            const int x = x0 + i, v = v0 + lx;
-            if (v < nrow && x < nx) {
-                const int p = vax == 2 ? (x * ny + w) * nz + v : (w * nx + x) * ny + v;
-                if (pass == 0) dc[p] = tc[lx][i];
+    for (int row = 0; row < 12; ++row) to[row][ly][lx] = o[row];
+    __syncthreads();
+    // write with v fastest: x axis p = (x ny + y) nz + z (y = w, z = v); z axis p = (z nx + x) ny + y (z = w, y = v)
+    const int xw = x0 + ly, vw = v0 + lx;
+    if (vw >= nrow || xw >= nx) return;
+    const int p = vax == 2 ? (xw * ny + w) * nz + vw : (w * nx + xw) * ny + vw;
+    dc[p] = tc[lx][ly];
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) dob[(size_t)(4 * pass + r4) * nsig + p] = to[r4][lx][i];
-            }
-        }
-        __syncthreads();
-    }
+    for (int row = 0; row < 12; ++row) dob[(size_t)row * nsig + p] = to[row][lx][ly];
 }
 
 // ---------------------------------------------------------------------------
@@ -1017,12 +1007,11 @@ hipError_t launch_plane_stage(const EnsDesc* d_ens, const int* d_bstart, int n_e
                               int precision, double2* cpl, void* opl, hipStream_t st)
 {
     if (total_blocks <= 0) return hipSuccess;
-    static_assert(kStageTile == 32, "the staging work-group is 32 x 8 threads");
     if (precision == 0)
-        hipLaunchKernelGGL(k_plane_stage<double>, dim3(total_blocks), dim3(kStageTile * 8), 0, st, d_ens, d_bstart, n_ens, d_obs,
+        hipLaunchKernelGGL(k_plane_stage<double>, dim3(total_blocks), dim3(kStageTile * kStageTile), 0, st, d_ens, d_bstart, n_ens, d_obs,
                            hist_c, (const double*)hist_o, m_in, cpl, (double*)opl);
     else
-        hipLaunchKernelGGL(k_plane_stage<float>, dim3(total_blocks), dim3(kStageTile * 8), 0, st, d_ens, d_bstart, n_ens, d_obs,
+        hipLaunchKernelGGL(k_plane_stage<float>, dim3(total_blocks), dim3(kStageTile * kStageTile), 0, st, d_ens, d_bstart, n_ens, d_obs,
                            hist_c, (const float*)hist_o, m_in, cpl, (float*)opl);
     return hipGetLastError();
 }

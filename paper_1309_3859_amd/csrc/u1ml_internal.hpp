@@ -297,7 +297,8 @@ hipError_t launch_gfac(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int
                        const double2* avg_t, const double2* wf, int q, double2* gf, const double* results,
                        const int* d_ring, hipStream_t st);
 // measurement m_in's slab phases and O rows copied to the plane-major order of each charge axis;
-// d_bstart: per ensemble n_dirs * s_in * ceil(Nx/32) * ceil(max extent/32) * max extent work-groups
+// d_bstart: per ensemble n_dirs * s_in * ceil(Nx/kStageTile) * ceil(max extent/kStageTile) * max extent work-groups
+constexpr int kStageTile = 16;
 hipError_t launch_plane_stage(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks,
                               const ObsDesc* d_obs, const double2* hist_c, const void* hist_o, int m_in,
                               int precision, double2* cpl, void* opl, hipStream_t st);
