@@ -717,44 +717,53 @@ __global__ void __launch_bounds__((fft_threads<RA, RB>()), (fft_threads<RA, RB>(
 
 // ---------------------------------------------------------------------------
 // Spectral sums of one measurement.  Work-group per (ensemble, axis, slab,
-// probe group, run of kMacK values of k); the 12 O rows of those k for every
-// x_par are staged in LDS once and shared by all separations r:
+// probe group, run of kMacK values of k, kind); the 6 O rows of those k and
+// that kind for every x_par are staged in LDS once and shared by all
+// separations r:
 //   F[...][c][kind][g][k] += sum_{x_par} O^_{row}(x_par + l) (k) * h^~_r(x_par) (k)
 // with l = l_g + (mode_g ? l_mid(r, c) : 0) and row = 2 o(c, axis) + kind.
 // Work-item (k, r slot) takes r = slot, slot + kMacThreads / kMacK, ...  Every
 // sum runs over x_par in ascending order.
 //
 // Bound by the latency of its loads: 48^3 x 12 with 19 separations moves 430
-// MB in 1728 work-groups of three waves, two to a CU.  So the O rows go
-// straight from memory to LDS (global_load_lds), all in flight together with
-// the first T spectra and the running sums, and the T spectra then come in
-// two register buffers of kMacAhead values, one summed while the other loads
-// (8 instead of 6 values: the same within noise).  NC, the number of
-// components, is a constant, so that no branch separates the LDS reads of one
-// position from the next.  Staged through registers, with every load awaited
-// where it was used, the launch took 240 us; now 152 us (2.8 TB/s).
+// MB.
+// So the O rows go straight from memory to LDS (global_load_lds), all in
+// flight together with the first T spectra and the running sums; the T
+// spectra then come in two register buffers of kMacAhead values, one summed
+// while the other loads (8 or 12 instead of 6: the same within noise); and a
+// work-group holds one kind, so that four fit a CU's LDS instead of two (the
+// kinds of a tile share the T spectra through the L2 of their XCD: memory
+// reads stay the same).  NC, the number of components, is a constant, so that
+// no branch separates the LDS reads of one position from the next.  240 us
+// with the O rows of both kinds staged through registers and every load
+// awaited where it was used, 152 us with copies and buffers, 140 us now
+// (3.1 TB/s).
 // ---------------------------------------------------------------------------
 constexpr int kMacAhead = 6;
 
 template <int NC>
-__global__ void __launch_bounds__(kMacThreads, 2) k_spec_mac(const EnsDesc* __restrict__ ens,
+__global__ void __launch_bounds__(kMacThreads, 3) k_spec_mac(const EnsDesc* __restrict__ ens,
                                                              const int* __restrict__ bstart, int n_ens,
                                                              const ObsDesc* __restrict__ obs,
                                                              const int* __restrict__ rlist, const int* __restrict__ comps,
                                                              const int* __restrict__ gdesc, const double2* __restrict__ sph,
-                                                             const double2* __restrict__ spo, double2* __restrict__ facc)
+                                                             const double2* __restrict__ spo, double2* __restrict__ facc,
+                                                             int n_tiles)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    double2* os = reinterpret_cast<double2*>(lds_raw);  // [row][x_par][kk]
+    double2* os = reinterpret_cast<double2*>(lds_raw);  // [orientation][x_par][kk]
     constexpr int KC = kMacK, A = kMacAhead;
-    const int e = find_ens_s(bstart, n_ens, blockIdx.x);
+    // the two kinds of a tile eight work-groups apart: the same XCD, whose L2 then holds the T spectra for both
+    const int kind = (blockIdx.x >> 3) & 1, tile = (int)(blockIdx.x & 7u) + (int)(blockIdx.x >> 4) * 8;
+    if (tile >= n_tiles) return;  // uniform: padding of the launch to a multiple of 16
+    const int e = find_ens_s(bstart, n_ens, tile);
     const EnsDesc& E = ens[e];
     const ObsDesc& O = *obs;
     const int nsig = E.nsig, Si = E.s_in, R = O.n_r, NG = O.n_groups;
     int n12max = 0;
     for (int i = 0; i < O.n_dirs; ++i) n12max = max(n12max, nsig / extent(E, O.dirs[i]));
     const int nkc = (n12max + KC - 1) / KC;
-    int local = blockIdx.x - bstart[e];
+    int local = tile - bstart[e];
     const int kc = local % nkc;
     local /= nkc;
     const int g = local % NG;
@@ -769,15 +778,15 @@ __global__ void __launch_bounds__(kMacThreads, 2) k_spec_mac(const EnsDesc* __re
     const size_t ps = (size_t)id * Si + s;
     const int kk = threadIdx.x % KC, slot = threadIdx.x / KC;
     const int k = min(k0 + kk, n12 - 1);  // past the plane's end: a copy of the last k, not stored
-    // element i = (row N + x_par) KC + kk of the tile: 64 consecutive ones per wave and round
+    // element i = (orientation N + x_par) KC + kk of the tile: 64 consecutive ones per wave and round
     {
-        const double2* src = spo + E.spo_off + ps * 12 * nsig + k;
-        const int n_os = 12 * N * KC, lane = threadIdx.x & 63;
+        const double2* src = spo + E.spo_off + (ps * 12 + kind) * nsig + k;
+        const int n_os = 6 * N * KC, lane = threadIdx.x & 63;
         for (int j = (int)threadIdx.x & ~63; j < n_os; j += kMacThreads) {
             const int i = j + lane;
             if (i < n_os) {  // lane % KC is kk: KC divides 64
-                const int t = i / KC;
-                __builtin_amdgcn_global_load_lds((const void*)(src + (size_t)t * n12),
+                const int t = i / KC, o = t / N;
+                __builtin_amdgcn_global_load_lds((const void*)(src + (size_t)(t + o * N) * n12),
                                                  (__attribute__((address_space(3))) void*)(os + j), 16, 0, 0);
             }
         }
@@ -795,38 +804,32 @@ __global__ void __launch_bounds__(kMacThreads, 2) k_spec_mac(const EnsDesc* __re
             for (int u = 0; u < A; ++u) b[u] = h[(size_t)min(x0 + u, N - 1) * n12];
         };
         fetch(b0, 0);
-        const size_t sl0 = (ps * R + irc) * NC * 2 * NG + g;
+        const size_t sl0 = ((ps * R + irc) * NC * 2 + kind) * NG + g;
         double2* F = facc + E.facc_off + sl0 * n12max + k;
-        const size_t fstep = (size_t)NG * n12max;
-        double2 f[NC][2];
+        const size_t fstep = 2 * (size_t)NG * n12max;
+        double2 f[NC];
 #pragma unroll
-        for (int ic = 0; ic < NC; ++ic)
-#pragma unroll
-            for (int kind = 0; kind < 2; ++kind) f[ic][kind] = F[(size_t)(2 * ic + kind) * fstep];
+        for (int ic = 0; ic < NC; ++ic) f[ic] = F[(size_t)ic * fstep];
         // LDS offsets of O at x_par + l: xa for components that lie across the axis, xb for those that span it
         const int lg = gdesc[2 * g], mid = gdesc[2 * g + 1];
         int xa = ((((lg + (mid ? r / 2 : 0)) % N) + N) % N) * KC + kk;
         int xb = ((((lg + (mid ? (r - 1) / 2 : 0)) % N) + N) % N) * KC + kk;
         int ob[NC], span[NC];  // span: all bits set or none
-        double re[NC][2], im[NC][2];
+        double re[NC], im[NC];
 #pragma unroll
         for (int ic = 0; ic < NC; ++ic) {
             const int c = comps[ic];
             span[ic] = spans_axis(c) ? -1 : 0;
-            ob[ic] = 2 * orient_of(c, dir) * wrap;
-            re[ic][0] = im[ic][0] = re[ic][1] = im[ic][1] = 0.0;
+            ob[ic] = orient_of(c, dir) * wrap;
+            re[ic] = im[ic] = 0.0;
         }
         auto sum = [&](const double2& b) {
             const int dx = xb - xa;
 #pragma unroll
             for (int ic = 0; ic < NC; ++ic) {
-                const int o = ob[ic] + xa + (dx & span[ic]);
-#pragma unroll
-                for (int kind = 0; kind < 2; ++kind) {
-                    const double2 a = os[o + kind * wrap];
-                    re[ic][kind] += a.x * b.x - a.y * b.y;
-                    im[ic][kind] += a.x * b.y + a.y * b.x;
-                }
+                const double2 a = os[ob[ic] + xa + (dx & span[ic])];
+                re[ic] += a.x * b.x - a.y * b.y;
+                im[ic] += a.x * b.y + a.y * b.x;
             }
             xa += KC;
             xb += KC;
@@ -856,10 +859,7 @@ __global__ void __launch_bounds__(kMacThreads, 2) k_spec_mac(const EnsDesc* __re
             if (x0 + A + u < N) sum(b1[u]);
         if (!act || k0 + kk >= n12) continue;
 #pragma unroll
-        for (int ic = 0; ic < NC; ++ic)
-#pragma unroll
-            for (int kind = 0; kind < 2; ++kind)
-                F[(size_t)(2 * ic + kind) * fstep] = make_double2(f[ic][kind].x + re[ic][kind], f[ic][kind].y + im[ic][kind]);
+        for (int ic = 0; ic < NC; ++ic) F[(size_t)ic * fstep] = make_double2(f[ic].x + re[ic], f[ic].y + im[ic]);
     }
 }
 
@@ -1077,12 +1077,12 @@ hipError_t launch_spec_mac(const EnsDesc* d_ens, const int* d_bstart, int n_ens,
                            const double2* sph, const double2* spo, double2* facc, hipStream_t st)
 {
     if (total_blocks <= 0) return hipSuccess;
-    const dim3 gr(total_blocks), bl(kMacThreads);
+    const dim3 gr((total_blocks + 7) / 8 * 16), bl(kMacThreads);
     const size_t lds = spec_mac_lds(npm);
 #define U1ML_MAC(NC)                                                                                                   \
     case NC:                                                                                                           \
         hipLaunchKernelGGL(k_spec_mac<NC>, gr, bl, lds, st, d_ens, d_bstart, n_ens, d_obs, d_r, d_comp, d_gdesc, sph,  \
-                           spo, facc);                                                                                 \
+                           spo, facc, total_blocks);                                                                   \
         break;
     switch (n_comp) {
         case 0: return hipSuccess;

@@ -2015,7 +2015,7 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         int lds_max = 0;
         hipError_t ea = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device);
         const size_t dft_lds = P.spectral ? plane_lds(c->spec_n12max, c->spec_npm) : 0;
-        const size_t mac_lds = P.spectral ? spec_mac_lds(c->spec_npm) : 0;
+        const size_t mac_lds = P.spectral ? 2 * spec_mac_lds(c->spec_npm) : 0;  // both kinds: the form's limit on the extents
         const size_t slab_bytes = *std::max_element(P.slab_lds_bytes, P.slab_lds_bytes + 3);
         const size_t need = std::max({c->con_lds, c->ins_lds, dft_lds, mac_lds, slab_bytes});
         if (ea != hipSuccess || (size_t)lds_max < need) {

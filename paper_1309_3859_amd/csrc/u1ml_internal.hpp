@@ -308,11 +308,11 @@ hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_en
                              int n12max, int npm, const ObsDesc* d_obs, const int* d_r, const double2* cpl,
                              const void* opl, const double2* gf, double2* sph, double2* spo, int precision, int tile,
                              hipStream_t st);
-// spectral sums: work-groups of kMacThreads per (axis, slab, probe group, kMacK values of k);
-// dynamic LDS spec_mac_lds(largest extent)
+// spectral sums: work-groups of kMacThreads per (axis, slab, probe group, kMacK values of k), the
+// total_blocks of d_bstart, and kind; dynamic LDS spec_mac_lds(largest extent)
 constexpr int kMacK = 8;
 constexpr int kMacThreads = 192;
-inline size_t spec_mac_lds(int npm) { return (size_t)12 * npm * kMacK * 16; }
+inline size_t spec_mac_lds(int npm) { return (size_t)6 * npm * kMacK * 16; }
 hipError_t launch_spec_mac(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int npm, int n_comp,
                            const ObsDesc* d_obs, const int* d_r, const int* d_comp, const int* d_gdesc,
                            const double2* sph, const double2* spo, double2* facc, hipStream_t st);
