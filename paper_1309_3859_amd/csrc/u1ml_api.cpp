@@ -1296,8 +1296,8 @@ hipError_t upload_lane(const Lane& L)
 
 // Splits the batch into nl lanes of about equal volume (largest ensembles
 // first, each to the lane with the least volume so far; a lane keeps the
-// problem order), builds and uploads their tables.  Lanes past nl are
-// emptied; their device areas stay reserved.
+// problem order), builds and uploads their tables.  Lanes past nl, and with
+// nl = 1 all of them, are emptied; their device areas stay reserved.
 hipError_t split_lanes(u1ml_ctx* c, int nl)
 {
     // streams as they are needed: the runtime maps streams to a few hardware
@@ -1328,7 +1328,7 @@ hipError_t split_lanes(u1ml_ctx* c, int nl)
         if (L.g_sweep) (void)hipGraphExecDestroy(L.g_sweep);
         if (L.g_ml) (void)hipGraphExecDestroy(L.g_ml);
         L.g_sweep = L.g_ml = nullptr;
-        L.idx = l < nl ? parts[l] : std::vector<int>();
+        L.idx = nl > 1 && l < nl ? parts[l] : std::vector<int>();  // one lane: the whole-batch lane runs, with its own tables
         std::sort(L.idx.begin(), L.idx.end());
         L.n = (int)L.idx.size();
         L.h_ens.clear();
