@@ -1244,7 +1244,7 @@ hipError_t launch_combine(const EnsDesc* d_ens, const int* d_bstart, int n_ens, 
 //                    only) and sum_S B(S) W_S 2^-E (insertions) to
 //                    double-double accumulators; a fixed-order tree reduces the
 //                    work-group into part[wg][26][hi, lo];
-//   k_product_final: the chunks of each (e, r, probe) in chunk order.
+//   k_product_final: the chunks of each (e, r, probe) and quantity by one wave.
 // src_t  = A * scale_t, src_to = B * scale_t (scale_t = 1 or 1/n_outer).
 // Bound by memory: B is read once (24^3 x 8, 11 separations, 10 probes, 6
 // components: 1.26 GB).  The loads of a slab's components are issued together
@@ -1323,20 +1323,24 @@ __global__ void __launch_bounds__(256) k_prod_exp(const EnsDesc* __restrict__ en
     if (threadIdx.x == 0) part[(size_t)blockIdx.x * kProdQ * 2] = (double)sh[0];
 }
 
-// one work-item per (e, r)
+// One wave per (e, r), its lanes sharing the chunks (one work-item per (e, r)
+// walked them at one memory latency each: 786 us for the 2048 chunks of 128^3 x 16, now 8 us)
 __global__ void __launch_bounds__(64) k_prod_exp_final(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart,
                                                        int n_ens, const ObsDesc* __restrict__ obs, int n_pgroups,
                                                        const double* __restrict__ part, double* __restrict__ results,
                                                        const int* __restrict__ ring)
 {
     const ObsDesc& O = *obs;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_ens * O.n_r) return;
-    const int e = i / O.n_r, ir = i % O.n_r;
+    const int e = blockIdx.x / O.n_r, ir = blockIdx.x % O.n_r;
+    if (e >= n_ens) return;
     const EnsDesc& E = ens[e];
     const int b0 = bstart[e] + ir * n_pgroups * E.prod_nch;  // probe group 0
     int emax = kNoExp;
-    for (int c = 0; c < E.prod_nch; ++c) emax = max(emax, (int)part[(size_t)(b0 + c) * kProdQ * 2]);
+#pragma unroll 4
+    for (int c = threadIdx.x; c < E.prod_nch; c += 64) emax = max(emax, (int)part[(size_t)(b0 + c) * kProdQ * 2]);
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) emax = max(emax, __shfl_xor(emax, w));
+    if (threadIdx.x != 0) return;
     record_of(E, O, results, ring)[O.n_doubles_per_config - O.n_r + ir] = emax == kNoExp ? 0.0 : (double)emax;
 }
 
@@ -1434,39 +1438,35 @@ __global__ void __launch_bounds__(256, 2) k_product(const EnsDesc* __restrict__ 
     }
 }
 
-// One work-item per (e, r, probe group, quantity): the chunk partials in
-// chunk order, normalised and written to the configuration's result row.
+// One wave per (e, r, probe group, quantity): lane l adds the partials of
+// chunks l, l + 64, ... in order, the lanes then add by a fixed tree; the sum
+// is normalised and written to the configuration's result row.
 __global__ void __launch_bounds__(64) k_product_final(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart,
                                                       int n_ens, const ObsDesc* __restrict__ obs, int n_pgroups,
                                                       const double* __restrict__ part, double* __restrict__ results,
                                                       const int* __restrict__ ring, int with_ins)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x;
     const ObsDesc& O = *obs;
     const int n_r = O.n_r;
-    if (i >= n_ens * n_r * n_pgroups * kProdQ) return;
     const int q = i % kProdQ;
     const int p = (i / kProdQ) % n_pgroups;
     const int ir = (i / (kProdQ * n_pgroups)) % n_r;
     const int e = i / (kProdQ * n_pgroups * n_r);
+    if (e >= n_ens) return;
     const EnsDesc& E = ens[e];
     const int nc = O.n_comp;
     if (q < 2 && p != 0) return;
     if (q >= 2 && (!with_ins || O.n_probe == 0 || q - 2 >= 4 * nc)) return;
     const int b0 = bstart[e] + (ir * n_pgroups + p) * E.prod_nch;
-    // chunks added in order; the loads of eight chunks are issued before their additions
     dd a{0.0, 0.0};
     const double* src = part + ((size_t)b0 * kProdQ + q) * 2;
     constexpr size_t cs = (size_t)kProdQ * 2;
-    int c = 0;
-    for (; c + 8 <= E.prod_nch; c += 8) {
-        double2 v[8];
+#pragma unroll 4
+    for (int c = threadIdx.x; c < E.prod_nch; c += 64) a = dd_add(a, dd{src[c * cs], src[c * cs + 1]});
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = make_double2(src[(c + u) * cs], src[(c + u) * cs + 1]);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) a = dd_add(a, dd{v[u].x, v[u].y});
-    }
-    for (; c < E.prod_nch; ++c) a = dd_add(a, dd{src[c * cs], src[c * cs + 1]});
+    for (int w = 32; w > 0; w >>= 1) a = dd_add(a, dd{__shfl_xor(a.hi, w), __shfl_xor(a.lo, w)});
+    if (threadIdx.x != 0) return;
     double* out = record_of(E, O, results, ring);
     const double nC = 1.0 / ((double)E.nsig * O.n_dirs);
     if (q < 2) {
@@ -1484,9 +1484,8 @@ hipError_t launch_prod_exp(const EnsDesc* d_ens, const int* d_bstart, int n_ens,
 {
     hipLaunchKernelGGL(k_prod_exp, dim3(total_blocks), dim3(256), 0, st, d_ens, d_bstart, n_ens, d_obs, n_pgroups,
                        src_t, use_outer, scale, part);
-    const int ne = n_ens * n_r;
-    hipLaunchKernelGGL(k_prod_exp_final, dim3((ne + 63) / 64), dim3(64), 0, st, d_ens, d_bstart, n_ens, d_obs,
-                       n_pgroups, part, results, d_ring);
+    hipLaunchKernelGGL(k_prod_exp_final, dim3(n_ens * n_r), dim3(64), 0, st, d_ens, d_bstart, n_ens, d_obs, n_pgroups,
+                       part, results, d_ring);
     return hipGetLastError();
 }
 
@@ -1500,9 +1499,8 @@ hipError_t launch_product(const EnsDesc* d_ens, const int* d_bstart, int n_ens, 
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_product, dim3(total_blocks), dim3(256), 0, st, d_ens, d_bstart, n_ens, d_obs, n_pgroups,
                        src_t, src_to, use_outer, scale, part, results, d_ring);
-    const int nq = n_ens * n_r * n_pgroups * kProdQ;
-    hipLaunchKernelGGL(k_product_final, dim3((nq + 63) / 64), dim3(64), 0, st, d_ens, d_bstart, n_ens, d_obs, n_pgroups,
-                       part, results, d_ring, src_to != nullptr ? 1 : 0);
+    hipLaunchKernelGGL(k_product_final, dim3(n_ens * n_r * n_pgroups * kProdQ), dim3(64), 0, st, d_ens, d_bstart, n_ens,
+                       d_obs, n_pgroups, part, results, d_ring, src_to != nullptr ? 1 : 0);
     return hipGetLastError();
 }
 
