@@ -121,7 +121,7 @@ struct Problem {
     bool pair_on[kPairClasses] = {};
     int pair_block[kPairClasses] = {};
     std::vector<PairTile> pair_tile[kPairClasses];
-    std::vector<PairRow> pair_rows;
+    int n_pair_rows = 0;
     std::map<std::array<int, 15>, int> pair_shape;  // shape -> first row
 
     // whole sweeps in LDS (k_slab), per class full / inner tau / outer tau: on, work-group size, LDS, work-groups
@@ -411,18 +411,15 @@ PairTile pair_tile(const PairGeo& G, double share, int max_threads, double* wave
 {
     PairTile best;
     double best_cost = 1e300;
-    for (int ly = 1; ly <= std::min(G.N[0], 64); ++ly)
-        for (int lz = 1; lz <= std::min(G.N[1], 64); ++lz)
-            for (int lt = G.masked ? G.N[2] : 1; lt <= std::min(G.N[2], 64); ++lt) {
+    const int cap = max_threads / G.nxh, lt0 = G.masked ? G.N[2] : 1;  // rows of a work-group
+    for (int ly = 1; ly <= std::min({G.N[0], 64, cap}); ++ly)
+        for (int lz = 1; lz <= std::min({G.N[1], 64, cap / ly}); ++lz)
+            for (int lt = lt0; lt <= std::min({G.N[2], 64, cap / (ly * lz)}); ++lt) {
                 const int L[3] = {ly, lz, lt};
-                const long long core = (long long)ly * lz * lt;
-                if (core * G.nxh > max_threads) break;
-                long long rows = core, tiles = G.slabs;
-                for (int k = 0; k < 3; ++k) {
-                    if (G.halo(k, L[k])) rows += 2 * core / L[k];
-                    tiles *= (G.N[k] + L[k] - 1) / L[k];
-                }
-                if (rows * G.nxh > max_threads) continue;
+                if (G.rows(L) > cap) continue;
+                long long tiles = G.slabs;
+                for (int k = 0; k < 3; ++k) tiles *= (G.N[k] + L[k] - 1) / L[k];
+                const int core = ly * lz * lt, rows = G.rows(L);
                 const double w1 = (double)((rows * G.nxh + 63) / 64), w2 = (double)((core * G.nxh + 63) / 64);
                 const double lat = std::ceil((double)tiles / share / 256) * std::max(1.0, w1 / 4);
                 const double thr = (double)tiles / share * (w1 + w2) / 2 / 1024;
@@ -437,15 +434,9 @@ PairTile pair_tile(const PairGeo& G, double share, int max_threads, double* wave
     return best;
 }
 
-// The rows of the tile with origin o (y, z, t) and core L; returns the first
-// row's index in the table.
-int pair_rows(Problem* P, const PairGeo& G, const int* o, const int* L)
+// The rows of the tile with origin o (y, z, t) and core L.
+void pair_rows(const PairGeo& G, int word, const int* o, const int* L, PairRow* rows)
 {
-    const std::array<int, 15> key = G.shape(o, L);
-    auto it = P->pair_shape.find(key);
-    if (it != P->pair_shape.end()) return it->second;
-    const int word = P->precision == U1ML_FP64 ? 8 : 4;
-    const int first = (int)P->pair_rows.size();
     int halo[3], n = L[0] * L[1] * L[2];  // first halo row of axis k: the faces below, then the faces above
     for (int k = 0; k < 3; ++k) {
         halo[k] = n;
@@ -459,7 +450,10 @@ int pair_rows(Problem* P, const PairGeo& G, const int* o, const int* L)
     // byte offset from the origin of the row displaced by d, and one step further along axis k
     auto offset = [&](const int* d, int k, int step) {
         int c[3];
-        for (int a = 0; a < 3; ++a) c[a] = (o[a] + d[a] + (a == k ? step : 0) + 2 * G.ext[a]) % G.ext[a] - o[a];
+        for (int a = 0; a < 3; ++a) {  // at most two steps past either end, extents are at least 2
+            const int x = o[a] + d[a] + (a == k ? step : 0);
+            c[a] = (x < 0 ? x + G.ext[a] : x >= G.ext[a] ? x - G.ext[a] : x) - o[a];
+        }
         return word * G.nxh * (c[0] + G.ext[0] * (c[1] + G.ext[1] * c[2]));
     };
     auto fill = [&](PairRow* r, const int* d) {
@@ -469,8 +463,6 @@ int pair_rows(Problem* P, const PairGeo& G, const int* o, const int* L)
         r->p3 = offset(d, 2, 1), r->m3 = offset(d, 2, -1);
         r->par = (d[0] + d[1] + d[2]) & 1;
     };
-    P->pair_rows.resize(first + n, PairRow{});
-    PairRow* rows = &P->pair_rows[first];
     int i[3];
     for (i[2] = 0; i[2] < L[2]; ++i[2])
         for (i[1] = 0; i[1] < L[1]; ++i[1])
@@ -501,8 +493,6 @@ int pair_rows(Problem* P, const PairGeo& G, const int* o, const int* L)
                     *lds[k] = code[1] << 16 | code[0];
                 }
             }
-    P->pair_shape[key] = first;
-    return first;
 }
 
 // Every tile of ensemble k in class cls: f(origin, core extents), time
@@ -606,13 +596,33 @@ void plan_pairs(Problem* P)
         const double t_one = 1.9 + 2 * 0.55 * std::max(lat, one / 1024), t_two = 2 * (1.9 + 0.4 * std::max(1.0, two / 1024));
         P->pair_on[cls] = ok && t_one < 0.9 * t_two;
     }
-    P->pair_rows.clear();
+    P->n_pair_rows = 0;
     P->pair_shape.clear();
     for (int cls = 0; cls < kPairClasses; ++cls)
         for (int k = 0; P->pair_on[cls] && k < P->n_ens; ++k) {
             const PairGeo G(P->ens[k], cls, P->pair_tau(cls));
-            pair_for_tiles(*P, cls, k, [&](const int* o, const int* L) { pair_rows(P, G, o, L); });
+            pair_for_tiles(*P, cls, k, [&](const int* o, const int* L) {
+                if (P->pair_shape.try_emplace(G.shape(o, L), P->n_pair_rows).second) P->n_pair_rows += G.rows(L);
+            });
         }
+}
+
+// the row table of the shapes that plan_pairs found
+std::vector<PairRow> build_pair_rows(const Problem& P)
+{
+    std::vector<PairRow> rows(P.n_pair_rows, PairRow{});
+    const int word = P.precision == U1ML_FP64 ? 8 : 4;
+    int next = 0;  // shapes come in the order of their first rows
+    for (int cls = 0; cls < kPairClasses; ++cls)
+        for (int k = 0; P.pair_on[cls] && k < P.n_ens; ++k) {
+            const PairGeo G(P.ens[k], cls, P.pair_tau(cls));
+            pair_for_tiles(P, cls, k, [&](const int* o, const int* L) {
+                if (P.pair_shape.at(G.shape(o, L)) != next) return;
+                pair_rows(G, word, o, L, &rows[next]);
+                next += G.rows(L);
+            });
+        }
+    return rows;
 }
 
 bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::string* err)
@@ -835,7 +845,7 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
     Lo->bmap_stride = blocks64;
     Lo->s_bmap = take(sizeof(UpdBlock) * kUpdateClasses * blocks64);
     Lo->s_mmap = take(sizeof(MeasBlock) * mblocks);
-    Lo->s_prow = take(sizeof(PairRow) * P.pair_rows.size());
+    Lo->s_prow = take(sizeof(PairRow) * P.n_pair_rows);
     size_t pair_bytes[kPairClasses] = {};
     for (int cls = 0; cls < kPairClasses; ++cls) {
         size_t blocks = kXcds;  // padding of the XCD-aware block order
@@ -2039,7 +2049,8 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
     up(c->d_pgroup, P.pgroup.data(), sizeof(int) * P.pgroup.size());
     up(c->d_gdesc, P.gdesc.data(), sizeof(int) * P.gdesc.size());
     up(c->d_pblk, P.pblk.data(), sizeof(int) * P.pblk.size());
-    up(c->d_prow, P.pair_rows.data(), sizeof(PairRow) * P.pair_rows.size());
+    const std::vector<PairRow> prow = build_pair_rows(P);
+    up(c->d_prow, prow.data(), sizeof(PairRow) * prow.size());
     up(c->d_upd, zeros.data(), sizeof(uint32_t) * n);
     if (st == U1ML_OK) {
         hipError_t e = upload_lane(c->whole);
