@@ -310,7 +310,8 @@ typedef struct {
 } u1ml_tune_report;
 u1ml_status u1ml_autotune(u1ml_ctx* ctx, u1ml_tune_report* report);
 
-/* Sets the update kernels' work-group size (64, 128, 256, 512 or 1024). */
+/* Sets the work-group size (64, 128, 256, 512 or 1024) of update launches of
+ * one phase; launches of both parities and of whole sweeps have their own. */
 u1ml_status u1ml_set_block(u1ml_ctx* ctx, int block);
 
 /* Synchronises.  n_lanes = 2, 3 or 4 runs u1ml_sweeps and u1ml_multilevel
