@@ -1101,7 +1101,9 @@ void build_update_tabs(const u1ml_ctx* c, Lane& L)
             // walked as they lie.
             const int plane = E.nxh * E.ny, word = P.precision == U1ML_FP64 ? 8 : 4;
             const bool grouped = plane % c->block == 0;
-            const int step = std::max(1, (1 << 20) / (E.nt * c->block * 8 * word)) * c->block;
+            // (a step's bytes reach 2^32 where long time extents meet planes smaller than a work-group)
+            const long long bytes = (long long)E.nt * c->block * 8 * word;
+            const int step = (int)std::max(1ll, (1 << 20) / bytes) * c->block;
             const int group = grouped ? std::min(step, plane) : r.slice;
             const int nz = grouped ? E.nz : 1, width = grouped ? plane : r.slice;
             for (int g0 = 0; g0 < width; g0 += group)

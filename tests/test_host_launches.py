@@ -1,0 +1,32 @@
+"""libu1ml's host side on the CPU (tests/helpers/host_hip.py): contexts of
+problems at the ends of the accepted range, and what their calls launch."""
+import pytest
+
+from helpers import host_hip
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    return host_hip.build(tmp_path_factory.mktemp("host_hip"))
+
+
+@pytest.mark.parametrize("ns,nt,precision,block", [((2, 2, 2), 262144, 0, 256), ((2, 2, 2), 65536, 0, 1024),
+                                                   ((2, 2, 2), 524288, 1, 256), ((64, 4, 2), 131072, 1, 1024),
+                                                   ((64, 8, 2), 65536, 0, 256)])
+def test_long_time_extents(so, ns, nt, precision, block):
+    """Bytes of a stretch of every time slice reach 2^32 (with planes that are
+    whole work-groups and with ones that are not): the tables are built, and a
+    phase covers every link."""
+    (grid,) = host_hip.run(so, f"""
+ctx = make(u1.Spec(ensembles=[u1.Ens({ns}, {nt}, 1.0)], levels=[(2, 1, 1)], r=[1], precision={precision}))
+ok(L.u1ml_set_block(ctx, {block}))
+ok(L.u1ml_init_links(ctx, u1.HOT))
+launches()
+ok(L.u1ml_phase(ctx, u1.OVERRELAX, 3, 0, 0, 0))
+(l,) = launches()
+assert l[0] == "k_update" and l[2][0] == {block}, l
+put(l[1][0])
+ok(L.u1ml_destroy(ctx))
+""")
+    links = ns[0] // 2 * ns[1] * ns[2] * nt
+    assert grid * block >= links
