@@ -23,6 +23,7 @@ static thread_local Dim3 t_grid, t_block;
 static thread_local size_t t_lds;
 static thread_local void* t_stream;
 static uintptr_t g_handle = 0x1000;
+static int g_error;
 
 static int handle(void** out)
 {
@@ -62,7 +63,7 @@ int hipLaunchKernel(const void* f, Dim3 g, Dim3 b, void**, size_t lds, void*)
     const uint64_t limit = 1ull << 32;  // work-items along an axis
     if (!g.x || !g.y || !g.z || g.x * (uint64_t)b.x >= limit || g.y > 65535u || g.z > 65535u ||
         b.x * (uint64_t)b.y * b.z > 1024 || lds > 160 * 1024)
-        return 9;  // hipErrorInvalidConfiguration
+        return g_error = 9;  // hipErrorInvalidConfiguration
     g_log.push_back(Launch{g_names[f].c_str(), {g.x, g.y, g.z}, {b.x, b.y, b.z}, lds});
     return 0;
 }
@@ -80,7 +81,12 @@ int hipGetDevice(int* d)
     *d = 0;
     return 0;
 }
-int hipGetLastError() { return 0; }
+int hipGetLastError()
+{
+    const int e = g_error;
+    g_error = 0;
+    return e;
+}
 const char* hipGetErrorString(int e) { return e == 9 ? "invalid configuration argument" : "error"; }
 int hipGetSymbolAddress(void** p, const void*) { return handle(p); }
 int hipMalloc(void** p, size_t) { return handle(p); }
