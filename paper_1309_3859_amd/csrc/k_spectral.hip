@@ -869,15 +869,79 @@ __global__ void __launch_bounds__(kMacThreads, 3) k_spec_mac(const EnsDesc* __re
 //   CO = scale sum_axis 1/(n1 n2) sum_k1 e^(2 pi i k1 p1/n1) A(k1, p2),
 //   A(k1, v) = sum_k2 F(k1, k2) e^(2 pi i k2 v/n2),  F(k) = sum_s F[axis][s][r][c][kind][g][k],
 // scale = 1/(N_sigma |M| N_t n_o n_i).  Each of the three sums runs in double-
-// double in ascending order; F and A are held in LDS as doubles, so a value
-// is rounded fewer times than its terms are.
+// double in ascending order, its products with the twiddles exact, and F and A
+// are held as pairs (hi, lo): the rounding of the twiddles is all that differs
+// from the exact sum of the spectra.  A's rows replace F's in LDS as they are
+// formed, so the pairs take the space of one plane of each.
 //
 // A probe by itself needs n1 n2 terms of every slab; the slabs first, then
 // the rows, then the columns take n1 n2 (S + n2) per work-group and n1 per
 // probe: 48^3 x 12 with 441 probes and 19 separations 13 million terms
-// instead of 600 million, 3.44 ms before and 51 us now.
+// instead of 600 million, 3.44 ms before and 97 us now (57 us
+// with F and A rounded to one double each, 1.2 to 1.4 times the error).
 // ---------------------------------------------------------------------------
 constexpr int kFinalThreads = 512;
+constexpr int kFinalRow = 4;  // values of A per work-item and pass over the rows
+
+// hi + lo += b, hi the rounded running sum, lo the sum of its errors
+__device__ inline void pair_add(double& hi, double& lo, double b)
+{
+    const double s = hi + b, t = s - hi;
+    lo += (hi - (s - t)) + (b - t);
+    hi = s;
+}
+
+struct cpair {
+    double2 hi, lo;
+    // += f w, f = fh + fl; the products of fh exact
+    __device__ inline void add_mul(double2 fh, double2 fl, double2 w)
+    {
+        const double p0 = fh.x * w.x, p1 = fh.y * w.y, p2 = fh.x * w.y, p3 = fh.y * w.x;
+        pair_add(hi.x, lo.x, p0);
+        pair_add(hi.x, lo.x, -p1);
+        pair_add(hi.y, lo.y, p2);
+        pair_add(hi.y, lo.y, p3);
+        lo.x += (fma(fh.x, w.x, -p0) - fma(fh.y, w.y, -p1)) + (fl.x * w.x - fl.y * w.y);
+        lo.y += (fma(fh.x, w.y, -p2) + fma(fh.y, w.x, -p3)) + (fl.x * w.y + fl.y * w.x);
+    }
+    __device__ inline void norm()
+    {
+        const double x = hi.x + lo.x, y = hi.y + lo.y;
+        lo = make_double2(lo.x - (x - hi.x), lo.y - (y - hi.y));
+        hi = make_double2(x, y);
+    }
+};
+
+// A's rows from k1 = row0 on, n values in all (n <= U kFinalThreads), over F's
+template <int U>
+__device__ inline void final_rows(double2* Fh, double2* Fl, const double2* w, int n2, int row0, int n)
+{
+    cpair a[U];
+    int f[U], v[U], ph[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = min((int)threadIdx.x + u * kFinalThreads, n - 1), row = i / n2;
+        f[u] = (row0 + row) * n2;
+        v[u] = i - row * n2;
+        ph[u] = 0;
+        a[u] = cpair{make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+    }
+    for (int k2 = 0; k2 < n2; ++k2)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a[u].add_mul(Fh[f[u] + k2], Fl[f[u] + k2], w[ph[u]]);
+            ph[u] += v[u];
+            if (ph[u] >= n2) ph[u] -= n2;
+        }
+    __syncthreads();  // these rows of F have been read
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if ((int)threadIdx.x + u * kFinalThreads < n) {
+            a[u].norm();
+            Fh[f[u] + v[u]] = a[u].hi;
+            Fl[f[u] + v[u]] = a[u].lo;
+        }
+}
 
 __global__ void __launch_bounds__(kFinalThreads) k_spec_final(const EnsDesc* __restrict__ ens, int n_ens,
                                                               const ObsDesc* __restrict__ obs,
@@ -900,9 +964,9 @@ __global__ void __launch_bounds__(kFinalThreads) k_spec_final(const EnsDesc* __r
     int n12max = 0;
     for (int i = 0; i < O.n_dirs; ++i) n12max = max(n12max, nsig / extent(E, O.dirs[i]));
     const int npm = max(E.nx, max(E.ny, E.nz));
-    double2* F = reinterpret_cast<double2*>(lds_raw);
-    double2* A = F + n12max;
-    double2* w1 = A + n12max;
+    double2* Fh = reinterpret_cast<double2*>(lds_raw);
+    double2* Fl = Fh + n12max;
+    double2* w1 = Fl + n12max;
     double2* w2 = w1 + npm;
     const double scale = 1.0 / ((double)nsig * O.n_dirs * E.nt * n_meas_total);
     double* out = results + ((size_t)(*ring) * O.n_ens_total + E.res_index) * O.n_doubles_per_config + 2ll * R;
@@ -935,35 +999,36 @@ __global__ void __launch_bounds__(kFinalThreads) k_spec_final(const EnsDesc* __r
                     re = dds_add(re, v.x);
                     im = dds_add(im, v.y);
                 }
-                F[k] = make_double2(re.hi + re.lo, im.hi + im.lo);
+                Fh[k] = make_double2(re.hi, im.hi);
+                Fl[k] = make_double2(re.lo, im.lo);
             }
             __syncthreads();
-            for (int k = threadIdx.x; k < n12; k += kFinalThreads) {
-                const int k1 = k / n2, v = k - k1 * n2;
-                const double2* f = F + k1 * n2;
-                dds re{0.0, 0.0}, im{0.0, 0.0};
-                int ph = 0;
-                for (int k2 = 0; k2 < n2; ++k2) {
-                    const double2 c = cmul(f[k2], w2[ph]);
-                    re = dds_add(re, c.x);
-                    im = dds_add(im, c.y);
-                    ph += v;
-                    if (ph >= n2) ph -= n2;
+            // whole rows a pass (k_spec_mac's LDS holds extents up to 106)
+            const int rows = max(1, kFinalRow * kFinalThreads / n2);
+            for (int k1 = 0; k1 < n1; k1 += rows) {
+                const int n = min(rows, n1 - k1) * n2;
+                switch ((n - 1) / kFinalThreads) {
+                case 0: final_rows<1>(Fh, Fl, w2, n2, k1, n); break;
+                case 1: final_rows<2>(Fh, Fl, w2, n2, k1, n); break;
+                case 2: final_rows<3>(Fh, Fl, w2, n2, k1, n); break;
+                default: final_rows<kFinalRow>(Fh, Fl, w2, n2, k1, n); break;
                 }
-                A[k] = make_double2(re.hi + re.lo, im.hi + im.lo);
             }
             __syncthreads();
             if (!mine) continue;
-            const double inv = 1.0 / (double)n12;
             const int q1 = ((p1 % n1) + n1) % n1, q2 = ((p2 % n2) + n2) % n2;
+            cpair a{make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
             int ph = 0;
             for (int k1 = 0; k1 < n1; ++k1) {
-                const double2 c = cmul(A[k1 * n2 + q2], w1[ph]);
-                are = dds_add(are, c.x * inv);
-                aim = dds_add(aim, c.y * inv);
+                a.add_mul(Fh[k1 * n2 + q2], Fl[k1 * n2 + q2], w1[ph]);
                 ph += q1;
                 if (ph >= n1) ph -= n1;
             }
+            a.norm();
+            const double n = (double)n12;  // a / n as a pair: the quotient and its remainder's
+            const double qx = a.hi.x / n, qy = a.hi.y / n;
+            are = dds_add(dds_add(are, qx), (fma(-qx, n, a.hi.x) + a.lo.x) / n);
+            aim = dds_add(dds_add(aim, qy), (fma(-qy, n, a.hi.y) + a.lo.y) / n);
         }
         if (!mine) continue;
         const size_t idx = ((size_t)ir * Np + p) * Nc * 2 + ck;

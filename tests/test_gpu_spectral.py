@@ -217,3 +217,72 @@ def test_full_map_of_largest_preset_sampled(env):
     say("  sampled max |dCO|", d, "scale", scale)
     assert d < 2e-5 * scale
     assert np.max(np.abs(got["C"][pick_r] - want["C"])) < 1e-12
+
+
+@pytest.mark.parametrize("ns,dirs", [((4, 24, 24), [0]), ((6, 10, 14), [0, 2]), ((2, 64, 64), [0]), ((2, 2, 106), [0])],
+                         ids=["24x24", "two axes", "64x64", "2x106"])
+def test_probe_sums_round_no_more_than_term_by_term(env, ns, dirs):
+    """The estimates against their definition, the sum over slabs and over the
+    plane of the accumulated spectra F(k) e^{2 pi i k p}, read back from the
+    workspace and summed in extended precision: root-mean-square error over the
+    probes, no larger than that of the plain sum, every term formed in FP64
+    ((w1 w2) F / (n1 n2)) and added without error.  Slabs alike (links constant
+    in time), so that their spectra add up."""
+    u1, O, _ = env
+    LD, CLD = np.longdouble, np.clongdouble
+    nt, R, comps = 12, 1, [0, 3]
+    rng = np.random.default_rng(5)
+    p1s = range(1 - min((ns[(d + 1) % 3] + 1) // 2 for d in dirs), min((ns[(d + 1) % 3] + 1) // 2 for d in dirs))
+    p2s = range(1 - min((ns[(d + 2) % 3] + 1) // 2 for d in dirs), min((ns[(d + 2) % 3] + 1) // 2 for d in dirs))
+    probes = [(0, a, b, 1) for a in p1s for b in p2s]
+    if len(probes) > 300:
+        probes = [probes[i] for i in rng.choice(len(probes), 300, replace=False)]
+    spec = u1.Spec(ensembles=[u1.Ens(ns, nt, 1.0)], levels=[(2, 1, 0)], r=[1], dirs=dirs, probes=probes, comps=comps,
+                   precision=u1.FP64, form=u1.FORM_SPECTRAL)
+    ctx = u1.Context(spec)
+    nsig = ns[0] * ns[1] * ns[2]
+    ctx.set_links(np.tile(rng.uniform(-np.pi, np.pi, 4 * nsig), nt))
+    say("probe sums", ns, dirs, len(probes))
+    ctx.multilevel()
+    got = spec.unpack(ctx.results()[0][0])["CO_mant"][0]  # [probe, comp, kind]
+
+    pl, nd, S, nc = ctx.plan, len(dirs), nt // 2, len(comps)
+    up = lambda n: (n + 255) // 256 * 256
+    rest = sum(pl[k] for k in ("link_bytes", "history_bytes", "average_bytes", "outer_bytes", "result_bytes",
+                               "spectral_bytes", "scratch_bytes"))
+    second = pl["ws_bytes"] - rest  # the other link buffer, where sweeps use one
+    assert second in (0, pl["link_bytes"])
+    off = second + rest - pl["scratch_bytes"] - pl["spectral_bytes"]
+    off += up(16 * nd * R * S * nsig) + up(16 * nd * S * R * nsig) + up(16 * nd * S * 12 * nsig)  # G and the spectra
+    n12max = max(nsig // ns[d] for d in dirs)
+    size = nd * S * R * nc * 2 * n12max * 16
+    F = ctx.ws[off: off + size].cpu().numpy().view(np.complex128).reshape(nd, S, R, nc, 2, n12max)
+
+    exact = np.zeros((len(probes), nc, 2), CLD)
+    plain = np.zeros((len(probes), nc, 2), CLD)
+    turn = 2 * LD(np.arctan2(LD(0), LD(-1)))
+    for i, d in enumerate(dirs):
+        n1, n2 = ns[(d + 1) % 3], ns[(d + 2) % 3]
+        f = F[i, :, 0, :, :, : n1 * n2].reshape(S, nc, 2, n1, n2)
+        fs = f.sum(axis=0, dtype=CLD)
+        # the twiddles' arguments 2 j / n are formed in FP64, in the estimates as here
+        arg = lambda n: LD(0.5) * turn * (2.0 * np.arange(n) / n).astype(LD)
+        tw = lambda n: [np.cos(arg(n)).astype(np.float64), np.sin(arg(n)).astype(np.float64)]
+        t1, t2 = tw(n1), tw(n2)
+        for k, (_, a, b, _) in enumerate(probes):
+            j1, j2 = (np.arange(n1) * a) % n1, (np.arange(n2) * b) % n2
+            w1, w2 = t1[0][j1] + 1j * t1[1][j1], t2[0][j2] + 1j * t2[1][j2]
+            exact[k] += (fs * (w1.astype(CLD)[:, None] * w2[None, :])).sum(axis=(-2, -1)) / (n1 * n2)
+            w = w1[:, None] * w2[None, :]
+            inv = 1.0 / (n1 * n2)
+            t = np.empty(f.shape, np.complex128)
+            t.real = (f.real * w.real - f.imag * w.imag) * inv
+            t.imag = (f.real * w.imag + f.imag * w.real) * inv
+            plain[k] += t.sum(axis=(0, -2, -1), dtype=CLD)
+    scale = 1.0 / (float(nsig) * nd * nt * 1.0)
+    rms = lambda x: float(np.sqrt(np.mean(np.abs((x - exact * LD(scale)) / scale) ** 2)))
+    mine, ref = rms(got.astype(CLD)), rms(plain.astype(np.complex128) * scale)
+    norm = float(np.abs(F).sum() / (n12max * nc * 2))
+    say("  rms error / sum of |terms|: estimates", mine / norm, "term by term", ref / norm)
+    assert np.abs(got - exact.astype(np.complex128) * scale).max() < 1e-13 * norm * scale
+    assert mine <= ref
