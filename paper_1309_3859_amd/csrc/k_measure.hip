@@ -20,6 +20,7 @@
 // average in registers and writes it once.  Products over slabs are carried
 // as (mantissa, binary exponent) pairs so they cannot underflow, and all sums
 // over sites are double-double in a fixed order, so results are reproducible.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.hpp"
@@ -1438,43 +1439,44 @@ __global__ void __launch_bounds__(256, 2) k_product(const EnsDesc* __restrict__ 
     }
 }
 
-// One wave per (e, r, probe group, quantity): lane l adds the partials of
+// One wave per (e, r, probe group, quantity) sum: lane l adds the partials of
 // chunks l, l + 64, ... in order, the lanes then add by a fixed tree; the sum
-// is normalised and written to the configuration's result row.
+// is normalised and written to the configuration's result row.  A launch has
+// at most kMaxGrid waves (a grid holds 2^32 work-items), which then take
+// several sums each.
 __global__ void __launch_bounds__(64) k_product_final(const EnsDesc* __restrict__ ens, const int* __restrict__ bstart,
-                                                      int n_ens, const ObsDesc* __restrict__ obs, int n_pgroups,
+                                                      unsigned n_sums, const ObsDesc* __restrict__ obs, int n_pgroups,
                                                       const double* __restrict__ part, double* __restrict__ results,
                                                       const int* __restrict__ ring, int with_ins)
 {
-    const int i = blockIdx.x;
     const ObsDesc& O = *obs;
-    const int n_r = O.n_r;
-    const int q = i % kProdQ;
-    const int p = (i / kProdQ) % n_pgroups;
-    const int ir = (i / (kProdQ * n_pgroups)) % n_r;
-    const int e = i / (kProdQ * n_pgroups * n_r);
-    if (e >= n_ens) return;
-    const EnsDesc& E = ens[e];
-    const int nc = O.n_comp;
-    if (q < 2 && p != 0) return;
-    if (q >= 2 && (!with_ins || O.n_probe == 0 || q - 2 >= 4 * nc)) return;
-    const int b0 = bstart[e] + (ir * n_pgroups + p) * E.prod_nch;
-    dd a{0.0, 0.0};
-    const double* src = part + ((size_t)b0 * kProdQ + q) * 2;
-    constexpr size_t cs = (size_t)kProdQ * 2;
+    const int n_r = O.n_r, nc = O.n_comp;
+    for (unsigned i = blockIdx.x; i < n_sums; i += gridDim.x) {
+        const int q = (int)(i % kProdQ);
+        const int p = (int)((i / kProdQ) % (unsigned)n_pgroups);
+        const int ir = (int)((i / (unsigned)(kProdQ * n_pgroups)) % (unsigned)n_r);
+        const int e = (int)(i / (unsigned)(kProdQ * n_pgroups) / (unsigned)n_r);
+        const EnsDesc& E = ens[e];
+        if (q < 2 && p != 0) continue;
+        if (q >= 2 && (!with_ins || O.n_probe == 0 || q - 2 >= 4 * nc)) continue;
+        const int b0 = bstart[e] + (ir * n_pgroups + p) * E.prod_nch;
+        dd a{0.0, 0.0};
+        const double* src = part + ((size_t)b0 * kProdQ + q) * 2;
+        constexpr size_t cs = (size_t)kProdQ * 2;
 #pragma unroll 4
-    for (int c = threadIdx.x; c < E.prod_nch; c += 64) a = dd_add(a, dd{src[c * cs], src[c * cs + 1]});
+        for (int c = threadIdx.x; c < E.prod_nch; c += 64) a = dd_add(a, dd{src[c * cs], src[c * cs + 1]});
 #pragma unroll
-    for (int w = 32; w > 0; w >>= 1) a = dd_add(a, dd{__shfl_xor(a.hi, w), __shfl_xor(a.lo, w)});
-    if (threadIdx.x != 0) return;
-    double* out = record_of(E, O, results, ring);
-    const double nC = 1.0 / ((double)E.nsig * O.n_dirs);
-    if (q < 2) {
-        out[2 * ir + q] = (a.hi + a.lo) * nC;
-    } else {
-        const int k = (q - 2) >> 1, im = (q - 2) & 1;
-        const long long idx = (((long long)ir * O.n_probe + p) * nc) * 2 + k;
-        out[2ll * n_r + 2 * idx + im] = (a.hi + a.lo) * (nC / (double)E.nt);
+        for (int w = 32; w > 0; w >>= 1) a = dd_add(a, dd{__shfl_xor(a.hi, w), __shfl_xor(a.lo, w)});
+        if (threadIdx.x != 0) continue;
+        double* out = record_of(E, O, results, ring);
+        const double nC = 1.0 / ((double)E.nsig * O.n_dirs);
+        if (q < 2) {
+            out[2 * ir + q] = (a.hi + a.lo) * nC;
+        } else {
+            const int k = (q - 2) >> 1, im = (q - 2) & 1;
+            const long long idx = (((long long)ir * O.n_probe + p) * nc) * 2 + k;
+            out[2ll * n_r + 2 * idx + im] = (a.hi + a.lo) * (nC / (double)E.nt);
+        }
     }
 }
 
@@ -1499,8 +1501,10 @@ hipError_t launch_product(const EnsDesc* d_ens, const int* d_bstart, int n_ens, 
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_product, dim3(total_blocks), dim3(256), 0, st, d_ens, d_bstart, n_ens, d_obs, n_pgroups,
                        src_t, src_to, use_outer, scale, part, results, d_ring);
-    hipLaunchKernelGGL(k_product_final, dim3(n_ens * n_r * n_pgroups * kProdQ), dim3(64), 0, st, d_ens, d_bstart, n_ens,
-                       d_obs, n_pgroups, part, results, d_ring, src_to != nullptr ? 1 : 0);
+    // (fewer than k_product's work-items, which are below 2^32)
+    const unsigned n_sums = (unsigned)n_ens * (unsigned)n_r * (unsigned)n_pgroups * kProdQ;
+    hipLaunchKernelGGL(k_product_final, dim3(std::min(n_sums, kMaxGrid)), dim3(64), 0, st, d_ens, d_bstart, n_sums, d_obs,
+                       n_pgroups, part, results, d_ring, src_to != nullptr ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -21,6 +21,8 @@
 // (axis, slab, r, component, kind, probe group); the probes' displacements
 // are read off once per configuration.  Memory is independent of the number
 // of probes.
+#include <algorithm>
+
 #include "device_common.hpp"
 #include "scaled.hpp"
 #include "u1ml_internal.hpp"
@@ -748,13 +750,13 @@ __global__ void __launch_bounds__(kMacThreads, 3) k_spec_mac(const EnsDesc* __re
                                                              const int* __restrict__ rlist, const int* __restrict__ comps,
                                                              const int* __restrict__ gdesc, const double2* __restrict__ sph,
                                                              const double2* __restrict__ spo, double2* __restrict__ facc,
-                                                             int n_tiles)
+                                                             int tile0, int n_tiles)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     double2* os = reinterpret_cast<double2*>(lds_raw);  // [orientation][x_par][kk]
     constexpr int KC = kMacK, A = kMacAhead;
     // the two kinds of a tile eight work-groups apart: the same XCD, whose L2 then holds the T spectra for both
-    const int kind = (blockIdx.x >> 3) & 1, tile = (int)(blockIdx.x & 7u) + (int)(blockIdx.x >> 4) * 8;
+    const int kind = (blockIdx.x >> 3) & 1, tile = tile0 + (int)(blockIdx.x & 7u) + (int)(blockIdx.x >> 4) * 8;
     if (tile >= n_tiles) return;  // uniform: padding of the launch to a multiple of 16
     const int e = find_ens_s(bstart, n_ens, tile);
     const EnsDesc& E = ens[e];
@@ -865,7 +867,8 @@ __global__ void __launch_bounds__(kMacThreads, 3) k_spec_mac(const EnsDesc* __re
 
 // ---------------------------------------------------------------------------
 // Probe estimates of the configuration.  Work-group per (ensemble, r,
-// component, kind, probe group); its probes p have
+// component, kind, probe group) sum, several of them where that is more than
+// kMaxGrid; its probes p have
 //   CO = scale sum_axis 1/(n1 n2) sum_k1 e^(2 pi i k1 p1/n1) A(k1, p2),
 //   A(k1, v) = sum_k2 F(k1, k2) e^(2 pi i k2 v/n2),  F(k) = sum_s F[axis][s][r][c][kind][g][k],
 // scale = 1/(N_sigma |M| N_t n_o n_i).  Each of the three sums runs in double-
@@ -877,7 +880,7 @@ __global__ void __launch_bounds__(kMacThreads, 3) k_spec_mac(const EnsDesc* __re
 // A probe by itself needs n1 n2 terms of every slab; the slabs first, then
 // the rows, then the columns take n1 n2 (S + n2) per work-group and n1 per
 // probe: 48^3 x 12 with 441 probes and 19 separations 13 million terms
-// instead of 600 million, 3.44 ms before and 97 us now (57 us
+// instead of 600 million, 3.44 ms before and 90 us now (57 us
 // with F and A rounded to one double each, 1.2 to 1.4 times the error).
 // ---------------------------------------------------------------------------
 constexpr int kFinalThreads = 512;
@@ -943,7 +946,7 @@ __device__ inline void final_rows(double2* Fh, double2* Fl, const double2* w, in
         }
 }
 
-__global__ void __launch_bounds__(kFinalThreads) k_spec_final(const EnsDesc* __restrict__ ens, int n_ens,
+__global__ void __launch_bounds__(kFinalThreads) k_spec_final(const EnsDesc* __restrict__ ens, unsigned n_sums,
                                                               const ObsDesc* __restrict__ obs,
                                                               const int* __restrict__ probes,
                                                               const int* __restrict__ pgroup,
@@ -953,87 +956,87 @@ __global__ void __launch_bounds__(kFinalThreads) k_spec_final(const EnsDesc* __r
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const ObsDesc& O = *obs;
     const int R = O.n_r, Np = O.n_probe, Nc = O.n_comp, NG = O.n_groups;
-    int t = blockIdx.x;  // (((e R + ir) Nc + ic) 2 + kind) NG + g
-    const int g = t % NG;
-    t /= NG;
-    const int rck = t % (R * Nc * 2), e = t / (R * Nc * 2);
-    if (e >= n_ens) return;
-    const int ir = rck / (Nc * 2), ck = rck - ir * Nc * 2;
-    const EnsDesc& E = ens[e];
-    const int nsig = E.nsig, Si = E.s_in;
-    int n12max = 0;
-    for (int i = 0; i < O.n_dirs; ++i) n12max = max(n12max, nsig / extent(E, O.dirs[i]));
-    const int npm = max(E.nx, max(E.ny, E.nz));
-    double2* Fh = reinterpret_cast<double2*>(lds_raw);
-    double2* Fl = Fh + n12max;
-    double2* w1 = Fl + n12max;
-    double2* w2 = w1 + npm;
-    const double scale = 1.0 / ((double)nsig * O.n_dirs * E.nt * n_meas_total);
-    double* out = results + ((size_t)(*ring) * O.n_ens_total + E.res_index) * O.n_doubles_per_config + 2ll * R;
-    for (int p0 = 0; p0 < Np; p0 += kFinalThreads) {  // as many probes as work-items, usually all
-        const int p = p0 + (int)threadIdx.x;
-        const bool mine = p < Np && pgroup[min(p, Np - 1)] == g;
-        const int p1 = mine ? probes[4 * p + 1] : 0, p2 = mine ? probes[4 * p + 2] : 0;
-        dds are{0.0, 0.0}, aim{0.0, 0.0};
-        for (int id = 0; id < O.n_dirs; ++id) {
-            const int dir = O.dirs[id];
-            const int n1 = extent(E, dir == 2 ? 0 : dir + 1), n2 = extent(E, dir == 0 ? 2 : dir - 1), n12 = n1 * n2;
-            __syncthreads();  // the previous axis is done with the tables
-            for (int j = threadIdx.x; j < n1; j += kFinalThreads) {
-                double sn, cs;
-                sincospi(2.0 * (double)j / (double)n1, &sn, &cs);
-                w1[j] = make_double2(cs, sn);
-            }
-            for (int j = threadIdx.x; j < n2; j += kFinalThreads) {
-                double sn, cs;
-                sincospi(2.0 * (double)j / (double)n2, &sn, &cs);
-                w2[j] = make_double2(cs, sn);
-            }
-            const size_t sstep = (size_t)R * Nc * 2 * NG * n12max;  // from one slab to the next
-            const double2* Fg = facc + E.facc_off + ((((size_t)id * Si * R + ir) * Nc * 2 + ck) * NG + g) * n12max;
-            for (int k = threadIdx.x; k < n12; k += kFinalThreads) {
-                dds re{0.0, 0.0}, im{0.0, 0.0};
+    for (unsigned sum = blockIdx.x; sum < n_sums; sum += gridDim.x) {  // (((e R + ir) Nc + ic) 2 + kind) NG + g
+        const int g = (int)(sum % (unsigned)NG);
+        const unsigned t = sum / (unsigned)NG;
+        const int rck = (int)(t % (unsigned)(R * Nc * 2)), e = (int)(t / (unsigned)(R * Nc * 2));
+        const int ir = rck / (Nc * 2), ck = rck - ir * Nc * 2;
+        const EnsDesc& E = ens[e];
+        const int nsig = E.nsig, Si = E.s_in;
+        int n12max = 0;
+        for (int i = 0; i < O.n_dirs; ++i) n12max = max(n12max, nsig / extent(E, O.dirs[i]));
+        const int npm = max(E.nx, max(E.ny, E.nz));
+        double2* Fh = reinterpret_cast<double2*>(lds_raw);
+        double2* Fl = Fh + n12max;
+        double2* w1 = Fl + n12max;
+        double2* w2 = w1 + npm;
+        const double scale = 1.0 / ((double)nsig * O.n_dirs * E.nt * n_meas_total);
+        double* out = results + ((size_t)(*ring) * O.n_ens_total + E.res_index) * O.n_doubles_per_config + 2ll * R;
+        for (int p0 = 0; p0 < Np; p0 += kFinalThreads) {  // as many probes as work-items, usually all
+            const int p = p0 + (int)threadIdx.x;
+            const bool mine = p < Np && pgroup[min(p, Np - 1)] == g;
+            const int p1 = mine ? probes[4 * p + 1] : 0, p2 = mine ? probes[4 * p + 2] : 0;
+            dds are{0.0, 0.0}, aim{0.0, 0.0};
+            for (int id = 0; id < O.n_dirs; ++id) {
+                const int dir = O.dirs[id];
+                const int n1 = extent(E, dir == 2 ? 0 : dir + 1), n2 = extent(E, dir == 0 ? 2 : dir - 1), n12 = n1 * n2;
+                __syncthreads();  // the previous axis is done with the tables
+                for (int j = threadIdx.x; j < n1; j += kFinalThreads) {
+                    double sn, cs;
+                    sincospi(2.0 * (double)j / (double)n1, &sn, &cs);
+                    w1[j] = make_double2(cs, sn);
+                }
+                for (int j = threadIdx.x; j < n2; j += kFinalThreads) {
+                    double sn, cs;
+                    sincospi(2.0 * (double)j / (double)n2, &sn, &cs);
+                    w2[j] = make_double2(cs, sn);
+                }
+                const size_t sstep = (size_t)R * Nc * 2 * NG * n12max;  // from one slab to the next
+                const double2* Fg = facc + E.facc_off + ((((size_t)id * Si * R + ir) * Nc * 2 + ck) * NG + g) * n12max;
+                for (int k = threadIdx.x; k < n12; k += kFinalThreads) {
+                    dds re{0.0, 0.0}, im{0.0, 0.0};
 #pragma unroll 4
-                for (int s = 0; s < Si; ++s) {
-                    const double2 v = Fg[s * sstep + k];
-                    re = dds_add(re, v.x);
-                    im = dds_add(im, v.y);
+                    for (int s = 0; s < Si; ++s) {
+                        const double2 v = Fg[s * sstep + k];
+                        re = dds_add(re, v.x);
+                        im = dds_add(im, v.y);
+                    }
+                    Fh[k] = make_double2(re.hi, im.hi);
+                    Fl[k] = make_double2(re.lo, im.lo);
                 }
-                Fh[k] = make_double2(re.hi, im.hi);
-                Fl[k] = make_double2(re.lo, im.lo);
-            }
-            __syncthreads();
-            // whole rows a pass (k_spec_mac's LDS holds extents up to 106)
-            const int rows = max(1, kFinalRow * kFinalThreads / n2);
-            for (int k1 = 0; k1 < n1; k1 += rows) {
-                const int n = min(rows, n1 - k1) * n2;
-                switch ((n - 1) / kFinalThreads) {
-                case 0: final_rows<1>(Fh, Fl, w2, n2, k1, n); break;
-                case 1: final_rows<2>(Fh, Fl, w2, n2, k1, n); break;
-                case 2: final_rows<3>(Fh, Fl, w2, n2, k1, n); break;
-                default: final_rows<kFinalRow>(Fh, Fl, w2, n2, k1, n); break;
+                __syncthreads();
+                // whole rows a pass (k_spec_mac's LDS holds extents up to 106)
+                const int rows = max(1, kFinalRow * kFinalThreads / n2);
+                for (int k1 = 0; k1 < n1; k1 += rows) {
+                    const int n = min(rows, n1 - k1) * n2;
+                    switch ((n - 1) / kFinalThreads) {
+                    case 0: final_rows<1>(Fh, Fl, w2, n2, k1, n); break;
+                    case 1: final_rows<2>(Fh, Fl, w2, n2, k1, n); break;
+                    case 2: final_rows<3>(Fh, Fl, w2, n2, k1, n); break;
+                    default: final_rows<kFinalRow>(Fh, Fl, w2, n2, k1, n); break;
+                    }
                 }
+                __syncthreads();
+                if (!mine) continue;
+                const int q1 = ((p1 % n1) + n1) % n1, q2 = ((p2 % n2) + n2) % n2;
+                cpair a{make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+                int ph = 0;
+                for (int k1 = 0; k1 < n1; ++k1) {
+                    a.add_mul(Fh[k1 * n2 + q2], Fl[k1 * n2 + q2], w1[ph]);
+                    ph += q1;
+                    if (ph >= n1) ph -= n1;
+                }
+                a.norm();
+                const double n = (double)n12;  // a / n as a pair: the quotient and its remainder's
+                const double qx = a.hi.x / n, qy = a.hi.y / n;
+                are = dds_add(dds_add(are, qx), (fma(-qx, n, a.hi.x) + a.lo.x) / n);
+                aim = dds_add(dds_add(aim, qy), (fma(-qy, n, a.hi.y) + a.lo.y) / n);
             }
-            __syncthreads();
             if (!mine) continue;
-            const int q1 = ((p1 % n1) + n1) % n1, q2 = ((p2 % n2) + n2) % n2;
-            cpair a{make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
-            int ph = 0;
-            for (int k1 = 0; k1 < n1; ++k1) {
-                a.add_mul(Fh[k1 * n2 + q2], Fl[k1 * n2 + q2], w1[ph]);
-                ph += q1;
-                if (ph >= n1) ph -= n1;
-            }
-            a.norm();
-            const double n = (double)n12;  // a / n as a pair: the quotient and its remainder's
-            const double qx = a.hi.x / n, qy = a.hi.y / n;
-            are = dds_add(dds_add(are, qx), (fma(-qx, n, a.hi.x) + a.lo.x) / n);
-            aim = dds_add(dds_add(aim, qy), (fma(-qy, n, a.hi.y) + a.lo.y) / n);
+            const size_t idx = ((size_t)ir * Np + p) * Nc * 2 + ck;
+            out[2 * idx] = (are.hi + are.lo) * scale;
+            out[2 * idx + 1] = (aim.hi + aim.lo) * scale;
         }
-        if (!mine) continue;
-        const size_t idx = ((size_t)ir * Np + p) * Nc * 2 + ck;
-        out[2 * idx] = (are.hi + are.lo) * scale;
-        out[2 * idx + 1] = (aim.hi + aim.lo) * scale;
     }
 }
 
@@ -1142,24 +1145,26 @@ hipError_t launch_spec_mac(const EnsDesc* d_ens, const int* d_bstart, int n_ens,
                            const double2* sph, const double2* spo, double2* facc, hipStream_t st)
 {
     if (total_blocks <= 0) return hipSuccess;
-    const dim3 gr((total_blocks + 7) / 8 * 16), bl(kMacThreads);
     const size_t lds = spec_mac_lds(npm);
+    for (int t0 = 0; t0 < total_blocks; t0 += (int)kMaxGrid) {  // usually one
+        const dim3 gr((std::min(total_blocks - t0, (int)kMaxGrid) + 7) / 8 * 16), bl(kMacThreads);
 #define U1ML_MAC(NC)                                                                                                   \
     case NC:                                                                                                           \
         hipLaunchKernelGGL(k_spec_mac<NC>, gr, bl, lds, st, d_ens, d_bstart, n_ens, d_obs, d_r, d_comp, d_gdesc, sph,  \
-                           spo, facc, total_blocks);                                                                   \
-        break;
-    switch (n_comp) {
-        case 0: return hipSuccess;
-        U1ML_MAC(1)
-        U1ML_MAC(2)
-        U1ML_MAC(3)
-        U1ML_MAC(4)
-        U1ML_MAC(5)
-        U1ML_MAC(6)
-        default: return hipErrorInvalidValue;
-    }
+                           spo, facc, t0, total_blocks);                                                               \
+            break;
+        switch (n_comp) {
+            case 0: return hipSuccess;
+            U1ML_MAC(1)
+            U1ML_MAC(2)
+            U1ML_MAC(3)
+            U1ML_MAC(4)
+            U1ML_MAC(5)
+            U1ML_MAC(6)
+            default: return hipErrorInvalidValue;
+        }
 #undef U1ML_MAC
+    }
     return hipGetLastError();
 }
 
@@ -1169,8 +1174,9 @@ hipError_t launch_spec_final(const EnsDesc* d_ens, int n_ens, const ObsDesc* d_o
                              double n_meas_total, double* results, const int* d_ring, hipStream_t st)
 {
     if (n_sums <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_spec_final, dim3((unsigned)(n_sums * n_ens)), dim3(kFinalThreads), plane_lds(n12max, npm), st,
-                       d_ens, n_ens, d_obs, d_probe, d_pgroup, facc, n_meas_total, results, d_ring);
+    const unsigned all = (unsigned)(n_sums * n_ens);
+    hipLaunchKernelGGL(k_spec_final, dim3(std::min(all, kMaxGrid)), dim3(kFinalThreads), plane_lds(n12max, npm), st,
+                       d_ens, all, d_obs, d_probe, d_pgroup, facc, n_meas_total, results, d_ring);
     return hipGetLastError();
 }
 

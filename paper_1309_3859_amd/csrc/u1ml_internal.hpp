@@ -179,6 +179,8 @@ __host__ __device__ inline bool mf_chunk_fits(int mc, int N, int R, int nrows, i
            (size_t)mc * N * 2 * R <= (size_t)kMfT && nrows <= kMfRows && R <= kMfR;
 }
 
+constexpr unsigned kMaxGrid = 1u << 22;  // work-groups of a launch where the work can exceed a grid's 2^32 work-items
+
 constexpr int kUpdateClasses = 4;  // temporal, spatial full, spatial inner tau, spatial outer tau
 constexpr int kProdChunk = 1024;    // slab products: (axis, site) items per work-group
 constexpr int kProdQ = 26;          // slab products: correlator re, im and 12 insertion quantities re, im

@@ -30,3 +30,26 @@ ok(L.u1ml_destroy(ctx))
 """)
     links = ns[0] // 2 * ns[1] * ns[2] * nt
     assert grid * block >= links
+
+
+@pytest.mark.parametrize("kw", [dict(n=16384, form=1, r=[1, 2, 3], probes=126, comps=1),
+                                dict(n=16384, form=2, r=[1, 2, 3, 1], probes=14, comps=6),
+                                dict(n=3000, L=16, form=2, r=[1], probes=62, comps=1)])
+def test_many_sums(so, kw):
+    """Batches whose sums, a wave or a work-group each, are more than a grid
+    holds: estimates of many probes on thousands of small lattices."""
+    host_hip.run(so, f"""
+kw = {kw}
+N = kw.get("L", 4)
+probes = [(l, a, b, m) for l in range(1 - N, N) for m in (0, 1) for a, b in
+          ([(0, 0)] if kw["probes"] < 100 else [(a, b) for a in (-1, 0, 1) for b in (-1, 0, 1)])]
+spec = u1.Spec(ensembles=[u1.Ens((N, N, N), 4, 1.0, key_id=i) for i in range(kw["n"])], levels=[(2, 1, 0)], r=kw["r"],
+               probes=probes[: kw["probes"]], comps=list(range(kw["comps"])), form=kw["form"])
+ctx = make(spec)
+ok(L.u1ml_set_lanes(ctx, 1))
+ok(L.u1ml_init_links(ctx, u1.HOT))
+launches()
+ok(L.u1ml_multilevel(ctx), ctx)
+assert any(l[0] == ("k_product_final" if kw["form"] == 1 else "k_spec_final") for l in launches())
+ok(L.u1ml_destroy(ctx))
+""", timeout=300)
