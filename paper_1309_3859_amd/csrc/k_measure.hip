@@ -228,7 +228,8 @@ struct MeasItem {
 // fraction of 40 and more divisions for each link, one link per work-item in
 // work-groups of one wave, so that they spread over the device (14 x 10 x 18 x 6
 // FP64: with the measurement, slices of a site in turn 21.9 us, four work-items
-// a site 18.3, so 7.2 and the measurement after it 7.7).  Launch: (blocks x 4, tau).
+// a site 18.3, so 7.2 and the measurement after it 7.7).  Launch: (blocks x 4,
+// tau, or 65535 where tau is more than a grid has along y).
 template <typename real>
 __global__ void __launch_bounds__(64) k_multihit(const EnsDesc* __restrict__ ens, const MeasBlock* __restrict__ blocks,
                                                  const real* __restrict__ links, double2* __restrict__ hit, int tau)
@@ -238,13 +239,15 @@ __global__ void __launch_bounds__(64) k_multihit(const EnsDesc* __restrict__ ens
     const MeasItem I(B, (int)(blockIdx.x & 3u) * 64 + (int)threadIdx.x);
     if (!I.active) return;
     const Geo g{B.nx, B.ny, E.nz, B.nt, B.nx >> 1, (B.nx >> 1) * B.ny, B.nsig >> 1};
-    const int t = I.s * tau + (int)blockIdx.y;
-    const Site c{I.x, I.y, I.z, t, g.sy * I.yz + g.st * t};
-    real ar, ai;
-    staple_sum<real, 3>(links + B.link_off, (unsigned)B.vh, g, c, (I.x + I.y + I.z + t) & 1, &ar, &ai);
-    const double R = sqrt((double)ar * (double)ar + (double)ai * (double)ai);
-    const double f = R > 0.0 ? bessel_ratio(E.beta * R) / R : 0.0;
-    hit[E.hit_off + (size_t)t * B.nsig + I.xs] = make_double2((double)ar * f, -(double)ai * f);
+    for (int k = (int)blockIdx.y; k < tau; k += (int)gridDim.y) {  // usually one
+        const int t = I.s * tau + k;
+        const Site c{I.x, I.y, I.z, t, g.sy * I.yz + g.st * t};
+        real ar, ai;
+        staple_sum<real, 3>(links + B.link_off, (unsigned)B.vh, g, c, (I.x + I.y + I.z + t) & 1, &ar, &ai);
+        const double R = sqrt((double)ar * (double)ar + (double)ai * (double)ai);
+        const double f = R > 0.0 ? bessel_ratio(E.beta * R) / R : 0.0;
+        hit[E.hit_off + (size_t)t * B.nsig + I.xs] = make_double2((double)ar * f, -(double)ai * f);
+    }
 }
 
 // What bounds it: the chain of one work-item on small lattices (its loads, two
@@ -367,7 +370,7 @@ static void launch_measure_t(const EnsDesc* d_ens, const MeasBlock* d_blocks, in
 {
     const dim3 g((total_blocks + 7) / 8 * 8), b(256);
     if (multihit) {
-        hipLaunchKernelGGL((k_multihit<real>), dim3(4 * total_blocks, tau), dim3(64), 0, st, d_ens, d_blocks,
+        hipLaunchKernelGGL((k_multihit<real>), dim3(4 * total_blocks, std::min(tau, 65535)), dim3(64), 0, st, d_ens, d_blocks,
                            (const real*)links, hit, tau);
         hipLaunchKernelGGL((k_measure<real, true>), g, b, 0, st, d_ens, d_blocks, (const real*)links, hit, hist_c,
                            (real*)hist_o, vac_part, m_in, m, tau, store_o, total_blocks);

@@ -53,3 +53,15 @@ ok(L.u1ml_multilevel(ctx), ctx)
 assert any(l[0] == ("k_product_final" if kw["form"] == 1 else "k_spec_final") for l in launches())
 ok(L.u1ml_destroy(ctx))
 """, timeout=300)
+
+
+@pytest.mark.parametrize("tau", [65536, 131072])
+def test_multihit_of_thick_slabs(so, tau):
+    """More time slices in a slab than a grid has along its second axis."""
+    host_hip.run(so, f"""
+ctx = make(u1.Spec(ensembles=[u1.Ens((2, 2, 2), 131072, 1.0)], levels=[({tau}, 1, 0)], r=[1], multihit=True))
+ok(L.u1ml_init_links(ctx, u1.HOT))
+ok(L.u1ml_multilevel(ctx), ctx)
+assert "k_multihit" in [l[0] for l in launches()]
+ok(L.u1ml_destroy(ctx))
+""")
