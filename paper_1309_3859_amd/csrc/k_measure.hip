@@ -30,10 +30,19 @@
 
 namespace u1ml {
 
+// (Bisection: a scan from the front costs a scalar load's latency an ensemble.
+// 512 lattices of 4^3 x 4, history form, 1 probe: a configuration 1510 us with
+// the scan, 498 with the bisection.)
 __device__ inline int find_ens_m(const int* __restrict__ bstart, int n_ens, int bid)
 {
     int e = 0;
-    while (e + 1 < n_ens && bid >= bstart[e + 1]) ++e;
+    for (int end = n_ens; end - e > 1;) {
+        const int mid = (e + end) >> 1;
+        if (bid >= bstart[mid])
+            e = mid;
+        else
+            end = mid;
+    }
     return e;
 }
 

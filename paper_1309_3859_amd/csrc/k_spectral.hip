@@ -34,7 +34,13 @@ namespace {
 __device__ inline int find_ens_s(const int* __restrict__ bstart, int n_ens, int bid)
 {
     int e = 0;
-    while (e + 1 < n_ens && bid >= bstart[e + 1]) ++e;
+    for (int end = n_ens; end - e > 1;) {
+        const int mid = (e + end) >> 1;
+        if (bid >= bstart[mid])
+            e = mid;
+        else
+            end = mid;
+    }
     return e;
 }
 
