@@ -9,7 +9,9 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/u1ml.h"
@@ -1309,9 +1311,11 @@ hipError_t upload_lane(const Lane& L)
 // Splits the batch into nl lanes of about equal volume (largest ensembles
 // first, each to the lane with the least volume so far; a lane keeps the
 // problem order), builds and uploads their tables.  Lanes past nl, and with
-// nl = 1 all of them, are emptied; their device areas stay reserved.
+// nl = 1 all of them, are emptied; their device areas stay reserved.  Where it
+// fails the context is left with one lane.
 hipError_t split_lanes(u1ml_ctx* c, int nl)
 {
+    c->n_lanes = 1;
     // streams as they are needed: the runtime maps streams to a few hardware
     // queues, and a lane that shares one with the context's stream (or with
     // another context's) waits for it
@@ -1734,6 +1738,17 @@ void phase_words(const u1ml_ensemble& E, int kind, int mu, int parity, int tau, 
     *updates = u;
 }
 
+// What an entry point returns for an exception, none of which crosses the
+// interface: they come from the containers' allocations.
+u1ml_status thrown(u1ml_ctx* c) noexcept
+{
+    try {
+        return set_err(c, U1ML_ENOMEM, "host allocation failed");
+    } catch (...) {
+        return U1ML_ENOMEM;
+    }
+}
+
 }  // namespace
 
 // ===========================================================================
@@ -1757,7 +1772,7 @@ const char* u1ml_status_str(u1ml_status s)
 const char* u1ml_last_error(const u1ml_ctx* ctx) { return ctx ? ctx->err.c_str() : g_err.c_str(); }
 
 u1ml_status u1ml_plan(const u1ml_problem* problem, u1ml_plan_info* out)
-{
+try {
     if (!out) return set_err(nullptr, U1ML_EINVAL, "plan output is NULL");
     Problem P;
     std::string err;
@@ -1767,42 +1782,29 @@ u1ml_status u1ml_plan(const u1ml_problem* problem, u1ml_plan_info* out)
     if (!compute_sizes(P, &S, out, &Lo, &err)) return set_err(nullptr, U1ML_ENOMEM, err);
     g_err.clear();
     return U1ML_OK;
+} catch (...) {
+    return thrown(nullptr);
 }
 
 u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes, void* hip_stream, u1ml_ctx** out)
-{
+try {
     if (!out) return set_err(nullptr, U1ML_EINVAL, "output pointer is NULL");
     *out = nullptr;
-    u1ml_ctx* c = new (std::nothrow) u1ml_ctx();
-    if (!c) return set_err(nullptr, U1ML_ENOMEM, "host allocation failed");
+    std::unique_ptr<u1ml_ctx, void (*)(u1ml_ctx*)> own(new u1ml_ctx(), release);
+    u1ml_ctx* const c = own.get();
     std::string err;
-    if (!read_problem(problem, &c->P, &err)) {
-        delete c;
-        return set_err(nullptr, U1ML_EINVAL, err);
-    }
-    if (!compute_sizes(c->P, &c->S, &c->plan, &c->Lo, &err)) {
-        delete c;
-        return set_err(nullptr, U1ML_ENOMEM, err);
-    }
-    if (!d_ws || ws_bytes < c->plan.ws_bytes) {
-        const size_t need = c->plan.ws_bytes;
-        delete c;
-        return set_err(nullptr, U1ML_EINVAL, "workspace too small: need " + std::to_string(need) + " bytes");
-    }
-    if (((uintptr_t)d_ws) % kAlign != 0) {
-        delete c;
-        return set_err(nullptr, U1ML_EINVAL, "workspace must be 256-byte aligned");
-    }
+    if (!read_problem(problem, &c->P, &err)) return set_err(nullptr, U1ML_EINVAL, err);
+    if (!compute_sizes(c->P, &c->S, &c->plan, &c->Lo, &err)) return set_err(nullptr, U1ML_ENOMEM, err);
+    if (!d_ws || ws_bytes < c->plan.ws_bytes)
+        return set_err(nullptr, U1ML_EINVAL, "workspace too small: need " + std::to_string(c->plan.ws_bytes) + " bytes");
+    if (((uintptr_t)d_ws) % kAlign != 0) return set_err(nullptr, U1ML_EINVAL, "workspace must be 256-byte aligned");
     c->ws = (char*)d_ws;
     c->stream = (hipStream_t)hip_stream;
     hipError_t he = hipGetDevice(&c->device);
     if (he == hipSuccess) he = static_scratch(&c->static_partials);
     // lane 1's stream, also the one that graphs are captured on
     if (he == hipSuccess) he = hipStreamCreateWithFlags(&c->lane_stream[1], hipStreamNonBlocking);
-    if (he != hipSuccess) {
-        delete c;
-        return set_err(nullptr, U1ML_EDEVICE, std::string("stream creation: ") + hipGetErrorString(he));
-    }
+    if (he != hipSuccess) return set_err(nullptr, U1ML_EDEVICE, std::string("stream creation: ") + hipGetErrorString(he));
     const Layout& Lo = c->Lo;
     char* w = c->ws;
     c->links = w + Lo.off_links;
@@ -1954,10 +1956,8 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
                                      fit_mc(E.ins_pbw) < std::min(8, (P.n_i + 3) / 4 * 4)))
                 --E.ins_pbw;
             const int mc = fit_mc(E.ins_pbw);
-            if (!mf_chunk_fits(mc, (int)nmax, (int)R, E.ins_pbw * 2 * kMfSlots, (int)word)) {
-                release(c);
+            if (!mf_chunk_fits(mc, (int)nmax, (int)R, E.ins_pbw * 2 * kMfSlots, (int)word))
                 return set_err(nullptr, U1ML_ENOTSUP, "history-form insertions: matrix-core chunk does not fit LDS");
-            }
             c->ins_block = kMfThreads;
             E.ins_mc = mc;
         } else if (!P.probes.empty() && !P.spectral) {
@@ -1979,12 +1979,10 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
             c->ins_block = std::max(c->ins_block, std::min(kInsThreads, (E.ins_pbw * unit + 63) / 64 * 64));
             const int nrows = E.ins_pbw * ks * 2;
             const int mc = fit_mc(E.ins_pbw);
-            if (!ins_chunk_fits(mc, (int)nmax, nrows, (int)word)) {
-                release(c);
+            if (!ins_chunk_fits(mc, (int)nmax, nrows, (int)word))
                 return set_err(nullptr, U1ML_ENOTSUP,
                                "history-form insertions: one measurement of a work-group's phases or O rows exceeds "
                                "its LDS buffer (use the spectral form)");
-            }
             E.ins_mc = mc;
         }
         E.prod_nch = (P.n_dirs * E.nsig + kProdChunk - 1) / kProdChunk;
@@ -2030,12 +2028,10 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         const size_t mac_lds = P.spectral ? 2 * spec_mac_lds(c->spec_npm) : 0;  // both kinds: the form's limit on the extents
         const size_t slab_bytes = *std::max_element(P.slab_lds_bytes, P.slab_lds_bytes + 3);
         const size_t need = std::max({c->con_lds, c->ins_lds, dft_lds, mac_lds, slab_bytes});
-        if (ea != hipSuccess || (size_t)lds_max < need) {
-            release(c);
+        if (ea != hipSuccess || (size_t)lds_max < need)
             return set_err(nullptr, ea != hipSuccess ? U1ML_EDEVICE : U1ML_ENOTSUP,
                            "work-group LDS of " + std::to_string(need) + " bytes exceeds the device limit of " +
                                std::to_string(lds_max));
-        }
     }
     std::vector<uint32_t> zeros(n, 0u);
     u1ml_status st = U1ML_OK;
@@ -2063,26 +2059,27 @@ u1ml_status u1ml_create(const u1ml_problem* problem, void* d_ws, size_t ws_bytes
         if (e == hipSuccess) e = split_lanes(c, default_lanes(P.ens, P.precision));
         if (e != hipSuccess) st = set_err(nullptr, U1ML_EDEVICE, std::string("lanes: ") + hipGetErrorString(e));
     }
-    if (st != U1ML_OK) {
-        release(c);
-        return st;
-    }
-    *out = c;
+    if (st != U1ML_OK) return st;
+    *out = own.release();
     return U1ML_OK;
+} catch (...) {
+    return thrown(nullptr);
 }
 
 u1ml_status u1ml_destroy(u1ml_ctx* ctx)
-{
+try {
     if (!ctx) return U1ML_OK;
     // every lane joins the context's stream, so this waits for all work that
     // still reads the workspace or runs the graphs about to be destroyed
     const hipError_t e = hipStreamSynchronize(ctx->stream);
     release(ctx);
     return e == hipSuccess ? U1ML_OK : set_err(nullptr, U1ML_EDEVICE, std::string("u1ml_destroy: ") + hipGetErrorString(e));
+} catch (...) {
+    return thrown(nullptr);  // (the context is gone)
 }
 
 u1ml_status u1ml_init_links(u1ml_ctx* ctx, int start)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (start != U1ML_COLD && start != U1ML_HOT) return set_err(ctx, U1ML_EINVAL, "start must be 0 (cold) or 1 (hot)");
     HIPCHK(ctx, launch_init_links(ctx->whole.d_ens, ctx->whole.tab_dev(kTabAll), ctx->P.n_ens, ctx->whole.tab_total(kTabAll),
@@ -2090,10 +2087,12 @@ u1ml_status u1ml_init_links(u1ml_ctx* ctx, int start)
     HIPCHK(ctx, launch_fill_zero(ctx->d_upd, align_up(sizeof(uint32_t) * ctx->P.n_ens), ctx->stream));
     ctx->initialised = true;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_sweeps(u1ml_ctx* ctx, int n)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (n < 0) return set_err(ctx, U1ML_EINVAL, "n must be >= 0");
     if (!ctx->initialised) return set_err(ctx, U1ML_ESTATE, "links not initialised");
@@ -2126,10 +2125,12 @@ u1ml_status u1ml_sweeps(u1ml_ctx* ctx, int n)
         return ctx->err != before && e == hipErrorUnknown ? U1ML_EDEVICE
                                                           : set_err(ctx, U1ML_EDEVICE, std::string("sweeps: ") + hipGetErrorString(e));
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_phase(u1ml_ctx* ctx, int kind, int mu, int parity, int tau, int pass_offset)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!ctx->initialised) return set_err(ctx, U1ML_ESTATE, "links not initialised");
     if ((kind < 0 || kind > 2) || mu < 0 || mu > 3 || (parity != 0 && parity != 1) || pass_offset < 0)
@@ -2139,10 +2140,12 @@ u1ml_status u1ml_phase(u1ml_ctx* ctx, int kind, int mu, int parity, int tau, int
     if (!ok) return set_err(ctx, U1ML_EINVAL, "tau must be <= 1 or one of the problem's level thicknesses");
     HIPCHK(ctx, enq_phase(ctx, ctx->whole, ctx->stream, kind, mu, parity, tau, pass_offset, kInPlace));
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_multilevel(u1ml_ctx* ctx)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!ctx->initialised) return set_err(ctx, U1ML_ESTATE, "links not initialised");
     if (ctx->ring_count >= ctx->P.max_configs)
@@ -2162,10 +2165,12 @@ u1ml_status u1ml_multilevel(u1ml_ctx* ctx)
                    : set_err(ctx, U1ML_EDEVICE, std::string("multilevel: ") + hipGetErrorString(e));
     ctx->ring_count++;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_copy_results(u1ml_ctx* ctx, double* host, size_t n_doubles, size_t* n_written)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!host && n_doubles) return set_err(ctx, U1ML_EINVAL, "host is NULL");
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
@@ -2178,10 +2183,12 @@ u1ml_status u1ml_copy_results(u1ml_ctx* ctx, double* host, size_t n_doubles, siz
     ctx->ring_count = 0;
     if (n_written) *n_written = nw;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_get_links(u1ml_ctx* ctx, int ens, double* host, size_t n)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (ens < 0 || ens >= ctx->P.n_ens) return set_err(ctx, U1ML_EINVAL, "ensemble index out of range");
     const long long V = 2ll * ctx->h_ens[ens].vh;
@@ -2190,10 +2197,12 @@ u1ml_status u1ml_get_links(u1ml_ctx* ctx, int ens, double* host, size_t n)
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     HIPCHK(ctx, hipMemcpy(host, ctx->stage, sizeof(double) * 4 * V, hipMemcpyDeviceToHost));
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_set_links(u1ml_ctx* ctx, int ens, const double* host, size_t n)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (ens < 0 || ens >= ctx->P.n_ens) return set_err(ctx, U1ML_EINVAL, "ensemble index out of range");
     const long long V = 2ll * ctx->h_ens[ens].vh;
@@ -2204,28 +2213,34 @@ u1ml_status u1ml_set_links(u1ml_ctx* ctx, int ens, const double* host, size_t n)
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     ctx->initialised = true;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_get_counter(u1ml_ctx* ctx, int ens, uint32_t* counter)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (ens < 0 || ens >= ctx->P.n_ens || !counter) return set_err(ctx, U1ML_EINVAL, "bad arguments");
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     HIPCHK(ctx, hipMemcpy(counter, ctx->d_upd + ens, sizeof(uint32_t), hipMemcpyDeviceToHost));
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_set_counter(u1ml_ctx* ctx, int ens, uint32_t counter)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (ens < 0 || ens >= ctx->P.n_ens) return set_err(ctx, U1ML_EINVAL, "bad arguments");
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     HIPCHK(ctx, hipMemcpy(ctx->d_upd + ens, &counter, sizeof(uint32_t), hipMemcpyHostToDevice));
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_plaquette(u1ml_ctx* ctx, double* out)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!out) return set_err(ctx, U1ML_EINVAL, "out is NULL");
     if (!ctx->initialised) return set_err(ctx, U1ML_ESTATE, "links not initialised");
@@ -2234,10 +2249,12 @@ u1ml_status u1ml_plaquette(u1ml_ctx* ctx, double* out)
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     HIPCHK(ctx, hipMemcpy(out, ctx->pout, sizeof(double) * 6 * ctx->P.n_ens, hipMemcpyDeviceToHost));
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_plaquette_noalloc(u1ml_ctx* ctx, double* d_out)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!d_out) return set_err(ctx, U1ML_EINVAL, "d_out is NULL");
     if (ctx->P.n_ens > kStaticPlaqEns)
@@ -2247,10 +2264,12 @@ u1ml_status u1ml_plaquette_noalloc(u1ml_ctx* ctx, double* d_out)
     HIPCHK(ctx, launch_plaquette(ctx->whole.d_ens, ctx->P.n_ens, 0, ctx->P.precision, ctx->links,
                                  ctx->static_partials, d_out, ctx->stream));
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_health(u1ml_ctx* ctx, uint64_t* n_bad)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!n_bad) return set_err(ctx, U1ML_EINVAL, "n_bad is NULL");
     HIPCHK(ctx, launch_fill_zero(ctx->d_count, 16, ctx->stream));
@@ -2261,52 +2280,77 @@ u1ml_status u1ml_health(u1ml_ctx* ctx, uint64_t* n_bad)
     HIPCHK(ctx, hipMemcpy(&v, ctx->d_count, sizeof v, hipMemcpyDeviceToHost));
     *n_bad = v;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_set_block(u1ml_ctx* ctx, int block)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (block != 64 && block != 128 && block != 256 && block != 512 && block != 1024)
         return set_err(ctx, U1ML_EINVAL, "block must be 64, 128, 256, 512 or 1024");
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    ctx->block = block;
-    for (Lane* L : all_lanes(ctx)) {
-        if (!L->n) continue;
-        build_update_tabs(ctx, *L);
-        HIPCHK(ctx, hipMemcpy(L->d_bstart, L->h_bstart.data(), sizeof(int) * 4 * (L->n + 1), hipMemcpyHostToDevice));
-        HIPCHK(ctx, upload_update_tabs(*L));
+    // every lane's tables before the first is replaced: a failed call changes nothing
+    std::vector<Lane*> lanes = all_lanes(ctx);
+    std::vector<Lane> built;
+    const int old = std::exchange(ctx->block, block);
+    try {
+        for (Lane* L : lanes) {
+            built.push_back(*L);
+            if (L->n) build_update_tabs(ctx, built.back());
+        }
+    } catch (...) {
+        ctx->block = old;
+        throw;
+    }
+    for (size_t l = 0; l < lanes.size(); ++l) {
+        *lanes[l] = std::move(built[l]);
+        const Lane& L = *lanes[l];
+        if (!L.n) continue;
+        HIPCHK(ctx, hipMemcpy(L.d_bstart, L.h_bstart.data(), sizeof(int) * 4 * (L.n + 1), hipMemcpyHostToDevice));
+        HIPCHK(ctx, upload_update_tabs(L));
     }
     drop_graphs(ctx);
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_set_lanes(u1ml_ctx* ctx, int n_lanes)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (n_lanes < 1 || n_lanes > kMaxLanes) return set_err(ctx, U1ML_EINVAL, "n_lanes must be 1, 2, 3 or 4");
     if (n_lanes > ctx->P.n_ens) return set_err(ctx, U1ML_EINVAL, "more lanes than ensembles");
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    if (n_lanes != ctx->n_lanes) HIPCHK(ctx, split_lanes(ctx, n_lanes));
-    // the lanes now in use continue the results ring where it stands
+    // the lanes then in use continue the results ring where it stands (the
+    // whole batch as well: it is in use if the split fails)
     const int ring[4] = {ctx->ring_count, 0, 0, 0};
+    HIPCHK(ctx, hipMemcpy(ctx->whole.d_ring, ring, sizeof ring, hipMemcpyHostToDevice));
+    if (n_lanes != ctx->n_lanes) HIPCHK(ctx, split_lanes(ctx, n_lanes));
     for (Lane* L : all_lanes(ctx))
         if (L->n) HIPCHK(ctx, hipMemcpy(L->d_ring, ring, sizeof ring, hipMemcpyHostToDevice));
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_get_lanes(u1ml_ctx* ctx, int* n_lanes)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!n_lanes) return set_err(ctx, U1ML_EINVAL, "n_lanes is NULL");
     *n_lanes = ctx->n_lanes;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_set_graphs(u1ml_ctx* ctx, int enable)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     ctx->use_graphs = enable != 0;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 namespace {
@@ -2343,14 +2387,16 @@ u1ml_status time_lane_phase(u1ml_ctx* ctx, const Lane& L, int kind, int mu, int 
 }  // namespace
 
 u1ml_status u1ml_time_phase(u1ml_ctx* ctx, int kind, int mu, int parity, int tau, int n_rep, double* us)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     return time_lane_phase(ctx, ctx->whole, kind, mu, parity, tau, n_rep, us);
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_time_phase_lane(u1ml_ctx* ctx, int lane, int kind, int mu, int parity, int tau, int n_rep,
                                  double* us, double* bytes, long* updates)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (lane < 0 || lane >= ctx->n_lanes) return set_err(ctx, U1ML_EINVAL, "lane out of range");
     if (!bytes || !updates) return set_err(ctx, U1ML_EINVAL, "bad arguments");
@@ -2369,10 +2415,12 @@ u1ml_status u1ml_time_phase_lane(u1ml_ctx* ctx, int lane, int kind, int mu, int 
     *bytes = b;
     *updates = u;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_phase_bytes(u1ml_ctx* ctx, int kind, int mu, int parity, int tau, double* bytes, long* updates)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!bytes || !updates || mu < 0 || mu > 3 || (parity & ~1) || kind < 0 || kind > 2)
         return set_err(ctx, U1ML_EINVAL, "bad arguments");
@@ -2388,20 +2436,22 @@ u1ml_status u1ml_phase_bytes(u1ml_ctx* ctx, int kind, int mu, int parity, int ta
     *bytes = b;
     *updates = u;
     return U1ML_OK;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_autotune(u1ml_ctx* ctx, u1ml_tune_report* report)
-{
+try {
     if (!ctx) return set_err(nullptr, U1ML_EINVAL, "ctx is NULL");
     if (!ctx->initialised) return set_err(ctx, U1ML_ESTATE, "links not initialised");
     const int cand[5] = {64, 128, 256, 512, 1024};
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     // save links and counters so tuning leaves no trace
     const size_t lbytes = ctx->Lo.sz_links;
+    std::vector<uint32_t> upd(ctx->P.n_ens);
     void* saved = nullptr;
     HIPCHK(ctx, hipMalloc(&saved, lbytes));
     hipError_t he = hipMemcpy(saved, ctx->links, lbytes, hipMemcpyDeviceToDevice);
-    std::vector<uint32_t> upd(ctx->P.n_ens);
     if (he == hipSuccess) he = hipMemcpy(upd.data(), ctx->d_upd, sizeof(uint32_t) * upd.size(), hipMemcpyDeviceToHost);
     if (he != hipSuccess) {
         (void)hipFree(saved);
@@ -2458,30 +2508,36 @@ u1ml_status u1ml_autotune(u1ml_ctx* ctx, u1ml_tune_report* report)
     rep.chosen_block = best_b;
     if (report) *report = rep;
     return st;
+} catch (...) {
+    return thrown(ctx);
 }
 
 u1ml_status u1ml_philox_fill(uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, size_t n,
                              uint32_t* d_out, void* hip_stream)
-{
+try {
     if (!d_out && n) return set_err(nullptr, U1ML_EINVAL, "d_out is NULL");
     if (n > 0xFFFFFFFFull) return set_err(nullptr, U1ML_EINVAL, "n must be < 2^32");
     hipError_t e = launch_philox_fill(k0, k1, c0, c1, c2, c3, n, d_out, (hipStream_t)hip_stream);
     if (e != hipSuccess) return set_err(nullptr, U1ML_EDEVICE, hipGetErrorString(e));
     return U1ML_OK;
+} catch (...) {
+    return thrown(nullptr);
 }
 
 u1ml_status u1ml_sincos_fill(const double* d_x, size_t n, double* d_s, double* d_c, void* hip_stream)
-{
+try {
     if ((!d_x || !d_s || !d_c) && n) return set_err(nullptr, U1ML_EINVAL, "NULL device pointer");
     if (n > 0xFFFFFFFFull) return set_err(nullptr, U1ML_EINVAL, "n must be < 2^32");
     hipError_t e = launch_sincos_fill(d_x, n, d_s, d_c, (hipStream_t)hip_stream);
     if (e != hipSuccess) return set_err(nullptr, U1ML_EDEVICE, hipGetErrorString(e));
     return U1ML_OK;
+} catch (...) {
+    return thrown(nullptr);
 }
 
 u1ml_status u1ml_vonmises_fill(double kappa, int precision, uint32_t seed, uint32_t key_id, uint32_t c0, uint32_t c1,
                                size_t n, double* d_out, int* d_attempts, void* hip_stream)
-{
+try {
     if (!d_out && n) return set_err(nullptr, U1ML_EINVAL, "d_out is NULL");
     if (!(kappa >= 0) || !std::isfinite(kappa)) return set_err(nullptr, U1ML_EINVAL, "kappa must be finite and >= 0");
     if (precision != U1ML_FP64 && precision != U1ML_FP32) return set_err(nullptr, U1ML_EINVAL, "bad precision");
@@ -2490,6 +2546,8 @@ u1ml_status u1ml_vonmises_fill(double kappa, int precision, uint32_t seed, uint3
                                         (hipStream_t)hip_stream);
     if (e != hipSuccess) return set_err(nullptr, U1ML_EDEVICE, hipGetErrorString(e));
     return U1ML_OK;
+} catch (...) {
+    return thrown(nullptr);
 }
 
 }  // extern "C"

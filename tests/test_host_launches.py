@@ -65,3 +65,43 @@ ok(L.u1ml_multilevel(ctx), ctx)
 assert "k_multihit" in [l[0] for l in launches()]
 ok(L.u1ml_destroy(ctx))
 """)
+
+
+@pytest.mark.parametrize("call", ["plan", "create", "set_block", "set_lanes"])
+def test_no_exception_leaves_the_library(so, call):
+    """Out of host memory: U1ML_ENOMEM with a message, and a context whose call
+    failed goes on as it was."""
+    host_hip.run(so, f"""
+import resource
+call = {call!r}
+ns, nt, n = ((2, 2, 2), 2, 2000000) if call == "plan" else ((8, 4, 4), 300000, 3)
+spec = u1.Spec(ensembles=[u1.Ens(ns, nt, 1.0, key_id=i) for i in range(n)], levels=[(60000 if n == 3 else 2, 1, 0)], r=[1])
+p = spec.struct()
+info = u1._PlanInfo()
+h = C.c_void_p()
+if call not in ("plan", "create"):
+    h = make(spec)
+    ok(L.u1ml_set_lanes(h, 1))
+    ok(L.u1ml_init_links(h, u1.HOT))
+    launches()
+    ok(L.u1ml_phase(h, u1.OVERRELAX, 3, 0, 0, 0))
+    before = launches()
+used = int(open("/proc/self/statm").read().split()[0]) * 4096
+resource.setrlimit(resource.RLIMIT_AS, (used + (64 << 20), -1))
+st = (L.u1ml_plan(C.byref(p), C.byref(info)) if call == "plan" else
+      L.u1ml_create(C.byref(p), C.c_void_p(1 << 40), 1 << 50, None, C.byref(h)) if call == "create" else
+      L.u1ml_set_block(h, 64) if call == "set_block" else L.u1ml_set_lanes(h, 3))
+resource.setrlimit(resource.RLIMIT_AS, (-1, -1))
+assert st == 2, st
+assert b"allocation" in L.u1ml_last_error(h if call[0] == "s" else None)
+if call in ("plan", "create"):
+    assert not h.value
+else:
+    ok(L.u1ml_phase(h, u1.OVERRELAX, 3, 0, 0, 0))
+    assert launches() == before
+    n_lanes = C.c_int()
+    ok(L.u1ml_get_lanes(h, C.byref(n_lanes)))
+    assert n_lanes.value == 1
+    ok(L.u1ml_multilevel(h))
+    ok(L.u1ml_destroy(h))
+""")
