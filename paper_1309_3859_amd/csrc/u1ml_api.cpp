@@ -125,6 +125,7 @@ struct Problem {
     std::vector<PairTile> pair_tile[kPairClasses];
     int n_pair_rows = 0;
     std::map<std::array<int, 15>, int> pair_shape;  // shape -> first row
+    std::vector<int> lattice;  // per ensemble: the first one of its extents
 
     // whole sweeps in LDS (k_slab), per class full / inner tau / outer tau: on, work-group size, LDS, work-groups
     bool slab_on[3] = {};
@@ -565,10 +566,14 @@ void plan_pairs(Problem* P)
     double vol = 0.0;
     size_t bytes = 0;
     const size_t word = P->precision == U1ML_FP64 ? 8 : 4;
-    for (const u1ml_ensemble& E : P->ens) {
+    std::map<std::array<int, 4>, int> first;
+    P->lattice.clear();
+    for (int k = 0; k < P->n_ens; ++k) {
+        const u1ml_ensemble& E = P->ens[k];
         const double v = (double)E.ns[0] * E.ns[1] * E.ns[2] * E.nt;
         vol += v;
         bytes += (size_t)(4.0 * v) * word;
+        P->lattice.push_back(first.emplace(std::array<int, 4>{E.ns[0], E.ns[1], E.ns[2], E.nt}, k).first->second);
     }
     const int max_threads = P->precision == U1ML_FP64 ? kPairThreads<double> : kPairThreads<float>;
     for (int cls = 0; cls < kPairClasses; ++cls) {
@@ -579,29 +584,42 @@ void plan_pairs(Problem* P)
         bool ok = 2 * bytes < 4294967296.0 && (cls % 3 != 2 || P->two);
         if (cls < 9) ok = ok && !P->slab_on[cls % 3];
         else ok = ok && !(P->slab_on[0] && P->slab_on[1] && (!P->two || P->slab_on[2]));
-        double one = 0.0, two = 0.0, lat = 1.0;
-        P->pair_block[cls] = 64;
-        for (int k = 0; ok && k < P->n_ens; ++k) {
-            const u1ml_ensemble& E = P->ens[k];
+        double one = 0.0, two = 0.0, least = 0.0;  // waves of either form; least: of one launch without halo
+        for (const u1ml_ensemble& E : P->ens) {
             const PairGeo G(E, cls, tau);
-            const double v = (double)E.ns[0] * E.ns[1] * E.ns[2] * E.nt;
-            double waves = 0.0;
-            const PairTile T = pair_tile(G, v / vol, max_threads, &waves);
-            ok = T.blocks > 0;
-            P->pair_tile[cls][k] = T;
-            one += waves;
             const double slice = (double)G.nxh * G.N[0] * G.N[1];
             two += std::ceil(slice / 64) * G.N[2] * G.slabs;
-            if (ok) P->pair_block[cls] = std::max(P->pair_block[cls], (G.rows(T.L) * G.nxh + 63) / 64 * 64);
+            least += slice / 64 * G.N[2] * G.slabs;
         }
-        lat = std::max(1.0, P->pair_block[cls] / 256.0);
-        const double t_one = 1.9 + 2 * 0.55 * std::max(lat, one / 1024), t_two = 2 * (1.9 + 0.4 * std::max(1.0, two / 1024));
-        P->pair_on[cls] = ok && t_one < 0.9 * t_two;
+        const double t_two = 2 * (1.9 + 0.4 * std::max(1.0, two / 1024));
+        auto t_one = [](double lat, double waves) { return 1.9 + 2 * 0.55 * std::max(lat, waves / 1024); };
+        ok = ok && t_one(1.0, least) < 0.9 * t_two;  // no tiles to look for otherwise
+        P->pair_block[cls] = 64;
+        std::vector<double> waves(ok ? P->n_ens : 0);
+        for (int k = 0; ok && k < P->n_ens; ++k) {
+            const int l = P->lattice[k];  // equal lattices have equal tiles
+            if (l == k) {
+                const u1ml_ensemble& E = P->ens[k];
+                const PairGeo G(E, cls, tau);
+                const double v = (double)E.ns[0] * E.ns[1] * E.ns[2] * E.nt;
+                const PairTile T = pair_tile(G, v / vol, max_threads, &waves[k]);
+                ok = T.blocks > 0;
+                P->pair_tile[cls][k] = T;
+                if (ok) P->pair_block[cls] = std::max(P->pair_block[cls], (G.rows(T.L) * G.nxh + 63) / 64 * 64);
+            } else {
+                P->pair_tile[cls][k] = P->pair_tile[cls][l];
+                waves[k] = waves[l];
+            }
+            one += waves[k];
+        }
+        const double lat = std::max(1.0, P->pair_block[cls] / 256.0);
+        P->pair_on[cls] = ok && t_one(lat, one) < 0.9 * t_two;
     }
     P->n_pair_rows = 0;
     P->pair_shape.clear();
     for (int cls = 0; cls < kPairClasses; ++cls)
         for (int k = 0; P->pair_on[cls] && k < P->n_ens; ++k) {
+            if (P->lattice[k] != k) continue;  // the rows of an equal lattice
             const PairGeo G(P->ens[k], cls, P->pair_tau(cls));
             pair_for_tiles(*P, cls, k, [&](const int* o, const int* L) {
                 if (P->pair_shape.try_emplace(G.shape(o, L), P->n_pair_rows).second) P->n_pair_rows += G.rows(L);
@@ -617,6 +635,7 @@ std::vector<PairRow> build_pair_rows(const Problem& P)
     int next = 0;  // shapes come in the order of their first rows
     for (int cls = 0; cls < kPairClasses; ++cls)
         for (int k = 0; P.pair_on[cls] && k < P.n_ens; ++k) {
+            if (P.lattice[k] != k) continue;
             const PairGeo G(P.ens[k], cls, P.pair_tau(cls));
             pair_for_tiles(P, cls, k, [&](const int* o, const int* L) {
                 if (P.pair_shape.at(G.shape(o, L)) != next) return;

@@ -105,3 +105,26 @@ else:
     ok(L.u1ml_multilevel(h))
     ok(L.u1ml_destroy(h))
 """)
+
+
+def test_planning_time_of_equal_lattices():
+    """A plan of 2048 equal lattices takes no more than ten times that of 2048
+    lattices whose sweeps run in LDS, for which no tiles are looked for."""
+    import ctypes as C
+    import time
+
+    from paper_1309_3859_amd import u1ml as u1
+
+    def seconds(n, ns, nt):
+        p = u1.Spec(ensembles=[u1.Ens(ns, nt, 1.0, key_id=i) for i in range(n)], levels=[(2, 1, 1)], r=[1]).struct()
+        info = u1._PlanInfo()
+        best = 1e9
+        for _ in range(5):
+            t = time.process_time()
+            assert u1.lib().u1ml_plan(C.byref(p), C.byref(info)) == 0
+            best = min(best, time.process_time() - t)
+        return best
+
+    base = seconds(2048, (4, 4, 4), 4)
+    assert seconds(2048, (8, 8, 8), 16) < 10 * base
+    assert seconds(512, (16, 16, 16), 8) < 10 * base
