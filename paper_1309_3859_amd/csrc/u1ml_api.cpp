@@ -580,8 +580,9 @@ void plan_pairs(Problem* P)
         P->pair_on[cls] = false;
         P->pair_tile[cls].assign(P->n_ens, PairTile());
         const int tau = P->pair_tau(cls);
-        // both buffers of an ensemble within 32-bit offsets of its links; not for sweeps in LDS
-        bool ok = 2 * bytes < 4294967296.0 && (cls % 3 != 2 || P->two);
+        // both buffers of an ensemble within 32-bit offsets of its links; not for sweeps in LDS, nor where a
+        // sweep is one pass (which ends in the first buffer, see enq_sweep)
+        bool ok = 2 * bytes < 4294967296.0 && (cls % 3 != 2 || P->two) && P->n_or > 0;
         if (cls < 9) ok = ok && !P->slab_on[cls % 3];
         else ok = ok && !(P->slab_on[0] && P->slab_on[1] && (!P->two || P->slab_on[2]));
         double one = 0.0, two = 0.0, least = 0.0;  // waves of either form; least: of one launch without halo
@@ -1480,13 +1481,12 @@ hipError_t enq_sweep(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau, int hb
 }
 
 // Before sweeps inside slabs of thickness tau: both link buffers hold the
-// frozen links.
+// frozen links, which are spatial ones.
 hipError_t enq_mirror(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau)
 {
     bool any = false;
-    if (c->P.slab_on[update_class_tau(c, tau)]) return hipSuccess;
     for (int mu = 0; mu < 3; ++mu) any = any || c->P.pair_on[3 * mu + update_class_tau(c, tau)];
-    if (!any && !c->P.pair_on[9]) return hipSuccess;
+    if (!any) return hipSuccess;
     return launch_mirror(L.d_ens, L.n, c->P.precision, c->links, (unsigned)c->Lo.off_alt, 256, st);
 }
 

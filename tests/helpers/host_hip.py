@@ -4,7 +4,7 @@ HIP calls go to host_hip.cpp.  The child runs `code` with these names:
   u1          the binding module
   make(spec)  a context (its workspace address is never read)
   ok(status)  asserts U1ML_OK
-  launches()  [(kernel name, grid, block, lds)] since the last call
+  launches()  [(kernel name, grid, block, lds, mangled name)] since the last call
   put(x)      leaves x (JSON) for the caller
 """
 import json
@@ -43,7 +43,7 @@ def launches():
     def name(mangled):  # _ZN4u1ml<length><name>...
         n, rest = re.match(r"_ZN4u1ml([0-9]+)(.*)", mangled).groups()
         return rest[: int(n)]
-    out = [(name(l.name.decode()), list(l.grid), list(l.block), l.lds) for l in v]
+    out = [(name(l.name.decode()), list(l.grid), list(l.block), l.lds, l.name.decode()) for l in v]
     H.host_hip_clear()
     return out
 

@@ -128,3 +128,27 @@ def test_planning_time_of_equal_lattices():
     base = seconds(2048, (4, 4, 4), 4)
     assert seconds(2048, (8, 8, 8), 16) < 10 * base
     assert seconds(512, (16, 16, 16), 8) < 10 * base
+
+
+@pytest.mark.parametrize("ns,nt,levels", [((24, 24, 24), 8, [(2, 3, 1)]), ((12, 12, 12), 12, [(4, 2, 1), (2, 2, 1)]),
+                                          ((4, 4, 4), 4, [(2, 2, 1)]), ((32, 32, 32), 32, [(2, 1, 1)])])
+@pytest.mark.parametrize("n_or", [0, 1, 2, 3])
+def test_second_link_buffer_only_where_it_is_used(so, ns, nt, levels, n_or):
+    """The other link buffer is reserved, and the frozen links copied to it, only
+    where sweeps update both parities of a spatial direction in one launch."""
+    second, names = host_hip.run(so, f"""
+spec = u1.Spec(ensembles=[u1.Ens({ns}, {nt}, 1.0)], levels={levels}, r=[1], n_or={n_or}, precision=u1.FP32)
+p = u1.plan(spec)
+put(p["ws_bytes"] - sum(p[k + "_bytes"] for k in ("link", "history", "average", "outer", "result", "scratch", "spectral")))
+ctx = make(spec)
+ok(L.u1ml_init_links(ctx, u1.HOT))
+launches()
+ok(L.u1ml_sweeps(ctx, 1))
+ok(L.u1ml_multilevel(ctx))
+put([l[4] for l in launches()])
+ok(L.u1ml_destroy(ctx))
+""")
+    pairs = [n for n in names if "k_pair" in n]
+    assert (second > 0) == bool(pairs)
+    if not any("ELi%dEE" % mu in n for n in pairs for mu in range(3)):
+        assert not any("k_mirror" in n for n in names)
