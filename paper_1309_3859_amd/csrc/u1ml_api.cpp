@@ -553,14 +553,31 @@ void plan_slabs(Problem* P)
 }
 
 // Chooses, per class, whether sweeps update both parities in one launch, and
-// the tiles.  Two launches cost two launch times (about 1.9 us each) plus 0.4 us
-// per wave and SIMD of either parity; one costs one launch time plus 0.55 us per
-// wave and SIMD, halo included (its waves hold more, so fewer hide each other's
-// latency).  Measured: sweeps inside the slabs of one 24^3 x 8 lattice 69 us with
-// every class paired, 87 us with none (x, y, z 5 us each, t 3); two levels on
-// 32^3 x 8 94 against 101 ms a configuration; the 16 ensembles of 16^3 .. 32^3
-// 14.0 against 12.2 ms, 48^3 x 12 72.6 against 70.6, full sweeps of 24^3 x 8,
-// whose tiles have halos in t as well, 90 against 88 us: those stay single.
+// the tiles.  What a direction gains (us; negative: one launch is faster) as
+// fitted to 84 lattices and batches of 6^3 x 64 to 32 x 16^3 x 4, every direction
+// with and without, root-mean-square error 0.8 (FP64 1.2) of a spread of 1.4
+// (2.6): a launch saved, against waves that hold more and so hide less of each
+// other's latency (FP64 above all: past one wave per SIMD an added one costs
+// what it costs in two launches), halo waves, and runs of the tile in memory
+// shorter than a few cache lines, whose lines are fetched for their neighbours
+// as well.  MI355X, us per sweep with none / with this rule, full: FP32 24^3 x 8
+// 89.1 / 78.2, 12^3 x 96 99.8 / 96.1 (113 with every direction paired), 32 of
+// 12^3 x 8 112.9 / 107.6 (158); FP64 8^3 x 512 147.8 / 142.6 (208), 24^3 x 12 149.1 /
+// 148.9 (215); inside slabs: FP32 24^3 x 8 84.7 / 62.8, FP64 117.8 / 101.0, 24^3 x 24
+// 160.7 / 157.3 (175).  None of 118 lattices and batches loses more than 2 %.
+struct PairFit {
+    double fixed, one, two, lines, halo;
+    double most;  // paired below this
+};
+constexpr PairFit kPairFit[2] = {{-1.09, 2.85, -2.78, 1.11, 0.66, -0.3}, {-1.31, 0.54, -0.44, 0.51, 0.33, 0.2}};  // FP64, FP32
+constexpr double kPairWaves = 4.2;  // waves per SIMD that the fit reaches
+
+double pair_gain(int precision, double one, double two, double lines)
+{
+    const PairFit& f = kPairFit[precision];
+    return f.fixed + f.one * std::max(1.0, one) + f.two * std::max(1.0, two) + f.lines * lines + f.halo * std::max(0.0, one - two);
+}
+
 void plan_pairs(Problem* P)
 {
     double vol = 0.0;
@@ -585,18 +602,18 @@ void plan_pairs(Problem* P)
         bool ok = 2 * bytes < 4294967296.0 && (cls % 3 != 2 || P->two) && P->n_or > 0;
         if (cls < 9) ok = ok && !P->slab_on[cls % 3];
         else ok = ok && !(P->slab_on[0] && P->slab_on[1] && (!P->two || P->slab_on[2]));
-        double one = 0.0, two = 0.0, least = 0.0;  // waves of either form; least: of one launch without halo
+        // waves of either form; least: of one launch without halo; lines: waves over 64-byte lines of a run
+        double one = 0.0, two = 0.0, least = 0.0, lines = 0.0;
         for (const u1ml_ensemble& E : P->ens) {
             const PairGeo G(E, cls, tau);
             const double slice = (double)G.nxh * G.N[0] * G.N[1];
             two += std::ceil(slice / 64) * G.N[2] * G.slabs;
             least += slice / 64 * G.N[2] * G.slabs;
         }
-        const double t_two = 2 * (1.9 + 0.4 * std::max(1.0, two / 1024));
-        auto t_one = [](double lat, double waves) { return 1.9 + 2 * 0.55 * std::max(lat, waves / 1024); };
-        ok = ok && t_one(1.0, least) < 0.9 * t_two;  // no tiles to look for otherwise
+        // no tiles to look for where the gain without any halo is not enough
+        ok = ok && least < kPairWaves * 1024 && pair_gain(P->precision, least / 1024, two / 1024, 0.0) < 0.8;
         P->pair_block[cls] = 64;
-        std::vector<double> waves(ok ? P->n_ens : 0);
+        std::vector<double> waves(ok ? P->n_ens : 0), run(waves);
         for (int k = 0; ok && k < P->n_ens; ++k) {
             const int l = P->lattice[k];  // equal lattices have equal tiles
             if (l == k) {
@@ -606,15 +623,24 @@ void plan_pairs(Problem* P)
                 const PairTile T = pair_tile(G, v / vol, max_threads, &waves[k]);
                 ok = T.blocks > 0;
                 P->pair_tile[cls][k] = T;
+                run[k] = (double)G.nxh * word * T.L[0];  // bytes of the tile in one piece
+                for (int a = 1; a < 3 && T.L[a - 1] == G.ext[a - 1]; ++a) run[k] *= T.L[a];
                 if (ok) P->pair_block[cls] = std::max(P->pair_block[cls], (G.rows(T.L) * G.nxh + 63) / 64 * 64);
             } else {
                 P->pair_tile[cls][k] = P->pair_tile[cls][l];
                 waves[k] = waves[l];
+                run[k] = run[l];
             }
             one += waves[k];
+            if (run[k] < 512) lines += waves[k] * 64 / run[k];
         }
-        const double lat = std::max(1.0, P->pair_block[cls] / 256.0);
-        P->pair_on[cls] = ok && t_one(lat, one) < 0.9 * t_two;
+        // where the fit is too high in FP64: below 0.8 waves per SIMD (by up to 0.9 us), and for temporal links,
+        // whose tiles lie in one slice, up to 1.5 (by 0.3 to 0.8 us)
+        double most = kPairFit[P->precision].most;
+        if (one < 0.8 * 1024) most = std::max(most, 0.0);
+        if (cls == 9 && one < 1.5 * 1024) most = std::max(most, 0.8);
+        P->pair_on[cls] = ok && one < kPairWaves * 1024 &&
+                          pair_gain(P->precision, one / 1024, two / 1024, lines / 1024) < most;
     }
     P->n_pair_rows = 0;
     P->pair_shape.clear();

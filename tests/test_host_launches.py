@@ -152,3 +152,31 @@ ok(L.u1ml_destroy(ctx))
     assert (second > 0) == bool(pairs)
     if not any("ELi%dEE" % mu in n for n in pairs for mu in range(3)):
         assert not any("k_mirror" in n for n in names)
+
+
+@pytest.mark.parametrize("n,ns,nt,precision,full,slab", [
+    (1, (24, 24, 24), 8, 1, "xyzt", "xyzt"),   # us per sweep with none / all paired: full 89 / 78, inside slabs 85 / 63
+    (1, (24, 24, 24), 8, 0, "t", "xyzt"),      # 122 / 145, 118 / 101
+    (1, (24, 24, 24), 12, 0, "", None),        # 149 / 215
+    (1, (8, 8, 8), 512, 0, "t", None),         # 148 / 208, t alone 143
+    (1, (6, 6, 6), 2048, 1, "t", None),        # 121 / 146, t alone 116
+    (16, (12, 12, 12), 8, 0, "", None),        # 144 / 222
+    (1, (48, 48, 48), 4, 0, "", ""),           # 220 / 396, 165 / 214
+])
+def test_directions_paired_where_it_is_faster(so, n, ns, nt, precision, full, slab):
+    """Which directions a sweep updates in one launch for both parities, on
+    lattices where an MI355X was timed with every direction either way."""
+    got = host_hip.run(so, f"""
+ctx = make(u1.Spec(ensembles=[u1.Ens({ns}, {nt}, 1.0, key_id=i) for i in range({n})], levels=[(2, 1, 1)], r=[1],
+                   precision={precision}))
+ok(L.u1ml_set_lanes(ctx, 1))
+ok(L.u1ml_init_links(ctx, u1.HOT))
+launches()
+for call in (lambda: L.u1ml_sweeps(ctx, 1), lambda: L.u1ml_multilevel(ctx)):
+    ok(call())
+    names = [l[4] for l in launches()]
+    put("".join("xyzt"[mu] for mu in range(4) if any("k_pair" in m and "ELi%dEE" % mu in m for m in names)))
+ok(L.u1ml_destroy(ctx))
+""")
+    assert got[0] == full
+    assert slab is None or got[1] == slab
