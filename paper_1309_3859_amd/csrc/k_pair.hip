@@ -28,29 +28,6 @@
 
 namespace u1ml {
 
-// Byte offsets of a site and its eight neighbours within one (direction,
-// parity) array.
-struct SiteNb {
-    unsigned c, p[4], m[4];
-};
-
-// The angles of the two staples of link (x, MU) in the plane (MU, NU), as the
-// one-parity kernel names them; SKIP: not th_mu(x +- nu) (v[1] and v[5]).
-template <typename real, int MU, int NU, bool SKIP>
-__device__ inline void gather_nb(const LinkBuf<real>& lb, unsigned vhb, const unsigned* src, const SiteNb& nb, int p,
-                                 real* v)
-{
-    const unsigned pp = (unsigned)p * vhb, pq = vhb - pp;
-    const unsigned nu_p = NU * 2 * vhb + pp + src[NU], nu_q = NU * 2 * vhb + pq + src[NU];
-    const unsigned mu_q = MU * 2 * vhb + pq + src[MU];
-    v[0] = lb.ld(nb.p[MU], nu_q);
-    if (!SKIP) v[1] = lb.ld(nb.p[NU], mu_q);
-    v[2] = lb.ld(nb.c, nu_p);
-    v[3] = lb.ld(nb.m[NU], nu_q);
-    v[4] = lb.ld(nb.p[MU] + (nb.m[NU] - nb.c), nu_p);
-    if (!SKIP) v[5] = lb.ld(nb.m[NU], mu_q);
-}
-
 template <typename real, int KIND, int MU>
 __global__ void __launch_bounds__(kPairThreads<real>)
     k_pair(const EnsDesc* __restrict__ ens, const PairBlock* __restrict__ blocks, const PairRow* __restrict__ rows,

@@ -9,7 +9,8 @@
 // every ensemble of the batch in the same launch: work-group b reads its time
 // slice, its stretch of that slice and the geometry from one
 // record (UpdBlock), the records dealt to the 8 XCDs in contiguous stretches
-// and, within an ensemble, ordered time slice fastest (set by the host).
+// and, within an ensemble, ordered time slice fastest (set by the host); where
+// slices are short, a work-group holds several of them (SpanBlock).
 // The staple of a link reads 18 angles: 12 of the other parity (coalesced,
 // shifted by one site), 6 of the same parity; none of them is written by the
 // phase, so the update is in place.  The all-link kernels below (start,
@@ -18,6 +19,7 @@
 #include <hip/hip_ext.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "link_update.hpp"
 #include "u1ml_internal.hpp"
@@ -103,6 +105,36 @@ __device__ inline void gather_slice(const LinkBuf<real>& lb, unsigned vhb, const
     v[5] = lb.ld(o_mn, mu_q + s_mn);
 }
 
+// Byte offsets of work-item tid's site and its neighbours for a work-group over
+// several time slices: t differs within a wave, so it is part of the offsets.
+template <typename real>
+struct SpanSite : SiteNb {
+    int odd_mask;  // all ones where x is odd
+
+    __device__ inline SpanSite(const SpanBlock& B, int tid, int par)
+    {
+        constexpr int w = sizeof(real);
+        const int j = B.i0 + tid;
+        const int ks = B.slice >= 1024 ? (int)(j >= B.slice) : fdiv_small(j, B.inv_slice);
+        const int i = j - ks * B.slice;
+        const int t = B.t0 + ks + (B.m ? (B.r0 + ks) / B.m : 0);
+        const int row = fdiv(i, B.nxh, B.inv_nxh), xh = i - row * B.nxh;
+        const int z = fdiv(row, B.ny, B.inv_ny), y = row - z * B.ny;
+        odd_mask = -((t + par + y + z) & 1);
+        const int sy = B.nxh * w, sz = sy * B.ny, st = B.slice * w, v = i * w;
+        const unsigned at = (unsigned)t * (unsigned)st;
+        c = at + (unsigned)v;
+        p[0] = c + (unsigned)(odd_mask & (xh == B.nxh - 1 ? w - sy : w));
+        m[0] = c + (unsigned)(~odd_mask & (xh == 0 ? sy - w : -w));
+        p[1] = c + (unsigned)(y == B.ny - 1 ? sy - sz : sy);
+        m[1] = c + (unsigned)(y == 0 ? sz - sy : -sy);
+        p[2] = c + (unsigned)(v >= st - sz ? sz - st : sz);
+        m[2] = c + (unsigned)(v < sz ? st - sz : -sz);
+        p[3] = t == B.nt - 1 ? (unsigned)v : c + (unsigned)st;
+        m[3] = t == 0 ? (unsigned)(B.nt - 1) * (unsigned)st + (unsigned)v : c - (unsigned)st;
+    }
+};
+
 // One work-item per link of one checkerboard phase.  What bounds it: memory on
 // lattices beyond the caches, launch and instruction latency on small ones (a
 // dependent launch costs 1.85 us with 18 loads and a store in it; each further
@@ -112,39 +144,59 @@ __device__ inline void gather_slice(const LinkBuf<real>& lb, unsigned vhb, const
 // slice.
 // WG: the heatbath's pending links are finished by work-group instead of by
 // wave (hb_retry_wg).
-template <typename real, int KIND, int MU, bool WG>
-__global__ void __launch_bounds__(1024) k_update(const EnsDesc* __restrict__ ens, const UpdBlock* __restrict__ blocks,
-                                                 real* __restrict__ links, const uint32_t* __restrict__ upd,
-                                                 int pass_offset, int parity, unsigned src0, unsigned src1,
-                                                 unsigned src2, unsigned src3, double metro_delta)
+// SPAN: a work-group goes on into the next time slices (SpanBlock), where slices
+// do not fill whole waves.
+template <typename real, int KIND, int MU, bool WG, bool SPAN>
+__global__ void __launch_bounds__(1024)
+    k_update(const EnsDesc* __restrict__ ens, const std::conditional_t<SPAN, SpanBlock, UpdBlock>* __restrict__ blocks,
+             real* __restrict__ links, const uint32_t* __restrict__ upd, int pass_offset, int parity, unsigned src0,
+             unsigned src1, unsigned src2, unsigned src3, double metro_delta)
 {
     constexpr unsigned w = sizeof(real);
     extern __shared__ __align__(16) unsigned char queue_bytes[];
     // the whole record before the first branch: its loads are one round trip
-    UpdBlock B = blocks[blockIdx.x];
-    asm volatile("" : "+s"(B.i0), "+s"(B.x0), "+s"(B.t0), "+s"(B.nxh), "+s"(B.inv_nxh), "+s"(B.link_off));
+    auto B = blocks[blockIdx.x];
+    int n;
+    if constexpr (SPAN) {
+        asm volatile("" : "+s"(B.i0), "+s"(B.t0), "+s"(B.nxh), "+s"(B.inv_nxh), "+s"(B.link_off));
+        n = B.n;
+    } else {
+        asm volatile("" : "+s"(B.i0), "+s"(B.x0), "+s"(B.t0), "+s"(B.nxh), "+s"(B.inv_nxh), "+s"(B.link_off));
+        n = B.slice - B.i0;
+    }
     const EnsDesc& E = ens[B.e];
-    const int tid = (int)threadIdx.x, n = B.slice - B.i0;
+    const int tid = (int)threadIdx.x;
     if ((WG ? 0 : tid & ~63) >= n) return;  // no link in this wave (work-group)
     const bool active = tid < n;
-    const SliceNb<real> nb(B, active ? tid : 0, parity);
+    const std::conditional_t<SPAN, SpanSite<real>, SliceNb<real>> nb(B, active ? tid : 0, parity);
     const LinkBuf<real> lb(links + B.link_off);
-    const unsigned vhb = (unsigned)B.vh * w, t0 = B.t0 * w, tp = B.tp * w, tm = B.tm * w;
+    const unsigned vhb = (unsigned)B.vh * w;
     const unsigned src[4] = {src0, src1, src2, src3};
 
     // every load of the update is issued before any arithmetic
     real v[3][6];
-    gather_slice<real, MU, Nu<MU, 0>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[0]);
-    gather_slice<real, MU, Nu<MU, 1>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[1]);
-    gather_slice<real, MU, Nu<MU, 2>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[2]);
-    const unsigned self = (MU * 2 + (unsigned)parity) * vhb + src[MU] + t0;
+    unsigned self = (MU * 2 + (unsigned)parity) * vhb + src[MU];
+    uint32_t half;  // half index of the link's site
+    if constexpr (SPAN) {
+        gather_nb<real, MU, Nu<MU, 0>::v, false>(lb, vhb, src, nb, parity, v[0]);
+        gather_nb<real, MU, Nu<MU, 1>::v, false>(lb, vhb, src, nb, parity, v[1]);
+        gather_nb<real, MU, Nu<MU, 2>::v, false>(lb, vhb, src, nb, parity, v[2]);
+        half = nb.c / w;
+    } else {
+        const unsigned t0 = B.t0 * w, tp = B.tp * w, tm = B.tm * w;
+        gather_slice<real, MU, Nu<MU, 0>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[0]);
+        gather_slice<real, MU, Nu<MU, 1>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[1]);
+        gather_slice<real, MU, Nu<MU, 2>::v>(lb, vhb, src, t0, tp, tm, nb, parity, v[2]);
+        self += t0;
+        half = (uint32_t)(B.i0 + tid) + B.t0;
+    }
     real old = real(0);
     if (KIND != 0) old = lb.ld(nb.c, self);
 
     // the first Philox block depends only on the link's id and the counter:
     // formed here, it runs while the link angles are still in flight
-    // canonical site x + Nx (y + Ny (z + Nz t)) = 2 (i + t0) + odd
-    const uint32_t lid = (uint32_t)MU + 8u * ((uint32_t)(B.i0 + tid) + B.t0) + (nb.odd_mask & 4u);
+    // canonical site x + Nx (y + Ny (z + Nz t)) = 2 half + odd
+    const uint32_t lid = (uint32_t)MU + 8u * half + (nb.odd_mask & 4u);
     const uint32_t ctr = KIND == 1 ? 0u : upd[B.e] + (uint32_t)pass_offset;
     Block4 b0{};
     if (KIND != 1) b0 = philox4x32_10(lid, ctr, 0u, KIND == 2 ? DOM_METRO : DOM_HB, E.seed, E.key_id);
@@ -169,28 +221,29 @@ __global__ void __launch_bounds__(1024) k_update(const EnsDesc* __restrict__ ens
 
 // With a start/stop event pair the launch goes through hipExtLaunchKernelGGL,
 // whose events take the dispatch's own begin and end timestamps.
-template <typename real, int KIND, int MU, bool WG>
+template <typename real, int KIND, int MU, bool WG, bool SPAN>
 static void launch_update_mu(const UpdLaunch& a)
 {
     const dim3 g(a.total_blocks), b(a.block);
     const size_t lds = KIND != 0 ? 0 : (WG ? 64 + sizeof(HbWgQ<real>) * b.x : sizeof(HbQ<real>) * b.x);
+    const auto* blocks = reinterpret_cast<const std::conditional_t<SPAN, SpanBlock, UpdBlock>*>(a.d_blocks);
     if (a.ev_start)
-        hipExtLaunchKernelGGL((k_update<real, KIND, MU, WG>), g, b, lds, a.st, a.ev_start, a.ev_stop, 0, a.d_ens,
-                              a.d_blocks, (real*)a.links, a.d_upd, a.pass_offset, a.parity, a.src[0], a.src[1],
+        hipExtLaunchKernelGGL((k_update<real, KIND, MU, WG, SPAN>), g, b, lds, a.st, a.ev_start, a.ev_stop, 0, a.d_ens,
+                              blocks, (real*)a.links, a.d_upd, a.pass_offset, a.parity, a.src[0], a.src[1],
                               a.src[2], a.src[3], a.metro_delta);
     else
-        hipLaunchKernelGGL((k_update<real, KIND, MU, WG>), g, b, lds, a.st, a.d_ens, a.d_blocks, (real*)a.links,
+        hipLaunchKernelGGL((k_update<real, KIND, MU, WG, SPAN>), g, b, lds, a.st, a.d_ens, blocks, (real*)a.links,
                            a.d_upd, a.pass_offset, a.parity, a.src[0], a.src[1], a.src[2], a.src[3], a.metro_delta);
 }
 
-template <typename real, int KIND, bool WG = false>
+template <typename real, int KIND, bool WG, bool SPAN>
 static void launch_update_t(const UpdLaunch& a)
 {
     switch (a.mu) {
-    case 0: launch_update_mu<real, KIND, 0, WG>(a); break;
-    case 1: launch_update_mu<real, KIND, 1, WG>(a); break;
-    case 2: launch_update_mu<real, KIND, 2, WG>(a); break;
-    default: launch_update_mu<real, KIND, 3, WG>(a); break;
+    case 0: launch_update_mu<real, KIND, 0, WG, SPAN>(a); break;
+    case 1: launch_update_mu<real, KIND, 1, WG, SPAN>(a); break;
+    case 2: launch_update_mu<real, KIND, 2, WG, SPAN>(a); break;
+    default: launch_update_mu<real, KIND, 3, WG, SPAN>(a); break;
     }
 }
 
@@ -203,14 +256,14 @@ static void launch_update_t(const UpdLaunch& a)
 template <typename real>
 constexpr int kHbWgBlocks = sizeof(real) == 8 ? 640 : 4096;
 
-template <typename real>
+template <typename real, bool SPAN>
 static void launch_update_r(const UpdLaunch& a)
 {
     const bool wg = a.total_blocks >= kHbWgBlocks<real> && a.block <= 512;
     switch (a.kind) {
-    case 0: wg ? launch_update_t<real, 0, true>(a) : launch_update_t<real, 0>(a); break;
-    case 1: launch_update_t<real, 1>(a); break;
-    default: launch_update_t<real, 2>(a); break;
+    case 0: wg ? launch_update_t<real, 0, true, SPAN>(a) : launch_update_t<real, 0, false, SPAN>(a); break;
+    case 1: launch_update_t<real, 1, false, SPAN>(a); break;
+    default: launch_update_t<real, 2, false, SPAN>(a); break;
     }
 }
 
@@ -219,9 +272,9 @@ hipError_t launch_update(const UpdLaunch& a)
     if (a.total_blocks <= 0) return hipSuccess;
     if ((a.ev_start == nullptr) != (a.ev_stop == nullptr) || a.kind < 0 || a.kind > 2) return hipErrorInvalidValue;
     if (a.precision == 0)
-        launch_update_r<double>(a);
+        a.span ? launch_update_r<double, true>(a) : launch_update_r<double, false>(a);
     else
-        launch_update_r<float>(a);
+        a.span ? launch_update_r<float, true>(a) : launch_update_r<float, false>(a);
     return hipGetLastError();
 }
 

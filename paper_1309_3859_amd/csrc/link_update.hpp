@@ -39,6 +39,29 @@ struct LinkBuf {
     }
 };
 
+// Byte offsets of a site and its eight neighbours within one (direction,
+// parity) array.
+struct SiteNb {
+    unsigned c, p[4], m[4];
+};
+
+// The angles of the two staples of link (x, MU) in the plane (MU, NU), as the
+// one-parity kernel names them; SKIP: not th_mu(x +- nu) (v[1] and v[5]).
+template <typename real, int MU, int NU, bool SKIP>
+__device__ inline void gather_nb(const LinkBuf<real>& lb, unsigned vhb, const unsigned* src, const SiteNb& nb, int p,
+                                 real* v)
+{
+    const unsigned pp = (unsigned)p * vhb, pq = vhb - pp;
+    const unsigned nu_p = NU * 2 * vhb + pp + src[NU], nu_q = NU * 2 * vhb + pq + src[NU];
+    const unsigned mu_q = MU * 2 * vhb + pq + src[MU];
+    v[0] = lb.ld(nb.p[MU], nu_q);
+    if (!SKIP) v[1] = lb.ld(nb.p[NU], mu_q);
+    v[2] = lb.ld(nb.c, nu_p);
+    v[3] = lb.ld(nb.m[NU], nu_q);
+    v[4] = lb.ld(nb.p[MU] + (nb.m[NU] - nb.c), nu_p);
+    if (!SKIP) v[5] = lb.ld(nb.m[NU], mu_q);
+}
+
 // Quotient a / b of a small index by an extent: 0 <= a < b + 2^10 and b <=
 // 2^22, or a < 2^21; inv_b = 1/b rounded.  (a + 1/2) / b lies at least 1/(2b) from an
 // integer, further than the rounding of the reciprocal and of the one product,

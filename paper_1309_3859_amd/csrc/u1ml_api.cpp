@@ -1009,6 +1009,7 @@ struct Lane {
     PairBlock* d_pmap[kPairClasses] = {};
     std::vector<PairBlock> h_pmap[kPairClasses];  // work-groups of the both-parities launches
     int upd_grid[kUpdateClasses] = {0, 0, 0, 0};  // grid size of each update class (multiple of 8)
+    bool span[kUpdateClasses] = {};               // the class's records are SpanBlocks
     int max_s_in = 1;                              // largest number of inner slabs in the lane
     hipStream_t stream = nullptr;
     hipGraphExec_t g_sweep = nullptr, g_ml = nullptr;
@@ -1106,11 +1107,24 @@ void build_update_tabs(const u1ml_ctx* c, Lane& L)
     const int skip[kUpdateClasses] = {0, 0, P.tau_i > 1 ? P.tau_i : 0, P.tau_o > 1 ? P.tau_o : 0};
     std::vector<long long> items(n);
     for (int cls = 0; cls < kUpdateClasses; ++cls) {
+        auto slices = [&](const EnsDesc& E) { return (long long)(skip[cls] ? E.nt - E.nt / skip[cls] : E.nt); };
+        // Work-groups that span time slices where slices leave more than a tenth of
+        // their waves' work-items idle and the launch has more waves than SIMDs (one
+        // slice a work-group has shorter addresses: below that, latency counts).  Full
+        // sweeps, us, slice by slice / spanning: FP32 4^3 x 16384 367 / 167, 6^3 x 4096
+        // 186 / 165, FP64 4^3 x 4096 214 / 175, 2^3 x 131072 6121 / 351.
+        long long by_slice = 0, packed = 0;
+        for (const EnsDesc& E : L.h_ens) {
+            const long long slice = (long long)E.nxh * E.ny * E.nz;
+            by_slice += slices(E) * ((slice + 63) / 64);
+            packed += (slices(E) * slice + 63) / 64;
+        }
+        L.span[cls] = by_slice > 4 * 256 && 10 * by_slice > 11 * packed;
         for (int e = 0; e < n; ++e) {
             const EnsDesc& E = L.h_ens[e];
             const long long slice = (long long)E.nxh * E.ny * E.nz;
-            const long long ns = skip[cls] ? E.nt - E.nt / skip[cls] : E.nt;
-            items[e] = ns * ((slice + c->block - 1) / c->block);
+            items[e] = L.span[cls] ? (slices(E) * slice + c->block - 1) / c->block
+                                   : slices(E) * ((slice + c->block - 1) / c->block);
         }
         build_tab(L, kTabUpd + cls, items, 1);
     }
@@ -1129,6 +1143,33 @@ void build_update_tabs(const u1ml_ctx* c, Lane& L)
         logical.reserve(total);
         for (int e = 0; e < n; ++e) {
             const EnsDesc& E = L.h_ens[e];
+            if (L.span[cls]) {
+                SpanBlock r;
+                std::memset(&r, 0, sizeof r);
+                r.e = E.res_index;
+                r.m = skip[cls] ? skip[cls] - 1 : 0;
+                r.nxh = E.nxh;
+                r.ny = E.ny;
+                r.slice = E.nxh * E.ny * E.nz;
+                r.vh = E.vh;
+                r.nt = E.nt;
+                r.inv_nxh = E.inv_nxh;
+                r.inv_ny = E.inv_ny;
+                r.inv_slice = E.inv_slice;
+                r.link_off = E.link_off;
+                const long long links = (long long)r.slice * (r.m ? E.nt - E.nt / skip[cls] : E.nt);
+                for (long long k = 0; k < links; k += c->block) {
+                    const int u = (int)(k / r.slice);  // the first link's slice among the updated ones
+                    r.i0 = (int)(k % r.slice);
+                    r.n = (int)std::min<long long>(c->block, links - k);
+                    r.r0 = r.m ? u % r.m : 0;
+                    r.t0 = r.m ? u / r.m * skip[cls] + 1 + r.r0 : u;
+                    UpdBlock b;
+                    std::memcpy(&b, &r, sizeof b);
+                    logical.push_back(b);
+                }
+                continue;
+            }
             UpdBlock r = pad;
             r.slice = E.nxh * E.ny * E.nz;
             r.nxh = E.nxh;
@@ -1172,7 +1213,14 @@ void build_update_tabs(const u1ml_ctx* c, Lane& L)
         }
         // padding blocks: a record that starts past its slice (every work-item inactive)
         UpdBlock idle = total > 0 ? logical[total - 1] : pad;
-        idle.i0 = idle.slice;
+        if (L.span[cls]) {
+            SpanBlock none;
+            std::memcpy(&none, &idle, sizeof none);
+            none.n = 0;
+            std::memcpy(&idle, &none, sizeof idle);
+        } else {
+            idle.i0 = idle.slice;
+        }
         for (int phys = 0; phys < per * kXcds; ++phys) {
             const int lg = (phys % kXcds) * per + phys / kXcds;
             L.h_bmap[cls].push_back(lg < total ? logical[lg] : idle);
@@ -1461,7 +1509,7 @@ hipError_t enq_phase(u1ml_ctx* c, const Lane& L, hipStream_t st, int kind, int m
     bool ok;
     const int cls = update_class(c, mu, tau, &ok);
     if (!ok) return hipErrorInvalidValue;
-    return launch_update(UpdLaunch{c->whole.d_ens, L.bmap_dev(cls), L.upd_grid[cls], c->block, c->P.precision, c->links,
+    return launch_update(UpdLaunch{c->whole.d_ens, L.bmap_dev(cls), L.span[cls], L.upd_grid[cls], c->block, c->P.precision, c->links,
                                    c->d_upd, pass_offset, kind, mu, parity, {src[0], src[1], src[2], src[3]},
                                    c->P.metro_delta, st, ev_start, ev_stop});
 }

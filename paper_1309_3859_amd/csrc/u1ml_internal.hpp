@@ -49,6 +49,19 @@ struct alignas(64) UpdBlock {
 };
 static_assert(sizeof(UpdBlock) == 64, "UpdBlock is one 64-byte scalar load");
 
+// One work-group of an update launch over short time slices: n links, from link
+// i0 of slice t0 on, over the slices that the phase updates (m in a row, the one
+// after them left out; m = 0: all), of which t0 is number r0 of its row.
+struct alignas(64) SpanBlock {
+    int e;  // the ensemble (problem order)
+    int i0, n;
+    int t0, r0, m;
+    int nxh, ny, slice, vh, nt;
+    float inv_nxh, inv_ny, inv_slice;
+    long long link_off;
+};
+static_assert(sizeof(SpanBlock) == sizeof(UpdBlock), "the two kinds of record share their tables");
+
 // One work-group of a launch that updates both parities of one direction: its
 // tile's origin, its work-items (rows of the tile with and without the halo,
 // times Nx/2) and its first entry in the table of rows.
@@ -196,6 +209,7 @@ hipError_t launch_init_links(const EnsDesc* d_ens, const int* d_bstart_all, int 
 struct UpdLaunch {
     const EnsDesc* d_ens;  // problem order
     const UpdBlock* d_blocks;
+    bool span;  // the records are SpanBlocks
     int total_blocks, block, precision;
     void* links;
     const uint32_t* d_upd;

@@ -126,3 +126,65 @@ def test_sweeps_equal_their_phases(ns, nt, levels, n_or, precision, update):
     for e in range(len(ens)):
         assert np.array_equal(a.links(e), b.links(e))
         assert a.counter(e) == 3 + offset
+
+
+# slices of 4, 32 and 108 links, enough of them that work-groups span slices
+# (more waves than SIMDs, a tenth of their work-items idle slice by slice);
+# 1100 slices are no whole number of work-groups
+SHORT = [((2, 2, 2), 1100), ((4, 4, 4), 1100), ((6, 6, 6), 620)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ns,nt", SHORT)
+def test_short_slices_match_oracle(ns, nt):
+    """Work-groups over several time slices: overrelaxation of every direction
+    and parity, all links and inside slabs of 2 and 4, with the bound of
+    test_overrelaxation_matches_oracle."""
+    import bench
+    from oracle import oracle as O
+    from paper_1309_3859_amd import u1ml
+
+    V = int(np.prod(ns)) * nt
+    spec = u1ml.Spec(ensembles=[u1ml.Ens(ns, nt, 1.1, seed=7, key_id=1)], levels=[(4, 1, 1), (2, 1, 1)], r=[1])
+    ctx = u1ml.Context(spec)
+    ref = O.Lattice(4, list(ns) + [nt], 1.1, seed=7, key_id=1)
+    th0 = random_links(V, 5)
+    size = bench.staple_abs(th0, ns, nt).reshape(-1)
+    for mu, p, tau in itertools.product(range(4), (0, 1), (0, 2, 4)):
+        print("phase", ns, nt, mu, p, tau, flush=True)
+        ctx.set_links(th0)
+        ref.set_links(th0)
+        ctx.phase(1, mu, p, tau)
+        ref.phase(1, mu, p, tau)
+        d = circ_dist(ctx.links(0), ref.links())
+        assert (d * size).max() < 1e-13
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ns,nt", SHORT)
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("update", [0, 1])
+def test_short_slices_equal_sweeps_in_lds(ns, nt, precision, update):
+    """One launch per phase over short slices against sweeps inside slabs in
+    LDS, bit for bit: every work-group size, heatbath retries by wave and (with
+    small work-groups in FP64) by work-group, Metropolis, a lattice of longer
+    slices in the batch."""
+    from paper_1309_3859_amd import u1ml
+
+    print("short slices", ns, nt, precision, update, flush=True)
+    ens = [u1ml.Ens(ns, nt, 1.05, seed=3, key_id=0), u1ml.Ens((6, 8, 10), 4, 0.9, seed=3, key_id=1)]
+    spec = u1ml.Spec(ensembles=ens, levels=[(2, 1, 1)], r=[1], precision=precision, n_or=2, update=update,
+                     metro_delta=0.7)
+    a = u1ml.Context(spec)
+    a.init_links(u1ml.HOT)
+    a.multilevel()
+    for block in (64, 256, 1024):
+        b = u1ml.Context(spec)
+        b.set_block(block)
+        b.init_links(u1ml.HOT)
+        for k in range(3):
+            kind = (u1ml.METROPOLIS if update else u1ml.HEATBATH) if k == 0 else u1ml.OVERRELAX
+            for mu, p in itertools.product(range(4), (0, 1)):
+                b.phase(kind, mu, p, 2, 0)
+        for e in range(2):
+            assert np.array_equal(a.links(e), b.links(e)), (block, e)
