@@ -526,6 +526,15 @@ void pair_for_tiles(const Problem& P, int cls, int k, F f)
 // measurement each, 8^3 (512) 55 / 45, 10^3 (1000) 65 / 59, 12^3 (1728) 63 / 83;
 // FP64 4^4 full 80 / 52, 6^3 x 4 (432) 94 / 83, 8^3 x 4 (1024) 92 / 157; slabs of
 // 8^3 (512) 90 / 78, 10^3 (1000) 99 / 121.
+// Not for batches that fill the device either way, where a launch per direction
+// hides more latency than work-groups that stand at their barriers, and no wave
+// idles for a slab that does not fill it.  us per sweep otherwise / in LDS, FP64
+// (whose compute units hold 16 of these waves): slabs of 8^3 512 / 768 / 1024 of
+// them 151 / 184 / 223, 124 / 185 / 245; 1024 / 2048 of 6^3 152 / 219, 136 / 258; full
+// 6^3 x 4, 768 / 1024 lattices 280 / 306, 240 / 323; 4096 / 8192 slabs of 2 x 4 x 4
+// 137 / 176, 138 / 259; rows of at most 2 half sites are slow otherwise: 8192 / 32768
+// slabs of 4^3 204 / 518, 144 / 513.  FP32 full 8 x 8 x 16 x 2, 1536 / 3072 lattices 333 /
+// 578, 311 / 617; 8192 / 16384 slabs of 2 x 4 x 4 96 / 137, 89 / 164.
 void plan_slabs(Problem* P)
 {
     const int word = P->precision == U1ML_FP64 ? 8 : 4;
@@ -535,17 +544,26 @@ void plan_slabs(Problem* P)
         const int tau = cls == 0 ? 0 : (cls == 1 ? P->tau_i : P->tau_o);
         bool ok = cls != 2 || P->two;
         size_t lds = 0, blocks = 0;
-        int threads = 64;
+        int threads = 64, nxh = 1;
+        double links_all = 0.0;  // of the largest phase, every work-group
         for (const u1ml_ensemble& E : P->ens) {
             const double links = (double)E.ns[0] / 2 * E.ns[1] * E.ns[2] * (tau ? tau : E.nt);  // of the largest phase
             ok = ok && links <= max_threads;
             if (ok) threads = std::max(threads, ((int)links + 63) / 64 * 64);
             blocks += tau ? E.nt / tau : 1;
+            links_all += links * (tau ? E.nt / tau : 1);
+            nxh = std::max(nxh, E.ns[0] / 2);
         }
         for (const u1ml_ensemble& E : P->ens)
             if (ok)
                 lds = std::max(lds, slab_lds(E.ns[0] / 2 * E.ns[1] * E.ns[2], tau ? tau + 1 : E.nt, threads, hb, word));
-        P->slab_on[cls] = ok && lds <= kSlabLds;
+        const int wg = threads / 64;
+        const double waves = (double)blocks * wg, filled = links_all / 64;
+        const double held = waves * 16 / (16 / wg * wg);  // waves and the places that they leave empty
+        const bool few = P->precision == U1ML_FP64
+                             ? held <= (held > 4 * filled ? 1024 : 6144) || (held <= 1.1 * filled && nxh <= 2)
+                             : (cls == 0 && threads > 768 ? waves <= 24576 : waves <= 8192 || waves <= 1.9 * filled);
+        P->slab_on[cls] = ok && lds <= kSlabLds && few;
         P->slab_block[cls] = threads;
         P->slab_lds_bytes[cls] = P->slab_on[cls] ? lds : 0;
         P->slab_blocks[cls] = P->slab_on[cls] ? blocks : 0;

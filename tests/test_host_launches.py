@@ -180,3 +180,34 @@ ok(L.u1ml_destroy(ctx))
 """)
     assert got[0] == full
     assert slab is None or got[1] == slab
+
+
+@pytest.mark.parametrize("n,ns,nt,precision,full,slab", [
+    # us per sweep in LDS / otherwise
+    (1, (4, 4, 4), 4, 0, True, True),
+    (4096, (4, 4, 4), 8, 0, True, True),     # full 528 / 582, slabs 513 / 518
+    (256, (8, 8, 8), 4, 0, False, True),     # slabs 124 / 151
+    (512, (8, 8, 8), 4, 0, False, False),    # 245 / 223
+    (2048, (8, 8, 8), 4, 0, False, False),   # 1056 / 944
+    (512, (6, 6, 6), 8, 0, False, False),    # 258 / 219
+    (768, (6, 6, 6), 4, 0, True, True),      # full 240 / 280, slabs 193 / 227
+    (1024, (6, 6, 6), 4, 0, False, False),   # 323 / 306, 256 / 221
+    (1024, (4, 6, 4), 8, 0, False, False),   # 326 / 301, 250 / 222
+    (1024, (2, 4, 4), 16, 0, True, False),   # 154 / 214, 259 / 176
+    (2048, (2, 4, 4), 16, 1, True, False),   # 97 / 162, 164 / 137
+    (1024, (8, 8, 16), 2, 1, True, True),    # full 208 / 217
+    (3072, (8, 8, 16), 2, 1, False, True),   # full 617 / 578, slabs 464 / 490
+])
+def test_sweeps_in_lds_where_it_is_faster(so, n, ns, nt, precision, full, slab):
+    """Which sweeps run in LDS, on batches where an MI355X was timed with both."""
+    got = host_hip.run(so, f"""
+ctx = make(u1.Spec(ensembles=[u1.Ens({ns}, {nt}, 1.0, key_id=i) for i in range({n})], levels=[(2, 1, 1)], r=[1],
+                   precision={precision}))
+ok(L.u1ml_init_links(ctx, u1.HOT))
+launches()
+for call in (lambda: L.u1ml_sweeps(ctx, 1), lambda: L.u1ml_multilevel(ctx)):
+    ok(call())
+    put(any(l[0] == "k_slab" for l in launches()))
+ok(L.u1ml_destroy(ctx))
+""")
+    assert got == [full, slab]
