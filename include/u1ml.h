@@ -322,8 +322,8 @@ u1ml_status u1ml_set_block(u1ml_ctx* ctx, int block);
  * lanes side by side fill the device where one does not, and the
  * arithmetic-bound heatbath phases of one lane overlap the memory-bound
  * overrelaxation phases of another.  n_lanes = 1 runs the whole batch on the
- * context's stream.  Default: 2 lanes for batches of at least 1.3 million
- * sites (FP64 links 0.7 million), else 1.  Every ensemble's
+ * context's stream.  Default: 2 lanes for batches of at least 1 million
+ * sites (FP64 links 0.5 million), else 1.  Every ensemble's
  * links and estimates are bit-identical for every lane count.  EINVAL for
  * n_lanes outside 1..4 or above the number of ensembles. */
 u1ml_status u1ml_set_lanes(u1ml_ctx* ctx, int n_lanes);

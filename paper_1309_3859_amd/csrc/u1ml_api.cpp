@@ -69,16 +69,16 @@ constexpr int kXcds = 8;  // accelerator complex dies of an MI355X, each with it
 constexpr int kMaxLanes = 4;  // streams that sweeps and configurations are spread over
 // Lanes a context starts with, by the batch's sites: two where a phase of half
 // the batch still fills the device, else one (a second stream costs more than
-// its overlap gains, and more than two never gain).  MI355X, us per sweep inside
-// slabs with 1 / 2 / 4 lanes: FP32 8 x 24^3 x 8 (0.88M sites) 122 / 140 / 173,
-// 16 x 24^3 x 8 (1.77M) 187 / 174 / 200, 32 x 24^3 x 8 329 / 280 / 300; FP64
-// 8 x 24^3 x 4 (0.44M) 164 / 177 / 207, 8 x 24^3 x 8 250 / 222 / 240,
-// 16 x 24^3 x 8 418 / 388 / 388.
+// its overlap gains, and more than two never gain).  MI355X, us per sweep, full /
+// inside slabs, 1 lane and 2 lanes: FP32 8 x 24^3 x 8 (0.88M sites) 147 / 111, 158 /
+// 133; 32 x 16^3 x 8 (1.05M) 161 / 120, 151 / 119; 256 x 8^3 x 8 160 / 72, 154 / 74;
+// 16 x 24^3 x 8 (1.77M) 225 / 165, 193 / 157; FP64 8 x 24^3 x 4 (0.44M) 214 / 158, 193 /
+// 169; 16 x 16^3 x 8 (0.52M) 218 / 160, 195 / 154; 8 x 24^3 x 8 303 / 235, 288 / 220.
 int default_lanes(const std::vector<u1ml_ensemble>& ens, int precision)
 {
     double sites = 0.0;
     for (const u1ml_ensemble& E : ens) sites += (double)E.ns[0] * E.ns[1] * E.ns[2] * E.nt;
-    return ens.size() > 1 && sites >= (precision == U1ML_FP64 ? 0.7e6 : 1.3e6) ? 2 : 1;
+    return ens.size() > 1 && sites >= (precision == U1ML_FP64 ? 0.5e6 : 1.0e6) ? 2 : 1;
 }
 
 // Tile of a both-parities launch (k_pair): core rows along y, z, t.

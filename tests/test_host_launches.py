@@ -211,3 +211,23 @@ for call in (lambda: L.u1ml_sweeps(ctx, 1), lambda: L.u1ml_multilevel(ctx)):
 ok(L.u1ml_destroy(ctx))
 """)
     assert got == [full, slab]
+
+
+@pytest.mark.parametrize("n,ns,nt,precision,lanes", [
+    # us per sweep, full / inside slabs, with 1 and with 2 lanes
+    (8, (24, 24, 24), 8, 1, 1),     # 147 / 111, 158 / 133
+    (256, (8, 8, 8), 8, 1, 2),      # 160 / 72, 154 / 74
+    (32, (16, 16, 16), 8, 1, 2),    # 161 / 120, 151 / 119
+    (8, (24, 24, 24), 4, 0, 1),     # 214 / 158, 193 / 169
+    (16, (16, 16, 16), 8, 0, 2),    # 218 / 160, 195 / 154
+])
+def test_lanes_where_two_are_faster(so, n, ns, nt, precision, lanes):
+    (got,) = host_hip.run(so, f"""
+ctx = make(u1.Spec(ensembles=[u1.Ens({ns}, {nt}, 1.0, key_id=i) for i in range({n})], levels=[(2, 1, 1)], r=[1],
+                   precision={precision}))
+k = C.c_int()
+ok(L.u1ml_get_lanes(ctx, C.byref(k)))
+put(k.value)
+ok(L.u1ml_destroy(ctx))
+""")
+    assert got == lanes
