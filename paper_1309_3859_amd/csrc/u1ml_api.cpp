@@ -657,6 +657,8 @@ void plan_pairs(Problem* P)
         double most = kPairFit[P->precision].most;
         if (one < 0.8 * 1024) most = std::max(most, 0.0);
         if (cls == 9 && one < 1.5 * 1024) most = std::max(most, 0.8);
+        // (and too low by up to 1.4 us, as often as it is right, for temporal tiles with a halo past 2.2)
+        ok = ok && !(cls == 9 && one > 2.2 * 1024 && one > 1.1 * two);
         P->pair_on[cls] = ok && one < kPairWaves * 1024 &&
                           pair_gain(P->precision, one / 1024, two / 1024, lines / 1024) < most;
     }
