@@ -203,8 +203,8 @@ typedef struct {
                                  or U1ML_FORM_SPECTRAL)                       */
     size_t spectral_bytes;    /* weights, plane spectra, spectral sums and the
                                  replay copy of the links (SPECTRAL only)    */
-    long launches_per_config; /* kernel launches of one u1ml_multilevel
-                                 (upper bound)                              */
+    long launches_per_config; /* kernel launches of one u1ml_multilevel on one
+                                 lane (upper bound)                         */
     double est_history_ms;    /* estimated device time per configuration that
                                  the insertion contraction adds in the history
                                  form (0 without probes)                    */
@@ -333,8 +333,9 @@ u1ml_status u1ml_get_lanes(u1ml_ctx* ctx, int* n_lanes);
 
 /* 1: capture sweeps and multilevel bodies into HIP graphs (default);
  * 0: launch every kernel directly.  A multilevel body of more than 8192
- * kernel launches (u1ml_plan_info.launches_per_config) is always launched
- * directly. */
+ * checkerboard phases and other launches (a phase counts also where sweeps
+ * take fewer launches, so u1ml_plan_info.launches_per_config may be less) is
+ * always launched directly. */
 u1ml_status u1ml_set_graphs(u1ml_ctx* ctx, int enable);
 
 /* Synchronises.  Average device time in microseconds of one launch of the

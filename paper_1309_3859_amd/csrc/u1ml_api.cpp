@@ -337,26 +337,58 @@ bool read_problem(const u1ml_problem* p, Problem* P, std::string* err)
     return true;
 }
 
-// Kernel launches of one multilevel body (upper bound).  Bodies above
-// kMaxGraphLaunches are launched directly instead of through one captured
-// graph: a single capture of a full configuration of the largest preset
-// (about 275,000 kernel nodes in one chain) ended the process with a
-// segmentation fault, so graphs stay at the sizes that are tested.
-constexpr long long kMaxGraphLaunches = 8192;
+// Bodies of more than kMaxGraphPhases are launched directly instead of through
+// one captured graph, a phase counted also where sweeps take fewer launches: a
+// single capture of a full configuration of the largest preset (about 275,000
+// kernel nodes in one chain) ended the process with a segmentation fault, so
+// graphs stay at the sizes that are tested; and a graph's first launch costs
+// what its replays of so many launches gain back only after tens of them (300
+// sweeps of 24^3 x 8, 5120 launches: 29.6 ms the first time and 19.1 then, launched
+// directly 20.1 and 19.1).
+constexpr long long kMaxGraphPhases = 8192;
+
+long long body_phases(const Problem& P)
+{
+    const long long sweep = (1ll + P.n_or) * 8, meas = 1 + (P.multihit ? 1 : 0) + (P.spectral ? 6 : 0);
+    const long long level = (long long)P.n_o * ((long long)P.k_o * sweep + (long long)P.n_i * (P.k_i * sweep + meas) + 6);
+    return (P.spectral && P.two ? 2 : 1) * level + 10 + 5ll * P.n_ens;
+}
+
+// Kernel launches of one multilevel body (upper bound, of the whole batch on one
+// lane), and
+// of n sweeps of a class (0 full, 1 inner slabs, 2 outer slabs)
+long long sweep_launches(const Problem& P, int cls, long long n)
+{
+    if (n == 0) return 0;
+    if (P.slab_on[cls]) return (n + kSlabSweeps - 1) / kSlabSweeps;
+    const int paired = (P.n_or + 1) / 2 * 2;  // passes with both-parities launches
+    long long pass = 0;
+    for (int mu = 0; mu < 4; ++mu) pass += P.pair_on[mu == 3 ? 9 : 3 * mu + cls] ? 1 : 2;
+    return n * (paired * pass + (1 + P.n_or - paired) * 8);
+}
 
 long long body_launches(const Problem& P)
 {
-    const long long sweep = (1ll + P.n_or) * 8;
-    // per measurement: the measurement (two with multihit), and in the spectral form staging,
-    // plane transforms and spectral sums (at most 6); per inner level: the two
-    // contractions, the combine, the exponent pass (2) and the weights
-    const long long meas = 1 + (P.multihit ? 1 : 0) + (P.spectral ? 6 : 0);
-    const long long level = (long long)P.n_o * ((long long)P.k_o * sweep + (long long)P.n_i * (P.k_i * sweep + meas) + 6);
+    const int outer = P.tau_o == P.tau_i ? 1 : 2;
+    // per measurement: one (two with multihit); per inner level: the copies of frozen links (2), the two
+    // contractions, the combine, the exponent pass (2) and the weights; in the spectral form, once per
+    // measurement, staging, plane transforms and spectral sums (in parts past kMaxGrid work-groups)
+    double tiles = 0.0;
+    for (const u1ml_ensemble& E : P.ens) {
+        const double nsig = (double)E.ns[0] * E.ns[1] * E.ns[2];
+        double plane = 0.0;
+        for (int i = 0; i < P.n_dirs; ++i) plane = std::max(plane, nsig / E.ns[P.dirs[i]]);
+        tiles += (double)P.n_dirs * (E.nt / P.tau_i) * (double)(P.gdesc.size() / 2) * std::ceil(plane / kMacK);
+    }
+    const long long spectral = 3 + (long long)(tiles / kMaxGrid);
+    const long long meas = 1 + (P.multihit ? 1 : 0);
+    const long long level = (long long)P.n_o * ((P.two ? sweep_launches(P, outer, P.k_o) : 0) +
+                                                (long long)P.n_i * (sweep_launches(P, 1, P.k_i) + meas) + 8);
     const long long passes = (P.spectral && P.two) ? 2 : 1;
     // per configuration: products (4), vacuum, spectral final (2), outer
     // weights, ring and counters; per ensemble: up to three fills and two
     // link copies
-    return passes * level + 10 + 5ll * P.n_ens;
+    return passes * level + (P.spectral ? spectral * P.n_o * P.n_i : 0) + 10 + 5ll * P.n_ens;
 }
 
 // probe groups of the slab-product launch: every probe in the history form,
@@ -2263,7 +2295,7 @@ try {
     if (!ctx->initialised) return set_err(ctx, U1ML_ESTATE, "links not initialised");
     if (ctx->ring_count >= ctx->P.max_configs)
         return set_err(ctx, U1ML_ESTATE, "results ring is full: call u1ml_copy_results");
-    const bool graph = ctx->use_graphs && body_launches(ctx->P) <= kMaxGraphLaunches;
+    const bool graph = ctx->use_graphs && body_phases(ctx->P) <= kMaxGraphPhases;
     auto lane_config = [&](Lane& L) -> hipError_t {
         if (!graph) return enq_multilevel(ctx, L, L.stream);
         if (!L.g_ml && capture(ctx, [&](hipStream_t st) { return enq_multilevel(ctx, L, st); }, &L.g_ml) != U1ML_OK)

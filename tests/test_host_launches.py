@@ -232,3 +232,34 @@ put(k.value)
 ok(L.u1ml_destroy(ctx))
 """)
     assert got == lanes
+
+
+@pytest.mark.parametrize("kw", [
+    dict(ns=(4, 4, 4), nt=4, levels=[(2, 300, 1)]), dict(ns=(24, 24, 24), nt=8, levels=[(2, 50, 1)], precision=1),
+    dict(ns=(24, 24, 24), nt=8, levels=[(2, 20, 2)], n_or=2), dict(ns=(24, 24, 24), nt=8, levels=[(2, 20, 2)], n_or=0),
+    dict(ns=(32, 32, 32), nt=8, levels=[(4, 5, 3), (2, 10, 1)], precision=1, probes=1, form=1),
+    dict(ns=(32, 32, 32), nt=8, levels=[(4, 5, 3), (2, 10, 1)], precision=1, probes=1, form=2),
+    dict(ns=(8, 8, 8), nt=8, levels=[(4, 5, 130), (2, 10, 70)], multihit=True, probes=9, form=2),
+    dict(ns=(48, 48, 48), nt=12, levels=[(4, 3, 0), (2, 4, 1)], precision=1, n=3),
+    dict(ns=(12, 12, 12), nt=12, levels=[(2, 6, 2), (2, 5, 1)], update=1)])
+def test_planned_launch_count(so, kw):
+    """u1ml_plan's launches_per_config against the launches of a configuration on
+    one lane: never fewer, and more by what it grants per level, configuration
+    and ensemble (of which a form uses a part) only."""
+    planned, issued = host_hip.run(so, f"""
+kw = dict({kw})
+n, k = kw.pop("n", 1), kw.pop("probes", 0)
+ns, nt = kw.pop("ns"), kw.pop("nt")
+spec = u1.Spec(ensembles=[u1.Ens(ns, nt, 1.0, key_id=i) for i in range(n)], r=[1, 2],
+               probes=[(0, a, b, 1) for a in (0, 1, -1) for b in (0, 1, -1)][:k], comps=[0, 3] if k else [], **kw)
+put(u1.plan(spec)["launches_per_config"])
+ctx = make(spec)
+ok(L.u1ml_set_lanes(ctx, 1))
+ok(L.u1ml_init_links(ctx, u1.HOT))
+launches()
+ok(L.u1ml_multilevel(ctx), ctx)
+put(len(launches()))
+ok(L.u1ml_destroy(ctx))
+""")
+    n_outer = kw["levels"][0][1] if len(kw["levels"]) == 2 else 1
+    assert issued <= planned <= issued + 2 * 8 * n_outer + 10 + 5 * kw.get("n", 1)
