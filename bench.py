@@ -597,7 +597,7 @@ def main():
                    "block": block,
                    "autotune": {"us_per_sweep": dict(zip(map(str, tune["block"]), tune["us_per_sweep"])),
                                 "chosen_block": tune["chosen_block"],
-                                "note": "work-group size only; the update kernels have no other tile dimension"}},
+                                "note": "work-group size of launches of one phase"}},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": counter_traffic() if args.workload == "c4" else None,

@@ -299,8 +299,10 @@ u1ml_status u1ml_plaquette_noalloc(u1ml_ctx* ctx, double* d_out);
  * [-pi, pi] by more than 2^-20 relative, all ensembles. */
 u1ml_status u1ml_health(u1ml_ctx* ctx, uint64_t* n_bad);
 
-/* Times every candidate work-group size of the update kernels on this
- * problem (results are bit-identical for all of them) and keeps the fastest.
+/* Times the sweeps inside the problem's (inner) slabs, as configurations run
+ * them, with every candidate work-group size of u1ml_set_block (results are
+ * bit-identical for all of them) and keeps the fastest; the present size stays
+ * where such a sweep has no launch of one phase, so that none of them matters.
  * Synchronises; restores links and counters afterwards. */
 typedef struct {
     int n_candidates;

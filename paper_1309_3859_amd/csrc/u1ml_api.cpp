@@ -1594,11 +1594,10 @@ hipError_t enq_pass(u1ml_ctx* c, const Lane& L, hipStream_t st, int kind, int ta
 // one sweep: stochastic pass (heatbath or Metropolis) with counter offset hb,
 // then n_or overrelaxation passes.  It starts and ends in the first link
 // buffer: of an odd number of passes the last one updates in place.
-// pairs: both-parities launches where the plan has them.
-hipError_t enq_sweep(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau, int hb, bool pairs = true)
+hipError_t enq_sweep(u1ml_ctx* c, const Lane& L, hipStream_t st, int tau, int hb)
 {
     const int stoch = c->P.update == U1ML_UPDATE_METROPOLIS ? U1ML_METROPOLIS : U1ML_HEATBATH;
-    const int paired = pairs ? (c->P.n_or + 1) / 2 * 2 : 0;  // passes that may turn the buffers over
+    const int paired = (c->P.n_or + 1) / 2 * 2;  // passes that may turn the buffers over
     unsigned src[4] = {0, 0, 0, 0};
     hipError_t e = hipSuccess;
     for (int k = 0; e == hipSuccess && k <= c->P.n_or; ++k)
@@ -2619,9 +2618,10 @@ try {
             st = set_err(ctx, U1ML_EDEVICE, "event creation failed");
             break;
         }
-        hipError_t e = enq_sweep(ctx, ctx->whole, ctx->stream, tau, 0, false);  // warm-up
+        hipError_t e = enq_mirror(ctx, ctx->whole, ctx->stream, tau);
+        if (e == hipSuccess) e = enq_sweeps(ctx, ctx->whole, ctx->stream, tau, 0, 1);  // warm-up
         if (e == hipSuccess) e = hipEventRecord(a, ctx->stream);
-        for (int k = 0; k < 5 && e == hipSuccess; ++k) e = enq_sweep(ctx, ctx->whole, ctx->stream, tau, 0, false);
+        for (int k = 0; k < 5 && e == hipSuccess; ++k) e = enq_sweeps(ctx, ctx->whole, ctx->stream, tau, 0, 1);
         if (e == hipSuccess) e = hipEventRecord(b, ctx->stream);
         if (e == hipSuccess) e = hipEventSynchronize(b);
         float ms = 0.f;
@@ -2649,6 +2649,10 @@ try {
         return st;
     }
     if (e1 != hipSuccess || e2 != hipSuccess) return set_err(ctx, U1ML_EDEVICE, "autotune restore failed");
+    // without a launch of one phase in the sweep the candidates are the same
+    bool single = ctx->P.n_or % 2 == 0;  // the last of an odd number of passes
+    for (int mu = 0; mu < 4; ++mu) single = single || !ctx->P.pair_on[mu == 3 ? 9 : 3 * mu + 1];
+    if (ctx->P.slab_on[1] || !single) best_b = old_block;
     st = u1ml_set_block(ctx, best_b);
     rep.chosen_block = best_b;
     if (report) *report = rep;

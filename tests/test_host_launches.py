@@ -263,3 +263,27 @@ ok(L.u1ml_destroy(ctx))
 """)
     n_outer = kw["levels"][0][1] if len(kw["levels"]) == 2 else 1
     assert issued <= planned <= issued + 2 * 8 * n_outer + 10 + 5 * kw.get("n", 1)
+
+
+@pytest.mark.parametrize("ns,nt,n_or,kernels", [((4, 4, 4), 4, 3, {"k_slab"}), ((24, 24, 24), 8, 3, {"k_mirror", "k_pair"}),
+                                                ((24, 24, 24), 8, 2, {"k_mirror", "k_pair", "k_update"}),
+                                                ((64, 64, 64), 8, 3, {"k_update"})])
+def test_autotune_times_the_sweeps_that_run(so, ns, nt, n_or, kernels):
+    """The launches that autotune times are those of a configuration's sweeps;
+    the work-group size stays where none of them depends on it."""
+    tuned, run, chosen = host_hip.run(so, f"""
+ctx = make(u1.Spec(ensembles=[u1.Ens({ns}, {nt}, 1.0)], levels=[(2, 1, 1)], r=[1], n_or={n_or}, precision=u1.FP32))
+ok(L.u1ml_init_links(ctx, u1.HOT))
+launches()
+rep = u1._TuneReport()
+ok(L.u1ml_autotune(ctx, C.byref(rep)))
+kinds = ("k_slab", "k_pair", "k_mirror", "k_update")
+put(sorted(set(l[0] for l in launches()) & set(kinds)))
+ok(L.u1ml_multilevel(ctx))
+put(sorted(set(l[0] for l in launches()) & set(kinds)))
+put(rep.chosen_block)
+ok(L.u1ml_destroy(ctx))
+""")
+    assert set(tuned) == set(run) == kernels
+    if "k_update" not in kernels:
+        assert chosen == 256
