@@ -188,3 +188,70 @@ def test_short_slices_equal_sweeps_in_lds(ns, nt, precision, update):
                 b.phase(kind, mu, p, 2, 0)
         for e in range(2):
             assert np.array_equal(a.links(e), b.links(e)), (block, e)
+
+
+# (precision, lattice, betas, work-group sizes): launches of at least 640 (FP64) or 4096 (FP32) work-groups of at most
+# 512 finish the heatbath's pending links by work-group, those of 1024 always by wave; the last work-group of
+# every slice is not full
+BY_GROUP = [(0, (30, 32, 34), (0.0, 0.2, 1.0), (64, 256, 512)), (1, (64, 62, 66), (0.3, 4.0), (64, 256, 512)),
+            (0, (64, 62, 66), (1.1, 6.0), (128, 512))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision,ns,betas,blocks", BY_GROUP)
+@pytest.mark.parametrize("start", [0, 1])
+def test_heatbath_retries_by_work_group_change_no_bit(precision, ns, betas, blocks, start):
+    """Heatbath phases of every direction and parity, retries dealt over the
+    work-group against retries dealt over the wave, from a cold and a hot start
+    (few and many pending links) and, with beta = 0, with none."""
+    from paper_1309_3859_amd import u1ml
+
+    ens = [u1ml.Ens(ns, 4, b, seed=5, key_id=k) for k, b in enumerate(betas)]
+    spec = u1ml.Spec(ensembles=ens, levels=[(2, 1, 1)], r=[1], precision=precision)
+    want = None
+    for block in (1024,) + blocks:
+        print("heatbath by work-group", precision, ns, block, start, flush=True)
+        ctx = u1ml.Context(spec)
+        ctx.set_block(block)
+        ctx.init_links(start)
+        for mu, p, tau in itertools.product(range(4), (0, 1), (0, 2)):
+            ctx.phase(u1ml.HEATBATH, mu, p, tau, pass_offset=tau + mu)
+        got = [ctx.links(e) for e in range(len(ens))]
+        ctx.close()
+        if want is None:
+            want = got
+        for a, b in zip(want, got):
+            assert np.array_equal(a, b), block
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("levels,n_or", [([(2, 2, 2)], 3), ([(4, 2, 1), (2, 2, 1)], 2)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_lanes_and_graphs_change_no_bit_outside_lds(levels, n_or, precision):
+    """Batches whose sweeps inside slabs are launches of both parities (their
+    slabs too large for LDS) and, in the last one, launches of one phase: one,
+    two and three lanes, graphs or direct launches, work-groups of 64 or 256."""
+    from paper_1309_3859_amd import u1ml
+
+    batches = [[((24, 24, 24), 4), ((12, 14, 16), 8), ((20, 10, 22), 4)],
+               [((48, 48, 48), 8), ((32, 40, 36), 4), ((30, 20, 26), 8)]]
+    for lattices in batches:
+        ens = [u1ml.Ens(ns, nt, 1.0 - 0.02 * k, seed=9, key_id=k) for k, (ns, nt) in enumerate(lattices)]
+        spec = u1ml.Spec(ensembles=ens, levels=levels, r=[1, 2], precision=precision, n_or=n_or, max_configs=2)
+        want = None
+        for lanes, graphs, block in ((1, True, 256), (2, True, 64), (3, False, 256), (2, False, 256)):
+            print("lanes outside LDS", levels, precision, lattices[0], lanes, graphs, block, flush=True)
+            ctx = u1ml.Context(spec)
+            ctx.set_lanes(lanes)
+            ctx.set_graphs(graphs)
+            ctx.set_block(block)
+            ctx.init_links(u1ml.HOT)
+            ctx.sweeps(2)
+            ctx.multilevel()
+            ctx.multilevel()
+            got = [ctx.results()] + [ctx.links(e) for e in range(3)] + [np.array([ctx.counter(e) for e in range(3)])]
+            ctx.close()
+            if want is None:
+                want = got
+            for a, b in zip(want, got):
+                assert np.array_equal(a, b), (lanes, graphs, block)
