@@ -873,8 +873,7 @@ __global__ void __launch_bounds__(kMacThreads, 3) k_spec_mac(const EnsDesc* __re
 
 // ---------------------------------------------------------------------------
 // Probe estimates of the configuration.  Work-group per (ensemble, r,
-// component, kind, probe group) sum, several of them where that is more than
-// kMaxGrid; its probes p have
+// component, kind, probe group); its probes p have
 //   CO = scale sum_axis 1/(n1 n2) sum_k1 e^(2 pi i k1 p1/n1) A(k1, p2),
 //   A(k1, v) = sum_k2 F(k1, k2) e^(2 pi i k2 v/n2),  F(k) = sum_s F[axis][s][r][c][kind][g][k],
 // scale = 1/(N_sigma |M| N_t n_o n_i).  Each of the three sums runs in double-
@@ -883,14 +882,20 @@ __global__ void __launch_bounds__(kMacThreads, 3) k_spec_mac(const EnsDesc* __re
 // from the exact sum of the spectra.  A's rows replace F's in LDS as they are
 // formed, so the pairs take the space of one plane of each.
 //
-// A probe by itself needs n1 n2 terms of every slab; the slabs first, then
-// the rows, then the columns take n1 n2 (S + n2) per work-group and n1 per
-// probe: 48^3 x 12 with 441 probes and 19 separations 13 million terms
-// instead of 600 million, 3.44 ms before and 90 us now (57 us
-// with F and A rounded to one double each, 1.2 to 1.4 times the error).
+// A probe by itself needs n1 n2 terms of every slab; the slabs first, then the
+// rows at the nv positions p2 that the group's probes have, then the columns
+// take n1 n2 (S + nv) per work-group and n1 per probe.  48^3 x 12 with 441
+// probes and 19 separations: 13 million terms instead of 600 million, 3.44 ms
+// before and 65 us now (57 us with F and A rounded to one double each, 1.2 to
+// 1.4 times the error).  The rows' chains of double-double sums bound it, so
+// two work-groups per CU: two values of A per work-item and one loop for both
+// tables of twiddles keep it at 128 registers without spills (four values and
+// rows at every position: 166, one work-group, 97 us).  A configuration of
+// 48^3 x 4 with 63 probes takes 622 us (931 us).
 // ---------------------------------------------------------------------------
 constexpr int kFinalThreads = 512;
-constexpr int kFinalRow = 4;  // values of A per work-item and pass over the rows
+constexpr int kFinalRow = 2;  // values of A per work-item and pass over the rows
+constexpr int kFinalExtent = 128;  // largest extent (k_spec_mac's LDS holds up to 106)
 
 // hi + lo += b, hi the rounded running sum, lo the sum of its errors
 __device__ inline void pair_add(double& hi, double& lo, double b)
@@ -921,17 +926,19 @@ struct cpair {
     }
 };
 
-// A's rows from k1 = row0 on, n values in all (n <= U kFinalThreads), over F's
+// A's rows from k1 = row0 on at the nv positions v[], n values in all (n <= U
+// kFinalThreads), over F's
 template <int U>
-__device__ inline void final_rows(double2* Fh, double2* Fl, const double2* w, int n2, int row0, int n)
+__device__ inline void final_rows(double2* Fh, double2* Fl, const double2* w, const int* vs, int nv, int n2, int row0, int n)
 {
     cpair a[U];
-    int f[U], v[U], ph[U];
+    int f[U], j[U], v[U], ph[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int i = min((int)threadIdx.x + u * kFinalThreads, n - 1), row = i / n2;
+        const int i = min((int)threadIdx.x + u * kFinalThreads, n - 1), row = i / nv;
         f[u] = (row0 + row) * n2;
-        v[u] = i - row * n2;
+        j[u] = i - row * nv;
+        v[u] = vs[j[u]];
         ph[u] = 0;
         a[u] = cpair{make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
     }
@@ -947,12 +954,12 @@ __device__ inline void final_rows(double2* Fh, double2* Fl, const double2* w, in
     for (int u = 0; u < U; ++u)
         if ((int)threadIdx.x + u * kFinalThreads < n) {
             a[u].norm();
-            Fh[f[u] + v[u]] = a[u].hi;
-            Fl[f[u] + v[u]] = a[u].lo;
+            Fh[f[u] + j[u]] = a[u].hi;
+            Fl[f[u] + j[u]] = a[u].lo;
         }
 }
 
-__global__ void __launch_bounds__(kFinalThreads) k_spec_final(const EnsDesc* __restrict__ ens, unsigned n_sums,
+__global__ void __launch_bounds__(kFinalThreads, 4) k_spec_final(const EnsDesc* __restrict__ ens, unsigned sum0,
                                                               const ObsDesc* __restrict__ obs,
                                                               const int* __restrict__ probes,
                                                               const int* __restrict__ pgroup,
@@ -960,89 +967,97 @@ __global__ void __launch_bounds__(kFinalThreads) k_spec_final(const EnsDesc* __r
                                                               double* __restrict__ results, const int* __restrict__ ring)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ int wanted[kFinalExtent], vs[kFinalExtent];  // whether a position v is a probe's, and those positions
     const ObsDesc& O = *obs;
     const int R = O.n_r, Np = O.n_probe, Nc = O.n_comp, NG = O.n_groups;
-    for (unsigned sum = blockIdx.x; sum < n_sums; sum += gridDim.x) {  // (((e R + ir) Nc + ic) 2 + kind) NG + g
-        const int g = (int)(sum % (unsigned)NG);
-        const unsigned t = sum / (unsigned)NG;
-        const int rck = (int)(t % (unsigned)(R * Nc * 2)), e = (int)(t / (unsigned)(R * Nc * 2));
-        const int ir = rck / (Nc * 2), ck = rck - ir * Nc * 2;
-        const EnsDesc& E = ens[e];
-        const int nsig = E.nsig, Si = E.s_in;
-        int n12max = 0;
-        for (int i = 0; i < O.n_dirs; ++i) n12max = max(n12max, nsig / extent(E, O.dirs[i]));
-        const int npm = max(E.nx, max(E.ny, E.nz));
-        double2* Fh = reinterpret_cast<double2*>(lds_raw);
-        double2* Fl = Fh + n12max;
-        double2* w1 = Fl + n12max;
-        double2* w2 = w1 + npm;
-        const double scale = 1.0 / ((double)nsig * O.n_dirs * E.nt * n_meas_total);
-        double* out = results + ((size_t)(*ring) * O.n_ens_total + E.res_index) * O.n_doubles_per_config + 2ll * R;
-        for (int p0 = 0; p0 < Np; p0 += kFinalThreads) {  // as many probes as work-items, usually all
-            const int p = p0 + (int)threadIdx.x;
-            const bool mine = p < Np && pgroup[min(p, Np - 1)] == g;
-            const int p1 = mine ? probes[4 * p + 1] : 0, p2 = mine ? probes[4 * p + 2] : 0;
-            dds are{0.0, 0.0}, aim{0.0, 0.0};
-            for (int id = 0; id < O.n_dirs; ++id) {
-                const int dir = O.dirs[id];
-                const int n1 = extent(E, dir == 2 ? 0 : dir + 1), n2 = extent(E, dir == 0 ? 2 : dir - 1), n12 = n1 * n2;
-                __syncthreads();  // the previous axis is done with the tables
-                for (int j = threadIdx.x; j < n1; j += kFinalThreads) {
-                    double sn, cs;
-                    sincospi(2.0 * (double)j / (double)n1, &sn, &cs);
-                    w1[j] = make_double2(cs, sn);
-                }
-                for (int j = threadIdx.x; j < n2; j += kFinalThreads) {
-                    double sn, cs;
-                    sincospi(2.0 * (double)j / (double)n2, &sn, &cs);
-                    w2[j] = make_double2(cs, sn);
-                }
-                const size_t sstep = (size_t)R * Nc * 2 * NG * n12max;  // from one slab to the next
-                const double2* Fg = facc + E.facc_off + ((((size_t)id * Si * R + ir) * Nc * 2 + ck) * NG + g) * n12max;
-                for (int k = threadIdx.x; k < n12; k += kFinalThreads) {
-                    dds re{0.0, 0.0}, im{0.0, 0.0};
-#pragma unroll 4
-                    for (int s = 0; s < Si; ++s) {
-                        const double2 v = Fg[s * sstep + k];
-                        re = dds_add(re, v.x);
-                        im = dds_add(im, v.y);
-                    }
-                    Fh[k] = make_double2(re.hi, im.hi);
-                    Fl[k] = make_double2(re.lo, im.lo);
-                }
-                __syncthreads();
-                // whole rows a pass (k_spec_mac's LDS holds extents up to 106)
-                const int rows = max(1, kFinalRow * kFinalThreads / n2);
-                for (int k1 = 0; k1 < n1; k1 += rows) {
-                    const int n = min(rows, n1 - k1) * n2;
-                    switch ((n - 1) / kFinalThreads) {
-                    case 0: final_rows<1>(Fh, Fl, w2, n2, k1, n); break;
-                    case 1: final_rows<2>(Fh, Fl, w2, n2, k1, n); break;
-                    case 2: final_rows<3>(Fh, Fl, w2, n2, k1, n); break;
-                    default: final_rows<kFinalRow>(Fh, Fl, w2, n2, k1, n); break;
-                    }
-                }
-                __syncthreads();
-                if (!mine) continue;
-                const int q1 = ((p1 % n1) + n1) % n1, q2 = ((p2 % n2) + n2) % n2;
-                cpair a{make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
-                int ph = 0;
-                for (int k1 = 0; k1 < n1; ++k1) {
-                    a.add_mul(Fh[k1 * n2 + q2], Fl[k1 * n2 + q2], w1[ph]);
-                    ph += q1;
-                    if (ph >= n1) ph -= n1;
-                }
-                a.norm();
-                const double n = (double)n12;  // a / n as a pair: the quotient and its remainder's
-                const double qx = a.hi.x / n, qy = a.hi.y / n;
-                are = dds_add(dds_add(are, qx), (fma(-qx, n, a.hi.x) + a.lo.x) / n);
-                aim = dds_add(dds_add(aim, qy), (fma(-qy, n, a.hi.y) + a.lo.y) / n);
+    const unsigned sum = sum0 + blockIdx.x;  // (((e R + ir) Nc + ic) 2 + kind) NG + g
+    const int g = (int)(sum % (unsigned)NG);
+    const unsigned t = sum / (unsigned)NG;
+    const int rck = (int)(t % (unsigned)(R * Nc * 2)), e = (int)(t / (unsigned)(R * Nc * 2));
+    const int ir = rck / (Nc * 2), ck = rck - ir * Nc * 2;
+    const EnsDesc& E = ens[e];
+    const int nsig = E.nsig, Si = E.s_in;
+    int n12max = 0;
+    for (int i = 0; i < O.n_dirs; ++i) n12max = max(n12max, nsig / extent(E, O.dirs[i]));
+    const int npm = max(E.nx, max(E.ny, E.nz));
+    double2* Fh = reinterpret_cast<double2*>(lds_raw);
+    double2* Fl = Fh + n12max;
+    double2* w1 = Fl + n12max;
+    double2* w2 = w1 + npm;
+    const double scale = 1.0 / ((double)nsig * O.n_dirs * E.nt * n_meas_total);
+    double* out = results + ((size_t)(*ring) * O.n_ens_total + E.res_index) * O.n_doubles_per_config + 2ll * R;
+    for (int p0 = 0; p0 < Np; p0 += kFinalThreads) {  // as many probes as work-items, usually all
+        const int p = p0 + (int)threadIdx.x;
+        const bool mine = p < Np && pgroup[min(p, Np - 1)] == g;
+        const int p1 = mine ? probes[4 * p + 1] : 0, p2 = mine ? probes[4 * p + 2] : 0;
+        dds are{0.0, 0.0}, aim{0.0, 0.0};
+        for (int id = 0; id < O.n_dirs; ++id) {
+            const int dir = O.dirs[id];
+            const int n1 = extent(E, dir == 2 ? 0 : dir + 1), n2 = extent(E, dir == 0 ? 2 : dir - 1), n12 = n1 * n2;
+            const int q1 = ((p1 % n1) + n1) % n1, q2 = ((p2 % n2) + n2) % n2;
+            __syncthreads();  // the previous axis is done with the tables
+            if (threadIdx.x < kFinalExtent) wanted[threadIdx.x] = 0;
+            __syncthreads();
+            if (mine) wanted[q2] = 1;
+            for (int i = threadIdx.x; i < n1 + n2; i += kFinalThreads) {
+                const bool first = i < n1;
+                const int j = first ? i : i - n1;
+                double sn, cs;
+                sincospi(2.0 * (double)j / (double)(first ? n1 : n2), &sn, &cs);
+                (first ? w1 : w2)[j] = make_double2(cs, sn);
             }
+            const size_t sstep = (size_t)R * Nc * 2 * NG * n12max;  // from one slab to the next
+            const double2* Fg = facc + E.facc_off + ((((size_t)id * Si * R + ir) * Nc * 2 + ck) * NG + g) * n12max;
+            for (int k = threadIdx.x; k < n12; k += kFinalThreads) {
+                dds re{0.0, 0.0}, im{0.0, 0.0};
+#pragma unroll 4
+                for (int s = 0; s < Si; ++s) {
+                    const double2 v = Fg[s * sstep + k];
+                    re = dds_add(re, v.x);
+                    im = dds_add(im, v.y);
+                }
+                Fh[k] = make_double2(re.hi, im.hi);
+                Fl[k] = make_double2(re.lo, im.lo);
+            }
+            __syncthreads();
+            // the wanted positions, two ballots of a wave (extents are at most 106)
+            const int lane = (int)threadIdx.x & 63;
+            const unsigned long long lo = __ballot(wanted[lane] != 0), hi = __ballot(wanted[64 + lane] != 0);
+            const int nlo = __popcll(lo), nv = nlo + __popcll(hi);
+            auto place = [&](int v) {
+                return v < 64 ? __popcll(lo & ((1ull << v) - 1)) : nlo + __popcll(hi & ((1ull << (v - 64)) - 1));
+            };
+            if (threadIdx.x < kFinalExtent && wanted[threadIdx.x]) vs[place((int)threadIdx.x)] = (int)threadIdx.x;
+            __syncthreads();
+            // whole rows a pass
+            const int rows = nv ? kFinalRow * kFinalThreads / nv : n1;
+            for (int k1 = 0; nv && k1 < n1; k1 += rows) {
+                const int n = min(rows, n1 - k1) * nv;
+                if (n <= kFinalThreads)
+                    final_rows<1>(Fh, Fl, w2, vs, nv, n2, k1, n);
+                else
+                    final_rows<kFinalRow>(Fh, Fl, w2, vs, nv, n2, k1, n);
+            }
+            __syncthreads();
             if (!mine) continue;
-            const size_t idx = ((size_t)ir * Np + p) * Nc * 2 + ck;
-            out[2 * idx] = (are.hi + are.lo) * scale;
-            out[2 * idx + 1] = (aim.hi + aim.lo) * scale;
+            const int at = place(q2);
+            cpair a{make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+            int ph = 0;
+            for (int k1 = 0; k1 < n1; ++k1) {
+                a.add_mul(Fh[k1 * n2 + at], Fl[k1 * n2 + at], w1[ph]);
+                ph += q1;
+                if (ph >= n1) ph -= n1;
+            }
+            a.norm();
+            const double n = (double)n12;  // a / n as a pair: the quotient and its remainder's
+            const double qx = a.hi.x / n, qy = a.hi.y / n;
+            are = dds_add(dds_add(are, qx), (fma(-qx, n, a.hi.x) + a.lo.x) / n);
+            aim = dds_add(dds_add(aim, qy), (fma(-qy, n, a.hi.y) + a.lo.y) / n);
         }
+        if (!mine) continue;
+        const size_t idx = ((size_t)ir * Np + p) * Nc * 2 + ck;
+        out[2 * idx] = (are.hi + are.lo) * scale;
+        out[2 * idx + 1] = (aim.hi + aim.lo) * scale;
     }
 }
 
@@ -1180,9 +1195,11 @@ hipError_t launch_spec_final(const EnsDesc* d_ens, int n_ens, const ObsDesc* d_o
                              double n_meas_total, double* results, const int* d_ring, hipStream_t st)
 {
     if (n_sums <= 0) return hipSuccess;
-    const unsigned all = (unsigned)(n_sums * n_ens);
-    hipLaunchKernelGGL(k_spec_final, dim3(std::min(all, kMaxGrid)), dim3(kFinalThreads), plane_lds(n12max, npm), st,
-                       d_ens, all, d_obs, d_probe, d_pgroup, facc, n_meas_total, results, d_ring);
+    const long long all = n_sums * n_ens;
+    for (long long s0 = 0; s0 < all; s0 += kMaxGrid)  // usually one
+        hipLaunchKernelGGL(k_spec_final, dim3((unsigned)std::min<long long>(all - s0, kMaxGrid)), dim3(kFinalThreads),
+                           plane_lds(n12max, npm), st, d_ens, (unsigned)s0, d_obs, d_probe, d_pgroup, facc,
+                           n_meas_total, results, d_ring);
     return hipGetLastError();
 }
 
