@@ -1105,6 +1105,19 @@ hipError_t launch_plane_stage(const EnsDesc* d_ens, const int* d_bstart, int n_e
     return hipGetLastError();
 }
 
+// sides with a transform in registers and their radices
+#define U1ML_FFT_SIDES(X)                                                                                              \
+    X(4, 3) X(4, 4) X(6, 3) X(5, 4) X(6, 4) X(6, 5) X(8, 4) X(6, 6) X(8, 5) X(12, 4) X(12, 5) X(8, 8)
+
+bool fft_in_registers(int side)
+{
+#define U1ML_FFT(RA, RB)                                                                                               \
+    if (side == RA * RB) return true;
+    U1ML_FFT_SIDES(U1ML_FFT)
+#undef U1ML_FFT
+    return false;
+}
+
 // square: the side of every plane of the launch, 0 if they differ or are not square; n12max, npm: largest plane and extent
 hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int square,
                              int n12max, int npm, const ObsDesc* d_obs, const int* d_r, const double2* cpl,
@@ -1126,18 +1139,7 @@ hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_en
                                st, d_ens, d_bstart, n_ens, d_obs, d_r, cpl, (const float*)opl, gf, sph, spo);          \
         return hipGetLastError();
         switch (square) {
-            U1ML_FFT(4, 3)
-            U1ML_FFT(4, 4)
-            U1ML_FFT(6, 3)
-            U1ML_FFT(5, 4)
-            U1ML_FFT(6, 4)
-            U1ML_FFT(6, 5)
-            U1ML_FFT(8, 4)
-            U1ML_FFT(6, 6)
-            U1ML_FFT(8, 5)
-            U1ML_FFT(12, 4)
-            U1ML_FFT(12, 5)
-            U1ML_FFT(8, 8)
+            U1ML_FFT_SIDES(U1ML_FFT)
         }
 #undef U1ML_FFT
     }

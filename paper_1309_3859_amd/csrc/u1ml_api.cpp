@@ -725,6 +725,26 @@ std::vector<PairRow> build_pair_rows(const Problem& P)
     return rows;
 }
 
+// History form, vector kernel: slot blocks per work-group of an ensemble whose
+// longest line has nmax sites, and measurements per LDS chunk buffer (static
+// LDS of the kernel): fewer slot blocks while a chunk would hold fewer than 8
+// measurements, or not even one.  False where one does not fit at all.
+bool ins_shape(const Problem& P, int ks, int nsb, int nmax, int* pbw, int* mc)
+{
+    const int kr = ins_kr(ks), word = P.precision == U1ML_FP64 ? 8 : 4;
+    const int unit = nmax * (((int)P.r.size() + kr - 1) / kr);  // tasks of one slot block
+    int b = std::max(1, std::min(std::min(nsb, kInsThreads / unit), kInsRowsMax / (2 * ks)));
+    auto fit_mc = [&](int bpw) {
+        int m = std::min(P.n_i, kInsPh);
+        while (m > 1 && !ins_chunk_fits(m, nmax, bpw * ks * 2, word)) --m;
+        return m;
+    };
+    while (b > 1 && (!ins_chunk_fits(1, nmax, b * ks * 2, word) || fit_mc(b) < std::min(8, P.n_i))) --b;
+    *pbw = b;
+    *mc = fit_mc(b);
+    return ins_chunk_fits(*mc, nmax, b * ks * 2, word);
+}
+
 bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::string* err)
 {
     const size_t word = P.precision == U1ML_FP64 ? 8 : 4;
@@ -735,62 +755,111 @@ bool compute_sizes(Problem& P, Sizes* S, u1ml_plan_info* info, Layout* Lo, std::
     // charge axis within 4096 sites.  AUTO estimates the device time each
     // form adds to a configuration and takes the smaller (history also when
     // the spectral form does not apply, spectral when the history form's
-    // per-site averages would exceed 64 GiB); the unit costs are MI355X
-    // measurements (FP32 links):
-    //   history:  contraction 6.6e12 FMA/s (the inner level's [TO] sums,
-    //             vector kernel) or 0.18 of the FP64 matrix-core peak per
-    //             16 x 16 x 4 step, padding included (matrix-core kernel:
-    //             3.3 ms per launch on the 24^3x8 workload below against 1.5 for the
-    //             vector kernel; a plain stream of these steps runs at 46
-    //             TFLOP/s on MI355X, FP64 vector FMA at 61);
-    //             two levels: the inner averages folded into the outer sums,
-    //             3 passes over them per outer update at 3 TB/s;
-    //   spectral: per measurement 20 us of launches, 14.2 ps per plane
-    //             element and field (staging and transforms), 0.198 ps per
-    //             flop of the spectral sums; two levels: the replay repeats
-    //             every update (5e10 link updates/s).
+    // per-site averages would exceed 64 GiB).  Fits to 260 random problems on
+    // MI355X (both link types, 6^3 to 48^3 and unequal extents, 1 to 64
+    // ensembles, 1 to 105 probes, one and two levels; 20 to 35 % rms):
+    //   history:  18 ns per work-group of the insertion sums and 9 ns per LDS
+    //             chunk of measurements (they overlap; the products run
+    //             beside them), O rows of lines that are not contiguous
+    //             staged at 1 TB/s, averages read back at 3.3 TB/s; two
+    //             levels: 50 us per outer update, averages written and folded
+    //             into the outer sums at 5.5 TB/s;
+    //   spectral: per measurement 15 us of dependent launches, 9.5 ps per
+    //             plane element and field (staging and transforms; planes
+    //             that the transforms in registers do not take 30 ps and 8 ns
+    //             per plane more), spectra and running sums read for the
+    //             spectral sums at 4.1 TB/s; two levels: the replay repeats
+    //             every update (FP32 9e10 link updates/s and 13 us per pass
+    //             over the lattice, FP64 4.3e10 and 21 us).
+    // On those problems the choice costs 0.2 % of the better form's time, 1.17
+    // times in the worst; with history at 6.6e12 FMA/s alone and 0.198 ps per
+    // flop of the spectral sums, fitted to earlier kernels, it cost 13 %, up to
+    // 5.7 times.
     // Measured per configuration (history / spectral, ms): 24^3x8, 9 probes,
-    // 100 updates 11.5 / 18.0; 24^3x8 in-plane map 18.1 / 19.4; 48^3x12 two
-    // levels 2 x 10, 1 probe 8.8 / 21.5, 8 probes 39.9 / 21.6.
+    // 100 updates 8.2 / 10.0; 24^3x8 in-plane map 13.1 / 13.0; 48^3x12 two
+    // levels 2 x 10, 1 probe 8.5 / 14.2, 8 probes 37.9 / 14.2.
+    // The history form's kernel: matrix cores where 0.18 of the FP64 matrix
+    // peak per 16 x 16 x 4 step, padding included, is less than 6.6e12 FMA/s
+    // of the vector kernel (3.3 ms per launch on 24^3x8 with 9 probes against
+    // 1.5; a plain stream of these steps runs at 46 TFLOP/s, FP64 vector FMA
+    // at 61); that rate covers the averages' traffic, too.
     {
-        bool plane_ok = true;
-        double hist_avg = 0.0, est_h = 0.0, est_s = 0.0, est_v = 0.0, est_m = 0.0;
-        const double n_meas = (double)P.n_i * (P.two ? P.n_o : 1);
-        const double n_steps = (double)((P.n_i + 3) / 4) * (P.two ? P.n_o : 1);  // MFMA steps of 4 measurements
-        size_t nblk8 = 0;
-        for (const auto& k : P.skeys) nblk8 += (k.size() + kMfSlots - 1) / kMfSlots;
-        const int word_o = P.precision == U1ML_FP64 ? 8 : 4;
+        bool plane_ok = true, hist_fits = true;
+        double hist_avg = 0.0, est_h = 0.0, est_s = 0.0, est_ins = 0.0, est_rd = 0.0, est_v = 0.0, est_m = 0.0;
+        const double n_lev = P.two ? P.n_o : 1, n_meas = (double)P.n_i * n_lev;
+        const double n_steps = (double)((P.n_i + 3) / 4) * n_lev;  // MFMA steps of 4 measurements
+        const int ks = P.ins_ks_vec;
+        size_t nblk8 = 0, nsb = 0;
+        for (const auto& k : P.skeys) {
+            nblk8 += (k.size() + kMfSlots - 1) / kMfSlots;
+            nsb += (k.size() + ks - 1) / ks;
+        }
+        const int word_o = (int)word;
         bool mf_ok = R <= (size_t)kMfR;
+        int side = -1, npm = 0;  // side of every plane if all are squares of one side, else 0; largest extent
+        for (const u1ml_ensemble& E : P.ens)
+            for (int i = 0; i < P.n_dirs; ++i)
+                for (int k = 1; k < 3; ++k) {
+                    const int len = E.ns[(P.dirs[i] + k) % 3];
+                    if (side < 0) side = len;
+                    if (side != len) side = 0;
+                }
+        const bool fast = fft_in_registers(side);
+        double upd = 0.0;
         for (const u1ml_ensemble& E : P.ens) {
             const double nsig = (double)E.ns[0] * E.ns[1] * E.ns[2];
-            for (int i = 0; i < P.n_dirs; ++i)
-                if (nsig / E.ns[P.dirs[i]] > 4096.0) plane_ok = false;
+            double lines = 0.0, planes = 0.0, strided = 0.0;  // lines of the axes; their planes; axes with strided lines
+            for (int i = 0; i < P.n_dirs; ++i) {
+                const int len = E.ns[P.dirs[i]];
+                if (nsig / len > 4096.0) plane_ok = false;
+                lines += nsig / len;
+                planes += len;
+                strided += P.dirs[i] != 0 || len * word % 16 != 0 ? 1.0 : 0.0;
+            }
             const int nmax = std::max(E.ns[0], std::max(E.ns[1], E.ns[2]));  // as the contraction is sized
+            npm = std::max(npm, nmax);
             if (!mf_chunk_fits(4, nmax, (int)R, 2 * kMfSlots, word_o)) mf_ok = false;
             const double per = (double)nd * R * Np * Nc * 2 * nsig * 16.0;
-            const double si = (double)(E.nt / P.tau_i);
-            hist_avg += per * si + (P.two ? per * (E.nt / P.tau_o) : 0.0);
+            const double si = (double)(E.nt / P.tau_i), so = P.two ? (double)(E.nt / P.tau_o) : 0.0;
+            hist_avg += per * si + per * so;
             est_v += n_meas * nd * si * nsig * R * Np * Nc * 4.0 / 6.6e12;
             est_m += n_steps * nd * si * nsig * (double)((R + 7) / 8) * nblk8 * 1024.0 / (0.18 * 39.3e12);
-            if (P.two) est_h += (double)P.n_o * per * si * 3.0 / 3.0e12;
-            est_s += n_meas * (20e-6 + nd * si * nsig * (R + 12) * 14.2e-12 + nd * si * (double)NG * nsig * R * Nc * 16.0 * 0.198e-12);
+            int pbw = 1, mc = 1;
+            if (Np && !ins_shape(P, ks, (int)nsb, nmax, &pbw, &mc)) hist_fits = false;
+            const double wgs = si * lines * (double)((nsb + pbw - 1) / pbw) * n_lev;
+            est_ins += wgs * (18e-9 + (double)((P.n_i + mc - 1) / mc) * 9e-9) +
+                       strided * n_meas * si * nsig * (double)nsb * ks * 2 * (double)word / 1.0e12;
+            est_rd += per * (P.two ? so : si) / 3.3e12;
+            if (P.two) est_h += n_lev * per * (si + 2 * so) / 5.5e12;
+            const double el = si * nsig * (R + 12);  // plane elements of one axis
+            const double run = si * R * Nc * 2 * (double)NG * lines * 16.0;  // the running sums, bytes
+            est_s += n_meas * (nd * el * (fast ? 9.5e-12 : 40e-12) + (fast ? 0.0 : si * planes * (R + 12) * 8e-9) +
+                               (nd * el * (double)NG * 16.0 + 2 * run) / 4.1e12);
             if (P.two) {
                 const double V = nsig * E.nt, vh = V / 2;
-                const double sp_i = vh / E.nt * (E.nt - E.nt / P.tau_i), sp_o = vh / E.nt * (E.nt - E.nt / P.tau_o);
-                const double upd = (double)P.n_o * ((double)P.k_o * (1 + P.n_or) * 2 * (vh + 3 * sp_o) +
-                                                    (double)P.n_i * P.k_i * (1 + P.n_or) * 2 * (vh + 3 * sp_i));
-                est_s += upd / 5e10;
+                const double sp_i = vh / E.nt * (E.nt - si), sp_o = vh / E.nt * (E.nt - so);
+                upd += n_lev * (1 + P.n_or) * 2 * ((double)P.k_o * (vh + 3 * sp_o) + (double)P.n_i * P.k_i * (vh + 3 * sp_i));
             }
         }
+        est_s += n_meas * 15e-6;
+        if (P.two) {
+            est_h += n_lev * 50e-6;
+            est_s += upd / (P.precision == U1ML_FP64 ? 4.3e10 : 9e10) +
+                     n_lev * ((double)P.k_o + (double)P.n_i * P.k_i) * (1 + P.n_or) *
+                         (P.precision == U1ML_FP64 ? 21e-6 : 13e-6);
+        }
         P.ins_mfma_est = Np && (P.ins_kernel == 2 || (P.ins_kernel == 0 && mf_ok && est_m < est_v));
-        est_h += P.ins_mfma_est ? est_m : est_v;
+        est_h += P.ins_mfma_est ? est_m : est_ins + est_rd;
         P.est_hist_ms = Np ? est_h * 1e3 : 0.0;
         P.est_spec_ms = (Np && plane_ok) ? est_s * 1e3 : -1.0;
         if (P.form_req == U1ML_FORM_SPECTRAL) {
             P.spectral = !P.probes.empty();  // planes checked by read_problem
         } else if (P.form_req == U1ML_FORM_AUTO) {
+            // no form whose LDS does not hold the problem (spectral: extents above 106) where the other's does
+            if (P.ins_mfma_est) hist_fits = true;
+            const bool spec_fits = 2 * spec_mac_lds(npm) <= kSlabLds;
             P.spectral = !P.probes.empty() && plane_ok &&
-                         (est_s < est_h || hist_avg > 64.0 * 1024 * 1024 * 1024);
+                         (hist_avg > 64.0 * 1024 * 1024 * 1024 || (spec_fits && (est_s < est_h || !hist_fits)));
         } else {
             P.spectral = false;
         }
@@ -2106,28 +2175,13 @@ try {
             E.ins_mc = mc;
         } else if (!P.probes.empty() && !P.spectral) {
             const int nsb = (int)(P.pblk.size() / kInsBlkInts);
-            const int ks = P.ins_ks, kr = ins_kr(ks);
+            const int kr = ins_kr(P.ins_ks);
             const int unit = (int)(nmax * ((R + kr - 1) / kr));  // tasks of one slot block
-            E.ins_pbw = std::max(1, std::min(std::min(nsb, kInsThreads / unit), kInsRowsMax / (2 * ks)));
-            // ins_mc measurements per LDS chunk buffer (static LDS of the kernel):
-            // fewer slot blocks per work-group while a chunk would hold fewer than 8
-            auto fit_mc = [&](int bpw) {
-                int mc = std::min(P.n_i, kInsPh);
-                while (mc > 1 && !ins_chunk_fits(mc, (int)nmax, bpw * ks * 2, (int)word)) --mc;
-                return mc;
-            };
-            // (fewer also while not even one measurement fits)
-            while (E.ins_pbw > 1 && (!ins_chunk_fits(1, (int)nmax, E.ins_pbw * ks * 2, (int)word) ||
-                                     fit_mc(E.ins_pbw) < std::min(8, P.n_i)))
-                --E.ins_pbw;
-            c->ins_block = std::max(c->ins_block, std::min(kInsThreads, (E.ins_pbw * unit + 63) / 64 * 64));
-            const int nrows = E.ins_pbw * ks * 2;
-            const int mc = fit_mc(E.ins_pbw);
-            if (!ins_chunk_fits(mc, (int)nmax, nrows, (int)word))
+            if (!ins_shape(P, P.ins_ks, nsb, (int)nmax, &E.ins_pbw, &E.ins_mc))
                 return set_err(nullptr, U1ML_ENOTSUP,
                                "history-form insertions: one measurement of a work-group's phases or O rows exceeds "
                                "its LDS buffer (use the spectral form)");
-            E.ins_mc = mc;
+            c->ins_block = std::max(c->ins_block, std::min(kInsThreads, (E.ins_pbw * unit + 63) / 64 * 64));
         }
         E.prod_nch = (P.n_dirs * E.nsig + kProdChunk - 1) / kProdChunk;
         E.res_index = e;

@@ -329,6 +329,7 @@ hipError_t launch_dft_planes(const EnsDesc* d_ens, const int* d_bstart, int n_en
 constexpr int kMacK = 8;
 constexpr int kMacThreads = 192;
 inline size_t spec_mac_lds(int npm) { return (size_t)6 * npm * kMacK * 16; }
+bool fft_in_registers(int side);  // whether square planes of that side have their transform in registers
 hipError_t launch_spec_mac(const EnsDesc* d_ens, const int* d_bstart, int n_ens, int total_blocks, int npm, int n_comp,
                            const ObsDesc* d_obs, const int* d_r, const int* d_comp, const int* d_gdesc,
                            const double2* sph, const double2* spo, double2* facc, hipStream_t st);

@@ -193,6 +193,25 @@ def test_contraction_form_follows_the_cost_estimates(u1):
     assert p["form"] == u1.FORM_HISTORY and p["est_spectral_ms"] == -1
 
 
+@pytest.mark.parametrize("ens, levels, n_r, n_p, form", [
+    ([((16, 16, 16), 8)] * 16, [(2, 20, 1)], 6, 27, 2),          # 10.1 / 5.2
+    ([((48, 48, 48), 4)], [(2, 10, 1)], 19, 9, 2),                # 5.1 / 2.2
+    ([((24, 24, 24), 8)], [(4, 4, 2), (2, 10, 1)], 8, 9, 1),      # 5.8 / 7.6
+    ([((24, 24, 24), 8)], [(2, 40, 1)], 11, 9, 1),                # 3.7 / 4.0
+    ([((8, 8, 128), 4)], [(2, 20, 1)], 3, 200, 1),               # no spectral sums: LDS holds extents up to 106
+], ids=["batch", "large", "two-levels", "few-probes", "long-extent"])
+def test_contraction_form_measured(u1, ens, levels, n_r, n_p, form):
+    """The form that AUTO takes where the averages' traffic, the work-groups
+    and chunks of the history form or the replay of the spectral one decide
+    (ms per configuration on MI355X, history / spectral, FP32 links, beside
+    each case); never one that the extents rule out."""
+    probes = [(i, a, b, 1) for i in range(-3, 4) for a in range(-3, 4) for b in range(-3, 4)]
+    probes.sort(key=lambda q: (abs(q[0]), abs(q[1]) + abs(q[2])))
+    spec = u1.Spec(ensembles=[u1.Ens(n, nt, 1.0, key_id=i) for i, (n, nt) in enumerate(ens)], levels=levels,
+                   r=list(range(1, n_r + 1)), probes=probes[:n_p], comps=list(range(6)), precision=u1.FP32)
+    assert u1.plan(spec)["form"] == form
+
+
 def test_large_bodies_are_launched_directly(u1):
     """Multilevel bodies above 8192 kernel launches are not captured into a
     single graph (the planner reports the launch count); the headline batch
