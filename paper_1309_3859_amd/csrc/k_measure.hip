@@ -182,8 +182,8 @@ __device__ inline double wave_sum(double a)
     return a;
 }
 
-// Sum of 12 per-thread doubles over the first four waves of a work-group in a
-// fixed order (lanes l and l + 32 of a wave added, the 128 pair sums staged in
+// Sum of 12 per-thread doubles over a work-group of four waves in a fixed
+// order (lanes l and l + 32 of a wave added, the 128 pair sums staged in
 // LDS, then each wave reduces three of the quantities), added to the block's
 // running double-double partials acc[12][2] of the configuration, which the
 // caller read beforehand (before, in lane kk those of quantity 3 wave + kk); the first
@@ -194,15 +194,12 @@ __device__ inline void block_sum12(const double* v, double2 before, double* acc,
 {
     __shared__ double red[12][128];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (wave < 4) {
 #pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            const double a = add_xor32(v[k]);
-            if (lane < 32) red[k][wave * 32 + lane] = a;
-        }
+    for (int k = 0; k < 12; ++k) {
+        const double a = add_xor32(v[k]);
+        if (lane < 32) red[k][wave * 32 + lane] = a;
     }
     __syncthreads();
-    if (wave >= 4) return;
     double sum[3];
 #pragma unroll
     for (int kk = 0; kk < 3; ++kk) sum[kk] = wave_sum(red[3 * wave + kk][lane] + red[3 * wave + kk][lane + 64]);

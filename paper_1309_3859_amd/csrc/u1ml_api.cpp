@@ -1451,7 +1451,7 @@ void build_lane_tables(const u1ml_ctx* c, Lane& L)
         site[e] = (long long)P.n_dirs * R * E.nsig;
         plane[e] = P.spectral ? (long long)P.n_dirs * E.s_in * ((long long)R + 12) * npm : 0;
         mac[e] = P.spectral ? (long long)P.n_dirs * E.s_in * NG * ((n12max + kMacK - 1) / kMacK) : 0;
-        // staging: work-groups of 32 x 32 tiles per (axis, slab), as k_plane_stage decodes them
+        // staging: work-groups of kStageTile x kStageTile tiles per (axis, slab), as k_plane_stage decodes them
         stage[e] = P.spectral ? (long long)P.n_dirs * E.s_in * ((E.nx + kStageTile - 1) / kStageTile) *
                                     ((npm + kStageTile - 1) / kStageTile) * npm
                               : 0;
