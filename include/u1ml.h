@@ -141,7 +141,8 @@ typedef struct {
  *           AUTO takes the form with the smaller estimated device time,
  *           u1ml_plan_info.est_history_ms / est_spectral_ms, from unit costs
  *           measured on MI355X, and the spectral form whenever the history
- *           form's per-site averages would exceed 64 GiB). */
+ *           form's per-site averages would exceed 64 GiB; neither where its
+ *           LDS does not hold the problem and the other's does). */
 typedef struct {
     int n_ens;
     const u1ml_ensemble* ens;
